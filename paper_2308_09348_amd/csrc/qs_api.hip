@@ -112,7 +112,10 @@ constexpr size_t r256(size_t n) { return (n + 255) / 256 * 256; }
 constexpr size_t kSamples = QS_NOALLOC_MAX_SAMPLES;
 constexpr size_t kEnvPoints = 2 * 65536 + 1;
 constexpr size_t kAccumWords = 2 + 1 + 3 * 4096 + 4 + 1;
-constexpr size_t kPartWords = (kSamples + qs::kMomTile - 1) / qs::kMomTile * qs::kPartials;
+// (rows of kMomRow samples below kDepItems items of kDepTile, else of kMomTile)
+constexpr size_t kPartWords =
+    std::max((kSamples + qs::kMomTile - 1) / qs::kMomTile,
+             (size_t)qs::kDepItems * qs::kDepTile / qs::kMomRow) * qs::kPartials;
 constexpr size_t kArr = r256(kSamples * 8), kArrf = r256(kSamples * 4);
 constexpr size_t kStatesOff = 0;
 constexpr size_t kEnv64Off = kStatesOff + 6 * kArr + kArrf;
@@ -812,6 +815,20 @@ const TuneEntry *find_tune(const qs_ctx *c, const TuneKey &k) {
     return nullptr;
 }
 
+// The deposit work item of launches without a tuned choice: 1024 samples, and
+// for small launches as few as leave about 512 items, so that they spread over
+// the device (256 CUs).  Measured on focused laws, items of 256 / 512 / 1024 /
+// 4096 samples: 5003 samples 39 / 69 / 122 / 454 us, 50,001 51 / 72 / 124 / 457 us,
+// 2^18 123 / 106 / 135 / 458 us, 2^20 357 / 266 / 219 / 460 us, 2^22 1308 / 794 /
+// 690 / 749 us (an earlier form of the kernel: 2^19 235 / 184 / 168 / 510 us; 128 shots
+// of 2^12 .. 2^18 1688 / 1551 / 1516 / 2056 us, their uneven ends need the smaller
+// items; 1500 shots 19.8 / 17.3 / 16.2 / 16.2 ms).
+int default_dep_tile(int64_t total) {
+    int tile = qs::kDepTile;
+    while (tile > qs::kMomRow && total / tile < qs::kDepItems) tile >>= 1;
+    return tile;
+}
+
 qs_status prepare_batch(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_beam *B,
                         const int64_t *n_samples, const qs_numerics *N, const qs_bins *H,
                         size_t out_size, Batch &b, bool noalloc = false,
@@ -865,7 +882,8 @@ qs_status prepare_batch(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_
     bp.c_theta = N->c_theta;
     // launch choices of this launch class (qs_tune), else the defaults
     const TuneEntry *tune = find_tune(c, tune_key(N, b.prec, b.max_nh, b.total, n_shots));
-    bp.dep_tile = tune ? tune->dep_tile : qs::kDepTile;
+    bp.dep_tile = tune ? tune->dep_tile : default_dep_tile(b.total);
+    bp.mom_row = bp.dep_tile < qs::kMomTile ? qs::kMomRow : qs::kMomTile;
     bp.phase_cap = tune ? tune->phase_cap : 0;
     bp.dep_cap = tune ? tune->dep_cap : 0;
 
@@ -965,7 +983,7 @@ qs_status prepare_batch(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_
         off += n_samples[k];
         item += (n_samples[k] + qs::kPhaseBlock - 1) / qs::kPhaseBlock;
         ditem += (n_samples[k] + bp.dep_tile - 1) / bp.dep_tile;
-        mtile += (n_samples[k] + qs::kMomTile - 1) / qs::kMomTile;
+        mtile += (n_samples[k] + bp.mom_row - 1) / bp.mom_row;
         gitem += (n_samples[k] + qs::kChiGroup - 1) / qs::kChiGroup;
         hoff += hb.n_e + 2 + hb.n_th + 2 + hb.n_a;
     }

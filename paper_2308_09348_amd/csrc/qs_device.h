@@ -1097,6 +1097,25 @@ __device__ __forceinline__ void wave_deposit(const LawLane &L, double w, float h
 // ===========================================================================
 // Wavefront reductions
 // ===========================================================================
+// The sum over the wavefront in lane 63, by DPP moves (no LDS traffic): within
+// rows of 16 lanes, then the row ends to the rows after.
+__device__ __forceinline__ double wave_sum_last(double v) {
+    auto step = [](double x, auto ctrl, auto rows) {
+        const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), decltype(ctrl)::value,
+                                                   decltype(rows)::value, 0xf, false);
+        const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), decltype(ctrl)::value,
+                                                   decltype(rows)::value, 0xf, false);
+        return x + __hiloint2double(hi, lo);
+    };
+    using std::integral_constant;
+    v = step(v, integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});  // row_shr:1
+    v = step(v, integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});  // row_shr:2
+    v = step(v, integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});  // row_shr:4
+    v = step(v, integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});  // row_shr:8
+    v = step(v, integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});  // row_bcast:15
+    v = step(v, integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});  // row_bcast:31
+    return v;
+}
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

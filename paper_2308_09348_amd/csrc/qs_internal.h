@@ -53,10 +53,15 @@ constexpr int kPMaxChi = P_N, kPMaxEmu = P_N + 1, kPMaxEsig = P_N + 2;
 
 constexpr int kPhaseBlock = 256;  // one phase work item = kPhaseBlock samples of one shot
 constexpr int kDepBlock = 256;
-constexpr int kDepTile = 4096;    // default deposit work item: kDepTile samples of one shot
-// Moment partial sums are kept per tile of kMomTile samples whatever the
-// deposit work item (a multiple of it), so the moments do not depend on it.
+constexpr int kDepTile = 1024;    // largest default deposit work item (samples of one shot)
+constexpr int kDepItems = 512;    // smaller items below this many of them (default_dep_tile)
+// Moment sums are formed per round of kMomRow samples (one a lane of a block of
+// kDepBlock), then per tile of kMomTile in round order, then over the tiles,
+// whatever the deposit work item (a multiple of either), so the moments do not
+// depend on it.  A deposit item below kMomTile writes its rounds' sums and the
+// finalize kernel adds them up in the same order.
 constexpr int kMomTile = 1024;
+constexpr int kMomRow = kDepBlock;
 constexpr int kPartials = P_N + 3;  // moment sums and maxima of a moment tile
 // Passes with FP64 steps (forward, tape forward, adjoint, and the
 // contraction of their tapes): a work item is a group of up to kChiGroup
@@ -95,7 +100,7 @@ struct ShotParams {
     int64_t state_off;   // index of its first sample state
     int64_t item0;       // its first phase work item
     int64_t ditem0;      // its first deposit work item
-    int64_t mtile0;      // its first moment tile (kMomTile samples each)
+    int64_t mtile0;      // its first moment row (BatchParams::mom_row samples each)
     int64_t gitem0;      // its first group (kChiGroup samples) of the passes with FP64 steps
     int64_t hist_off;    // its first histogram word in the accumulators
     // FP64 shadow: samples i with i % shadow_stride == 0 have the FP64 state
@@ -195,12 +200,14 @@ struct BatchParams {
     int32_t n_steps, n_shots, deposit;
     int32_t any_mode;  // some shot uses a higher transverse mode
     int32_t dep_tile;   // samples of one deposit work item (a tuning choice)
+    int32_t mom_row;    // samples of one row of moment sums (kMomRow or kMomTile)
     int32_t phase_cap;  // resident phase blocks per CU at most (0: all that fit)
     int32_t dep_cap;    // resident deposit blocks per CU at most (0: all that fit)
     int32_t prec;       // the pass's precision (Prec)
+    int32_t pad1;
     uint32_t key0, key1;
     double ksig_bins, c_theta;
-    int64_t n_items, n_ditems, n_mtiles;
+    int64_t n_items, n_ditems, n_mtiles;  // (n_mtiles: rows of moment sums)
     int64_t n_gitems;   // groups of the passes with FP64 steps
     const ShotParams *shots;
     const ShotOut *outs;
@@ -227,7 +234,7 @@ struct BatchParams {
     unsigned int *queue;           // [2]: phase and deposit work counters
     unsigned long long *fp64_steps;  // [n_shots]: wavefront phase steps taken in FP64 by
                                      // the forward pass's FP32 loop (null: not counted)
-    double *partials;              // [n_mtiles][kPartials]; adjoint: [n_items][kGradParams]
+    double *partials;              // [kPartials][n_mtiles]; adjoint: [n_items][kGradParams]
                                    // ([n_gitems][kGradParams] with FP64 steps)
 };
 

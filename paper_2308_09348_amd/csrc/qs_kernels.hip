@@ -470,18 +470,27 @@ __global__ __launch_bounds__(kPhaseBlock) void shadow_diff_kernel(BatchParams P,
     }
 }
 
-// Held to 128 VGPRs (four waves per SIMD; it takes 131 otherwise, which
-// leaves three): one spilled register, a quarter less time.
+// Held to 128 VGPRs (four waves per SIMD): 113 without spills, since the moment
+// sums of a round are formed before the laws are walked rather than carried
+// through them (focused laws, 2^22 samples: 731 -> 690 us; a fold of the sums by
+// halves took 47 scratch accesses and 8% more time).
 // SPLIT: the runs' upper-side tails in arrays of their own (16 bytes an edge
 // instead of 8; histograms of up to 64 KB of LDS words take it).
+// Small launches are bound by the rounds of 256 samples that a block takes one
+// after another (about 28 us each: the laws of 64 samples by one wavefront), so
+// the work item shrinks with the launch (default_dep_tile): 5003 samples 440 ->
+// 39 us, 2^18 445 -> 106 us, 2^20 447 -> 219 us (focused laws; items of 4096
+// before).
 template <bool SPLIT>
 __global__ __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(4))) void deposit_kernel(
     BatchParams P) {
+    constexpr int kGroups = kDepBlock / 64;        // wavefronts
+    constexpr int kRounds = kMomTile / kDepBlock;  // rounds of a moment tile
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int64_t slot;
-    __shared__ double red[kDepBlock / 64][P_N];
-    __shared__ float redmax[kDepBlock / 64];
-    __shared__ double redsh[kDepBlock / 64][2];
+    __shared__ double red[kRounds][kGroups][P_N];
+    __shared__ float redmax[kGroups];
+    __shared__ double redsh[kGroups][2];
     __shared__ unsigned int wsum[kDepBlock / 64];
     __shared__ int4 wrec[kDepBlock];
     __shared__ int2 wext[kDepBlock];
@@ -511,8 +520,8 @@ __global__ __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(4))) 
         unsigned int *ct = ce + nh_e;
         unsigned int *ca = ct + nh_t;
         const int nq = (SPLIT ? 2 : 1) * (sp.n_e + 1 + sp.n_th + 1), nc = nh_e + nh_t + sp.n_a;
-        for (int k = threadIdx.x; k < nq; k += blockDim.x) Qe[k] = 0ull;
-        for (int k = threadIdx.x; k < nc; k += blockDim.x) ce[k] = 0u;
+        for (int k = threadIdx.x; k < nq; k += kDepBlock) Qe[k] = 0ull;
+        for (int k = threadIdx.x; k < nc; k += kDepBlock) ce[k] = 0u;
         __syncthreads();
 
         int flags = 0;
@@ -520,17 +529,19 @@ __global__ __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(4))) 
         const int64_t i1 = i0 + P.dep_tile < sp.n_samples ? i0 + P.dep_tile : sp.n_samples;
         const float hfe = (float)(0.5 * sp.e_w), hft = (float)(0.5 * sp.th_w);
         const double inv_we = 1.0 / sp.e_w, inv_wt = 1.0 / sp.th_w;
-        for (int64_t t0 = i0; t0 < i1; t0 += kMomTile) {
-            const int64_t t1 = t0 + kMomTile < i1 ? t0 + kMomTile : i1;
-            double acc[P_N];
-#pragma unroll
-            for (int m = 0; m < P_N; ++m) acc[m] = 0.0;
+        for (int64_t t0 = i0; t0 < i1; t0 += P.mom_row) {
+            const int64_t t1 = t0 + P.mom_row < i1 ? t0 + P.mom_row : i1;
             float chimax = 0.0f;
             double emu = 0.0, esig = 0.0;  // FP64 shadow: largest differences
             // every lane runs every round (the wavefront deposit needs them all)
-            for (int64_t base = t0; base < t1; base += blockDim.x) {
+            int round = 0;
+            for (int64_t base = t0; base < t1; base += kDepBlock, ++round) {
                 const int64_t i = base + threadIdx.x;
-                LawLane le{-1, 0, -1, 0, 0.0f, 0.0f, 0.0f}, lt = le;
+                bool law = false;  // the sample deposits N(v_e, s_e^2) and N(v_t, s_t^2)
+                double v_e = 0.0, s_e = 0.0, v_t = 0.0, s_t = 0.0;
+                double acc[P_N];  // the round's moment sums
+#pragma unroll
+                for (int m = 0; m < P_N; ++m) acc[m] = 0.0;
                 if (i < i1) {
                     const int64_t k = sp.state_off + i;
                     const double mu_f = P.st.mu[k], s2_f = P.st.s2[k], S0 = P.st.S0[k];
@@ -555,25 +566,26 @@ __global__ __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(4))) 
                         ig0 = fma(fma(-g0, ig0, 1.0), ig0, ig0);
                         const double sigth =
                             1e3 * P.c_theta * 0.79788456080286535588 * a_eff * sigf * imu2;
-                        le = law_setup(mu_f, sigf, P.deposit, P.ksig_bins, sp.e_lo, sp.e_w, inv_we,
-                                       sp.n_e);
-                        lt = law_setup(thx_m, sigth, P.deposit, P.ksig_bins, sp.th_lo, sp.th_w,
-                                       inv_wt, sp.n_th);
+                        law = true;
+                        v_e = mu_f;
+                        s_e = sigf;
+                        v_t = thx_m;
+                        s_t = sigth;
                         {
                             int ka = (int)floor(S0 * (double)sp.n_a);
                             ka = min(max(ka, 0), sp.n_a - 1);
                             atomicAdd(&ca[ka], 1u);
                         }
                         const double de = mu_f - sp.gamma0;
-                        acc[P_S1E] += de;
-                        acc[P_S2E] += fma(de, de, fmax(s2_f, 0.0));
-                        acc[P_S1X] += thx_m;
-                        acc[P_S2X] += fma(thx_m, thx_m, sigth * sigth);
-                        acc[P_S1Y] += thy_m;
-                        acc[P_S2Y] += thy_m * thy_m;
-                        acc[P_SAEFF] += a_eff;
-                        acc[P_SRAD] += fma(-mu_f, ig0, 1.0);
-                        acc[P_SSIGF] += sigf;
+                        acc[P_S1E] = de;
+                        acc[P_S2E] = fma(de, de, fmax(s2_f, 0.0));
+                        acc[P_S1X] = thx_m;
+                        acc[P_S2X] = fma(thx_m, thx_m, sigth * sigth);
+                        acc[P_S1Y] = thy_m;
+                        acc[P_S2Y] = thy_m * thy_m;
+                        acc[P_SAEFF] = a_eff;
+                        acc[P_SRAD] = fma(-mu_f, ig0, 1.0);
+                        acc[P_SSIGF] = sigf;
                         if (sp.shadow_stride > 0 && i % sp.shadow_stride == 0) {
                             // the same sample integrated in FP64
                             const int64_t q = sp.shadow_off + i / sp.shadow_stride;
@@ -581,9 +593,9 @@ __global__ __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(4))) 
                             const double s64 = sqrt(fmax(P.sst.s2[q], 0.0));
                             if (m64 > 0.0) {
                                 const double d = mu_f - m64;
-                                acc[P_SHN] += 1.0;
-                                acc[P_SHMU] += d / m64;
-                                acc[P_SHG] += d;
+                                acc[P_SHN] = 1.0;
+                                acc[P_SHMU] = d / m64;
+                                acc[P_SHG] = d;
                                 emu = fmax(emu, fabs(d) / m64);
                                 esig = fmax(esig, fabs(sigf - s64) / m64);
                             }
@@ -606,90 +618,111 @@ __global__ __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(4))) 
                         }
                     }
                 }
+#pragma unroll
+                for (int m = 0; m < P_N; ++m) {
+                    if (m >= P_SHN && sp.shadow_stride == 0) break;
+                    const double v = wave_sum_last(acc[m]);
+                    if (lane == 63) red[round][wid][m] = v;
+                }
+                LawLane le{-1, 0, -1, 0, 0.0f, 0.0f, 0.0f}, lt = le;
+                if (law) {
+                    le = law_setup(v_e, s_e, P.deposit, P.ksig_bins, sp.e_lo, sp.e_w, inv_we,
+                                   sp.n_e);
+                    lt = law_setup(v_t, s_t, P.deposit, P.ksig_bins, sp.th_lo, sp.th_w, inv_wt,
+                                   sp.n_th);
+                }
                 wave_deposit<SPLIT>(le, sp.e_w, hfe, Qe, QeU, ce, WL);
                 wave_deposit<SPLIT>(lt, sp.th_w, hft, Qt, QtU, ct, WL);
             }
 
-            // ---- moment tile reduction (fixed order) ----
-#pragma unroll
-            for (int m = 0; m < P_N; ++m) {
-                const double v = wave_sum(acc[m]);
-                if (lane == 0) red[wid][m] = v;
-            }
+            // ---- one row of moment sums (fixed order) ----
             const float wm = wave_max(chimax);
-            const double we = wave_max(emu), ws = wave_max(esig);
-            if (lane == 0) {
-                redmax[wid] = wm;
-                redsh[wid][0] = we;
-                redsh[wid][1] = ws;
+            if (lane == 0) redmax[wid] = wm;
+            if (sp.shadow_stride > 0) {
+                const double we = wave_max(emu), ws = wave_max(esig);
+                if (lane == 0) {
+                    redsh[wid][0] = we;
+                    redsh[wid][1] = ws;
+                }
             }
             __syncthreads();
-            double *part = P.partials + (size_t)(sp.mtile0 + t0 / kMomTile) * kPartials;
+            double *part = P.partials + (size_t)(sp.mtile0 + t0 / P.mom_row);
             if (threadIdx.x < P_N) {
-                double sum = 0.0;
-                for (int w = 0; w < kDepBlock / 64; ++w) sum += red[w][threadIdx.x];
-                part[threadIdx.x] = sum;
+                double tile = 0.0;
+                if (threadIdx.x >= P_SHN && sp.shadow_stride == 0) round = 0;
+                for (int r = 0; r < round; ++r) {
+                    double sum = red[r][0][threadIdx.x];
+                    for (int g = 1; g < kGroups; ++g) sum += red[r][g][threadIdx.x];
+                    tile = r == 0 ? sum : tile + sum;
+                }
+                part[(size_t)threadIdx.x * P.n_mtiles] = tile;
             }
             if (threadIdx.x == 0) {
                 float m = 0.0f;
                 double e0 = 0.0, e1 = 0.0;
-                for (int w = 0; w < kDepBlock / 64; ++w) {
-                    m = fmaxf(m, redmax[w]);
-                    e0 = fmax(e0, redsh[w][0]);
-                    e1 = fmax(e1, redsh[w][1]);
+                for (int g = 0; g < kGroups; ++g) {
+                    m = fmaxf(m, redmax[g]);
+                    if (sp.shadow_stride > 0) {
+                        e0 = fmax(e0, redsh[g][0]);
+                        e1 = fmax(e1, redsh[g][1]);
+                    }
                 }
-                part[kPMaxChi] = m;
-                part[kPMaxEmu] = e0;
-                part[kPMaxEsig] = e1;
+                part[(size_t)kPMaxChi * P.n_mtiles] = m;
+                part[(size_t)kPMaxEmu * P.n_mtiles] = e0;
+                part[(size_t)kPMaxEsig * P.n_mtiles] = e1;
             }
-            __syncthreads();  // red is rewritten by the next tile
+            __syncthreads();  // red is rewritten by the next row
         }
         if (flags) atomicOr(&P.flags[s], flags);
         unsigned long long *G = P.hist + sp.hist_off;
         flush_edges<SPLIT>(Qe, QeU, ce, sp.n_e, G, wsum);
         flush_edges<SPLIT>(Qt, QtU, ct, sp.n_th, G + nh_e, wsum);
-        for (int k = threadIdx.x; k < sp.n_a; k += blockDim.x)
+        for (int k = threadIdx.x; k < sp.n_a; k += kDepBlock)
             if (ca[k]) atomicAdd(&G[nh_e + nh_t + k], kOne * ca[k]);
         __syncthreads();  // the next item clears the LDS words
     }
 }
 
 // ===========================================================================
-// Finalize: one block per shot, fixed-order reduction of its moment tiles
+// Finalize: one block per shot, fixed-order reduction of its moment rows
 // ===========================================================================
-__global__ __launch_bounds__(256) void finalize_kernel(BatchParams P) {
+// Bound by latency (one block).  One wavefront a column of the moment rows
+// (stored column after column): lane l adds the tiles l, l + 64, ..., then the
+// wavefront's sum: 16.3 -> 4.8 us at 5003 samples, 52 -> 23 us at 2^22, against
+// a block that took the columns in turn, each with a tree of eight barriers.
+constexpr int kFinBlock = 64 * 16;
+static_assert(kPartials <= kFinBlock / 64, "a wavefront a column");
+
+__global__ __launch_bounds__(kFinBlock) void finalize_kernel(BatchParams P) {
     const int s = blockIdx.x;
     const ShotParams &sp = P.shots[s];
     const ShotOut &so = P.outs[s];
-    const int64_t nd = (sp.n_samples + kMomTile - 1) / kMomTile;
+    const int64_t nrow = (sp.n_samples + P.mom_row - 1) / P.mom_row;
+    const int per = kMomTile / P.mom_row;  // rows of a moment tile
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     __shared__ double sums[kPartials];
     __shared__ double tree[256];
-    // each column: thread t sums items t, t + 256, ... then a fixed tree
-    for (int m = 0; m < kPartials; ++m) {
+    if (wid < kPartials) {
+        const double *col = P.partials + (size_t)wid * P.n_mtiles + sp.mtile0;
+        const bool mx = wid >= P_N;
         double acc = 0.0;
-        for (int64_t b = threadIdx.x; b < nd; b += blockDim.x) {
-            const double v = P.partials[(size_t)(sp.mtile0 + b) * kPartials + m];
-            acc = m >= P_N ? fmax(acc, v) : acc + v;
+#pragma unroll 4
+        for (int64_t b = (int64_t)lane * per; b < nrow; b += 64 * per) {
+            double v = col[b];
+            for (int r = 1; r < per && b + r < nrow; ++r)
+                v = mx ? fmax(v, col[b + r]) : v + col[b + r];
+            acc = mx ? fmax(acc, v) : acc + v;
         }
-        tree[threadIdx.x] = acc;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if (threadIdx.x < w) {
-                const double o = tree[threadIdx.x + w];
-                tree[threadIdx.x] = m >= P_N ? fmax(tree[threadIdx.x], o) : tree[threadIdx.x] + o;
-            }
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) sums[m] = tree[0];
-        __syncthreads();
+        acc = mx ? wave_max(acc) : wave_sum(acc);
+        if (lane == 0) sums[wid] = acc;
     }
     const int nh_e = sp.n_e + 2, nh_t = sp.n_th + 2;
     const unsigned long long *H = P.hist + sp.hist_off;
     const double scale = 1.0 / 4294967296.0;
-    for (int k = threadIdx.x; k < nh_e; k += blockDim.x) so.energy_hist[k] = (double)H[k] * scale;
-    for (int k = threadIdx.x; k < nh_t; k += blockDim.x)
+    for (int k = threadIdx.x; k < nh_e; k += kFinBlock) so.energy_hist[k] = (double)H[k] * scale;
+    for (int k = threadIdx.x; k < nh_t; k += kFinBlock)
         so.angle_hist[k] = (double)H[nh_e + k] * scale;
-    for (int k = threadIdx.x; k < sp.n_a; k += blockDim.x)
+    for (int k = threadIdx.x; k < sp.n_a; k += kFinBlock)
         so.a0eff_hist[k] = (double)H[nh_e + nh_t + k] * scale;
     __syncthreads();
     // FP64 shadow, histogram level: L1 and largest bin of the summed law
@@ -700,13 +733,14 @@ __global__ __launch_bounds__(256) void finalize_kernel(BatchParams P) {
         for (int h = 0; h < 2; ++h) {
             const int n0 = h == 0 ? 0 : nh_e, n1 = h == 0 ? nh_e : nh_e + nh_t;
             double l1 = 0.0, mx = 0.0;
-            for (int k = n0 + threadIdx.x; k < n1; k += blockDim.x) {
-                const double v = fabs((double)(long long)D[k]) * (1.0 / 1099511627776.0);
-                l1 += v;
-                mx = fmax(mx, v);
-            }
+            if (threadIdx.x < 256)
+                for (int k = n0 + threadIdx.x; k < n1; k += 256) {
+                    const double v = fabs((double)(long long)D[k]) * (1.0 / 1099511627776.0);
+                    l1 += v;
+                    mx = fmax(mx, v);
+                }
             for (int part = 0; part < 2; ++part) {
-                tree[threadIdx.x] = part == 0 ? l1 : mx;
+                if (threadIdx.x < 256) tree[threadIdx.x] = part == 0 ? l1 : mx;
                 __syncthreads();
                 for (int w = 128; w > 0; w >>= 1) {
                     if (threadIdx.x < w) {
@@ -906,7 +940,7 @@ hipError_t launch_shadow_diff(const BatchParams &p, int64_t n_items, int max_his
 }
 
 hipError_t launch_finalize(const BatchParams &p, hipStream_t s) {
-    finalize_kernel<<<p.n_shots, 256, 0, s>>>(p);
+    finalize_kernel<<<p.n_shots, kFinBlock, 0, s>>>(p);
     return hipGetLastError();
 }
 

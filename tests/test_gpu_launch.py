@@ -213,3 +213,26 @@ def test_profiled_calls_are_kept_for_the_sum(qs):
     ctx.forward(p, out=out, check=False)
     assert ctx.timings_sum()[0] == 3
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [1, 256, 257, 1025, 131_071, 262_145, (1 << 19) - 1])
+def test_small_launch_deposit_items(qs, tmp_path, n):
+    """Launches without a tuned choice take deposit items of 256, 512 or 1024
+    samples by their size, and below 1024 write a row of moment sums per 256
+    samples: the bits of items of 2048 samples (one row per 1024), and of the
+    launch that allocates nothing."""
+    p = _case(n_samples=n, n_steps=16)
+    plain = qs.Context(0)
+    ref = _np(plain.forward(p))
+    _same(_np(plain.forward(p, noalloc=True)), ref, "noalloc")
+    cache = tmp_path / "tune.txt"
+    plain.tune(p, cache_path=str(cache))
+    line = cache.read_text().split()
+    line[10:13] = ["2048", "0", "0"]
+    cache.write_text(" ".join(line) + "\n")
+    forced = qs.Context(0)
+    assert forced.tune(p, cache_path=str(cache))["dep_tile"] == 2048
+    _same(_np(forced.forward(p)), ref, "items of 2048")
+    assert ref["energy_hist"].sum() == n
+    plain.close()
+    forced.close()
