@@ -952,9 +952,9 @@ __device__ __forceinline__ void grad_item_reduce(const BatchParams &P, int64_t i
 // waves per SIMD; every other pass is held to 256 (two waves): the FP64 ones
 // would otherwise take a few registers more and run one wave per SIMD, and
 // the mixed ones are held to two by the FP64 table staging in LDS anyway.
-// Mixed precision (FP64 steps): the work items are groups of kChiGroup
-// samples taken in rounds in order of their chi scale; every lane of a
-// wavefront runs, lanes past the group's end repeat its last sample.
+// Mixed precision (FP64 steps): a work item is a round of a group's samples in
+// order of their chi scale; every lane of a wavefront runs, lanes past the
+// group's end repeat its last sample.
 template <int PREC, bool QUANTUM, bool LOCAL, bool TAPE>
 __global__ __launch_bounds__(kPhaseBlock)
 __attribute__((amdgpu_waves_per_eu((TAPE && PREC == PREC_F32) ? 3 : 2))) void tangent_kernel(
@@ -965,10 +965,6 @@ __attribute__((amdgpu_waves_per_eu((TAPE && PREC == PREC_F32) ? 3 : 2))) void ta
     __shared__ double2 stage[kWave64 ? (kPhaseBlock / 64) * kStageChunks : 1];
     __shared__ int64_t slot;
     __shared__ double red[kPhaseBlock / 64][kGradParams];
-    // FP64 steps where chi is high: the group's samples in order of their chi
-    // scale, as the forward pass orders its items (chi_order)
-    __shared__ float okey[kWave64 ? kChiGroup : 1];
-    __shared__ unsigned short oidx[kWave64 ? kChiGroup : 1];
     double2 *wstage = stage + (kWave64 ? (threadIdx.x >> 6) * kStageChunks : 0);
     if (kTab32) {
         const float4 *src = reinterpret_cast<const float4 *>(P.rad32d);
@@ -1024,23 +1020,16 @@ __attribute__((amdgpu_waves_per_eu((TAPE && PREC == PREC_F32) ? 3 : 2))) void ta
         double g[kGradParams];
 #pragma unroll
         for (int p = 0; p < kGradParams; ++p) g[p] = 0.0;
+        if (item >= P.n_items) break;
+        const int s = __builtin_amdgcn_readfirstlane(find_shot(P.shots, P.n_shots, item, false));
+        const ShotParams &sp = P.shots[s];
         if constexpr (kWave64) {
-            if (item >= P.n_gitems) break;
-            const int s = __builtin_amdgcn_readfirstlane(find_group_shot(P.shots, P.n_shots, item));
-            const ShotParams &sp = P.shots[s];
-            const int64_t base = (item - sp.gitem0) * kChiGroup;
+            const int64_t first = (item - sp.item0) * kPhaseBlock, base = first & ~(kChiGroup - 1ll);
             const int cnt = (int)min((int64_t)kChiGroup, sp.n_samples - base);
-            chi_order<kChiGroup, kPhaseBlock>(sp, P.key0, P.key1, base, sp.n_samples, okey, oidx);
-            for (int r = 0; r * kPhaseBlock < cnt; ++r) {
-                const int rank = r * kPhaseBlock + (int)threadIdx.x;
-                if (r * kPhaseBlock + (int)(threadIdx.x & ~63u) >= cnt) continue;  // whole wavefront
-                const bool live = rank < cnt;
-                one(sp, s, base + oidx[live ? rank : cnt - 1], live, g);
-            }
+            const int rank = (int)(first - base) + (int)threadIdx.x;
+            if ((rank & ~63) < cnt)  // some lane of the wavefront has a sample
+                one(sp, s, ordered_sample(P, sp, base, cnt, rank), rank < cnt, g);
         } else {
-            if (item >= P.n_items) break;
-            const int s = __builtin_amdgcn_readfirstlane(find_shot(P.shots, P.n_shots, item, false));
-            const ShotParams &sp = P.shots[s];
             const int64_t i = (item - sp.item0) * kPhaseBlock + threadIdx.x;
             if (i < sp.n_samples) one(sp, s, i, true, g);
         }
@@ -1049,85 +1038,124 @@ __attribute__((amdgpu_waves_per_eu((TAPE && PREC == PREC_F32) ? 3 : 2))) void ta
 }
 
 // The adjoint from a tape: contraction of the recorded derivatives with the
-// law sensitivities (memory-bound: 144 bytes a sample).
-// OBS: some shot also has angle-histogram or moment weights (the memory-bound
-// contraction of the energy terms alone keeps its small register budget).
-// GROUPED: the tape of a pass with FP64 steps, summed over the groups of its
-// tangent pass in the same order (rounds in chi order, each lane adding its
-// samples' terms round by round, then the block reduction), so that the
-// result equals the recomputing adjoint's bit for bit.
-template <bool OBS, bool GROUPED>
+// law sensitivities (144 bytes read a sample).
+// OBS: some shot also has angle-histogram or moment weights (the contraction
+// of the energy terms alone keeps its small register budget).
+// The gradient terms gi of sample i from its tape entries; W: the shot's energy
+// weights.  False if the sample's state is not finite.
+template <bool OBS>
+__device__ __forceinline__ bool contract_sample(const BatchParams &P, const ShotParams &sp, int s,
+                                                int64_t i, const double *W, double *gi) {
+    const int64_t n = P.tape_n;
+    const double *t = P.tape + sp.state_off + i;
+    const double mu = t[0], s2 = t[n];
+    double dm[kGradParams], ds[kGradParams];
+#pragma unroll
+    for (int p = 0; p < kGradParams; ++p) {
+        dm[p] = t[(2 + p) * n];
+        ds[p] = t[(2 + kGradParams + p) * n];
+        gi[p] = 0.0;
+    }
+    if (!(mu > 0.0 && isfinite(mu) && isfinite(s2))) return false;
+    const ShotGrad &go = P.gouts[s];
+    if (go.d_energy) {
+        double lv, ls;
+        law_sensitivity(mu, s2, P.deposit, P.ksig_bins, sp.e_lo, sp.e_w, sp.n_e, W, lv, ls);
+#pragma unroll
+        for (int p = 0; p < kGradParams; ++p) gi[p] = fma(lv, dm[p], ls * ds[p]);
+    }
+    if (OBS) observable_sensitivity(P, sp, go, i, mu, s2, dm, ds, gi);
+    return true;
+}
+
+template <bool OBS>
 __global__ __launch_bounds__(kPhaseBlock) void contract_kernel(BatchParams P) {
     // the energy-histogram weights of the block's current shot (n_e + 2
     // words), read from LDS by every edge of every sample's law
     extern __shared__ double wsh[];
     __shared__ int64_t slot;
     __shared__ double red[kPhaseBlock / 64][kGradParams];
-    __shared__ float okey[GROUPED ? kChiGroup : 1];
-    __shared__ unsigned short oidx[GROUPED ? kChiGroup : 1];
     int s_w = -1;  // the shot whose weights wsh holds (block-uniform)
-    auto load_w = [&](int s, const ShotParams &sp) {
-        if (s == s_w) return;
-        // the previous item's reads ended at its reduction's barrier
-        const double *W = P.gouts[s].d_energy;
-        if (W)
-            for (int k = threadIdx.x; k < sp.n_e + 2; k += blockDim.x) wsh[k] = W[k];
-        __syncthreads();
-        s_w = s;
-    };
-    auto one = [&](const ShotParams &sp, int s, int64_t i, double *g) {
-        const int64_t n = P.tape_n;
-        const double *t = P.tape + sp.state_off + i;
-        const double mu = t[0], s2 = t[n];
-        if (mu > 0.0 && isfinite(mu) && isfinite(s2)) {
-            const ShotGrad &go = P.gouts[s];
-            double dm[kGradParams], ds[kGradParams], gi[kGradParams];
-#pragma unroll
-            for (int p = 0; p < kGradParams; ++p) {
-                dm[p] = t[(2 + p) * n];
-                ds[p] = t[(2 + kGradParams + p) * n];
-                gi[p] = 0.0;
-            }
-            if (go.d_energy) {
-                double lv, ls;
-                law_sensitivity(mu, s2, P.deposit, P.ksig_bins, sp.e_lo, sp.e_w, sp.n_e, wsh,
-                                lv, ls);
-#pragma unroll
-                for (int p = 0; p < kGradParams; ++p) gi[p] = fma(lv, dm[p], ls * ds[p]);
-            }
-            if (OBS) observable_sensitivity(P, sp, go, i, mu, s2, dm, ds, gi);
-#pragma unroll
-            for (int p = 0; p < kGradParams; ++p) g[p] += gi[p];
-        } else {
-            atomicOr(&P.flags[s], kFlagNonFinite);
-        }
-    };
     for (;;) {
         const int64_t item = next_item(&P.queue[0], &slot);
+        if (item >= P.n_items) break;
+        const int s = __builtin_amdgcn_readfirstlane(find_shot(P.shots, P.n_shots, item, false));
+        const ShotParams &sp = P.shots[s];
+        if (s != s_w) {
+            // the previous item's reads ended at its reduction's barrier
+            const double *W = P.gouts[s].d_energy;
+            if (W)
+                for (int k = threadIdx.x; k < sp.n_e + 2; k += blockDim.x) wsh[k] = W[k];
+            __syncthreads();
+            s_w = s;
+        }
         double g[kGradParams];
 #pragma unroll
         for (int p = 0; p < kGradParams; ++p) g[p] = 0.0;
-        if constexpr (GROUPED) {
-            if (item >= P.n_gitems) break;
-            const int s = __builtin_amdgcn_readfirstlane(find_group_shot(P.shots, P.n_shots, item));
-            const ShotParams &sp = P.shots[s];
-            const int64_t base = (item - sp.gitem0) * kChiGroup;
-            const int cnt = (int)min((int64_t)kChiGroup, sp.n_samples - base);
-            load_w(s, sp);
-            chi_order<kChiGroup, kPhaseBlock>(sp, P.key0, P.key1, base, sp.n_samples, okey, oidx);
-            for (int r = 0; r * kPhaseBlock < cnt; ++r) {
-                const int rank = r * kPhaseBlock + (int)threadIdx.x;
-                if (rank < cnt) one(sp, s, base + oidx[rank], g);
-            }
-        } else {
-            if (item >= P.n_items) break;
-            const int s = __builtin_amdgcn_readfirstlane(find_shot(P.shots, P.n_shots, item, false));
-            const ShotParams &sp = P.shots[s];
-            const int64_t i = (item - sp.item0) * kPhaseBlock + threadIdx.x;
-            load_w(s, sp);
-            if (i < sp.n_samples) one(sp, s, i, g);
-        }
+        const int64_t i = (item - sp.item0) * kPhaseBlock + threadIdx.x;
+        if (i < sp.n_samples && !contract_sample<OBS>(P, sp, s, i, wsh, g))
+            atomicOr(&P.flags[s], kFlagNonFinite);
         grad_item_reduce(P, item, g, red);
+    }
+}
+
+// The same for the tape of a pass with FP64 steps, a group of kChiGroup samples
+// at a time.  The tangent pass sums a group's terms a round of kPhaseBlock chi
+// ranks at a time; the tape is in sample order.  The terms are formed in sample
+// order (every tape line read once, whole) and go through LDS, from where
+// each round is summed as the tangent pass sums it, so that the result equals
+// the recomputing adjoint's bit for bit.  (Reading the tape in chi order fetched
+// every line about eight times: 2^21 samples 1283 -> 583 us with the order in a
+// kernel of its own.)
+constexpr int kContractBlock = 512;
+
+template <bool OBS>
+__global__ __launch_bounds__(kContractBlock) void contract_group_kernel(BatchParams P,
+                                                                        int lds_weights) {
+    extern __shared__ double terms[];  // [kGradParams][kChiGroup], then the shot's energy weights
+    double *wsh = terms + kGradParams * kChiGroup;
+    __shared__ int64_t slot;
+    __shared__ double red[kChiGroup / 64][kGradParams];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    int s_w = -1;  // the shot whose weights wsh holds (block-uniform)
+    for (;;) {
+        const int64_t group = next_item(&P.queue[0], &slot);
+        if (group >= P.n_gitems) break;
+        const int s = __builtin_amdgcn_readfirstlane(find_group_shot(P.shots, P.n_shots, group));
+        const ShotParams &sp = P.shots[s];
+        const int64_t base = (group - sp.gitem0) * kChiGroup;
+        const int cnt = (int)min((int64_t)kChiGroup, sp.n_samples - base);
+        const double *W = P.gouts[s].d_energy;
+        if (lds_weights && s != s_w && W)
+            for (int k = threadIdx.x; k < sp.n_e + 2; k += kContractBlock) wsh[k] = W[k];
+        s_w = s;
+        __syncthreads();  // (also: the previous group's terms have been summed)
+        for (int q = threadIdx.x; q < cnt; q += kContractBlock) {
+            double g[kGradParams];
+            if (!contract_sample<OBS>(P, sp, s, base + q, lds_weights ? wsh : W, g))
+                atomicOr(&P.flags[s], kFlagNonFinite);
+#pragma unroll
+            for (int p = 0; p < kGradParams; ++p) terms[p * kChiGroup + q] = g[p];
+        }
+        __syncthreads();
+        for (int k = wid; 64 * k < cnt; k += kContractBlock / 64) {  // wavefronts of chi ranks
+            const int r = 64 * k + lane;
+            const int q = r < cnt ? P.order[sp.state_off + base + r] : 0;
+#pragma unroll
+            for (int p = 0; p < kGradParams; ++p) {
+                const double v = wave_sum(r < cnt ? terms[p * kChiGroup + q] : 0.0);
+                if (lane == 0) red[k][p] = v;
+            }
+        }
+        __syncthreads();
+        constexpr int kWaves = kPhaseBlock / 64;
+        const int round = threadIdx.x / kGradParams, p = threadIdx.x % kGradParams;
+        if (round * kPhaseBlock < cnt) {
+            double sum = 0.0;
+            for (int w = 0; w < kWaves; ++w)
+                if (64 * (kWaves * round + w) < cnt) sum += red[kWaves * round + w][p];
+            P.partials[(size_t)(sp.item0 + base / kPhaseBlock + round) * kGradParams + p] = sum;
+        }
     }
 }
 
@@ -1136,11 +1164,7 @@ __global__ __launch_bounds__(256) void grad_finalize_kernel(BatchParams P) {
     const int s = blockIdx.x;
     const ShotParams &sp = P.shots[s];
     const ShotGrad &so = P.gouts[s];
-    // partials per group with FP64 steps, else per phase item
-    const bool grouped = P.prec == PREC_F32MIX;
-    const int64_t ni = grouped ? (sp.n_samples + kChiGroup - 1) / kChiGroup
-                               : (sp.n_samples + kPhaseBlock - 1) / kPhaseBlock;
-    const int64_t first = grouped ? sp.gitem0 : sp.item0;
+    const int64_t ni = (sp.n_samples + kPhaseBlock - 1) / kPhaseBlock, first = sp.item0;
     __shared__ double tree[256];
     for (int p = 0; p < kGradParams; ++p) {
         double acc = 0.0;
@@ -1235,9 +1259,8 @@ static const void *select_tangent(int prec, int rr, int amp) {
 hipError_t launch_tangent(const BatchParams &p, const float *env32, const double *env64, int prec,
                           int rr, int amp, bool tape, hipStream_t s) {
     const void *fn = tape ? select_tangent<true>(prec, rr, amp) : select_tangent<false>(prec, rr, amp);
-    const bool grouped = prec == PREC_F32MIX && rr == 1;
     int grid = 0;
-    hipError_t e = resident_grid(fn, kPhaseBlock, 0, grouped ? p.n_gitems : p.n_items, &grid);
+    hipError_t e = resident_grid(fn, kPhaseBlock, 0, p.n_items, &grid);
     if (e != hipSuccess) return e;
     BatchParams pc = p;
     const float *e32 = env32;
@@ -1247,20 +1270,27 @@ hipError_t launch_tangent(const BatchParams &p, const float *env32, const double
 }
 
 hipError_t launch_contract(const BatchParams &p, bool obs, int max_ne, hipStream_t s) {
-    // a tape of a pass with FP64 steps is summed over that pass's groups
+    // a tape of a pass with FP64 steps is summed over that pass's rounds
     const bool grouped = p.prec == PREC_F32MIX;
-    const void *fn =
-        grouped ? (obs ? reinterpret_cast<const void *>(&contract_kernel<true, true>)
-                       : reinterpret_cast<const void *>(&contract_kernel<false, true>))
-                : (obs ? reinterpret_cast<const void *>(&contract_kernel<true, false>)
-                       : reinterpret_cast<const void *>(&contract_kernel<false, false>));
-    const size_t lds = (size_t)(max_ne + 2) * sizeof(double);  // at most 32 KB (n_e <= 4096)
+    const void *fn = grouped ? (obs ? reinterpret_cast<const void *>(&contract_group_kernel<true>)
+                                    : reinterpret_cast<const void *>(&contract_group_kernel<false>))
+                             : (obs ? reinterpret_cast<const void *>(&contract_kernel<true>)
+                                    : reinterpret_cast<const void *>(&contract_kernel<false>));
+    const int block = grouped ? kContractBlock : kPhaseBlock;
+    // the energy weights in LDS: at most 32 KB (n_e <= 4096); beside a group's
+    // terms (128 KB) those that fit, else they are read from memory
+    const size_t wb = (size_t)(max_ne + 2) * sizeof(double);
+    int lds_weights = grouped ? wb <= 24 * 1024 : 1;
+    const size_t lds = (grouped ? (size_t)kGradParams * kChiGroup * sizeof(double) : 0) +
+                       (lds_weights ? wb : 0);
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     int grid = 0;
-    hipError_t e = resident_grid(fn, kPhaseBlock, lds, grouped ? p.n_gitems : p.n_items, &grid);
+    if (e == hipSuccess)
+        e = resident_grid(fn, block, lds, grouped ? p.n_gitems : p.n_items, &grid);
     if (e != hipSuccess) return e;
     BatchParams pc = p;
-    void *args[] = {&pc};
-    return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(kPhaseBlock), args, lds, s);
+    void *args[] = {&pc, &lds_weights};  // (the ungrouped kernel takes the first)
+    return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(block), args, lds, s);
 }
 
 hipError_t launch_grad_finalize(const BatchParams &p, hipStream_t s) {

@@ -60,6 +60,8 @@ struct qs_ctx {
     size_t shadow_cap = 0;
     unsigned char *states = nullptr;  // per-sample final states (SampleState arrays)
     size_t states_cap = 0;
+    uint16_t *order = nullptr;  // chi order of the samples (passes with FP64 steps)
+    size_t order_cap = 0;
     // per-shot tables: pinned staging on the host, a device copy.  Calls
     // take the staging blocks in turn, so the host can stage a call while
     // the copies of the kStageSlots - 1 calls before it still wait on the
@@ -105,8 +107,8 @@ struct qs_ctx {
 // the per-sample final states (6 double arrays and 1 float array of
 // QS_NOALLOC_MAX_SAMPLES), the FP64 and FP32 envelope tables (2 n_steps + 1
 // points at the largest n_steps), the accumulators (work counters, the status
-// flags, the histogram words of the largest bins), the moment partials (one
-// row per 1024-sample tile) and the device copy of the shot table.
+// flags, the histogram words of the largest bins), the moment partials, the chi
+// order of the samples and the device copy of the shot table.
 namespace na {
 constexpr size_t r256(size_t n) { return (n + 255) / 256 * 256; }
 constexpr size_t kSamples = QS_NOALLOC_MAX_SAMPLES;
@@ -122,7 +124,8 @@ constexpr size_t kEnv64Off = kStatesOff + 6 * kArr + kArrf;
 constexpr size_t kEnv32Off = kEnv64Off + r256(kEnvPoints * 8);
 constexpr size_t kAccumOff = kEnv32Off + r256(kEnvPoints * 4);
 constexpr size_t kPartOff = kAccumOff + r256(kAccumWords * 8);
-constexpr size_t kTabOff = kPartOff + r256(kPartWords * 8);
+constexpr size_t kOrderOff = kPartOff + r256(kPartWords * 8);
+constexpr size_t kTabOff = kOrderOff + r256(kSamples * sizeof(uint16_t));
 constexpr size_t kTabBytes = r256(sizeof(qs::ShotParams) + sizeof(qs::ShotOut));
 constexpr size_t kBytes = kTabOff + kTabBytes;
 static_assert(kBytes < ((size_t)56 << 20), "the no-allocation scratch stays under 56 MiB");
@@ -477,6 +480,7 @@ void qs_destroy(qs_ctx *c) {
         (void)hipFree(c->partials);
         (void)hipFree(c->shadow);
         (void)hipFree(c->states);
+        (void)hipFree(c->order);
         (void)hipFree(c->shot_tab);
         for (int k = 0; k < kStageSlots; ++k) {
             if (c->stage[k]) (void)hipHostFree(c->stage[k]);
@@ -1097,7 +1101,9 @@ qs_status forward_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_b
     double *env64 = nullptr;
     unsigned long long *accum = nullptr;
     double *partials = nullptr;
+    uint16_t *order = nullptr;
     unsigned char *states = nullptr, *shot_tab = nullptr;
+    const bool ordered = b.prec == qs::PREC_F32MIX;  // FP64 steps: samples in chi order
     if (noalloc) {
         // one shot, no shadow, no tape: every part fits its slot of `scratch`
         // (the sizes were validated; these checks keep the carve honest)
@@ -1111,6 +1117,7 @@ qs_status forward_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_b
         env32 = reinterpret_cast<float *>(base + na::kEnv32Off);
         accum = reinterpret_cast<unsigned long long *>(base + na::kAccumOff);
         partials = reinterpret_cast<double *>(base + na::kPartOff);
+        order = reinterpret_cast<uint16_t *>(base + na::kOrderOff);
         states = base + na::kStatesOff;
         shot_tab = base + na::kTabOff;
     } else {
@@ -1124,8 +1131,11 @@ qs_status forward_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_b
         if ((st = grow(c, &c->states, &c->states_cap, 6 * arr + arrf + 6 * sarr + sarrf,
                        "sample states")) != QS_OK)
             return st;
+        if (ordered && (st = grow(c, &c->order, &c->order_cap, (size_t)b.total, "chi order")) != QS_OK)
+            return st;
         if ((st = grow(c, &c->shot_tab, &c->shot_tab_cap, b.tab_bytes, "shot table")) != QS_OK)
             return st;
+        order = c->order;
         env32 = c->env32;
         env64 = c->env64;
         accum = c->accum;
@@ -1139,6 +1149,7 @@ qs_status forward_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_b
     bp.rad64 = c->rad64;
     bp.rad32d = c->rad32d;
     bp.rad64d = c->rad64d;
+    bp.order = ordered ? order : nullptr;
     bp.st.mu = reinterpret_cast<double *>(states);
     bp.st.s2 = reinterpret_cast<double *>(states + arr);
     bp.st.S0 = reinterpret_cast<double *>(states + 2 * arr);
@@ -1185,6 +1196,8 @@ qs_status forward_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_b
         if ((e = qs::launch_zero(accum, accum_words, q)) != hipSuccess)
             return hip_fail(c, e, "zero kernel");
         if ((e = mark(2)) != hipSuccess) return hip_fail(c, e, "event record");
+        if (ordered && (e = qs::launch_order(bp, q)) != hipSuccess)
+            return hip_fail(c, e, "order kernel");
         if (tape) {
             // the forward pass that also records the parameter derivatives
             if ((e = qs::launch_tangent(bp, env32, env64, b.prec, N->rr_model, N->amp_mode,
@@ -1340,6 +1353,9 @@ qs_status backward_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_
     if ((st = grow(c, &c->partials, &c->part_cap, (size_t)bp.n_items * qs::kGradParams,
                    "gradient partials")) != QS_OK)
         return st;
+    const bool ordered = b.prec == qs::PREC_F32MIX;  // FP64 steps: samples in chi order
+    if (ordered && (st = grow(c, &c->order, &c->order_cap, (size_t)b.total, "chi order")) != QS_OK)
+        return st;
     if ((st = grow(c, &c->shot_tab, &c->shot_tab_cap, b.tab_bytes, "shot table")) != QS_OK)
         return st;
     bp.shots = reinterpret_cast<const qs::ShotParams *>(c->shot_tab);
@@ -1354,6 +1370,7 @@ qs_status backward_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_
     bp.partials = c->partials;
     bp.tape = const_cast<double *>(tape);  // read only by the contraction kernel
     bp.tape_n = b.total;
+    bp.order = ordered ? c->order : nullptr;
 
     hipError_t e;
     if ((st = upload_batch(c, b, s)) != QS_OK) return st;
@@ -1362,6 +1379,8 @@ qs_status backward_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_
         return hip_fail(c, e, "envelope kernel");
     if ((e = qs::launch_zero(c->accum, accum_words, s)) != hipSuccess)
         return hip_fail(c, e, "zero kernel");
+    if (ordered && (e = qs::launch_order(bp, s)) != hipSuccess)
+        return hip_fail(c, e, "order kernel");
     if (tape) {
         bool obs = false;
         int max_ne = 1;
@@ -1513,6 +1532,11 @@ qs_status photons_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_b
     if ((st = grow(c, &c->partials, &c->part_cap, (size_t)pitem * qs::kPhotPartials,
                    "photon partials")) != QS_OK)
         return st;
+    static_assert(qs::kPhotTile == qs::kChiGroup, "a photon item takes a group in chi order");
+    const bool ordered = b.prec == qs::PREC_F32MIX;  // FP64 steps: samples in chi order
+    if (ordered && (st = grow(c, &c->order, &c->order_cap, (size_t)b.total, "chi order")) != QS_OK)
+        return st;
+    bp.order = ordered ? c->order : nullptr;
     if ((st = grow(c, &c->shot_tab, &c->shot_tab_cap, b.tab_bytes, "shot table")) != QS_OK)
         return st;
     bp.shots = reinterpret_cast<const qs::ShotParams *>(c->shot_tab);
@@ -1533,6 +1557,8 @@ qs_status photons_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_b
         return hip_fail(c, e, "envelope kernel");
     if ((e = qs::launch_zero(c->accum, accum_words, s)) != hipSuccess)
         return hip_fail(c, e, "zero kernel");
+    if (ordered && (e = qs::launch_order(bp, s)) != hipSuccess)
+        return hip_fail(c, e, "order kernel");
     if ((e = qs::launch_photon(bp, c->env32, c->env64, b.prec, N->rr_model, N->amp_mode, s)) !=
         hipSuccess)
         return hip_fail(c, e, "photon kernel");

@@ -466,17 +466,11 @@ __device__ __forceinline__ void draw_sample(const ShotParams &sp, uint32_t key0,
     S0 = sp.plane_wave ? 1.0 : pd.S(0.0);
 }
 
-// Order in which the lanes of a block take the G consecutive samples of a
-// group (from `base`) in passes with FP64 steps where chi exceeds a
-// threshold.  A wavefront steps in FP64 when any of its lanes needs it, so its
-// lanes should hold samples of similar chi: they take the samples in
-// increasing order of S0 gamma0, the chi scale of a sample at its collision
-// point.  The order is stable (ties by index), so every launch of a group
-// forms the same wavefronts.  s_idx[r] receives the group offset of rank r;
-// offsets at or past `end` (no sample) rank last.  B threads take part.
-// An FP32 estimate of that key, for passes whose results do not depend on the
-// order (no FP64 steps): the first counter block's normals by Box-Muller in
-// FP32, the collision point without the divergence's shift (below 1e-2 um).
+// Order in which the lanes of a block take the samples of an FP32 pass: by an
+// FP32 estimate of the chi scale S0 gamma0 of a sample at its collision point
+// (the first counter block's normals by Box-Muller in FP32, the collision
+// point without the divergence's shift, below 1e-2 um).  The results of these
+// passes do not depend on the order.
 __device__ __forceinline__ float chi_key32(const ShotParams &sp, uint32_t k0, uint32_t k1,
                                            int64_t i) {
     uint32_t c[4] = {(uint32_t)(i * (int64_t)sp.draw_stride), (uint32_t)sp.shot_word, 0u, 0u};
@@ -497,31 +491,18 @@ __device__ __forceinline__ float chi_key32(const ShotParams &sp, uint32_t k0, ui
     return g0 * spatial(x, y, fmaf(0.5f, z, (float)sp.z_delay), sp.inv_w0sqf, sp.inv_zRf);
 }
 
-// FAST: the FP32 key (passes without FP64 steps, where any order gives the same
-// results); else the FP64 one.
-template <int G, int B, bool FAST = false>
-__device__ __forceinline__ void chi_order(const ShotParams &sp, uint32_t key0, uint32_t key1,
-                                          int64_t base, int64_t end, float *s_key,
-                                          unsigned short *s_idx) {
+// Order of the G samples from `base` on by chi_key32 (stable: ties by index);
+// s_idx[r] receives the offset of rank r; offsets at or past `end` (no sample)
+// rank last.  B threads take part.
+template <int G, int B>
+__device__ __forceinline__ void chi_order32(const ShotParams &sp, uint32_t key0, uint32_t key1,
+                                            int64_t base, int64_t end, float *s_key,
+                                            unsigned short *s_idx) {
     static_assert(G % B == 0 && G <= 65536, "group of whole rounds, 16-bit offsets");
     __syncthreads();  // the previous group's order is no longer read
     for (int q = threadIdx.x; q < G; q += B) {
-        float key = __builtin_inff();
         const int64_t i = base + q;
-        if (i < end) {
-            if constexpr (FAST) {
-                key = chi_key32(sp, key0, key1, i);
-            } else {
-                // (the Gaussian focus's factor also orders samples of a higher
-                // mode: any order gives the same results up to the FP64-step
-                // choice)
-                double g0, thx, thy, S0;
-                Path<double, false> pd{};
-                draw_sample<false>(sp, key0, key1, i, g0, thx, thy, pd, S0);
-                key = (float)(S0 * g0);
-            }
-        }
-        s_key[q] = key;
+        s_key[q] = i < end ? chi_key32(sp, key0, key1, i) : __builtin_inff();
     }
     __syncthreads();
     for (int q = threadIdx.x; q < G; q += B) {
@@ -534,6 +515,14 @@ __device__ __forceinline__ void chi_order(const ShotParams &sp, uint32_t key0, u
         s_idx[rank] = (unsigned short)q;
     }
     __syncthreads();
+}
+
+// Sample of lane rank `rank` of a group of cnt samples from `base` on of a shot
+// in a pass with FP64 steps (order_kernel); ranks at or past cnt (no sample)
+// take the last rank's.
+__device__ __forceinline__ int64_t ordered_sample(const BatchParams &P, const ShotParams &sp,
+                                                  int64_t base, int cnt, int rank) {
+    return base + P.order[sp.state_off + base + min(rank, cnt - 1)];
 }
 
 // One RK4 step of (mu, sig2) from psi_j with amplitudes a1 = a(psi_j),

@@ -63,11 +63,11 @@ constexpr int kDepItems = 512;    // smaller items below this many of them (defa
 constexpr int kMomTile = 1024;
 constexpr int kMomRow = kDepBlock;
 constexpr int kPartials = P_N + 3;  // moment sums and maxima of a moment tile
-// Passes with FP64 steps (forward, tape forward, adjoint, and the
-// contraction of their tapes): a work item is a group of up to kChiGroup
-// samples of one shot, which the block takes in rounds of kPhaseBlock in
-// order of their chi scale, so that wavefronts hold samples of similar chi
-// over a wider pool than one phase item; gradient partials are per group.
+// Passes with FP64 steps (forward, tape forward, adjoint, the contraction of
+// their tapes, photons): the samples of a group of up to kChiGroup consecutive
+// samples of one shot are taken in order of their chi scale (order_kernel), so
+// that wavefronts hold samples of similar chi over a wider pool than one work
+// item; a work item is a round of kPhaseBlock of them (photons: its own round).
 constexpr int kChiGroup = 2048;
 constexpr int kMoments = 21;        // moments a shot returns (QS_M_N)
 
@@ -101,7 +101,7 @@ struct ShotParams {
     int64_t item0;       // its first phase work item
     int64_t ditem0;      // its first deposit work item
     int64_t mtile0;      // its first moment row (BatchParams::mom_row samples each)
-    int64_t gitem0;      // its first group (kChiGroup samples) of the passes with FP64 steps
+    int64_t gitem0;      // its first group (kChiGroup samples) in passes with FP64 steps
     int64_t hist_off;    // its first histogram word in the accumulators
     // FP64 shadow: samples i with i % shadow_stride == 0 have the FP64 state
     // shadow_off + i / shadow_stride (shadow_stride 0: none); a shot view
@@ -211,6 +211,8 @@ struct BatchParams {
     int64_t n_gitems;   // groups of the passes with FP64 steps
     const ShotParams *shots;
     const ShotOut *outs;
+    uint16_t *order;      // passes with FP64 steps: sample state_off + (group start) + r holds
+                          // the offset in its group of the sample of chi rank r
     const float *rad32;   // [kCells32 * 16]
     const double *rad64;  // [kCells64 * 16]
     const float *rad32d;  // [kCells32 * 4 * kDerivFuncs]
@@ -235,7 +237,6 @@ struct BatchParams {
     unsigned long long *fp64_steps;  // [n_shots]: wavefront phase steps taken in FP64 by
                                      // the forward pass's FP32 loop (null: not counted)
     double *partials;              // [kPartials][n_mtiles]; adjoint: [n_items][kGradParams]
-                                   // ([n_gitems][kGradParams] with FP64 steps)
 };
 
 // ---- launchers (qs_kernels.hip) -------------------------------------------
@@ -245,6 +246,7 @@ size_t radiation_work_doubles();
 hipError_t launch_envelope(double psi_max, double h, int n_steps, int envelope, double omega_tau,
                            float *env32, double *env64, hipStream_t s);
 hipError_t launch_zero(unsigned long long *p, size_t n64, hipStream_t s);
+hipError_t launch_order(const BatchParams &p, hipStream_t s);
 hipError_t launch_phase(const BatchParams &p, const float *env32, const double *env64, int prec,
                         int rr, int amp, hipStream_t s);
 size_t deposit_lds_bytes(int max_hist_words);

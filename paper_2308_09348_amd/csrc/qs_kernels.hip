@@ -262,14 +262,13 @@ __attribute__((amdgpu_waves_per_eu((PREC == PREC_F32 && QUANTUM) ? 4 : 1))) void
     __shared__ double2 stage[kWave64 ? (kPhaseBlock / 64) * kStageChunks : 1];
     __shared__ int64_t slot;
     // FP32 passes: the lanes take the item's samples in order of their chi
-    // scale (chi_order), so that neighbouring lanes read nearby table cells;
-    // with FP64 steps the work items are groups of kChiGroup samples taken in
-    // rounds in that order, so that wavefronts step alike
-    constexpr bool kOrder = PREC != PREC_F64 && QUANTUM && !NODES;
+    // scale (chi_order32), so that neighbouring lanes read nearby table cells;
+    // with FP64 steps an item is a round of a group's samples in that order
+    // (order_kernel), so that wavefronts step alike
+    constexpr bool kOrder = PREC == PREC_F32 && QUANTUM && !NODES;
     constexpr bool kGroup = PREC == PREC_F32MIX && QUANTUM && !NODES;
-    constexpr int kOrderN = kGroup ? kChiGroup : kPhaseBlock;
-    __shared__ float okey[kOrder ? kOrderN : 1];
-    __shared__ unsigned short oidx[kOrder ? kOrderN : 1];
+    __shared__ float okey[kOrder ? kPhaseBlock : 1];
+    __shared__ unsigned short oidx[kOrder ? kPhaseBlock : 1];
     if (kTab32) {
         const float4 *src = reinterpret_cast<const float4 *>(P.rad32);
         float4 *dst = reinterpret_cast<float4 *>(tab32);
@@ -294,30 +293,23 @@ __attribute__((amdgpu_waves_per_eu((PREC == PREC_F32 && QUANTUM) ? 4 : 1))) void
     int s_prev = 0;  // the shot of the block's previous item
     for (;;) {
         const int64_t item = next_item(&P.queue[0], &slot);
+        if (item >= P.n_items) break;
+        const int s = __builtin_amdgcn_readfirstlane(
+            find_shot_from(P.shots, P.n_shots, item, false, s_prev));
+        s_prev = s;
+        const ShotParams &sp = P.shots[s];
         if constexpr (kGroup) {
-            if (item >= P.n_gitems) break;
-            const int s = __builtin_amdgcn_readfirstlane(find_group_shot(P.shots, P.n_shots, item));
-            const ShotParams &sp = P.shots[s];
-            const int64_t base = (item - sp.gitem0) * kChiGroup;
+            const int64_t first = (item - sp.item0) * kPhaseBlock, base = first & ~(kChiGroup - 1ll);
             const int cnt = (int)min((int64_t)kChiGroup, sp.n_samples - base);
-            chi_order<kChiGroup, kPhaseBlock>(sp, P.key0, P.key1, base, sp.n_samples, okey, oidx);
-            for (int r = 0; r * kPhaseBlock < cnt; ++r) {
-                const int rank = r * kPhaseBlock + (int)threadIdx.x;
-                if (r * kPhaseBlock + (int)(threadIdx.x & ~63u) >= cnt) continue;  // whole wavefront
-                const bool live = rank < cnt;
-                one(sp, s, base + oidx[live ? rank : cnt - 1], live);
-            }
+            const int rank = (int)(first - base) + (int)threadIdx.x;
+            if ((rank & ~63) < cnt)  // some lane of the wavefront has a sample
+                one(sp, s, ordered_sample(P, sp, base, cnt, rank), rank < cnt);
         } else {
-            if (item >= P.n_items) break;
-            const int s = __builtin_amdgcn_readfirstlane(
-                find_shot_from(P.shots, P.n_shots, item, false, s_prev));
-            s_prev = s;
-            const ShotParams &sp = P.shots[s];
             const int64_t base = (item - sp.item0) * kPhaseBlock;
             int off = threadIdx.x;
             if constexpr (kOrder) {
-                chi_order<kPhaseBlock, kPhaseBlock, true>(sp, P.key0, P.key1, base, sp.n_samples,
-                                                          okey, oidx);
+                chi_order32<kPhaseBlock, kPhaseBlock>(sp, P.key0, P.key1, base, sp.n_samples, okey,
+                                                      oidx);
                 off = oidx[threadIdx.x];
             }
             const int64_t i = base + off;
@@ -819,6 +811,63 @@ __global__ void envelope_kernel(double psi_max, double h, int n_steps, int envel
     env32[k] = (float)e;
 }
 
+// Passes with FP64 steps.  A wavefront steps in FP64 when any of its lanes
+// needs it, so its lanes should hold samples of similar chi: the samples of a
+// group are taken in increasing order of S0 gamma0, the chi scale of a sample
+// at its collision point (ties by index; the Gaussian focus's factor also
+// orders samples of a higher mode: any order gives the same results up to the
+// FP64-step choice).  One block a group: keys from the FP64 draw, then a
+// bitonic sort in LDS of (key, offset) words, padded to a power of two.
+// A kernel of its own, so that the rounds of a group can go to any blocks of
+// the pass (a group a block left most CUs idle below 2^20 samples: 2^18 samples
+// of a quantum shot, 2048 steps, 15.0 -> 6.4 ms), and the pass keeps no LDS for
+// it.  28 us for 128 groups, 110 us for 1024, about half of it the FP64 draws (the
+// rank by 2048 comparisons a sample that a group took in the pass: 140 us).
+constexpr int kOrderBlock = kChiGroup / 2;
+
+__global__ __launch_bounds__(kOrderBlock) void order_kernel(BatchParams P) {
+    __shared__ unsigned long long w[kChiGroup];
+    const int64_t group = blockIdx.x;
+    const int s = __builtin_amdgcn_readfirstlane(find_group_shot(P.shots, P.n_shots, group));
+    const ShotParams &sp = P.shots[s];
+    const int64_t base = (group - sp.gitem0) * kChiGroup;
+    const int cnt = (int)min((int64_t)kChiGroup, sp.n_samples - base);
+    int m = 64;  // words sorted
+    while (m < cnt) m <<= 1;
+    for (int q = threadIdx.x; q < m; q += kOrderBlock) {
+        uint32_t key = 0xffffffffu;  // past the samples
+        if (q < cnt) {
+            double g0, thx, thy, S0;
+            Path<double, false> pd{};
+            draw_sample<false>(sp, P.key0, P.key1, base + q, g0, thx, thy, pd, S0);
+            // the float's bits in increasing order (+0: one zero)
+            const uint32_t b = __float_as_uint((float)(S0 * g0) + 0.0f);
+            key = b & 0x80000000u ? ~b : b | 0x80000000u;
+        }
+        w[q] = ((unsigned long long)key << 32) | (unsigned int)q;
+    }
+    __syncthreads();
+    for (int k = 2; k <= m; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            // pairs at most 64 apart stay within the 128 words of a wavefront
+            if (j >= 64)
+                __syncthreads();
+            else
+                wave_sync_lds();
+            if (threadIdx.x < m / 2) {
+                const int t = (int)threadIdx.x, a = ((t & -j) << 1) | (t & (j - 1)), b = a + j;
+                const unsigned long long x = w[a], y = w[b];
+                if ((x > y) == ((a & k) == 0)) {
+                    w[a] = y;
+                    w[b] = x;
+                }
+            }
+        }
+    __syncthreads();
+    for (int q = threadIdx.x; q < cnt; q += kOrderBlock)
+        P.order[sp.state_off + base + q] = (uint16_t)w[q];
+}
+
 __global__ void zero_kernel(unsigned long long *p, size_t n) {
     for (size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x; k < n;
          k += (size_t)gridDim.x * blockDim.x)
@@ -840,6 +889,13 @@ hipError_t launch_zero(unsigned long long *p, size_t n64, hipStream_t s) {
     if (n64 == 0) return hipSuccess;
     const int grid = (int)((n64 + 255) / 256 < 1024 ? (n64 + 255) / 256 : 1024);
     zero_kernel<<<grid, 256, 0, s>>>(p, n64);
+    return hipGetLastError();
+}
+
+hipError_t launch_order(const BatchParams &p, hipStream_t s) {
+    if (p.n_gitems < 1) return hipSuccess;
+    if (p.n_gitems > (int64_t)INT_MAX) return hipErrorInvalidValue;  // (2^36 samples: 2^25)
+    order_kernel<<<(unsigned)p.n_gitems, kOrderBlock, 0, s>>>(p);
     return hipGetLastError();
 }
 
@@ -874,11 +930,8 @@ hipError_t launch_phase(const BatchParams &p, const float *env32, const double *
                         int rr, int amp, hipStream_t s) {
     const void *fn = select_phase(prec, rr, amp, p.any_mode != 0);
     if (!fn) return hipErrorInvalidValue;
-    // FP64 steps: work items are groups of kChiGroup samples
-    const bool grouped = prec == PREC_F32MIX && rr == 1;
     int grid = 0;
-    hipError_t e =
-        resident_grid(fn, kPhaseBlock, 0, grouped ? p.n_gitems : p.n_items, &grid, p.phase_cap);
+    hipError_t e = resident_grid(fn, kPhaseBlock, 0, p.n_items, &grid, p.phase_cap);
     if (e != hipSuccess) return e;
     BatchParams pc = p;
     const float *e32 = env32;

@@ -145,3 +145,29 @@ def test_mixed_batch_equals_single_shots(gpu):
         assert torch.equal(grads[k], gpu.backward(q, ws[k], tape=t1)), k
         assert torch.equal(again[k], grads[k]), k
         off += s["n_samples"]
+
+
+@pytest.mark.parametrize("n_e", [200, 4096])
+@pytest.mark.parametrize("n", [1, 64, 65, 257, 2047, 2049, 4097])
+def test_mixed_rounds_of_a_group(gpu, n, n_e):
+    """The samples of a group of 2048 are taken in chi order, 256 a work item,
+    and the tape is contracted a group at a time (energy weights in LDS, or
+    from memory above 3070 bins): every sample is taken (its record holds its own
+    draw, as in the FP64 pass, which takes them in sample order), and the
+    adjoint from the tape is the recomputing adjoint's bit for bit."""
+    import torch
+    p = _case(n_samples=n, n_steps=96, n_e=n_e, deposit="cic")
+    tape = gpu.new_tape(n).fill_(float("nan"))
+    out = gpu.forward(p, tape=tape)
+    assert torch.isfinite(tape).all()
+    plain = gpu.forward(p, sample_stride=1, n_sample_records=n)
+    ref = gpu.forward(dict(p, precision="fp64"), sample_stride=1, n_sample_records=n)
+    for col in (2, 3, 5, 7):  # both angles, a0,eff, gamma0
+        assert torch.equal(plain["samples"][:, col], ref["samples"][:, col]), col
+    assert plain["energy_hist"].sum().item() == pytest.approx(n, abs=1e-6)
+    kw = dict(d_angle=_t(_weights(p["n_th"], 3)), d_moments=_t(np.linspace(0.1, 1.0, 21)),
+              moments=out["moments"])
+    for more in ({}, kw):
+        w = _t(_weights(n_e))
+        a, b = gpu.backward(p, w, **more), gpu.backward(p, w, tape=tape, **more)
+        assert torch.isfinite(a).all() and torch.equal(a, b), (a, b)
