@@ -1023,8 +1023,11 @@ __attribute__((amdgpu_waves_per_eu((TAPE && PREC == PREC_F32) ? 3 : 2))) void ta
         if (item >= P.n_items) break;
         const int s = __builtin_amdgcn_readfirstlane(find_shot(P.shots, P.n_shots, item, false));
         const ShotParams &sp = P.shots[s];
+        int64_t row = item;  // of the gradient partials: the shot's round
         if constexpr (kWave64) {
-            const int64_t first = (item - sp.item0) * kPhaseBlock, base = first & ~(kChiGroup - 1ll);
+            const int64_t first = ordered_round<kPhaseBlock>(sp.n_samples, item - sp.item0);
+            const int64_t base = first & ~(kChiGroup - 1ll);
+            row = sp.item0 + first / kPhaseBlock;
             const int cnt = (int)min((int64_t)kChiGroup, sp.n_samples - base);
             const int rank = (int)(first - base) + (int)threadIdx.x;
             if ((rank & ~63) < cnt)  // some lane of the wavefront has a sample
@@ -1033,7 +1036,7 @@ __attribute__((amdgpu_waves_per_eu((TAPE && PREC == PREC_F32) ? 3 : 2))) void ta
             const int64_t i = (item - sp.item0) * kPhaseBlock + threadIdx.x;
             if (i < sp.n_samples) one(sp, s, i, true, g);
         }
-        if (!TAPE) grad_item_reduce(P, item, g, red);
+        if (!TAPE) grad_item_reduce(P, row, g, red);
     }
 }
 

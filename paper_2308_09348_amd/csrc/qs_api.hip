@@ -1469,7 +1469,9 @@ qs_status photons_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_b
     // cos^2-weighted one), for the classical-loss bound of the energy range
     const double I2 = L[0].envelope == QS_ENV_GAUSS ? b.omega_tau * std::sqrt(kPi / (4.0 * std::log(2.0)))
                                                     : 0.75 * b.omega_tau;
-    int64_t pitem = 0;
+    const int block = qs::phot_block(b.prec);
+    int64_t pitem = 0, edges = 0;
+    int max_edges = 0;
     for (int k = 0; k < n_shots; ++k) {
         qs::ShotPhot &p = sph[k];
         p = qs::ShotPhot{};
@@ -1519,7 +1521,10 @@ qs_status photons_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_b
         p.errors = shadow ? nullptr : PO[k].errors;
         p.pitem0 = pitem;
         p.grid_off = (int64_t)k * qs::kPhNodes;
-        pitem += (n_samples[k] + qs::kPhotTile - 1) / qs::kPhotTile;
+        p.s_off = edges;
+        pitem += (n_samples[k] + block - 1) / block;
+        edges += PB[k].n_ph + 2;
+        max_edges = std::max(max_edges, PB[k].n_ph + 2);
     }
     bp.n_pitems = pitem;
 
@@ -1529,10 +1534,10 @@ qs_status photons_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_b
     if ((st = grow(c, &c->env32, &c->env32_cap, nenv, "envelope table")) != QS_OK) return st;
     if ((st = grow(c, &c->env64, &c->env64_cap, nenv, "envelope table")) != QS_OK) return st;
     if ((st = grow(c, &c->accum, &c->accum_cap, accum_words, "accumulators")) != QS_OK) return st;
-    if ((st = grow(c, &c->partials, &c->part_cap, (size_t)pitem * qs::kPhotPartials,
+    const size_t part_words = (size_t)pitem * qs::kPhotPartials;
+    if ((st = grow(c, &c->partials, &c->part_cap, part_words + (size_t)edges,
                    "photon partials")) != QS_OK)
         return st;
-    static_assert(qs::kPhotTile == qs::kChiGroup, "a photon item takes a group in chi order");
     const bool ordered = b.prec == qs::PREC_F32MIX;  // FP64 steps: samples in chi order
     if (ordered && (st = grow(c, &c->order, &c->order_cap, (size_t)b.total, "chi order")) != QS_OK)
         return st;
@@ -1549,6 +1554,7 @@ qs_status photons_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_b
     bp.flags = reinterpret_cast<int *>(c->accum + 1);
     bp.pgrid = c->accum + 1 + flag_words;
     bp.partials = c->partials;
+    bp.psum = c->partials + part_words;
 
     hipError_t e;
     if ((st = upload_batch(c, b, s)) != QS_OK) return st;
@@ -1563,7 +1569,7 @@ qs_status photons_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_b
         hipSuccess)
         return hip_fail(c, e, "photon kernel");
     const double c_ph = kAlpha * aS / (2.0 * std::sqrt(3.0) * kPi);
-    if ((e = qs::launch_photon_finalize(bp, c_ph, s)) != hipSuccess)
+    if ((e = qs::launch_photon_finalize(bp, max_edges, c_ph, s)) != hipSuccess)
         return hip_fail(c, e, "photon finalize kernel");
     if (view ? view->report : want_err && !shadow) {
         // the report of the view passes, or zeros

@@ -157,7 +157,9 @@ constexpr size_t kPhTabBytes = sizeof(double) * kPhCellOff + sizeof(float) * 4 *
 // r_lo .. r_lo + nu - 1) x kPhNV columns (t = sqrt(mu), uniform), weights
 // in fixed point.
 constexpr int kPhNU = 64, kPhNV = 64, kPhNodes = kPhNU * kPhNV;
-constexpr int kPhotTile = 2048;          // one photon work item = kPhotTile samples
+// Samples of a photon work item: one a lane of a block (twice as many in passes
+// with FP64 steps).
+constexpr int phot_block(int prec) { return prec == PREC_F32MIX ? 512 : 256; }
 // photon energy, electron loss, soft weight; then the Sec. 5.1 angular sums:
 // number, number x theta_x^2, number x theta_y^2, energy, energy x theta_x^2,
 // energy x theta_y^2
@@ -174,6 +176,7 @@ struct ShotPhot {
     int32_t *status;             // optional
     double *angles;              // optional [6]: Sec. 5.1 photon angular moments
     int64_t pitem0;              // first photon work item
+    int64_t s_off;               // its edge sums [n_ph + 2] (BatchParams::psum)
     int64_t grid_off;            // its grid in the accumulators (kPhNodes words)
     double *errors;              // optional [14]: FP64-shadow report of the shot
 };
@@ -222,6 +225,7 @@ struct BatchParams {
     const double *phtab;    // photon CDF table
     unsigned long long *pgrid;  // per-shot emission grids
     int64_t n_pitems;
+    double *psum;            // per shot: the spectrum's cumulative sums at the bin edges
     double *tape;           // derivative tape: [2 + 2 kGradParams][tape_n]
     int64_t tape_n;         // samples over the batch (tape field stride)
     SampleState st;
@@ -236,7 +240,8 @@ struct BatchParams {
     unsigned int *queue;           // [2]: phase and deposit work counters
     unsigned long long *fp64_steps;  // [n_shots]: wavefront phase steps taken in FP64 by
                                      // the forward pass's FP32 loop (null: not counted)
-    double *partials;              // [kPartials][n_mtiles]; adjoint: [n_items][kGradParams]
+    double *partials;              // [kPartials][n_mtiles]; adjoint: [n_items][kGradParams];
+                                   // photons: [kPhotPartials][n_pitems]
 };
 
 // ---- launchers (qs_kernels.hip) -------------------------------------------
@@ -265,7 +270,8 @@ size_t photon_work_doubles();
 hipError_t build_photon_table(double *phtab, double *work, size_t work_doubles, hipStream_t s);
 hipError_t launch_photon(const BatchParams &p, const float *env32, const double *env64, int prec,
                          int rr, int amp, hipStream_t s);
-hipError_t launch_photon_finalize(const BatchParams &p, double c_ph, hipStream_t s);
+hipError_t launch_photon_finalize(const BatchParams &p, int max_edges, double c_ph,
+                                  hipStream_t s);
 // FP64-shadow report of a photon pass: the batch is the FP64 view pass, whose
 // outputs sit `span` doubles after those of the FP32 view pass; span 0 writes
 // zeros (no shadow).  One block per shot with errors.

@@ -299,7 +299,8 @@ __attribute__((amdgpu_waves_per_eu((PREC == PREC_F32 && QUANTUM) ? 4 : 1))) void
         s_prev = s;
         const ShotParams &sp = P.shots[s];
         if constexpr (kGroup) {
-            const int64_t first = (item - sp.item0) * kPhaseBlock, base = first & ~(kChiGroup - 1ll);
+            const int64_t first = ordered_round<kPhaseBlock>(sp.n_samples, item - sp.item0);
+            const int64_t base = first & ~(kChiGroup - 1ll);
             const int cnt = (int)min((int64_t)kChiGroup, sp.n_samples - base);
             const int rank = (int)(first - base) + (int)threadIdx.x;
             if ((rank & ~63) < cnt)  // some lane of the wavefront has a sample
@@ -821,8 +822,7 @@ __global__ void envelope_kernel(double psi_max, double h, int n_steps, int envel
 // A kernel of its own, so that the rounds of a group can go to any blocks of
 // the pass (a group a block left most CUs idle below 2^20 samples: 2^18 samples
 // of a quantum shot, 2048 steps, 15.0 -> 6.4 ms), and the pass keeps no LDS for
-// it.  28 us for 128 groups, 110 us for 1024, about half of it the FP64 draws (the
-// rank by 2048 comparisons a sample that a group took in the pass: 140 us).
+// it.  28 us for 128 groups, 110 us for 1024.
 constexpr int kOrderBlock = kChiGroup / 2;
 
 __global__ __launch_bounds__(kOrderBlock) void order_kernel(BatchParams P) {

@@ -752,15 +752,15 @@ __device__ __forceinline__ int find_phot(const ShotPhot *ph, int n_shots, int64_
 // a CU; the others run blocks of 256, two a CU.  Either way two waves per
 // SIMD, and the registers are held to that (the FP64 and mixed-precision
 // passes would otherwise take a few more and run one).
-template <int PREC>
-constexpr int phot_block() {
-    return PREC == PREC_F32MIX ? 2 * kDepBlock : kDepBlock;
-}
-
+// An item is one sample a lane.  With items of 2048 samples, taken one after
+// another by a block to flush its grid less often, 65,537 samples x 1024 steps
+// ran on 33 of 256 CUs in 11.1 ms, against 1.63 ms; eight shots of 2^18 x 512 steps
+// take 13.0 ms with those items and 12.5 ms with these (x 128 steps: 3.61 and
+// 3.56 ms), so the more frequent flushes cost less than the even load gives.
 template <int PREC, bool QUANTUM, bool LOCAL>
-__global__ __launch_bounds__(phot_block<PREC>()) __attribute__((amdgpu_waves_per_eu(2))) void photon_kernel(
+__global__ __launch_bounds__(phot_block(PREC)) __attribute__((amdgpu_waves_per_eu(2))) void photon_kernel(
     BatchParams P, const float *__restrict__ env32, const double *__restrict__ env64) {
-    constexpr int kBlock = phot_block<PREC>();
+    constexpr int kBlock = phot_block(PREC);
     // mixed precision: every lane of a wavefront runs (lanes past an item's
     // end repeat its last sample without depositing), for the table reads
     constexpr bool kWave64 = PREC == PREC_F32MIX;
@@ -804,18 +804,22 @@ __global__ __launch_bounds__(phot_block<PREC>()) __attribute__((amdgpu_waves_per
         __syncthreads();
         PhotAcc acc{0.0, 0.0, 0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         double loss = 0.0;
-        const int64_t i0 = (item - pp.pitem0) * kPhotTile;
-        const int64_t i1 = i0 + kPhotTile < sp.n_samples ? i0 + kPhotTile : sp.n_samples;
+        int64_t row = item;  // of the partial sums
         if constexpr (kWave64) {
-            // the item's samples in order of their chi scale; every lane of a
-            // wavefront with a sample runs
-            const int cnt = (int)(i1 - i0);
-            for (int rank = (int)threadIdx.x; (rank & ~63) < cnt; rank += kBlock)
-                photon_sample<PREC, QUANTUM, LOCAL>(
-                    P, sp, pp, ordered_sample(P, sp, i0, cnt, rank), env32, env64, tab32, lgrid,
-                    tot, ncell, wstage, rank < cnt, acc, loss);
+            // a round of a group's samples in order of their chi scale; every
+            // lane of a wavefront with a sample runs
+            const int64_t first = ordered_round<kBlock>(sp.n_samples, item - pp.pitem0);
+            const int64_t base = first & ~(kChiGroup - 1ll);
+            row = pp.pitem0 + first / kBlock;
+            const int cnt = (int)min((int64_t)kChiGroup, sp.n_samples - base);
+            const int rank = (int)(first - base) + (int)threadIdx.x;
+            if ((rank & ~63) < cnt)
+                photon_sample<PREC, QUANTUM, LOCAL>(P, sp, pp, ordered_sample(P, sp, base, cnt, rank),
+                                                    env32, env64, tab32, lgrid, tot, ncell, wstage,
+                                                    rank < cnt, acc, loss);
         } else {
-            for (int64_t i = i0 + threadIdx.x; i < i1; i += blockDim.x)
+            const int64_t i = (item - pp.pitem0) * kBlock + threadIdx.x;
+            if (i < sp.n_samples)
                 photon_sample<PREC, QUANTUM, LOCAL>(P, sp, pp, i, env32, env64, tab32, grid, tot,
                                                     ncell, wstage, true, acc, loss);
         }
@@ -824,14 +828,14 @@ __global__ __launch_bounds__(phot_block<PREC>()) __attribute__((amdgpu_waves_per
                                          acc.ny, acc.ee, acc.ex, acc.ey};
 #pragma unroll
         for (int m = 0; m < kPhotPartials; ++m) {
-            const double w = wave_sum(v[m]);
-            if (lane == 0) red[wid][m] = w;
+            const double w = wave_sum_last(v[m]);
+            if (lane == 63) red[wid][m] = w;
         }
         __syncthreads();
         if (threadIdx.x < kPhotPartials) {
             double sum = 0.0;
             for (int w = 0; w < kBlock / 64; ++w) sum += red[w][threadIdx.x];
-            P.partials[(size_t)item * kPhotPartials + threadIdx.x] = sum;
+            P.partials[(size_t)threadIdx.x * P.n_pitems + row] = sum;
         }
         for (int k = threadIdx.x; k < nodes; k += blockDim.x) {
             const int l = (k / pp.nv) * kPhLdsRow + k % pp.nv;
@@ -843,128 +847,111 @@ __global__ __launch_bounds__(phot_block<PREC>()) __attribute__((amdgpu_waves_per
     }
 }
 
-// One block per shot: the item sums in a fixed order, then the spectrum.
-// With S_k = sum over grid nodes of W_node Phi(e_k / mu_node; chi_node) / chi_node
-// (nodes in index order), bin k holds C (S_{k+1} - S_k), the underflow C S_0
-// and the overflow C (S_total - S_n), C = 2^-24 (2 a0 / a_S) h C_ph.
-constexpr int kPhMaxEdgesPerThread = (4096 + 2 + 255) / 256;
+// The spectrum's cumulative sums at the bin edges of every shot,
+//   S_k = sum over grid nodes of W_node Phi(e_k / mu_node; chi_node) / chi_node
+// (index n_ph + 1 stands for the total), with the node weights W: the grid
+// convolved with [-1/12, 7/6, -1/12] along each axis (the deposit's tent
+// deconvolved to second order), over the grid's rows and the table rows just
+// below and above it; columns beyond the grid's are left out (the host keeps
+// its outer columns empty).
+// One wavefront an edge, lane m the grid's column m, rows in order, then the
+// wavefront's sum.  y = 2 xi / (3 chi (1 - xi)) is a function of the edge and
+// the column over chi, so its cube root (the table's coordinate) is one cbrt a
+// lane times a factor a row.  Bound by the latency of the table reads, spread
+// over blocks of a few edges: a block a shot, a thread an edge and the nodes one
+// after another, each with its own cbrt and division, took 1.48 ms (one shot) to
+// 2.57 ms (eight quantum shots), against 45 and 60 us.
+constexpr int kPhEdges = 8;  // edges a block
 
-__global__ __launch_bounds__(256) void photon_finalize_kernel(BatchParams P, double c_ph) {
+__global__ __launch_bounds__(256) void photon_spectrum_kernel(BatchParams P) {
+    const ShotPhot &pp = P.phot[blockIdx.y];
+    const int n_edges = pp.n_ph + 2, e0 = blockIdx.x * kPhEdges;
+    if (e0 >= n_edges) return;
+    // the grid with an empty column on either side; the rows' cube roots
+    __shared__ double G[kPhNU * (kPhNV + 2)];
+    __shared__ double inv_cbrt_chi[kPhNU + 2];
+    const int nu = pp.nu, nv = pp.nv, ld = nv + 2;
+    const unsigned long long *grid = P.pgrid + pp.grid_off;
+    for (int k = threadIdx.x; k < nu * ld; k += blockDim.x) {
+        const int n = k / ld, m = k - n * ld - 1;
+        G[k] = m >= 0 && m < nv ? (double)grid[n * nv + m] : 0.0;
+    }
+    if (threadIdx.x < nu + 2)
+        inv_cbrt_chi[threadIdx.x] =
+            exp(-(kPhU0 + (pp.r_lo + (int)threadIdx.x - 1) * kPhDu) * (1.0 / 3.0));
+    __syncthreads();
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const bool col = lane < nv;
+    const int m = col ? lane : 0;
+    const double t = pp.t_lo + m * pp.dt, inv_mu = 1.0 / (t * t);
+    const double dz = ph_dz(), inv_dz = 1.0 / dz, zmax = kPhNZ * dz;
+    for (int e = e0 + wid; e < min(e0 + kPhEdges, n_edges); e += 4) {
+        const double xi = e == pp.n_ph + 1 ? 2.0 : (pp.ph_lo + e * pp.ph_w) * inv_mu;
+        const double root = xi < 1.0 ? cbrt(fmax(2.0 * xi / (3.0 * (1.0 - xi)), 0.0)) : zmax * 1e9;
+        double S = 0.0, c0 = 0.0, c1 = 0.0;  // convolved rows n - 2, n - 1
+        for (int n = 0; n < nu + 2; ++n) {   // node row n - 1
+            double c2 = 0.0;
+            if (n < nu) {
+                const double *g = G + n * ld + m;
+                c2 = fma(7.0 / 6.0, g[1], -1.0 / 12.0 * (g[0] + g[2]));
+            }
+            const int r = pp.r_lo + n - 1;
+            const double w = fma(7.0 / 6.0, c1, -1.0 / 12.0 * (c0 + c2));
+            c0 = c1;
+            c1 = c2;
+            if (r < 0 || r >= kPhRows || !__any(col && w != 0.0 && xi > 0.0)) continue;
+            // Phi / chi: the stored Phi / (chi z) by a cubic in z, times z
+            const double *row = P.phtab + (size_t)r * (kPhNZ + 1);
+            const double z = fmin(root * inv_cbrt_chi[n], zmax), u = z * inv_dz;
+            const int j = min(max((int)u - 1, 0), kPhNZ - 3);
+            const double x = u - j;
+            const double xa = x * (x - 3.0), xb = (x - 1.0) * (x - 2.0);
+            const double v = z >= zmax ? row[kPhNZ]
+                                       : (-(1.0 / 6.0) * xb * ((x - 3.0) * row[j] - x * row[j + 3]) +
+                                          0.5 * xa * ((x - 2.0) * row[j + 1] - (x - 1.0) * row[j + 2]));
+            if (xi > 0.0) S = fma(w, v * z, S);
+        }
+        S = wave_sum(col ? S : 0.0);
+        if (lane == 0) P.psum[pp.s_off + e] = S;
+    }
+}
+
+// One block per shot: the items' sums in a fixed order (a wavefront a column),
+// then the spectrum: bin k holds C (S_{k+1} - S_k), the underflow C S_0 and the
+// overflow C (S_total - S_n), C = 2^-24 (2 a0 / a_S) h C_ph.
+constexpr int kPhFinBlock = 640;
+static_assert(kPhotPartials <= kPhFinBlock / 64, "a wavefront a column");
+
+__global__ __launch_bounds__(kPhFinBlock) void photon_finalize_kernel(BatchParams P, double c_ph) {
     const int s = blockIdx.x;
     const ShotParams &sp = P.shots[s];
     const ShotPhot &pp = P.phot[s];
-    __shared__ double tree[256];
     __shared__ double sums[kPhotPartials];
-    // weights of the non-zero nodes (the grid and a row above and below),
-    // then S_k
-    __shared__ double nzw[kPhNodes + 2 * kPhNV + 2];
-    __shared__ unsigned short nzi[kPhNodes + 2 * kPhNV];
-    __shared__ int cnt[257];
-    const int tid = threadIdx.x;
-    const int64_t ni = (sp.n_samples + kPhotTile - 1) / kPhotTile;
-    for (int m = 0; m < kPhotPartials; ++m) {
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    if (wid < kPhotPartials) {
+        const int64_t nr = (sp.n_samples + phot_block(P.prec) - 1) / phot_block(P.prec);
+        const double *col = P.partials + (size_t)wid * P.n_pitems + pp.pitem0;
         double a = 0.0;
-        for (int64_t b = tid; b < ni; b += blockDim.x)
-            a += P.partials[(size_t)(pp.pitem0 + b) * kPhotPartials + m];
-        tree[tid] = a;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if (tid < w) tree[tid] += tree[tid + w];
-            __syncthreads();
-        }
-        if (tid == 0) sums[m] = tree[0];
-        __syncthreads();
+#pragma unroll 4
+        for (int64_t q = lane; q < nr; q += 64) a += col[q];
+        a = wave_sum(a);
+        if (lane == 0) sums[wid] = a;
     }
-    // node weights: the grid convolved with [-1/12, 7/6, -1/12] along each
-    // axis (the deposit's tent deconvolved to second order), over the grid's
-    // rows and the table rows just below and above it; columns beyond the
-    // grid's are left out (the host keeps its outer columns empty); the
-    // non-zero nodes compacted in index order
-    const int nv = pp.nv, nu = pp.nu;
-    const int nodes = (nu + 2) * nv;  // extended row e = grid row e - 1
-    const unsigned long long *G = P.pgrid + pp.grid_off;
-    auto node_weight = [&](int k) -> double {
-        const int e = k / nv, m = k - e * nv;
-        const int r = pp.r_lo + e - 1;
-        if (r < 0 || r >= kPhRows) return 0.0;
-        double acc = 0.0;
-        for (int a = -1; a <= 1; ++a) {
-            const int n = e - 1 + a;
-            if (n < 0 || n >= nu) continue;
-            double row = 0.0;
-            for (int b = -1; b <= 1; ++b) {
-                const int mm = m + b;
-                if (mm < 0 || mm >= nv) continue;
-                row += (b == 0 ? 7.0 / 6.0 : -1.0 / 12.0) * (double)G[n * nv + mm];
-            }
-            acc += (a == 0 ? 7.0 / 6.0 : -1.0 / 12.0) * row;
-        }
-        return acc;
-    };
-    const int kPer = (nodes + 255) / 256;
-    int mine = 0;
-    for (int q = 0; q < kPer; ++q) {
-        const int k = tid * kPer + q;
-        if (k < nodes && node_weight(k) != 0.0) ++mine;
-    }
-    cnt[tid + 1] = mine;
-    if (tid == 0) cnt[0] = 0;
-    __syncthreads();
-    if (tid == 0)
-        for (int t = 1; t <= 256; ++t) cnt[t] += cnt[t - 1];
-    __syncthreads();
-    int pos = cnt[tid];
-    for (int q = 0; q < kPer; ++q) {
-        const int k = tid * kPer + q;
-        if (k >= nodes) break;
-        const double w = node_weight(k);
-        if (w != 0.0) {
-            nzi[pos] = (unsigned short)k;
-            nzw[pos] = w;
-            ++pos;
-        }
-    }
-    __syncthreads();
-    const int nnz = cnt[256];
-    // edge sums: thread tid owns edges tid, tid + 256, ...; index n_ph + 1
-    // stands for the total
-    const int n_edges = pp.n_ph + 2;
-    double S[kPhMaxEdgesPerThread];
-    for (int q = 0; q < kPhMaxEdgesPerThread; ++q) S[q] = 0.0;
-    for (int z = 0; z < nnz; ++z) {
-        const int k = nzi[z];
-        const int e = k / nv, m = k - e * nv;
-        const int r = pp.r_lo + e - 1;
-        const double chi = exp(kPhU0 + r * kPhDu);
-        const double t = pp.t_lo + m * pp.dt;
-        const double inv_mu = 1.0 / (t * t);
-        const double w = nzw[z];
-        for (int q = 0; q < kPhMaxEdgesPerThread; ++q) {
-            const int e = tid + 256 * q;
-            if (e >= n_edges) break;
-            const double xi = e == pp.n_ph + 1 ? 2.0 : (pp.ph_lo + e * pp.ph_w) * inv_mu;
-            S[q] = fma(w, ph_cdf_row(P.phtab, r, chi, xi), S[q]);
-        }
-    }
-    __syncthreads();  // nzw is reused for S
-    for (int q = 0; q < kPhMaxEdgesPerThread; ++q) {
-        const int e = tid + 256 * q;
-        if (e < n_edges) nzw[e] = S[q];
-    }
+    const double *S = P.psum + pp.s_off;
     __syncthreads();
     const double C = (1.0 / kPhScale) * (2.0 * sp.a0 * P.two_over_aS * 0.5) * P.h * c_ph;
     // C = 2^-24 (2 a0 / a_S) h C_ph  (two_over_aS / 2 = 1 / a_S)
     const double soft = sums[2] * (2.0 * sp.a0 * P.two_over_aS * 0.5) * P.h * c_ph *
                         (5.0 * 3.14159265358979323846 / 2.0);
     const int n = pp.n_ph;
-    for (int k = tid; k < n + 2; k += blockDim.x) {
+    for (int k = tid; k < n + 2; k += kPhFinBlock) {
         double v;
         if (k < n)
-            v = C * (nzw[k + 1] - nzw[k]);
+            v = C * (S[k + 1] - S[k]);
         else if (k == n)
-            v = C * nzw[0];
+            v = C * S[0];
         else
-            v = C * (nzw[n + 1] - nzw[n]);
+            v = C * (S[n + 1] - S[n]);
         if (pp.ph_lo > 0.0 ? k == n : k == 0) v += soft;
         pp.hist[k] = v;
     }
@@ -1076,7 +1063,7 @@ hipError_t launch_photon(const BatchParams &p, const float *env32, const double 
     else
         fn = q ? (l ? photon_ptr<PREC_F32, true, true>() : photon_ptr<PREC_F32, true, false>())
                : (l ? photon_ptr<PREC_F32, false, true>() : photon_ptr<PREC_F32, false, false>());
-    const int block = prec == PREC_F32MIX && q ? phot_block<PREC_F32MIX>() : kDepBlock;
+    const int block = phot_block(p.prec);
     int grid = 0;
     hipError_t e = resident_grid(fn, block, 0, p.n_pitems, &grid);
     if (e != hipSuccess) return e;
@@ -1087,8 +1074,12 @@ hipError_t launch_photon(const BatchParams &p, const float *env32, const double 
     return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(block), args, 0, s);
 }
 
-hipError_t launch_photon_finalize(const BatchParams &p, double c_ph, hipStream_t s) {
-    photon_finalize_kernel<<<p.n_shots, 256, 0, s>>>(p, c_ph);
+hipError_t launch_photon_finalize(const BatchParams &p, int max_edges, double c_ph,
+                                  hipStream_t s) {
+    photon_spectrum_kernel<<<dim3((max_edges + kPhEdges - 1) / kPhEdges, p.n_shots), 256, 0, s>>>(p);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    photon_finalize_kernel<<<p.n_shots, kPhFinBlock, 0, s>>>(p, c_ph);
     return hipGetLastError();
 }
 

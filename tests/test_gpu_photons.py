@@ -257,3 +257,33 @@ def test_photon_number_of_full_quantum_batch_shots(gpu, k):
     print("photon number: spectrum", n_spec, "stages", n_stage, "rel", n_spec / n_stage - 1)
     assert int(g["status"][0]) == 0
     assert n_stage > 0 and abs(n_spec - n_stage) <= 2e-5 * n_stage
+
+
+@pytest.mark.parametrize("n", [1, 65, 256, 257, 511, 513, 2047, 2049])
+def test_photon_work_items(gpu, n):
+    """A work item is 256 samples in sample order, or with FP64 steps 512 in chi
+    order within groups of 2048: with every step in FP64 the second kind gives
+    the spectrum and energies of the FP64 pass, the first kind, to 1e-12 (as
+    for every mixed pass promoted everywhere), about the sizes of the items."""
+    p = _case("quantum-local", n_samples=n, n_steps=64)
+    a = _np(gpu.photons(dict(p, precision="fp64")))
+    b = _np(gpu.photons(dict(p, chi_fp64=1e-30)))
+    assert np.all(np.abs(a["photon_hist"] - b["photon_hist"]) <= 1e-12 * a["photon_hist"].sum())
+    assert np.allclose(a["energy"], b["energy"], rtol=1e-12, atol=0)
+
+
+@pytest.mark.parametrize("n_ph", [1, 6, 7, 8, 585])
+def test_photon_edges_merge(gpu, n_ph):
+    """The cumulative sums at the bin edges are formed eight edges to a block:
+    a window of n_ph bins is that of 7 n_ph bins (4095 at most) merged, edge
+    by edge, up to the FP64 sums over at most 66 x 64 nodes (1e-12 of the
+    photon number is 4096 roundings of it)."""
+    p = _case("quantum-local", n_samples=300, n_ph=n_ph)
+    # (the same grid: its rows reach down to the lowest edge or the bin width)
+    lo = 1.0 / 16.0
+    width = (p["ph_hi"] - lo) / n_ph
+    g = _np(gpu.photons(dict(p, ph_lo=lo + width, ph_hi=p["ph_hi"] + width)))["photon_hist"]
+    f = _np(gpu.photons(dict(p, ph_lo=lo + width, ph_hi=p["ph_hi"] + width,
+                             n_ph=7 * n_ph)))["photon_hist"]
+    merged = np.concatenate([f[:7 * n_ph].reshape(n_ph, 7).sum(1), f[7 * n_ph:]])
+    assert np.all(np.abs(g - merged) <= 1e-12 * g.sum()), np.abs(g - merged).max() / g.sum()
