@@ -72,15 +72,8 @@ __device__ __forceinline__ RadJ<float> rad6_cell_eval(const RadCell6 &cell, floa
 // functions, combined here.
 __device__ __forceinline__ void rad6_plain64(const double *__restrict__ tab, double chi,
                                              double v[kDerivFuncs]) {
-    const uint64_t b = (uint64_t)__double_as_longlong(chi);
-    int64_t c = (int64_t)(b >> (52 - kSB64)) - ((int64_t)(1023 + kEMin) << kSB64) + 1;
-    double t = __longlong_as_double((long long)(((b & ((1ull << (52 - kSB64)) - 1)) << kSB64) |
-                                                0x3ff0000000000000ull)) - 1.0;
-    if (c < 1) {
-        c = 0;
-        t = chi * 0x1p20;
-    }
-    c = c < kCells64 - 1 ? c : kCells64 - 1;
+    double t;
+    const int c = rad_index64(chi, t);
     const double *q = tab + (size_t)c * (4 * kDerivFuncs);
 #pragma unroll
     for (int f = 0; f < kDerivFuncs; ++f)
@@ -372,11 +365,11 @@ __device__ __forceinline__ SpD<float> spatial_d(float x, float y, float z, float
 __device__ __forceinline__ SpD<double> spatial_d(double x, double y, double z, double inv_w0sq,
                                                  double inv_zR, double inv_w0) {
     const double zz = z * inv_zR;
-    const double q = fma(zz, zz, 1.0);
-    const double iq = 1.0 / q;
+    const double rq = inv_sqrt64(fma(zz, zz, 1.0));
+    const double iq = rq * rq;
     const double p = fma(x, x, y * y) * inv_w0sq * iq;
     SpD<double> r;
-    r.S = exp(-p) * sqrt(iq);
+    r.S = exp_neg64(-p) * rq;
     const double m = -2.0 * inv_w0sq * iq;
     r.Lx = m * x;
     r.Ly = m * y;

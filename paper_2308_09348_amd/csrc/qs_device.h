@@ -165,16 +165,16 @@ __device__ __forceinline__ void rad_cell_eval(const RadCell32 &cell, float chi, 
 // FP64 cell of chi and the coordinate t in the cell (cell 0 is linear in chi
 // below 2^kEMin; chi beyond the table is clamped to the last cell and
 // reported by the caller).
+// All in the upper word: the cell from its top bits, t = (chi - cell start)
+// 2^(SB - e), both operations exact.
 __device__ __forceinline__ int rad_index64(double chi, double &t) {
-    const uint64_t b = (uint64_t)__double_as_longlong(chi);
-    int64_t c = (int64_t)(b >> (52 - kSB64)) - ((int64_t)(1023 + kEMin) << kSB64) + 1;
-    t = __longlong_as_double((long long)(((b & ((1ull << (52 - kSB64)) - 1)) << kSB64) |
-                                         0x3ff0000000000000ull)) - 1.0;
-    if (c < 1) {
-        c = 0;
-        t = chi * 0x1p20;
-    }
-    return (int)(c < kCells64 - 1 ? c : kCells64 - 1);
+    constexpr int kLow = 20 - kSB64;  // bits of the upper word below the cell index
+    const uint32_t hi = (uint32_t)__double2hiint(chi);
+    const int c = (int)(hi >> kLow) - ((1023 + kEMin) << kSB64) + 1;
+    const double start = __hiloint2double((int)(hi >> kLow << kLow), 0);
+    const double inv = __hiloint2double((int)((uint32_t)(2046 + kSB64) - (hi >> 20)) << 20, 0);
+    t = c < 1 ? chi * 0x1p20 : (chi - start) * inv;
+    return min(max(c, 0), kCells64 - 1);
 }
 
 __device__ __forceinline__ void rad_cell_eval64(const double *q, double t, double &g, double &G1,
@@ -354,6 +354,37 @@ __device__ __forceinline__ void rhs(T mu, T s2, T a, const Phys<T> &ph, const Ta
     ds2 = fma(T(2) * A1, s2, D);
 }
 
+// 1/sqrt(q) for q >= 1: the hardware estimate (about 2^-24) and one step of third
+// order, within an ulp (q beyond 1e300 counts as 1e300, the factor it gives as 0).
+__device__ __forceinline__ double inv_sqrt64(double q) {
+    q = fmin(q, 1e300);
+    const double y = __builtin_amdgcn_rsq(q);
+    const double e = fma(-q * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+// e^x for x <= 0 (0 below -800): x = k ln 2 + r, |r| <= ln 2 / 2, the Taylor
+// polynomial of degree 12 (remainder 1.7e-16 relative), scaled by 2^k.
+__device__ __forceinline__ double exp_neg64(double x) {
+    x = fmax(x, -800.0);
+    const double k = rint(x * 1.44269504088896340736);
+    const double r = fma(-k, 1.9082149292705877e-10, fma(-k, 0.693147180369123816490, x));
+    double p = 1.0 / 479001600.0;
+    p = fma(p, r, 1.0 / 39916800.0);
+    p = fma(p, r, 1.0 / 3628800.0);
+    p = fma(p, r, 1.0 / 362880.0);
+    p = fma(p, r, 1.0 / 40320.0);
+    p = fma(p, r, 1.0 / 5040.0);
+    p = fma(p, r, 1.0 / 720.0);
+    p = fma(p, r, 1.0 / 120.0);
+    p = fma(p, r, 1.0 / 24.0);
+    p = fma(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    p = fma(p, r, 1.0);
+    p = fma(p, r, 1.0);
+    return ldexp(p, (int)k);
+}
+
 // Spatial factor a/a0 of eq. a0eff at (x, y, z) [um].  The FP32 version uses
 // the hardware reciprocal, reciprocal square root and base-2 exponential
 // (about one ulp each; the exponent's argument rounding adds |r2/q| ulps,
@@ -368,10 +399,9 @@ __device__ __forceinline__ float spatial(float x, float y, float z, float inv_w0
 __device__ __forceinline__ double spatial(double x, double y, double z, double inv_w0sq,
                                           double inv_zR) {
     const double zz = z * inv_zR;
-    const double q = fma(zz, zz, 1.0);
-    const double iq = 1.0 / q;
+    const double rq = inv_sqrt64(fma(zz, zz, 1.0));  // 1/sqrt(q); 1/q = rq^2
     const double r2 = fma(x, x, y * y) * inv_w0sq;
-    return exp(-r2 * iq) * sqrt(iq);
+    return exp_neg64(-r2 * (rq * rq)) * rq;
 }
 
 // Higher transverse modes (amplitude only, peak 1 in the focal plane): with

@@ -406,11 +406,12 @@ __device__ __forceinline__ void photon_stage(T mu, T s2, T a, const Phys<T> &ph,
     ds2 = fma(T(-2) * u * mu * s2, t[1], ph.CD * aa * a2 * mu2 * mu2 * t[3]);
 }
 
-// Per-sample constants of the photon pass in precision T.
-template <class T>
+// Per-sample constants of the photon pass in precision T (MODES: some shot of
+// the launch uses a higher transverse mode; see Path).
+template <class T, bool MODES>
 struct PhotCtx {
     const T *env;
-    Path<T> pt;
+    Path<T, MODES> pt;
     Phys<T> ph;
     T a0, a0S0, h, psi0, ell, thx, thy;
     float inv_a0, tas;
@@ -447,8 +448,8 @@ struct PhotState {
 // ANG32: the angular sums' terms in FP32 with the photon number from the FP32
 // cells' cubics (the FP64 steps of a mixed-precision pass, whose angular
 // moments are held to the FP32 pass's bar; the FP64 pass takes them in FP64).
-template <class T, bool QUANTUM, class R = FwdRad<T>, bool ANG32 = false>
-__device__ __forceinline__ void photon_step(const PhotCtx<T> &c, const ShotPhot &pp,
+template <class T, bool QUANTUM, bool MODES, class R = FwdRad<T>, bool ANG32 = false>
+__device__ __forceinline__ void photon_step(const PhotCtx<T, MODES> &c, const ShotPhot &pp,
                                             const float *tot, int j, PhotState<T> &st, R &rad,
                                             unsigned long long *grid, PhotAcc &acc) {
     const T h = c.h, hh = T(0.5) * h;
@@ -550,7 +551,7 @@ __device__ __forceinline__ void photon_step(const PhotCtx<T> &c, const ShotPhot 
     st.aS_prev = aS4;
 }
 
-template <int PREC, bool QUANTUM, bool LOCAL>
+template <int PREC, bool QUANTUM, bool LOCAL, bool MODES>
 __device__ __forceinline__ void photon_sample(const BatchParams &P, const ShotParams &sp,
                                               const ShotPhot &pp, int64_t i,
                                               const float *__restrict__ env32,
@@ -575,7 +576,7 @@ __device__ __forceinline__ void photon_sample(const BatchParams &P, const ShotPa
     const double g0 = sc.g0;
     const double thx = sc.thx;
     const double thy = sc.thy;
-    Path<double> pd;
+    Path<double, MODES> pd;
     pd.xc = fma(thx, 0.5 * z, x);
     pd.yc = fma(thy, 0.5 * z, y);
     pd.thx = thx;
@@ -589,7 +590,7 @@ __device__ __forceinline__ void photon_sample(const BatchParams &P, const ShotPa
     pd.inv_norm = sp.mode_inv_norm;
     const double S0 = sp.plane_wave ? 1.0 : pd.S(0.0);
 
-    PhotCtx<T> c;
+    PhotCtx<T, MODES> c;
     if constexpr (PREC == PREC_F64)
         c.env = env64;
     else
@@ -661,7 +662,7 @@ __device__ __forceinline__ void photon_sample(const BatchParams &P, const ShotPa
                 // FP64 steps while some lane of the wavefront has chi above
                 // the threshold at a step start (the forward pass's rule);
                 // the FP32 pair, amplitudes and cell are rebuilt at the exit
-                PhotCtx<double> cd;
+                PhotCtx<double, MODES> cd;
                 cd.env = env64;
                 cd.pt = pd;
                 cd.ph = Phys<double>{P.K, P.CD, P.two_over_aS};
@@ -692,7 +693,7 @@ __device__ __forceinline__ void photon_sample(const BatchParams &P, const ShotPa
                 sd.chi_hi = 0.0;
                 FwdRadWave radd(P.rad64, stage);
                 for (;;) {
-                    photon_step<double, QUANTUM, FwdRadWave, true>(cd, pp, tot, j, sd, radd, grid,
+                    photon_step<double, QUANTUM, MODES, FwdRadWave, true>(cd, pp, tot, j, sd, radd, grid,
                                                                    acc);
                     ++j;
                     if (j >= N) break;
@@ -713,7 +714,7 @@ __device__ __forceinline__ void photon_sample(const BatchParams &P, const ShotPa
                 continue;
             }
         }
-        photon_step<T, QUANTUM>(c, pp, tot, j, st, rad, grid, acc);
+        photon_step<T, QUANTUM, MODES>(c, pp, tot, j, st, rad, grid, acc);
         ++j;
     }
     if (!c.live) return;
@@ -757,7 +758,7 @@ __device__ __forceinline__ int find_phot(const ShotPhot *ph, int n_shots, int64_
 // ran on 33 of 256 CUs in 11.1 ms, against 1.63 ms; eight shots of 2^18 x 512 steps
 // take 13.0 ms with those items and 12.5 ms with these (x 128 steps: 3.61 and
 // 3.56 ms), so the more frequent flushes cost less than the even load gives.
-template <int PREC, bool QUANTUM, bool LOCAL>
+template <int PREC, bool QUANTUM, bool LOCAL, bool MODES>
 __global__ __launch_bounds__(phot_block(PREC)) __attribute__((amdgpu_waves_per_eu(2))) void photon_kernel(
     BatchParams P, const float *__restrict__ env32, const double *__restrict__ env64) {
     constexpr int kBlock = phot_block(PREC);
@@ -814,13 +815,13 @@ __global__ __launch_bounds__(phot_block(PREC)) __attribute__((amdgpu_waves_per_e
             const int cnt = (int)min((int64_t)kChiGroup, sp.n_samples - base);
             const int rank = (int)(first - base) + (int)threadIdx.x;
             if ((rank & ~63) < cnt)
-                photon_sample<PREC, QUANTUM, LOCAL>(P, sp, pp, ordered_sample(P, sp, base, cnt, rank),
+                photon_sample<PREC, QUANTUM, LOCAL, MODES>(P, sp, pp, ordered_sample(P, sp, base, cnt, rank),
                                                     env32, env64, tab32, lgrid, tot, ncell, wstage,
                                                     rank < cnt, acc, loss);
         } else {
             const int64_t i = (item - pp.pitem0) * kBlock + threadIdx.x;
             if (i < sp.n_samples)
-                photon_sample<PREC, QUANTUM, LOCAL>(P, sp, pp, i, env32, env64, tab32, grid, tot,
+                photon_sample<PREC, QUANTUM, LOCAL, MODES>(P, sp, pp, i, env32, env64, tab32, grid, tot,
                                                     ncell, wstage, true, acc, loss);
         }
         if (acc.flags) atomicOr(&P.flags[s], acc.flags);
@@ -1047,22 +1048,28 @@ hipError_t build_photon_table(double *phtab, double *work, size_t work_doubles, 
 }
 
 template <int PREC, bool QUANTUM, bool LOCAL>
-static const void *photon_ptr() {
-    return reinterpret_cast<const void *>(&photon_kernel<PREC, QUANTUM, LOCAL>);
+static const void *photon_ptr(bool modes) {
+    return modes ? reinterpret_cast<const void *>(&photon_kernel<PREC, QUANTUM, LOCAL, true>)
+                 : reinterpret_cast<const void *>(&photon_kernel<PREC, QUANTUM, LOCAL, false>);
+}
+
+template <int PREC>
+static const void *select_photon(bool q, bool l, bool modes) {
+    if (q) return l ? photon_ptr<PREC, true, true>(modes) : photon_ptr<PREC, true, false>(modes);
+    return l ? photon_ptr<PREC, false, true>(modes) : photon_ptr<PREC, false, false>(modes);
 }
 
 hipError_t launch_photon(const BatchParams &p, const float *env32, const double *env64, int prec,
                          int rr, int amp, hipStream_t s) {
-    const bool q = rr == 1, l = amp == 1;
+    const bool q = rr == 1, l = amp == 1, modes = p.any_mode != 0;
     const void *fn;
     if (prec == PREC_F64)
-        fn = q ? (l ? photon_ptr<PREC_F64, true, true>() : photon_ptr<PREC_F64, true, false>())
-               : (l ? photon_ptr<PREC_F64, false, true>() : photon_ptr<PREC_F64, false, false>());
+        fn = select_photon<PREC_F64>(q, l, modes);
     else if (prec == PREC_F32MIX && q)  // FP64 steps are a quantum-model option
-        fn = l ? photon_ptr<PREC_F32MIX, true, true>() : photon_ptr<PREC_F32MIX, true, false>();
+        fn = l ? photon_ptr<PREC_F32MIX, true, true>(modes)
+               : photon_ptr<PREC_F32MIX, true, false>(modes);
     else
-        fn = q ? (l ? photon_ptr<PREC_F32, true, true>() : photon_ptr<PREC_F32, true, false>())
-               : (l ? photon_ptr<PREC_F32, false, true>() : photon_ptr<PREC_F32, false, false>());
+        fn = select_photon<PREC_F32>(q, l, modes);
     const int block = phot_block(p.prec);
     int grid = 0;
     hipError_t e = resident_grid(fn, block, 0, p.n_pitems, &grid);
