@@ -991,6 +991,15 @@ qs_status prepare_batch(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_
         gitem += (n_samples[k] + qs::kChiGroup - 1) / qs::kChiGroup;
         hoff += hb.n_e + 2 + hb.n_th + 2 + hb.n_a;
     }
+    // the end of the FP64 table's cells that the shots' chi can reach (with the
+    // energies within 6.5 standard deviations, as the photon grid's range)
+    double chi_max = 0.0;
+    for (int k = 0; k < n_shots; ++k)
+        chi_max = std::max(chi_max, bp.two_over_aS * L[k].a0 *
+                                        (B[k].gamma0 + 6.5 * B[k].sigma_gamma) * 1.02);
+    const int e_top = std::min(std::max(chi_max > 0.0 ? std::ilogb(chi_max) : qs::kEMin, qs::kEMin),
+                               qs::kEMax);
+    bp.win_top = 1 + ((e_top - qs::kEMin + 1) << qs::kSB64);
     bp.n_items = item;
     bp.n_ditems = ditem;
     bp.n_mtiles = mtile;

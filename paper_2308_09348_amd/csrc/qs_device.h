@@ -166,14 +166,20 @@ __device__ __forceinline__ void rad_cell_eval(const RadCell32 &cell, float chi, 
 // below 2^kEMin; chi beyond the table is clamped to the last cell and
 // reported by the caller).
 // All in the upper word: the cell from its top bits, t = (chi - cell start)
-// 2^(SB - e), both operations exact.
-__device__ __forceinline__ int rad_index64(double chi, double &t) {
+// 2^(SB - e), both operations exact.  rad_cell64: before the clamps, for chi in
+// the octave cells.
+__device__ __forceinline__ int rad_cell64(double chi, double &t) {
     constexpr int kLow = 20 - kSB64;  // bits of the upper word below the cell index
     const uint32_t hi = (uint32_t)__double2hiint(chi);
-    const int c = (int)(hi >> kLow) - ((1023 + kEMin) << kSB64) + 1;
     const double start = __hiloint2double((int)(hi >> kLow << kLow), 0);
     const double inv = __hiloint2double((int)((uint32_t)(2046 + kSB64) - (hi >> 20)) << 20, 0);
-    t = c < 1 ? chi * 0x1p20 : (chi - start) * inv;
+    t = (chi - start) * inv;
+    return (int)(hi >> kLow) - ((1023 + kEMin) << kSB64) + 1;
+}
+
+__device__ __forceinline__ int rad_index64(double chi, double &t) {
+    const int c = rad_cell64(chi, t);
+    if (c < 1) t = chi * 0x1p20;
     return min(max(c, 0), kCells64 - 1);
 }
 
@@ -314,6 +320,47 @@ struct RadTabWave {
             c = cn;
         }
         rad_cell_eval64(q, t, g, G1, G2, h);
+    }
+};
+
+// The FP64 table from LDS: the N cells from c0 >= 1 on (the top of the launch's
+// chi range), each 16-byte eighth of the cells in an array of its own, so that
+// lanes on neighbouring cells read neighbouring 16-byte words.  A cell outside
+// the window (chi below it, at a sign change of the carrier or in the far tail
+// of a weak shot) is read from the global table, in a branch of its own: were
+// the two reads alternatives, the compiler would merge part of them into flat
+// loads, which wait for both memories.  The values are those rad_eval64 reads.
+template <int N>
+struct RadTabWin {
+    const double2 *win;  // [8][N]
+    const double *p;     // the whole table, cell-major
+    int c0;
+    __device__ __forceinline__ void eval(double chi, double &g, double &G1, double &G2,
+                                         double &h) const {
+        double t, q[16];
+        const unsigned k = (unsigned)(rad_cell64(chi, t) - c0);
+        const double2 *w = win + min(k, (unsigned)N - 1);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const double2 v = w[e * N];
+            q[2 * e] = v.x;
+            q[2 * e + 1] = v.y;
+        }
+        if (__any(k >= (unsigned)N)) {
+            if (k >= (unsigned)N) {
+                const double *c = p + (size_t)rad_index64(chi, t) * kCellVals;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) q[e] = c[e];
+            }
+        }
+        rad_cell_eval64(q, t, g, G1, G2, h);
+    }
+    // the first cell of the window for a launch whose chi stays below cell top
+    __device__ __forceinline__ static int first(int top) { return max(top - N, 1); }
+    // all threads of the block; a barrier must follow
+    __device__ __forceinline__ static void load(double2 *win, const double *p, int c0) {
+        const double2 *src = reinterpret_cast<const double2 *>(p) + 8 * (size_t)c0;
+        for (int k = threadIdx.x; k < 8 * N; k += blockDim.x) win[(k & 7) * N + (k >> 3)] = src[k];
     }
 };
 

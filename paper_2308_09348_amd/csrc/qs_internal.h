@@ -22,6 +22,12 @@ constexpr int kSB64 = 6;  // FP64 table: 64 sub-cells per octave (global)
 constexpr int kCells32 = 1 + (kEMax - kEMin + 1) * (1 << kSB32);
 constexpr int kCells64 = 1 + (kEMax - kEMin + 1) * (1 << kSB64);
 constexpr int kCellVals = 16;
+// Cells of the FP64 table held in LDS (128 bytes each; a block takes a CU's LDS):
+// 19.5 octaves of chi in FP64 passes, 16.2 beside the FP32 table in passes with
+// FP64 steps.
+constexpr int kWin64 = 1248;
+constexpr int kWinMix = 1040;
+static_assert(kWin64 < kCells64, "a window of the table");
 // Derivative tables (adjoint): six functions per cell, in the order g,
 // chi g', chi^2 g'', h, chi^3 g''', chi h'; FP32 function-major
 // ([function][cell][power]), FP64 cell-major ([cell][function][power]).
@@ -216,6 +222,8 @@ struct BatchParams {
     const ShotOut *outs;
     uint16_t *order;      // passes with FP64 steps: sample state_off + (group start) + r holds
                           // the offset in its group of the sample of chi rank r
+    int32_t win_top;      // FP64 table cells above which no sample's chi lies
+    int32_t pad2;
     const float *rad32;   // [kCells32 * 16]
     const double *rad64;  // [kCells64 * 16]
     const float *rad32d;  // [kCells32 * 4 * kDerivFuncs]

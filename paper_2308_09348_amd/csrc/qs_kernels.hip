@@ -33,13 +33,12 @@ namespace qs {
 // lane of the wavefront has chi above the threshold at the step start: the
 // amplitude's spatial factor is carried from one step's end to the next
 // step's start, as in the FP64 loop.  Returns the first step not taken.
-template <bool QUANTUM, bool MODES>
+template <bool QUANTUM, bool MODES, class Tab>
 __device__ __forceinline__ int fp64_segment(const BatchParams &P, const ShotParams &sp,
                                             const Path<double, MODES> &pd, bool local,
                                             double a0S0, const double *__restrict__ env64, int j,
-                                            double2 *stage, double &mu, double &s2, float &cmx,
+                                            const Tab &tabd, double &mu, double &s2, float &cmx,
                                             double &chd) {
-    const RadTabWave tabd(P.rad64, stage);
     const Phys<double> phd{P.K, P.CD, P.two_over_aS};
     const int N = P.n_steps;
     double aS1 = local ? sp.a0 * pd.S(fma((double)j, P.h, -P.psi_max) * P.ell_per_psi) : a0S0;
@@ -52,7 +51,7 @@ __device__ __forceinline__ int fp64_segment(const BatchParams &P, const ShotPara
             aS4 = sp.a0 * pd.S((psi + P.h) * P.ell_per_psi);
         }
         double dm, ds;
-        rk4_increment<double, QUANTUM, RadTabWave>(mu, s2, aS1 * env64[2 * j],
+        rk4_increment<double, QUANTUM, Tab>(mu, s2, aS1 * env64[2 * j],
                                                    aSh * env64[2 * j + 1], aS4 * env64[2 * j + 2],
                                                    P.h, phd, tabd, dm, ds, chd);
         mu += dm;
@@ -67,16 +66,12 @@ __device__ __forceinline__ int fp64_segment(const BatchParams &P, const ShotPara
     return j;
 }
 
-template <int PREC, bool QUANTUM, bool LOCAL, bool NODES = false, bool MODES = false>
-// stage: this wavefront's staging rows for the FP64 table (quantum passes
-// with FP64 steps; every lane of the wavefront runs, live says whether the
-// lane's sample is real and its state is stored).
+template <int PREC, bool QUANTUM, bool LOCAL, bool NODES, bool MODES, class Tab>
 __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotParams &sp, int64_t i,
                                              const float *__restrict__ env32,
                                              const double *__restrict__ env64,
-                                             const float *tab32, double2 *stage, bool live,
-                                             int &flags, int &nprom) {
-    const RadTabWave tabd(P.rad64, stage);
+                                             const float *tab32, const Tab &tabd, int &flags,
+                                             int &nprom) {
     const RadTab<float> tabf{tab32};
     const Phys<float> phf{P.Kf, P.CDf, P.two_over_aSf};
     const Phys<double> phd{P.K, P.CD, P.two_over_aS};
@@ -120,7 +115,7 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
             const double a4 = aS4 * env64[2 * j + 2];
             cmx = fmaxf(cmx, (float)(P.two_over_aS * mu * fabs(a1)));
             double dm, ds;
-            rk4_increment<double, QUANTUM, RadTabWave>(mu, s2, a1, ah, a4, P.h, phd, tabd, dm, ds,
+            rk4_increment<double, QUANTUM, Tab>(mu, s2, a1, ah, a4, P.h, phd, tabd, dm, ds,
                                                        chd);
             mu += dm;
             s2 += ds;
@@ -178,7 +173,7 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
                     double s2d = (double)s2 + (double)s2_lo;
                     g0_rest = 0.0;
                     const int j0 = j;
-                    j = fp64_segment<QUANTUM>(P, sp, pd, local, a0S0, env64, j, stage, mud, s2d,
+                    j = fp64_segment<QUANTUM>(P, sp, pd, local, a0S0, env64, j, tabd, mud, s2d,
                                               cmx, chd);
                     nprom += j - j0;  // wave-uniform
                     mu = (float)mud;
@@ -235,7 +230,6 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
         const double aN = (local ? sp.a0 * pd.S(P.psi_max * P.ell_per_psi) : a0S0) * env64[2 * N];
         cmx = fmaxf(cmx, (float)(P.two_over_aS * mu_f * fabs(aN)));
     }
-    if (!live) return;
     if (QUANTUM && !(chi_hi < chi_top)) flags |= kFlagRange;
     if (!(mu_f > 0.0) || !isfinite(mu_f) || !isfinite(s2_f)) flags |= kFlagNonFinite;
     const int64_t k = sp.state_off + i;
@@ -248,48 +242,28 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
     P.st.cmx[k] = cmx;
 }
 
+// FP32 passes and classical FP64 passes: blocks take items of kPhaseBlock
+// samples.
 template <int PREC, bool QUANTUM, bool LOCAL, bool NODES = false, bool MODES = false>
 __global__ __launch_bounds__(kPhaseBlock)
 __attribute__((amdgpu_waves_per_eu((PREC == PREC_F32 && QUANTUM) ? 4 : 1))) void phase_kernel(BatchParams P,
                                                             const float *__restrict__ env32,
                                                             const double *__restrict__ env64) {
-    constexpr bool kTab32 = QUANTUM && PREC != PREC_F64;
-    // FP64 table staging (quantum passes with FP64 steps): every lane of a
-    // wavefront takes part in the table reads, so lanes past the end of the
-    // shot run its last sample again without storing it
-    constexpr bool kWave64 = QUANTUM && PREC != PREC_F32;
-    __shared__ __align__(16) float tab32[kTab32 ? kCells32 * kCellVals : 4];
-    __shared__ double2 stage[kWave64 ? (kPhaseBlock / 64) * kStageChunks : 1];
+    static_assert(PREC == PREC_F32 || !QUANTUM, "phase64_kernel");
+    __shared__ __align__(16) float tab32[QUANTUM ? kCells32 * kCellVals : 4];
     __shared__ int64_t slot;
-    // FP32 passes: the lanes take the item's samples in order of their chi
-    // scale (chi_order32), so that neighbouring lanes read nearby table cells;
-    // with FP64 steps an item is a round of a group's samples in that order
-    // (order_kernel), so that wavefronts step alike
-    constexpr bool kOrder = PREC == PREC_F32 && QUANTUM && !NODES;
-    constexpr bool kGroup = PREC == PREC_F32MIX && QUANTUM && !NODES;
+    // quantum passes: the lanes take the item's samples in order of their chi
+    // scale (chi_order32), so that neighbouring lanes read nearby table cells
+    constexpr bool kOrder = QUANTUM && !NODES;
     __shared__ float okey[kOrder ? kPhaseBlock : 1];
     __shared__ unsigned short oidx[kOrder ? kPhaseBlock : 1];
-    if (kTab32) {
+    if (QUANTUM) {
         const float4 *src = reinterpret_cast<const float4 *>(P.rad32);
         float4 *dst = reinterpret_cast<float4 *>(tab32);
         for (int k = threadIdx.x; k < kCells32 * kCellVals / 4; k += blockDim.x) dst[k] = src[k];
         __syncthreads();
     }
-    double2 *wstage = stage + (kWave64 ? (threadIdx.x >> 6) * kStageChunks : 0);
-    // one sample (a lane that is not live runs the sample for the
-    // wavefront's table reads and stores nothing)
-    auto one = [&](const ShotParams &sp, int s, int64_t i, bool live) {
-        int flags = 0, nprom = 0;
-        phase_sample<PREC, QUANTUM, LOCAL, NODES, MODES>(P, sp, i, env32, env64, tab32, wstage,
-                                                         live, flags, nprom);
-        if (flags) atomicOr(&P.flags[s], flags);
-        if (PREC == PREC_F32MIX && P.fp64_steps != nullptr) {
-            // FP64 wave-steps of the wavefronts that hold a sample of the shot
-            const bool count = __any(live);
-            if (count && nprom > 0 && (threadIdx.x & 63) == 0)
-                atomicAdd(&P.fp64_steps[s], (unsigned long long)nprom);
-        }
-    };
+    const RadTab<double> tabd{P.rad64};  // (not read)
     int s_prev = 0;  // the shot of the block's previous item
     for (;;) {
         const int64_t item = next_item(&P.queue[0], &slot);
@@ -298,24 +272,85 @@ __attribute__((amdgpu_waves_per_eu((PREC == PREC_F32 && QUANTUM) ? 4 : 1))) void
             find_shot_from(P.shots, P.n_shots, item, false, s_prev));
         s_prev = s;
         const ShotParams &sp = P.shots[s];
-        if constexpr (kGroup) {
-            const int64_t first = ordered_round<kPhaseBlock>(sp.n_samples, item - sp.item0);
+        const int64_t base = (item - sp.item0) * kPhaseBlock;
+        int off = threadIdx.x;
+        if constexpr (kOrder) {
+            chi_order32<kPhaseBlock, kPhaseBlock>(sp, P.key0, P.key1, base, sp.n_samples, okey,
+                                                  oidx);
+            off = oidx[threadIdx.x];
+        }
+        const int64_t i = base + off;
+        if (i < sp.n_samples) {
+            int flags = 0, nprom = 0;
+            phase_sample<PREC, QUANTUM, LOCAL, NODES, MODES>(P, sp, i, env32, env64, tab32, tabd,
+                                                             flags, nprom);
+            if (flags) atomicOr(&P.flags[s], flags);
+        }
+    }
+}
+
+// Quantum passes with FP64 steps (all of them, or where chi is high).  One
+// block a CU holds the FP64 table's cells that the launch reaches in LDS (and
+// the FP32 table); its wavefronts take items of 64 samples each on their own,
+// in passes with FP32 steps in order of the group's chi scale (order_kernel).
+// Bound by FP64 issue: with the table read a wavefront at a time from L2 through
+// LDS staging rows, two wavefronts a SIMD, 2^20 FP64 samples x 512 steps took
+// 8.8 ms, now 6.6 ms (VALU busy 0.79 of the time, by counters); eight quantum
+// shots of 2^18 x 1024 with FP64 steps 17.8 -> 11.5 ms.  Four wavefronts a SIMD in
+// 128 registers in FP64 passes; three in 168 with FP32 steps beside (at four the
+// FP32 steps spill: 23.4 ms; at two 12.7 ms).
+template <int PREC>
+constexpr int phase64_block() {
+    return PREC == PREC_F32MIX ? 768 : 1024;
+}
+
+template <int PREC, bool LOCAL, bool NODES, bool MODES>
+__global__ __launch_bounds__(phase64_block<PREC>()) void phase64_kernel(
+    BatchParams P, const float *__restrict__ env32, const double *__restrict__ env64) {
+    constexpr bool kMix = PREC == PREC_F32MIX;
+    constexpr int kWin = kMix ? kWinMix : kWin64;
+    extern __shared__ double2 win[];  // [8][kWin]
+    __shared__ __align__(16) float tab32[kMix ? kCells32 * kCellVals : 4];
+    const RadTabWin<kWin> tabd{win, P.rad64, RadTabWin<kWin>::first(P.win_top)};
+    RadTabWin<kWin>::load(win, P.rad64, tabd.c0);
+    if (kMix) {
+        const float4 *src = reinterpret_cast<const float4 *>(P.rad32);
+        float4 *dst = reinterpret_cast<float4 *>(tab32);
+        for (int k = threadIdx.x; k < kCells32 * kCellVals / 4; k += blockDim.x) dst[k] = src[k];
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    constexpr int kPer = kPhaseBlock / 64;
+    int s_prev = 0;  // the shot of the wavefront's previous item
+    for (;;) {
+        unsigned int taken = 0;
+        if (lane == 0) taken = atomicAdd(&P.queue[0], 1u);
+        const int64_t item = __builtin_amdgcn_readfirstlane(taken);
+        if (item >= kPer * P.n_items) break;
+        const int s = __builtin_amdgcn_readfirstlane(
+            find_shot_from(P.shots, P.n_shots, item / kPer, false, s_prev));
+        s_prev = s;
+        const ShotParams &sp = P.shots[s];
+        const int64_t k = item - kPer * sp.item0;
+        int64_t i = 64 * k + lane;
+        bool live = i < sp.n_samples;
+        if constexpr (kMix && !NODES) {
+            if (64 * k >= sp.n_samples) continue;
+            const int64_t first = ordered_round<64>(sp.n_samples, k);
             const int64_t base = first & ~(kChiGroup - 1ll);
             const int cnt = (int)min((int64_t)kChiGroup, sp.n_samples - base);
-            const int rank = (int)(first - base) + (int)threadIdx.x;
-            if ((rank & ~63) < cnt)  // some lane of the wavefront has a sample
-                one(sp, s, ordered_sample(P, sp, base, cnt, rank), rank < cnt);
-        } else {
-            const int64_t base = (item - sp.item0) * kPhaseBlock;
-            int off = threadIdx.x;
-            if constexpr (kOrder) {
-                chi_order32<kPhaseBlock, kPhaseBlock>(sp, P.key0, P.key1, base, sp.n_samples, okey,
-                                                      oidx);
-                off = oidx[threadIdx.x];
-            }
-            const int64_t i = base + off;
-            const bool live = i < sp.n_samples;
-            if (kWave64 || live) one(sp, s, live ? i : sp.n_samples - 1, live);
+            const int rank = (int)(first - base) + lane;
+            live = rank < cnt;
+            i = ordered_sample(P, sp, base, cnt, rank);
+        }
+        if (live) {
+            int flags = 0, nprom = 0;
+            phase_sample<PREC, true, LOCAL, NODES, MODES>(P, sp, i, env32, env64, tab32, tabd,
+                                                          flags, nprom);
+            if (flags) atomicOr(&P.flags[s], flags);
+            // FP64 wave-steps of the wavefronts of the shot
+            if (kMix && P.fp64_steps != nullptr && nprom > 0 && lane == 0)
+                atomicAdd(&P.fp64_steps[s], (unsigned long long)nprom);
         }
     }
 }
@@ -899,69 +934,102 @@ hipError_t launch_order(const BatchParams &p, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int PREC, bool QUANTUM, bool LOCAL>
-static const void *phase_ptr(bool modes) {
-    if (modes) return reinterpret_cast<const void *>(&phase_kernel<PREC, QUANTUM, LOCAL, false, true>);
-    return reinterpret_cast<const void *>(&phase_kernel<PREC, QUANTUM, LOCAL>);
+// The phase kernel of a pass: quantum passes with FP64 steps run
+// phase64_kernel (wide: its block size and LDS follow from the launch).
+struct PhaseKernel {
+    const void *fn;
+    int block;  // threads (wide: at most)
+    size_t lds;
+    bool wide;
+};
+
+template <int PREC, bool LOCAL, bool NODES, bool MODES>
+static PhaseKernel phase64_of() {
+    return {reinterpret_cast<const void *>(&phase64_kernel<PREC, LOCAL, NODES, MODES>),
+            phase64_block<PREC>(),
+            sizeof(double2) * 8 * (PREC == PREC_F32MIX ? kWinMix : kWin64), true};
+}
+
+template <int PREC, bool QUANTUM, bool LOCAL, bool NODES, bool MODES>
+static PhaseKernel phase_of() {
+    if constexpr (QUANTUM && PREC != PREC_F32)
+        return phase64_of<PREC, LOCAL, NODES, MODES>();
+    else
+        return {reinterpret_cast<const void *>(&phase_kernel<PREC, QUANTUM, LOCAL, NODES, MODES>),
+                kPhaseBlock, 0, false};
 }
 
 // modes: some shot of the launch uses a higher transverse mode
-static const void *select_phase(int prec, int rr, int amp, bool modes) {
-    const bool q = rr == 1, l = amp == 1;
-    if (prec == PREC_F32MIX && !q) prec = PREC_F32;  // no radiation table, no promotion
-#define QS_SEL(P)                                              \
-    if (prec == P) {                                           \
-        if (q && l) return phase_ptr<P, true, true>(modes);    \
-        if (q && !l) return phase_ptr<P, true, false>(modes);  \
-        if (!q && l) return phase_ptr<P, false, true>(modes);  \
-        return phase_ptr<P, false, false>(modes);              \
-    }
-    QS_SEL(PREC_F32)
-    QS_SEL(PREC_F64)
-    if (prec == PREC_F32MIX) {
-        if (l) return phase_ptr<PREC_F32MIX, true, true>(modes);
-        return phase_ptr<PREC_F32MIX, true, false>(modes);
-    }
-#undef QS_SEL
-    return nullptr;
+template <int PREC, bool QUANTUM>
+static PhaseKernel select_phase(bool local, bool modes) {
+    if (local)
+        return modes ? phase_of<PREC, QUANTUM, true, false, true>()
+                     : phase_of<PREC, QUANTUM, true, false, false>();
+    return modes ? phase_of<PREC, QUANTUM, false, false, true>()
+                 : phase_of<PREC, QUANTUM, false, false, false>();
 }
 
-hipError_t launch_phase(const BatchParams &p, const float *env32, const double *env64, int prec,
-                        int rr, int amp, hipStream_t s) {
-    const void *fn = select_phase(prec, rr, amp, p.any_mode != 0);
-    if (!fn) return hipErrorInvalidValue;
-    int grid = 0;
-    hipError_t e = resident_grid(fn, kPhaseBlock, 0, p.n_items, &grid, p.phase_cap);
-    if (e != hipSuccess) return e;
+static hipError_t run_phase(const PhaseKernel &k, const BatchParams &p, const float *env32,
+                            const double *env64, hipStream_t s) {
+    int grid = 0, block = k.block;
+    hipError_t e;
+    if (k.wide) {
+        // a block a CU, with as many wavefronts as the launch has work for
+        // (small launches: one a SIMD at most before a second)
+        int device = 0, ncu = 0;
+        e = hipGetDevice(&device);
+        if (e == hipSuccess)
+            e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds);
+        if (e != hipSuccess) return e;
+        const int64_t waves = p.n_items * (kPhaseBlock / 64);
+        int64_t per = (waves + ncu - 1) / ncu;
+        int most = block / 64;
+        if (p.phase_cap > 0 && most > p.phase_cap * (kPhaseBlock / 64))
+            most = p.phase_cap * (kPhaseBlock / 64);
+        if (per > most) per = most;
+        if (per < 1) per = 1;
+        block = 64 * (int)per;
+        const int64_t blocks = (waves + per - 1) / per;
+        grid = (int)(blocks < ncu ? (blocks < 1 ? 1 : blocks) : ncu);
+    } else {
+        e = resident_grid(k.fn, block, 0, p.n_items, &grid, p.phase_cap);
+        if (e != hipSuccess) return e;
+    }
     BatchParams pc = p;
     const float *e32 = env32;
     const double *e64 = env64;
     void *args[] = {&pc, &e32, &e64};
-    return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(kPhaseBlock), args, 0, s);
+    return hipLaunchKernel(k.fn, dim3((unsigned)grid), dim3(block), args, k.lds, s);
 }
 
-template <int PREC, bool QUANTUM>
-static const void *node_ptr() {
-    return reinterpret_cast<const void *>(&phase_kernel<PREC, QUANTUM, false, true>);
+hipError_t launch_phase(const BatchParams &p, const float *env32, const double *env64, int prec,
+                        int rr, int amp, hipStream_t s) {
+    const bool q = rr == 1, l = amp == 1, m = p.any_mode != 0;
+    if (prec == PREC_F32MIX && !q) prec = PREC_F32;  // no radiation table, no promotion
+    PhaseKernel k{};
+    if (prec == PREC_F32) k = q ? select_phase<PREC_F32, true>(l, m) : select_phase<PREC_F32, false>(l, m);
+    if (prec == PREC_F64) k = q ? select_phase<PREC_F64, true>(l, m) : select_phase<PREC_F64, false>(l, m);
+    if (prec == PREC_F32MIX) k = select_phase<PREC_F32MIX, true>(l, m);
+    if (!k.fn) return hipErrorInvalidValue;
+    return run_phase(k, p, env32, env64, s);
 }
 
 hipError_t launch_phase_nodes(const BatchParams &p, const float *env32, const double *env64,
                               int prec, int rr, hipStream_t s) {
     const bool q = rr == 1;
     if (prec == PREC_F32MIX && !q) prec = PREC_F32;
-    const void *fn = nullptr;
-    if (prec == PREC_F32) fn = q ? node_ptr<PREC_F32, true>() : node_ptr<PREC_F32, false>();
-    if (prec == PREC_F64) fn = q ? node_ptr<PREC_F64, true>() : node_ptr<PREC_F64, false>();
-    if (prec == PREC_F32MIX) fn = node_ptr<PREC_F32MIX, true>();
-    if (!fn) return hipErrorInvalidValue;
-    int grid = 0;
-    hipError_t e = resident_grid(fn, kPhaseBlock, 0, p.n_items, &grid, p.phase_cap);
-    if (e != hipSuccess) return e;
-    BatchParams pc = p;
-    const float *e32 = env32;
-    const double *e64 = env64;
-    void *args[] = {&pc, &e32, &e64};
-    return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(kPhaseBlock), args, 0, s);
+    PhaseKernel k{};
+    if (prec == PREC_F32)
+        k = q ? phase_of<PREC_F32, true, false, true, false>()
+              : phase_of<PREC_F32, false, false, true, false>();
+    if (prec == PREC_F64)
+        k = q ? phase_of<PREC_F64, true, false, true, false>()
+              : phase_of<PREC_F64, false, false, true, false>();
+    if (prec == PREC_F32MIX) k = phase_of<PREC_F32MIX, true, false, true, false>();
+    if (!k.fn) return hipErrorInvalidValue;
+    return run_phase(k, p, env32, env64, s);
 }
 
 // edge weights (u64, one per edge) and counters (u32, one per bin and two

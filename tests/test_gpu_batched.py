@@ -81,3 +81,24 @@ def test_batch_repeat_is_deterministic(gpu):
     for x, y in zip(a, b):
         for key in x:
             assert np.array_equal(x[key], y[key])
+
+
+@pytest.mark.parametrize("precision,chi64", [("fp64", 0.0), ("fp32", 1e-30)])
+@pytest.mark.parametrize("amp", ["local", "a0eff"])
+def test_fp64_table_window_of_a_batch(gpu, precision, chi64, amp):
+    """FP64 steps read the table's cells below the largest chi of the launch
+    from LDS and lower cells from memory: shots whose chi lies 20 octaves and
+    more below another's (and one without a field) give in one batch the bits
+    they give alone, where the window ends at their own chi.  Sample counts
+    about the 64 of a work item."""
+    base = dict(workloads.scaled(workloads.focused_3d(), n_steps=256), precision=precision,
+                chi_fp64=chi64, amp_mode=amp)
+    shots = [dict(base, n_samples=n, a0=a0, gamma0=g0, sigma_gamma=0.02 * g0, e_hi=1.5 * g0)
+             for n, a0, g0 in ((65, 150.0, 3e4), (64, 0.02, 300.0), (63, 1e-4, 100.0),
+                               (1, 0.0, 2000.0), (300, 2.0, 1000.0))]
+    batch = [_np(o) for o in gpu.forward_batched(shots)]
+    for k, p in enumerate(shots):
+        single = _np(gpu.forward(dict(p, shot=p["shot"] + k)))
+        assert single["energy_hist"].sum() == p["n_samples"]
+        for key in ("energy_hist", "angle_hist", "a0eff_hist", "moments", "status"):
+            assert np.array_equal(batch[k][key], single[key]), (k, key)
