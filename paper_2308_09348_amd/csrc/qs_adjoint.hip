@@ -70,14 +70,18 @@ __device__ __forceinline__ RadJ<float> rad6_cell_eval(const RadCell6 &cell, floa
 
 // FP64 table, cell-major [cell][g, G1, G2, h, G3, H1][power]: the plain
 // functions, combined here.
+__device__ __forceinline__ void rad6_cell_eval64(const double *q, double t,
+                                                 double v[kDerivFuncs]) {
+#pragma unroll
+    for (int f = 0; f < kDerivFuncs; ++f)
+        v[f] = fma(t, fma(t, fma(t, q[4 * f + 3], q[4 * f + 2]), q[4 * f + 1]), q[4 * f]);
+}
+
 __device__ __forceinline__ void rad6_plain64(const double *__restrict__ tab, double chi,
                                              double v[kDerivFuncs]) {
     double t;
     const int c = rad_index64(chi, t);
-    const double *q = tab + (size_t)c * (4 * kDerivFuncs);
-#pragma unroll
-    for (int f = 0; f < kDerivFuncs; ++f)
-        v[f] = fma(t, fma(t, fma(t, q[4 * f + 3], q[4 * f + 2]), q[4 * f + 1]), q[4 * f]);
+    rad6_cell_eval64(tab + (size_t)c * (4 * kDerivFuncs), t, v);
 }
 
 __device__ __forceinline__ RadJ<double> radj_combine(const double v[kDerivFuncs]) {
@@ -86,16 +90,10 @@ __device__ __forceinline__ RadJ<double> radj_combine(const double v[kDerivFuncs]
                         h, H1};
 }
 
-__device__ __forceinline__ RadJ<double> radj_eval64(const double *__restrict__ tab, double chi) {
-    double v[kDerivFuncs];
-    rad6_plain64(tab, chi, v);
-    return radj_combine(v);
-}
-
 // Where a stage takes its radiation functions from.  FP32: the LDS table,
 // read at stages 2 and 4 only -- stage 3 reuses stage 2's cell and the next
 // step's stage 1 reuses stage 4's (as in the forward phase loop).  FP64: the
-// global table at every stage.
+// table's window in LDS at every stage.
 template <class T>
 struct RadSrc;
 template <>
@@ -116,12 +114,17 @@ struct RadSrc<float> {
 };
 template <>
 struct RadSrc<double> {
-    const double *tab;
+    const TabWindow<kWinDeriv64, kDerivFuncs> *win;
     __device__ __forceinline__ void init(double) {}
-    __device__ __forceinline__ RadJ<double> s1(double chi) { return radj_eval64(tab, chi); }
-    __device__ __forceinline__ RadJ<double> s2(double chi) { return radj_eval64(tab, chi); }
-    __device__ __forceinline__ RadJ<double> s3(double chi) { return radj_eval64(tab, chi); }
-    __device__ __forceinline__ RadJ<double> s4(double chi) { return radj_eval64(tab, chi); }
+    __device__ __forceinline__ RadJ<double> ev(double chi) {
+        double v[kDerivFuncs];
+        win->eval(chi, v);
+        return radj_combine(v);
+    }
+    __device__ __forceinline__ RadJ<double> s1(double chi) { return ev(chi); }
+    __device__ __forceinline__ RadJ<double> s2(double chi) { return ev(chi); }
+    __device__ __forceinline__ RadJ<double> s3(double chi) { return ev(chi); }
+    __device__ __forceinline__ RadJ<double> s4(double chi) { return ev(chi); }
 };
 
 __device__ __forceinline__ float recip(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -671,19 +674,18 @@ __device__ __forceinline__ void tangent_update(const StepLin<T, QUANTUM> &L, con
 // FP64 steps of the mixed-precision tangent loop, from step j on for as long
 // as some lane of the wavefront has chi above the threshold at a step start
 // (the rule of the forward pass).  The state advances by the forward pass's
-// FP64 step (FP64 amplitudes, the FP64 table read a wavefront at a time);
+// FP64 step (FP64 amplitudes, the FP64 table's window in LDS);
 // the tangents by the FP32 step linearisation at the state rounded to FP32,
 // with the FP32 amplitude derivatives and derivative table as in the FP32
 // steps (the linearisation is rounded to FP32 either way), with the FP32
 // loop's table cells carried from stage to stage as there.  A1, da1 and those
 // cells carry over to the step the segment returns, the first not taken.
-template <bool LOCAL, int ND, int GD>
+template <bool LOCAL, int ND, int GD, class Tab>
 __device__ __forceinline__ int tangent_fp64_segment(
     const BatchParams &P, const AdjPath<double> &pd, double S0d, const AdjPath<float> &pf,
-    float S0f, const float *__restrict__ env32, const double *__restrict__ env64, double2 *stage,
+    float S0f, const float *__restrict__ env32, const double *__restrict__ env64, const Tab &tabd,
     RadSrc<float> &rad, const Phys<float> &phf, int j, double &mu, double &s2, float *vm,
     float *vs, float *da1, StageAmp<float> &A1, float &cmx, float &chi_hi, double &chd) {
-    const RadTabWave tabd(P.rad64, stage);
     const Phys<double> phd{P.K, P.CD, P.two_over_aS};
     const int N = P.n_steps;
     const double h = P.h, psi0 = -P.psi_max, ell = P.ell_per_psi;
@@ -706,7 +708,7 @@ __device__ __forceinline__ int tangent_fp64_segment(
             da[1] = 0.0f;
         }
     };
-    double a1 = amp64(fma((double)j, h, psi0), env64[2 * j]);
+    AmpFactors<double> F1(amp64(fma((double)j, h, psi0), env64[2 * j]), phd);
     for (;;) {
         // tangents: FP32 linearisation at the rounded state
         const float psif = fmaf((float)j, hf, psi0f);
@@ -725,13 +727,12 @@ __device__ __forceinline__ int tangent_fp64_segment(
         const double ah = amp64(fma(0.5, h, psi), env64[2 * j + 1]);
         const double a4 = amp64(psi + h, env64[2 * j + 2]);
         double dm, ds;
-        rk4_increment<double, true, RadTabWave>(mu, s2, a1, ah, a4, h, phd, tabd, dm, ds, chd);
+        rk4_q64(mu, s2, F1, ah, a4, h, phd, tabd, dm, ds, chd);
         mu += dm;
         s2 += ds;
-        a1 = a4;
         ++j;
         if (j >= N) break;
-        const double chi = phd.two_over_aS * mu * fabs(a1);
+        const double chi = F1.cpm * mu;
         cmx = fmaxf(cmx, (float)chi);
         if (!__any(chi > (double)P.chi_fp64)) break;
     }
@@ -749,26 +750,20 @@ struct SampleTangent {
 };
 
 // One sample: trajectory, tangents, and the chain to the eight parameters.
-template <int PREC, bool QUANTUM, bool LOCAL>
+// rad: the radiation functions of the linearisation; tabd: those of the FP64
+// steps of a mixed-precision pass.
+template <int PREC, bool QUANTUM, bool LOCAL, class Src, class Tab>
 __device__ __forceinline__ void tangent_sample(const BatchParams &P, const ShotParams &sp,
                                                int64_t i, const float *__restrict__ env32,
-                                               const double *__restrict__ env64,
-                                               const float *tab32, double2 *stage,
-                                               SampleTangent &o, int &flags) {
+                                               const double *__restrict__ env64, Src rad,
+                                               const Tab &tabd, SampleTangent &o, int &flags) {
     using T = typename std::conditional<PREC == PREC_F64, double, float>::type;
-    // FP32 with FP64 steps where chi is above the threshold (quantum only;
-    // stage: the wavefront's staging rows for the FP64 table, every lane
-    // active)
+    // FP32 with FP64 steps where chi is above the threshold (quantum only)
     constexpr bool MIX = PREC == PREC_F32MIX;
     static_assert(!MIX || QUANTUM, "FP64 steps are a quantum-model option");
     constexpr int ND = LOCAL ? kDirLocal : kDirA0eff;
     constexpr int GD = LOCAL ? 5 : 1;  // the gamma0 direction: no amplitude forcing
     const int N = P.n_steps;
-    RadSrc<T> rad;
-    if constexpr (PREC == PREC_F64)
-        rad.tab = P.rad64d;
-    else
-        rad.tab = tab32;
     const T *env;
     if constexpr (PREC == PREC_F64)
         env = env64;
@@ -829,7 +824,7 @@ __device__ __forceinline__ void tangent_sample(const BatchParams &P, const ShotP
                 AdjSample sd;
                 adj_sample(P, sp, opaque_index(i), sd);
                 j = tangent_fp64_segment<LOCAL, ND, GD>(P, sd.p, sd.d0.S, pth, S0, env32, env64,
-                                                        stage, rad, ph, j, mud, s2d, vm, vs, da1,
+                                                        tabd, rad, ph, j, mud, s2d, vm, vs, da1,
                                                         A1, cmx, chi_hi, chd);
                 mu = (float)mud;
                 mu_lo = (float)(mud - (double)mu);
@@ -919,117 +914,155 @@ __device__ __forceinline__ void tangent_sample(const BatchParams &P, const ShotP
     }
 }
 
-// Fixed-order reduction of the block's eight sums into the item's partials.
-__device__ __forceinline__ void grad_item_reduce(const BatchParams &P, int64_t item,
-                                                 const double *g, double (*red)[kGradParams]) {
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+// The sums of a wavefront's eight values into a row of the gradient partials
+// (stored column after column).
+__device__ __forceinline__ void grad_row(const BatchParams &P, int64_t row, const double *g) {
 #pragma unroll
     for (int p = 0; p < kGradParams; ++p) {
-        const double v = wave_sum(g[p]);
-        if (lane == 0) red[wid][p] = v;
+        const double v = wave_sum_last(g[p]);
+        if ((threadIdx.x & 63) == 63) P.partials[(size_t)p * kGradRows * P.n_items + row] = v;
     }
-    __syncthreads();
-    if (threadIdx.x < kGradParams) {
-        double sum = 0.0;
-        for (int w = 0; w < kPhaseBlock / 64; ++w) sum += red[w][threadIdx.x];
-        P.partials[(size_t)item * kGradParams + threadIdx.x] = sum;
-    }
-    // red is rewritten only after the next item's barriers
 }
 
-// TAPE = false: the adjoint -- each sample's derivatives contracted at once
-// with its law sensitivities, summed per item.  TAPE = true: the forward pass
-// that also records the derivatives: final states for the deposit kernel and
-// the tape (mu, sig2 and their eight derivatives, structure of arrays).
-// Occupancy: the FP32 tape pass is latency-bound and fits 168 VGPRs, three
-// waves per SIMD; every other pass is held to 256 (two waves): the FP64 ones
-// would otherwise take a few registers more and run one wave per SIMD, and
-// the mixed ones are held to two by the FP64 table staging in LDS anyway.
-// Mixed precision (FP64 steps): a work item is a round of a group's samples in
-// order of their chi scale; every lane of a wavefront runs, lanes past the
-// group's end repeat its last sample.
+// One sample of the tangent kernels.  TAPE = true: the forward pass that also
+// records the derivatives: the final state for the deposit kernel and the tape
+// entries (mu, sig2 and their eight derivatives, structure of arrays).  TAPE =
+// false: the adjoint: its derivatives contracted at once with its law
+// sensitivities, into g.
+template <int PREC, bool QUANTUM, bool LOCAL, bool TAPE, class Src, class Tab>
+__device__ __forceinline__ void tangent_one(const BatchParams &P, const ShotParams &sp, int s,
+                                            int64_t i, const float *__restrict__ env32,
+                                            const double *__restrict__ env64, const Src &rad,
+                                            const Tab &tabd, double *g) {
+    int flags = 0;
+    SampleTangent o;
+    tangent_sample<PREC, QUANTUM, LOCAL>(P, sp, i, env32, env64, rad, tabd, o, flags);
+    if (TAPE) {
+        const int64_t k = sp.state_off + i;
+        P.st.mu[k] = o.mu;
+        P.st.s2[k] = o.s2;
+        P.st.S0[k] = o.S0;
+        P.st.g0[k] = o.g0;
+        P.st.thx[k] = o.thx;
+        P.st.thy[k] = o.thy;
+        P.st.cmx[k] = o.cmx;
+        double *tp = P.tape + k;
+        const int64_t n = P.tape_n;
+        tp[0] = o.mu;
+        tp[n] = o.s2;
+#pragma unroll
+        for (int p = 0; p < kGradParams; ++p) {
+            tp[(2 + p) * n] = o.dmu[p];
+            tp[(2 + kGradParams + p) * n] = o.ds2[p];
+        }
+    } else if (!(flags & kFlagNonFinite)) {
+        const ShotGrad &go = P.gouts[s];
+        if (go.d_energy) {
+            double lv, ls;
+            law_sensitivity(o.mu, o.s2, P.deposit, P.ksig_bins, sp.e_lo, sp.e_w, sp.n_e,
+                            go.d_energy, lv, ls);
+#pragma unroll
+            for (int p = 0; p < kGradParams; ++p) g[p] = fma(lv, o.dmu[p], ls * o.ds2[p]);
+        }
+        observable_sensitivity(P, sp, go, i, o.mu, o.s2, o.dmu, o.ds2, g);
+    }
+    if (flags) atomicOr(&P.flags[s], flags);
+}
+
+// FP32 passes and classical FP64 passes: blocks take items of kPhaseBlock
+// samples.  Occupancy: the FP32 tape pass is latency-bound and fits 168 VGPRs,
+// three waves per SIMD; every other pass is held to 256 (two waves).
 template <int PREC, bool QUANTUM, bool LOCAL, bool TAPE>
 __global__ __launch_bounds__(kPhaseBlock)
 __attribute__((amdgpu_waves_per_eu((TAPE && PREC == PREC_F32) ? 3 : 2))) void tangent_kernel(
     BatchParams P, const float *__restrict__ env32, const double *__restrict__ env64) {
-    constexpr bool kTab32 = QUANTUM && PREC != PREC_F64;
-    constexpr bool kWave64 = PREC == PREC_F32MIX;
-    __shared__ __align__(16) float tab32[kTab32 ? kCells32 * 4 * kDerivFuncs : 4];
-    __shared__ double2 stage[kWave64 ? (kPhaseBlock / 64) * kStageChunks : 1];
+    static_assert(PREC == PREC_F32 || !QUANTUM, "tangent64_kernel");
+    __shared__ __align__(16) float tab32[QUANTUM ? kCells32 * 4 * kDerivFuncs : 4];
     __shared__ int64_t slot;
-    __shared__ double red[kPhaseBlock / 64][kGradParams];
-    double2 *wstage = stage + (kWave64 ? (threadIdx.x >> 6) * kStageChunks : 0);
-    if (kTab32) {
+    if (QUANTUM) {
         const float4 *src = reinterpret_cast<const float4 *>(P.rad32d);
         float4 *dst = reinterpret_cast<float4 *>(tab32);
         for (int k = threadIdx.x; k < kCells32 * kDerivFuncs; k += blockDim.x) dst[k] = src[k];
         __syncthreads();
     }
-    // one sample: the tape entries and final state (TAPE), else its terms
-    // of the gradient added to g
-    auto one = [&](const ShotParams &sp, int s, int64_t i, bool live, double *g) {
-        int flags = 0;
-        SampleTangent o;
-        tangent_sample<PREC, QUANTUM, LOCAL>(P, sp, i, env32, env64, tab32, wstage, o, flags);
-        if (!live) return;  // ran for the wavefront's table reads only
-        if (TAPE) {
-            const int64_t k = sp.state_off + i;
-            P.st.mu[k] = o.mu;
-            P.st.s2[k] = o.s2;
-            P.st.S0[k] = o.S0;
-            P.st.g0[k] = o.g0;
-            P.st.thx[k] = o.thx;
-            P.st.thy[k] = o.thy;
-            P.st.cmx[k] = o.cmx;
-            double *tp = P.tape + k;
-            const int64_t n = P.tape_n;
-            tp[0] = o.mu;
-            tp[n] = o.s2;
-#pragma unroll
-            for (int p = 0; p < kGradParams; ++p) {
-                tp[(2 + p) * n] = o.dmu[p];
-                tp[(2 + kGradParams + p) * n] = o.ds2[p];
-            }
-        } else if (!(flags & kFlagNonFinite)) {
-            const ShotGrad &go = P.gouts[s];
-            double gi[kGradParams];
-#pragma unroll
-            for (int p = 0; p < kGradParams; ++p) gi[p] = 0.0;
-            if (go.d_energy) {
-                double lv, ls;
-                law_sensitivity(o.mu, o.s2, P.deposit, P.ksig_bins, sp.e_lo, sp.e_w, sp.n_e,
-                                go.d_energy, lv, ls);
-#pragma unroll
-                for (int p = 0; p < kGradParams; ++p) gi[p] = fma(lv, o.dmu[p], ls * o.ds2[p]);
-            }
-            observable_sensitivity(P, sp, go, i, o.mu, o.s2, o.dmu, o.ds2, gi);
-#pragma unroll
-            for (int p = 0; p < kGradParams; ++p) g[p] += gi[p];
-        }
-        if (flags) atomicOr(&P.flags[s], flags);
-    };
+    using T = typename std::conditional<PREC == PREC_F64, double, float>::type;
+    RadSrc<T> rad{};  // (classical: not read)
+    if constexpr (PREC == PREC_F32) rad.tab = tab32;
     for (;;) {
         const int64_t item = next_item(&P.queue[0], &slot);
-        double g[kGradParams];
-#pragma unroll
-        for (int p = 0; p < kGradParams; ++p) g[p] = 0.0;
         if (item >= P.n_items) break;
         const int s = __builtin_amdgcn_readfirstlane(find_shot(P.shots, P.n_shots, item, false));
         const ShotParams &sp = P.shots[s];
-        int64_t row = item;  // of the gradient partials: the shot's round
-        if constexpr (kWave64) {
-            const int64_t first = ordered_round<kPhaseBlock>(sp.n_samples, item - sp.item0);
+        double g[kGradParams];
+#pragma unroll
+        for (int p = 0; p < kGradParams; ++p) g[p] = 0.0;
+        const int64_t i = (item - sp.item0) * kPhaseBlock + threadIdx.x;
+        if (i < sp.n_samples)
+            tangent_one<PREC, QUANTUM, LOCAL, TAPE>(P, sp, s, i, env32, env64, rad, 0, g);
+        if (!TAPE) grad_row(P, item * kGradRows + (threadIdx.x >> 6), g);
+    }
+}
+
+// Quantum passes with FP64 steps (all of them, or where chi is high): as
+// phase64_kernel, one block a CU with a window of the FP64 table in LDS (FP64
+// passes: of the derivative table; with FP32 steps: of the forward table,
+// beside the FP32 derivative table), its wavefronts taking items of 64 samples
+// on their own, with FP32 steps in order of the group's chi scale.  Two
+// wavefronts a SIMD (256 registers; the passes with FP32 steps spill about 100
+// accesses, most of them where FP64 steps begin and end).  Bound by VALU issue:
+// eight quantum shots of 2^18 x 512 with the tape 26.9 -> 18.2 ms, 100,001 FP64
+// samples x 512 3.74 -> 2.75 ms, 5000 2.02 -> 1.35 ms, against the tables read from
+// L2 (with FP32 steps a wavefront at a time through LDS staging rows).
+constexpr int kTangent64Block = 512;
+
+template <int PREC, bool LOCAL, bool TAPE>
+__global__ __launch_bounds__(kTangent64Block) void tangent64_kernel(
+    BatchParams P, const float *__restrict__ env32, const double *__restrict__ env64) {
+    constexpr bool kMix = PREC == PREC_F32MIX;
+    extern __shared__ double2 win[];
+    __shared__ __align__(16) float tab32[kMix ? kCells32 * 4 * kDerivFuncs : 4];
+    using Win = typename std::conditional<kMix, TabWindow<kWinDerivMix, 4>,
+                                          TabWindow<kWinDeriv64, kDerivFuncs>>::type;
+    const Win tabd(win, kMix ? P.rad64 : P.rad64d);
+    using T = typename std::conditional<kMix, float, double>::type;
+    RadSrc<T> rad{};
+    if constexpr (kMix) {
+        const float4 *src = reinterpret_cast<const float4 *>(P.rad32d);
+        float4 *dst = reinterpret_cast<float4 *>(tab32);
+        for (int k = threadIdx.x; k < kCells32 * kDerivFuncs; k += blockDim.x) dst[k] = src[k];
+        rad.tab = tab32;
+    } else {
+        rad.win = &tabd;
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    int s_prev = 0;  // the shot of the wavefront's previous item
+    for (;;) {
+        unsigned int taken = 0;
+        if (lane == 0) taken = atomicAdd(&P.queue[0], 1u);
+        const int64_t item = __builtin_amdgcn_readfirstlane(taken);
+        if (item >= kGradRows * P.n_items) break;
+        const int s = __builtin_amdgcn_readfirstlane(
+            find_shot_from(P.shots, P.n_shots, item / kGradRows, false, s_prev));
+        s_prev = s;
+        const ShotParams &sp = P.shots[s];
+        const int64_t k = item - kGradRows * sp.item0;
+        if (64 * k >= sp.n_samples) continue;
+        int64_t first = 64 * k, i = first + lane;
+        bool live = i < sp.n_samples;
+        if constexpr (kMix) {
+            first = ordered_round<64>(sp.n_samples, k);
             const int64_t base = first & ~(kChiGroup - 1ll);
-            row = sp.item0 + first / kPhaseBlock;
             const int cnt = (int)min((int64_t)kChiGroup, sp.n_samples - base);
-            const int rank = (int)(first - base) + (int)threadIdx.x;
-            if ((rank & ~63) < cnt)  // some lane of the wavefront has a sample
-                one(sp, s, ordered_sample(P, sp, base, cnt, rank), rank < cnt, g);
-        } else {
-            const int64_t i = (item - sp.item0) * kPhaseBlock + threadIdx.x;
-            if (i < sp.n_samples) one(sp, s, i, true, g);
+            const int rank = (int)(first - base) + lane;
+            live = rank < cnt;
+            i = ordered_sample(P, sp, base, cnt, rank);
         }
-        if (!TAPE) grad_item_reduce(P, row, g, red);
+        double g[kGradParams];
+#pragma unroll
+        for (int p = 0; p < kGradParams; ++p) g[p] = 0.0;
+        if (live) tangent_one<PREC, true, LOCAL, TAPE>(P, sp, s, i, env32, env64, rad, tabd, g);
+        if (!TAPE) grad_row(P, kGradRows * sp.item0 + first / 64, g);
     }
 }
 
@@ -1070,7 +1103,6 @@ __global__ __launch_bounds__(kPhaseBlock) void contract_kernel(BatchParams P) {
     // words), read from LDS by every edge of every sample's law
     extern __shared__ double wsh[];
     __shared__ int64_t slot;
-    __shared__ double red[kPhaseBlock / 64][kGradParams];
     int s_w = -1;  // the shot whose weights wsh holds (block-uniform)
     for (;;) {
         const int64_t item = next_item(&P.queue[0], &slot);
@@ -1078,7 +1110,7 @@ __global__ __launch_bounds__(kPhaseBlock) void contract_kernel(BatchParams P) {
         const int s = __builtin_amdgcn_readfirstlane(find_shot(P.shots, P.n_shots, item, false));
         const ShotParams &sp = P.shots[s];
         if (s != s_w) {
-            // the previous item's reads ended at its reduction's barrier
+            // (the previous item's reads ended at next_item's barriers)
             const double *W = P.gouts[s].d_energy;
             if (W)
                 for (int k = threadIdx.x; k < sp.n_e + 2; k += blockDim.x) wsh[k] = W[k];
@@ -1091,15 +1123,15 @@ __global__ __launch_bounds__(kPhaseBlock) void contract_kernel(BatchParams P) {
         const int64_t i = (item - sp.item0) * kPhaseBlock + threadIdx.x;
         if (i < sp.n_samples && !contract_sample<OBS>(P, sp, s, i, wsh, g))
             atomicOr(&P.flags[s], kFlagNonFinite);
-        grad_item_reduce(P, item, g, red);
+        grad_row(P, item * kGradRows + (threadIdx.x >> 6), g);
     }
 }
 
 // The same for the tape of a pass with FP64 steps, a group of kChiGroup samples
-// at a time.  The tangent pass sums a group's terms a round of kPhaseBlock chi
-// ranks at a time; the tape is in sample order.  The terms are formed in sample
+// at a time.  The tangent pass sums a group's terms a wavefront of 64 chi ranks
+// at a time; the tape is in sample order.  The terms are formed in sample
 // order (every tape line read once, whole) and go through LDS, from where
-// each round is summed as the tangent pass sums it, so that the result equals
+// they are summed as the tangent pass sums them, so that the result equals
 // the recomputing adjoint's bit for bit.  (Reading the tape in chi order fetched
 // every line about eight times: 2^21 samples 1283 -> 583 us with the order in a
 // kernel of its own.)
@@ -1111,7 +1143,6 @@ __global__ __launch_bounds__(kContractBlock) void contract_group_kernel(BatchPar
     extern __shared__ double terms[];  // [kGradParams][kChiGroup], then the shot's energy weights
     double *wsh = terms + kGradParams * kChiGroup;
     __shared__ int64_t slot;
-    __shared__ double red[kChiGroup / 64][kGradParams];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     int s_w = -1;  // the shot whose weights wsh holds (block-uniform)
     for (;;) {
@@ -1137,44 +1168,33 @@ __global__ __launch_bounds__(kContractBlock) void contract_group_kernel(BatchPar
         for (int k = wid; 64 * k < cnt; k += kContractBlock / 64) {  // wavefronts of chi ranks
             const int r = 64 * k + lane;
             const int q = r < cnt ? P.order[sp.state_off + base + r] : 0;
+            double g[kGradParams];
 #pragma unroll
-            for (int p = 0; p < kGradParams; ++p) {
-                const double v = wave_sum(r < cnt ? terms[p * kChiGroup + q] : 0.0);
-                if (lane == 0) red[k][p] = v;
-            }
-        }
-        __syncthreads();
-        constexpr int kWaves = kPhaseBlock / 64;
-        const int round = threadIdx.x / kGradParams, p = threadIdx.x % kGradParams;
-        if (round * kPhaseBlock < cnt) {
-            double sum = 0.0;
-            for (int w = 0; w < kWaves; ++w)
-                if (64 * (kWaves * round + w) < cnt) sum += red[kWaves * round + w][p];
-            P.partials[(size_t)(sp.item0 + base / kPhaseBlock + round) * kGradParams + p] = sum;
+            for (int p = 0; p < kGradParams; ++p) g[p] = r < cnt ? terms[p * kChiGroup + q] : 0.0;
+            grad_row(P, kGradRows * sp.item0 + base / 64 + k, g);
         }
     }
 }
 
-// One block per shot: fixed-order sum of the shot's item partials.
-__global__ __launch_bounds__(256) void grad_finalize_kernel(BatchParams P) {
+// One block per shot: fixed-order sum of the shot's rows, two wavefronts a
+// column (rows l, l + 128, ... and l + 64, l + 192, ... for lane l).
+constexpr int kGradFinBlock = 64 * 2 * kGradParams;
+
+__global__ __launch_bounds__(kGradFinBlock) void grad_finalize_kernel(BatchParams P) {
     const int s = blockIdx.x;
     const ShotParams &sp = P.shots[s];
     const ShotGrad &so = P.gouts[s];
-    const int64_t ni = (sp.n_samples + kPhaseBlock - 1) / kPhaseBlock, first = sp.item0;
-    __shared__ double tree[256];
-    for (int p = 0; p < kGradParams; ++p) {
-        double acc = 0.0;
-        for (int64_t b = threadIdx.x; b < ni; b += blockDim.x)
-            acc += P.partials[(size_t)(first + b) * kGradParams + p];
-        tree[threadIdx.x] = acc;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if (threadIdx.x < w) tree[threadIdx.x] += tree[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) so.grad[p] = tree[0];
-        __syncthreads();
-    }
+    const int64_t rows = (sp.n_samples + 63) / 64;
+    __shared__ double half[2][kGradParams];
+    const int lane = threadIdx.x & 63, p = (threadIdx.x >> 6) >> 1, h = (threadIdx.x >> 6) & 1;
+    const double *col = P.partials + (size_t)p * kGradRows * P.n_items + kGradRows * sp.item0;
+    double acc = 0.0;
+#pragma unroll 8
+    for (int64_t b = 64 * h + lane; b < rows; b += 128) acc += col[b];
+    acc = wave_sum(acc);
+    if (lane == 0) half[h][p] = acc;
+    __syncthreads();
+    if (threadIdx.x < kGradParams) so.grad[threadIdx.x] = half[0][threadIdx.x] + half[1][threadIdx.x];
     if (threadIdx.x == 0 && so.status) {
         const int fl = P.flags[s];
         *so.status = (fl & kFlagNonFinite) ? 4 : ((fl & kFlagRange) ? 6 : 0);
@@ -1231,38 +1251,39 @@ __global__ void rad_derivs_kernel(const float *rad32d, const double *rad64d, int
 // Launchers
 // ===========================================================================
 template <int PREC, bool QUANTUM, bool LOCAL, bool TAPE>
-static const void *tangent_ptr() {
-    return reinterpret_cast<const void *>(&tangent_kernel<PREC, QUANTUM, LOCAL, TAPE>);
+static PassKernel tangent_of() {
+    if constexpr (QUANTUM && PREC != PREC_F32)
+        return {reinterpret_cast<const void *>(&tangent64_kernel<PREC, LOCAL, TAPE>),
+                kTangent64Block,
+                PREC == PREC_F32MIX ? sizeof(double2) * kCellVals / 2 * kWinDerivMix
+                                    : sizeof(double2) * 2 * kDerivFuncs * kWinDeriv64,
+                true};
+    else
+        return {reinterpret_cast<const void *>(&tangent_kernel<PREC, QUANTUM, LOCAL, TAPE>),
+                kPhaseBlock, 0, false};
 }
 
 template <bool TAPE>
-static const void *select_tangent(int prec, int rr, int amp) {
+static PassKernel select_tangent(int prec, int rr, int amp) {
     const bool q = rr == 1, l = amp == 1;
     if (prec == PREC_F64)
-        return q ? (l ? tangent_ptr<PREC_F64, true, true, TAPE>()
-                      : tangent_ptr<PREC_F64, true, false, TAPE>())
-                 : (l ? tangent_ptr<PREC_F64, false, true, TAPE>()
-                      : tangent_ptr<PREC_F64, false, false, TAPE>());
+        return q ? (l ? tangent_of<PREC_F64, true, true, TAPE>()
+                      : tangent_of<PREC_F64, true, false, TAPE>())
+                 : (l ? tangent_of<PREC_F64, false, true, TAPE>()
+                      : tangent_of<PREC_F64, false, false, TAPE>());
     if (prec == PREC_F32MIX && q)  // FP64 steps are a quantum-model option
-        return l ? tangent_ptr<PREC_F32MIX, true, true, TAPE>()
-                 : tangent_ptr<PREC_F32MIX, true, false, TAPE>();
-    return q ? (l ? tangent_ptr<PREC_F32, true, true, TAPE>()
-                  : tangent_ptr<PREC_F32, true, false, TAPE>())
-             : (l ? tangent_ptr<PREC_F32, false, true, TAPE>()
-                  : tangent_ptr<PREC_F32, false, false, TAPE>());
+        return l ? tangent_of<PREC_F32MIX, true, true, TAPE>()
+                 : tangent_of<PREC_F32MIX, true, false, TAPE>();
+    return q ? (l ? tangent_of<PREC_F32, true, true, TAPE>()
+                  : tangent_of<PREC_F32, true, false, TAPE>())
+             : (l ? tangent_of<PREC_F32, false, true, TAPE>()
+                  : tangent_of<PREC_F32, false, false, TAPE>());
 }
 
 hipError_t launch_tangent(const BatchParams &p, const float *env32, const double *env64, int prec,
                           int rr, int amp, bool tape, hipStream_t s) {
-    const void *fn = tape ? select_tangent<true>(prec, rr, amp) : select_tangent<false>(prec, rr, amp);
-    int grid = 0;
-    hipError_t e = resident_grid(fn, kPhaseBlock, 0, p.n_items, &grid);
-    if (e != hipSuccess) return e;
-    BatchParams pc = p;
-    const float *e32 = env32;
-    const double *e64 = env64;
-    void *args[] = {&pc, &e32, &e64};
-    return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(kPhaseBlock), args, 0, s);
+    return run_pass(tape ? select_tangent<true>(prec, rr, amp) : select_tangent<false>(prec, rr, amp),
+                    p, env32, env64, 0, s);
 }
 
 hipError_t launch_contract(const BatchParams &p, bool obs, int max_ne, hipStream_t s) {
@@ -1290,7 +1311,7 @@ hipError_t launch_contract(const BatchParams &p, bool obs, int max_ne, hipStream
 }
 
 hipError_t launch_grad_finalize(const BatchParams &p, hipStream_t s) {
-    grad_finalize_kernel<<<p.n_shots, 256, 0, s>>>(p);
+    grad_finalize_kernel<<<p.n_shots, kGradFinBlock, 0, s>>>(p);
     return hipGetLastError();
 }
 

@@ -90,7 +90,8 @@ __device__ __forceinline__ void sample_coords(const ShotParams &sp, uint32_t k0,
 }
 
 // ===========================================================================
-// Radiation functions: g, chi g', chi^2 g'', h from per-cell cubics
+// Radiation functions: the combinations T1 = g, T2 = 2g + chi g', T3 = g + 2 chi g' +
+// chi^2 g''/2 and T4 = h from per-cell cubics
 // ===========================================================================
 __device__ __forceinline__ void rad_eval32(const float *__restrict__ tab, float chi, float &g,
                                            float &G1, float &G2, float &hq) {
@@ -162,24 +163,19 @@ __device__ __forceinline__ void rad_cell_eval(const RadCell32 &cell, float chi, 
     hq = fmaf(t, fmaf(t, fmaf(t, cell.q3.w, cell.q3.z), cell.q3.y), cell.q3.x);
 }
 
-// FP64 cell of chi and the coordinate t in the cell (cell 0 is linear in chi
-// below 2^kEMin; chi beyond the table is clamped to the last cell and
-// reported by the caller).
+// FP64 cell of chi and the coordinate t in the cell (chi beyond the table is
+// clamped to the last cell and reported by the caller).
 // All in the upper word: the cell from its top bits, t = (chi - cell start)
-// 2^(SB - e), both operations exact.  rad_cell64: before the clamps, for chi in
-// the octave cells.
-__device__ __forceinline__ int rad_cell64(double chi, double &t) {
+// 2^(SB - e), both operations exact; cell 0 takes the coordinate of cell 1,
+// t = 64 (chi / 2^kEMin64 - 1) in [-64, 0).
+__device__ __forceinline__ int rad_index64(double chi, double &t) {
     constexpr int kLow = 20 - kSB64;  // bits of the upper word below the cell index
     const uint32_t hi = (uint32_t)__double2hiint(chi);
-    const double start = __hiloint2double((int)(hi >> kLow << kLow), 0);
-    const double inv = __hiloint2double((int)((uint32_t)(2046 + kSB64) - (hi >> 20)) << 20, 0);
+    const uint32_t hc = max(hi, (uint32_t)(1023 + kEMin64) << 20);
+    const double start = __hiloint2double((int)(hc >> kLow << kLow), 0);
+    const double inv = __hiloint2double((int)((uint32_t)(2046 + kSB64) - (hc >> 20)) << 20, 0);
     t = (chi - start) * inv;
-    return (int)(hi >> kLow) - ((1023 + kEMin) << kSB64) + 1;
-}
-
-__device__ __forceinline__ int rad_index64(double chi, double &t) {
-    const int c = rad_cell64(chi, t);
-    if (c < 1) t = chi * 0x1p20;
+    const int c = (int)(hi >> kLow) - ((1023 + kEMin64) << kSB64) + 1;
     return min(max(c, 0), kCells64 - 1);
 }
 
@@ -191,75 +187,20 @@ __device__ __forceinline__ void rad_cell_eval64(const double *q, double t, doubl
     hq = fma(t, fma(t, fma(t, q[15], q[14]), q[13]), q[12]);
 }
 
-__device__ __forceinline__ void rad_eval64(const double *__restrict__ tab, double chi, double &g,
-                                           double &G1, double &G2, double &hq) {
-    double t;
-    const int c = rad_index64(chi, t);
-    rad_cell_eval64(tab + (size_t)c * kCellVals, t, g, G1, G2, hq);
-}
-
-// The FP64 cells of all 64 lanes of a wavefront, fetched together.  A cell
-// is 128 bytes, one cache line; read lane by lane, every load instruction
-// would touch 64 lines.  Here four lanes read 64 bytes of one cell, so every
-// load instruction touches 16 lines and uses each fully for its half, and
-// the cells reach their lanes through a per-wavefront LDS staging area: one
-// row a lane holding half a cell (first the lower, then the upper 64 bytes),
-// rows padded to 80 bytes so that the row reads of eight lanes fall on
-// distinct banks.  Every lane of the wavefront must be active; the values
-// are those rad_eval64 reads.
-constexpr int kStageStride = 5;                  // 16-byte chunks a row
-constexpr int kStageChunks = 64 * kStageStride;  // per wavefront
-
 __device__ __forceinline__ void wave_sync_lds() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The same for cells of 64 PASSES bytes (8 PASSES doubles, row after row):
-// PASSES rounds of the staged read above, one 64-byte part of every cell each.
-template <int PASSES>
-__device__ __forceinline__ void coop_rows64(const double *__restrict__ tab, int c,
-                                            double2 *__restrict__ stage, double *q) {
-    const int lane = (int)(threadIdx.x & 63u);
-    const int k = lane & 3;
-    const double2 *cell[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int cr = __shfl(c, 16 * r + (lane >> 2), 64);
-        cell[r] = reinterpret_cast<const double2 *>(tab + (size_t)cr * (8 * PASSES)) + k;
-    }
-    const double2 *row = stage + lane * kStageStride;
-#pragma unroll
-    for (int part = 0; part < PASSES; ++part) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            stage[(16 * r + (lane >> 2)) * kStageStride + k] = cell[r][4 * part];
-        wave_sync_lds();
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const double2 v = row[m];
-            q[8 * part + 2 * m] = v.x;
-            q[8 * part + 2 * m + 1] = v.y;
-        }
-        wave_sync_lds();  // the next part overwrites the rows
-    }
-}
-
-__device__ __forceinline__ void coop_cell64(const double *__restrict__ tab, int c,
-                                            double2 *__restrict__ stage, double q[16]) {
-    static_assert(kCellVals == 16, "a forward-table cell is two 64-byte parts");
-    coop_rows64<2>(tab, c, stage, q);
-}
-
-// Chi at coordinate t in [0, 1) of a table cell (SB: sub-cells per octave;
-// cell 0 is linear in chi below 2^kEMin), the four Chebyshev nodes of a cell
+// Chi at coordinate t in [0, 1) of a table cell (sb: sub-cells per octave, emin:
+// the lowest octave; cell 0 is linear in chi below 2^emin), the four Chebyshev nodes of a cell
 // and the monomial coefficients l[0..3] of the Lagrange polynomial of node m
 // (a cubic through the node values v_m is sum_m v_m l_m(t)).
-__device__ __forceinline__ double cell_chi(int cell, double t, int sb) {
-    if (cell == 0) return t * 0x1p-20;
+__device__ __forceinline__ double cell_chi(int cell, double t, int sb, int emin) {
+    if (cell == 0) return ldexp(t, emin);
     const int c = cell - 1;
-    const int e = kEMin + (c >> sb);
+    const int e = emin + (c >> sb);
     const int sub = c & ((1 << sb) - 1);
     return ldexp(1.0 + ((double)sub + t) / (double)(1 << sb), e);
 }
@@ -284,83 +225,50 @@ __device__ __forceinline__ void cheb_basis(int m, double l[4]) {
     l[0] = -(r[0] * r[1] * r[2]) / den;
 }
 
-template <class T>
-struct RadTab;
-template <>
-struct RadTab<float> {
-    const float *p;
-    __device__ __forceinline__ void eval(float chi, float &g, float &G1, float &G2, float &h) const {
-        rad_eval32(p, chi, g, G1, G2, h);
-    }
+// The table of a pass without FP64 steps of the quantum model.
+struct NoTable {
+    __device__ __forceinline__ void eval(double, double *) const {}
 };
-template <>
-struct RadTab<double> {
-    const double *p;
-    __device__ __forceinline__ void eval(double chi, double &g, double &G1, double &G2,
-                                         double &h) const {
-        rad_eval64(p, chi, g, G1, G2, h);
-    }
-};
-// FP64 table read cooperatively by the whole wavefront (see coop_cell64).
-// The last cells read stay in registers: a stage whose lanes all fall in the
-// cells they already hold (the third RK4 stage mostly, and the first stage
-// after the fourth at the same amplitude) reads nothing.
-struct RadTabWave {
-    const double *p;
-    double2 *stage;
-    mutable double q[16];
-    mutable int c = -1;
-    __device__ __forceinline__ RadTabWave(const double *tab, double2 *st) : p(tab), stage(st) {}
-    __device__ __forceinline__ void eval(double chi, double &g, double &G1, double &G2,
-                                         double &h) const {
-        double t;
-        const int cn = rad_index64(chi, t);
-        if (__any(cn != c)) {
-            coop_cell64(p, cn, stage, q);
-            c = cn;
-        }
-        rad_cell_eval64(q, t, g, G1, G2, h);
-    }
-};
-
-// The FP64 table from LDS: the N cells from c0 >= 1 on (the top of the launch's
-// chi range), each 16-byte eighth of the cells in an array of its own, so that
-// lanes on neighbouring cells read neighbouring 16-byte words.  A cell outside
-// the window (chi below it, at a sign change of the carrier or in the far tail
-// of a weak shot) is read from the global table, in a branch of its own: were
-// the two reads alternatives, the compiler would merge part of them into flat
-// loads, which wait for both memories.  The values are those rad_eval64 reads.
-template <int N>
-struct RadTabWin {
-    const double2 *win;  // [8][N]
+// An FP64 table of F functions (cells of F cubics) with N of its cells in LDS, its
+// first or (BASED) those from c0 on, each 16-byte word of the cells in an array
+// of its own, so that lanes on neighbouring cells read neighbouring 16-byte
+// words.  Where some lane's cell lies outside them the wavefront reads the
+// global table.  The two branches meet in the functions' values: meeting in the
+// coefficients took 4 F more registers, and reads of the same width in both are
+// merged by the compiler into flat loads, which wait for both memories.  The
+// values are those of the global table.
+template <int N, int F, bool BASED = false>
+struct TabWindow {
+    const double2 *win;  // [2 F][N]
     const double *p;     // the whole table, cell-major
     int c0;
-    __device__ __forceinline__ void eval(double chi, double &g, double &G1, double &G2,
-                                         double &h) const {
-        double t, q[16];
-        const unsigned k = (unsigned)(rad_cell64(chi, t) - c0);
-        const double2 *w = win + min(k, (unsigned)N - 1);
+    __device__ __forceinline__ void eval(double chi, double v[F]) const {
+        double t;
+        const int c = rad_index64(chi, t), k = BASED ? c - c0 : c;
+        if (__all((unsigned)k < (unsigned)N)) {
+            const double2 *w = win + k;
+            double2 q[2 * F];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const double2 v = w[e * N];
-            q[2 * e] = v.x;
-            q[2 * e + 1] = v.y;
-        }
-        if (__any(k >= (unsigned)N)) {
-            if (k >= (unsigned)N) {
-                const double *c = p + (size_t)rad_index64(chi, t) * kCellVals;
+            for (int e = 0; e < 2 * F; ++e) q[e] = w[e * N];
 #pragma unroll
-                for (int e = 0; e < 16; ++e) q[e] = c[e];
-            }
+            for (int f = 0; f < F; ++f)
+                v[f] = fma(t, fma(t, fma(t, q[2 * f + 1].y, q[2 * f + 1].x), q[2 * f].y), q[2 * f].x);
+        } else {
+            const double *q = p + (size_t)c * (4 * F);
+#pragma unroll
+            for (int f = 0; f < F; ++f)
+                v[f] = fma(t, fma(t, fma(t, q[4 * f + 3], q[4 * f + 2]), q[4 * f + 1]), q[4 * f]);
         }
-        rad_cell_eval64(q, t, g, G1, G2, h);
     }
-    // the first cell of the window for a launch whose chi stays below cell top
-    __device__ __forceinline__ static int first(int top) { return max(top - N, 1); }
-    // all threads of the block; a barrier must follow
-    __device__ __forceinline__ static void load(double2 *win, const double *p, int c0) {
-        const double2 *src = reinterpret_cast<const double2 *>(p) + 8 * (size_t)c0;
-        for (int k = threadIdx.x; k < 8 * N; k += blockDim.x) win[(k & 7) * N + (k >> 3)] = src[k];
+    // filled by all threads of the block; a barrier must follow
+    __device__ __forceinline__ TabWindow(double2 *w, const double *tab, int first = 0)
+        : win(w), p(tab), c0(first) {
+        static_assert(N <= kCells64, "a part of the table");
+        const double2 *src = reinterpret_cast<const double2 *>(tab) + 2 * F * (size_t)first;
+        for (int k = threadIdx.x; k < 2 * F * N; k += blockDim.x) {
+            const int cell = k / (2 * F);
+            w[(k - cell * (2 * F)) * N + cell] = src[k];
+        }
     }
 };
 
@@ -375,31 +283,6 @@ template <class T>
 struct Phys {
     T K, CD, two_over_aS;
 };
-
-template <class T, bool QUANTUM, class Tab = RadTab<T>>
-__device__ __forceinline__ void rhs(T mu, T s2, T a, const Phys<T> &ph, const Tab &tab,
-                                    T &dmu, T &ds2, T &chi_hi) {
-    const T a2 = a * a;
-    const T Ka2 = ph.K * a2;
-    if (!QUANTUM) {
-        dmu = -Ka2 * mu * mu;
-        ds2 = T(0);
-        return;
-    }
-    const T aa = fabs(a);
-    const T chi = ph.two_over_aS * mu * aa;
-    chi_hi = fmax(chi_hi, chi);
-    T g, G1, G2, hq;
-    tab.eval(chi, g, G1, G2, hq);
-    const T two_g = T(2) * g;
-    const T A = -Ka2 * mu * mu * g;
-    const T A1 = -Ka2 * mu * (two_g + G1);
-    const T A2 = -Ka2 * (two_g + T(4) * G1 + G2);
-    const T mu2 = mu * mu;
-    const T D = ph.CD * a2 * aa * mu2 * mu2 * hq;
-    dmu = fma(T(0.5) * A2, s2, A);
-    ds2 = fma(T(2) * A1, s2, D);
-}
 
 // 1/sqrt(q) for q >= 1: the hardware estimate (about 2^-24) and one step of third
 // order, within an ulp (q beyond 1e300 counts as 1e300, the factor it gives as 0).
@@ -624,50 +507,76 @@ __device__ __forceinline__ int64_t ordered_sample(const BatchParams &P, const Sh
     return base + P.order[sp.state_off + base + min(rank, cnt - 1)];
 }
 
-// One RK4 step of (mu, sig2) from psi_j with amplitudes a1 = a(psi_j),
-// ah = a(psi_j + h/2), a4 = a(psi_j + h); returns the increments.
-template <class T, bool QUANTUM, class Tab = RadTab<T>>
-__device__ __forceinline__ void rk4_increment(T mu, T s2, T a1, T ah, T a4, T h,
-                                              const Phys<T> &ph, const Tab &tab, T &dmu,
-                                              T &ds2, T &chi_hi) {
+// One RK4 step of the classical model (g = 1, sig2 stays 0) from psi_j with
+// amplitudes a1 = a(psi_j), ah = a(psi_j + h/2), a4 = a(psi_j + h).
+template <class T>
+__device__ __forceinline__ T rk4_classical(T mu, T a1, T ah, T a4, T h, const Phys<T> &ph) {
     const T hh = T(0.5) * h;
-    T k1m, k1s, k2m, k2s, k3m, k3s, k4m, k4s;
-    rhs<T, QUANTUM, Tab>(mu, s2, a1, ph, tab, k1m, k1s, chi_hi);
-    rhs<T, QUANTUM, Tab>(fma(hh, k1m, mu), fma(hh, k1s, s2), ah, ph, tab, k2m, k2s, chi_hi);
-    rhs<T, QUANTUM, Tab>(fma(hh, k2m, mu), fma(hh, k2s, s2), ah, ph, tab, k3m, k3s, chi_hi);
-    rhs<T, QUANTUM, Tab>(fma(h, k3m, mu), fma(h, k3s, s2), a4, ph, tab, k4m, k4s, chi_hi);
+    auto f = [&](T m, T a) { return -(ph.K * (a * a)) * m * m; };
+    const T k1 = f(mu, a1);
+    const T k2 = f(fma(hh, k1, mu), ah);
+    const T k3 = f(fma(hh, k2, mu), ah);
+    const T k4 = f(fma(h, k3, mu), a4);
     const T h6 = h * T(1.0 / 6.0);
-    dmu = h6 * (k1m + T(2) * (k2m + k3m) + k4m);
-    ds2 = h6 * (k1s + T(2) * (k2s + k3s) + k4s);
+    return h6 * (k1 + T(2) * (k2 + k3) + k4);
 }
 
-// Moment right-hand side (quantum model) from the FP32 table's combined
-// functions at chi = two_over_aS mu |a|:  T1 = g,  T2 = 2g + chi g',
-// T3 = g + 2 chi g' + chi^2 g''/2,  T4 = h, so that
+// Moment right-hand side (quantum model) from the table's combined functions
+// at chi = two_over_aS mu |a|:
 //   dmu/dpsi   = -K a^2 (mu^2 T1 + sig2 T3),
 //   dsig2/dpsi = -2 K a^2 mu sig2 T2 + C_D a^2 |a| mu^4 T4.
 // The factors that depend on the amplitude only are formed once per phase
 // point (stages 2 and 3 share one, stage 4 hands its to the next stage 1).
-struct AmpQ {
-    float nu;   // -K a^2
-    float nu2;  // -2 K a^2
-    float cd;   // C_D a^2 |a|
-    float cpm;  // chi per unit mu: 2 |a| / a_S
-    __device__ __forceinline__ AmpQ() {}
-    __device__ __forceinline__ AmpQ(float a, const Phys<float> &ph) {
-        const float aa = fabsf(a), a2 = a * a;
+template <class T>
+struct AmpFactors {
+    T nu;   // -K a^2
+    T nu2;  // -2 K a^2
+    T cd;   // C_D a^2 |a|
+    T cpm;  // chi per unit mu: 2 |a| / a_S
+    __device__ __forceinline__ AmpFactors() {}
+    __device__ __forceinline__ AmpFactors(T a, const Phys<T> &ph) {
+        const T aa = fabs(a), a2 = a * a;
         nu = -ph.K * a2;
-        nu2 = 2.0f * nu;
+        nu2 = T(2) * nu;
         cd = ph.CD * aa * a2;
         cpm = ph.two_over_aS * aa;
     }
 };
+using AmpQ = AmpFactors<float>;
 
-__device__ __forceinline__ void rhs_q32(float mu, float s2, const AmpQ &A, float T1, float T2,
-                                        float T3, float T4, float &dmu, float &ds2) {
-    const float mu2 = mu * mu;
-    dmu = A.nu * fmaf(mu2, T1, s2 * T3);
-    ds2 = fmaf(A.nu2 * mu * s2, T2, A.cd * (mu2 * mu2) * T4);
+template <class T>
+__device__ __forceinline__ void rhs_quantum(T mu, T s2, const AmpFactors<T> &A, T T1, T T2, T T3,
+                                            T T4, T &dmu, T &ds2) {
+    const T mu2 = mu * mu;
+    dmu = A.nu * fma(mu2, T1, s2 * T3);
+    ds2 = fma(A.nu2 * mu * s2, T2, A.cd * (mu2 * mu2) * T4);
+}
+
+// One FP64 RK4 step of the quantum moment system; A1 (the factors at psi_j) is
+// replaced by those at psi_j + h.
+template <class Tab>
+__device__ __forceinline__ void rk4_q64(double mu, double s2, AmpFactors<double> &A1, double ah,
+                                        double a4, double h, const Phys<double> &ph,
+                                        const Tab &tab, double &dmu, double &ds2,
+                                        double &chi_hi) {
+    const double hh = 0.5 * h;
+    double k1m, k1s, k2m, k2s, k3m, k3s, k4m, k4s;
+    auto stage = [&](double m, double s, const AmpFactors<double> &A, double &km, double &ks) {
+        const double chi = A.cpm * m;
+        chi_hi = fmax(chi_hi, chi);
+        double T[4];
+        tab.eval(chi, T);
+        rhs_quantum(m, s, A, T[0], T[1], T[2], T[3], km, ks);
+    };
+    stage(mu, s2, A1, k1m, k1s);
+    const AmpFactors<double> Ah(ah, ph);
+    stage(fma(hh, k1m, mu), fma(hh, k1s, s2), Ah, k2m, k2s);
+    stage(fma(hh, k2m, mu), fma(hh, k2s, s2), Ah, k3m, k3s);
+    A1 = AmpFactors<double>(a4, ph);
+    stage(fma(h, k3m, mu), fma(h, k3s, s2), A1, k4m, k4s);
+    const double h6 = h * (1.0 / 6.0);
+    dmu = h6 * (k1m + 2.0 * (k2m + k3m) + k4m);
+    ds2 = h6 * (k1s + 2.0 * (k2s + k3s) + k4s);
 }
 
 // One FP32 RK4 step of the quantum moment system with two table reads:
@@ -683,7 +592,7 @@ __device__ __forceinline__ void rk4_q32(float mu, float s2, AmpQ &A1, float ah, 
     const float c1 = A1.cpm * mu;
     rad_cell_eval(carry, c1, g, G1, G2, hq);
     float k1m, k1s;
-    rhs_q32(mu, s2, A1, g, G1, G2, hq, k1m, k1s);
+    rhs_quantum(mu, s2, A1, g, G1, G2, hq, k1m, k1s);
     // stage 2 (table read)
     const AmpQ Ah(ah, ph);
     const float m2 = fmaf(hh, k1m, mu), s22 = fmaf(hh, k1s, s2);
@@ -692,13 +601,13 @@ __device__ __forceinline__ void rk4_q32(float mu, float s2, AmpQ &A1, float ah, 
     rad_lookup32(tab, c2, mid);
     rad_cell_eval(mid, c2, g, G1, G2, hq);
     float k2m, k2s;
-    rhs_q32(m2, s22, Ah, g, G1, G2, hq, k2m, k2s);
+    rhs_quantum(m2, s22, Ah, g, G1, G2, hq, k2m, k2s);
     // stage 3 (same phase as stage 2: reuse its cell)
     const float m3 = fmaf(hh, k2m, mu), s23 = fmaf(hh, k2s, s2);
     const float c3 = Ah.cpm * m3;
     rad_cell_eval(mid, c3, g, G1, G2, hq);
     float k3m, k3s;
-    rhs_q32(m3, s23, Ah, g, G1, G2, hq, k3m, k3s);
+    rhs_quantum(m3, s23, Ah, g, G1, G2, hq, k3m, k3s);
     // stage 4 (table read; its cell serves the next step's stage 1)
     A1 = AmpQ(a4, ph);
     const float m4 = fmaf(h, k3m, mu), s24 = fmaf(h, k3s, s2);
@@ -706,7 +615,7 @@ __device__ __forceinline__ void rk4_q32(float mu, float s2, AmpQ &A1, float ah, 
     rad_lookup32(tab, c4, carry);
     rad_cell_eval(carry, c4, g, G1, G2, hq);
     float k4m, k4s;
-    rhs_q32(m4, s24, A1, g, G1, G2, hq, k4m, k4s);
+    rhs_quantum(m4, s24, A1, g, G1, G2, hq, k4m, k4s);
     // the range check takes the chi of the table reads: stages 1 and 3
     // evaluate the cells of stages 4 and 2 at a chi a hair away (the state
     // moved by less than one step's increment)
@@ -1234,6 +1143,50 @@ inline hipError_t resident_grid(const void *fn, int block, size_t lds, int64_t i
     if (g > items) g = items;
     *grid = (int)(g < 1 ? 1 : g);
     return hipSuccess;
+}
+
+// A kernel over the phase items of a launch.  wide: one block a CU (its LDS holds
+// a window of the FP64 table), whose wavefronts take items of 64 samples; block
+// is then the most threads.
+struct PassKernel {
+    const void *fn;
+    int block;
+    size_t lds;
+    bool wide;
+};
+
+// cap: resident blocks of kPhaseBlock threads a CU at most (0: all that fit).
+inline hipError_t run_pass(const PassKernel &k, const BatchParams &p, const float *env32,
+                           const double *env64, int cap, hipStream_t s) {
+    int grid = 0, block = k.block;
+    hipError_t e;
+    if (k.wide) {
+        // as many wavefronts a CU as the launch has work for
+        int device = 0, ncu = 0;
+        e = hipGetDevice(&device);
+        if (e == hipSuccess)
+            e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds);
+        if (e != hipSuccess) return e;
+        constexpr int kPer = kPhaseBlock / 64;
+        const int64_t waves = p.n_items * kPer;
+        int64_t per = (waves + ncu - 1) / ncu;
+        const int64_t most = cap > 0 && cap * kPer < block / 64 ? cap * kPer : block / 64;
+        if (per > most) per = most;
+        if (per < 1) per = 1;
+        block = 64 * (int)per;
+        const int64_t blocks = (waves + per - 1) / per;
+        grid = (int)(blocks < ncu ? (blocks < 1 ? 1 : blocks) : ncu);
+    } else {
+        e = resident_grid(k.fn, block, k.lds, p.n_items, &grid, cap);
+        if (e != hipSuccess) return e;
+    }
+    BatchParams pc = p;
+    const float *e32 = env32;
+    const double *e64 = env64;
+    void *args[] = {&pc, &e32, &e64};
+    return hipLaunchKernel(k.fn, dim3((unsigned)grid), dim3(block), args, k.lds, s);
 }
 
 }  // namespace qs

@@ -8,8 +8,8 @@
 namespace qs {
 
 // ---- radiation-function tables -------------------------------------------
-// g, chi g', chi^2 g'', h are stored as one cubic per cell in the local
-// coordinate t in [0, 1).  Cell 0 covers chi in [0, 2^kEMin); cell
+// g, 2g + chi g', g + 2 chi g' + chi^2 g''/2 and h (the combinations of the
+// drift) are stored as one cubic per cell in the local coordinate t in [0, 1).  Cell 0 covers chi in [0, 2^kEMin); cell
 // 1 + (e - kEMin) * 2^SB + s covers the s-th of 2^SB equal sub-intervals of
 // the octave [2^e, 2^(e+1)), e = kEMin .. kEMax.  Each cell holds 16 values:
 // four functions x four monomial coefficients (t^0 .. t^3).  The FP32 table is
@@ -20,14 +20,26 @@ constexpr int kEMax = 7;
 constexpr int kSB32 = 4;  // FP32 table: 16 sub-cells per octave (LDS resident)
 constexpr int kSB64 = 6;  // FP64 table: 64 sub-cells per octave (global)
 constexpr int kCells32 = 1 + (kEMax - kEMin + 1) * (1 << kSB32);
-constexpr int kCells64 = 1 + (kEMax - kEMin + 1) * (1 << kSB64);
+// The FP64 tables begin at 2^kEMin64: below it one cubic is within 1.6e-13 of g
+// and 2.3e-12 of the other combinations (5.1e-12 of chi h'), less than the cells
+// above 2^-4 (up to 3e-11 and 7e-11).
+constexpr int kEMin64 = -12;
+constexpr int kCells64 = 1 + (kEMax - kEMin64 + 1) * (1 << kSB64);
 constexpr int kCellVals = 16;
 // Cells of the FP64 table held in LDS (128 bytes each; a block takes a CU's LDS):
-// 19.5 octaves of chi in FP64 passes, 16.2 beside the FP32 table in passes with
+// chi below 178 in FP64 passes, below 18 beside the FP32 table in passes with
 // FP64 steps.
 constexpr int kWin64 = 1248;
 constexpr int kWinMix = 1040;
-static_assert(kWin64 < kCells64, "a window of the table");
+// The derivative passes: the derivative table (192 bytes a cell) below chi 1.9, or
+// the forward table beside the FP32 derivative table below 4.6.
+constexpr int kWinDeriv64 = 832;
+constexpr int kWinDerivMix = 912;
+// The photon pass, beside the emission grid: chi below 9.2 in FP64 passes; with
+// FP64 steps 7 octaves from the one below the threshold on (0.03 to 4 at 0.1),
+// where those steps' stages mostly lie.
+constexpr int kWinPhot64 = 976;
+constexpr int kWinPhotMix = 440;
 // Derivative tables (adjoint): six functions per cell, in the order g,
 // chi g', chi^2 g'', h, chi^3 g''', chi h'; FP32 function-major
 // ([function][cell][power]), FP64 cell-major ([cell][function][power]).
@@ -163,9 +175,11 @@ constexpr size_t kPhTabBytes = sizeof(double) * kPhCellOff + sizeof(float) * 4 *
 // r_lo .. r_lo + nu - 1) x kPhNV columns (t = sqrt(mu), uniform), weights
 // in fixed point.
 constexpr int kPhNU = 64, kPhNV = 64, kPhNodes = kPhNU * kPhNV;
-// Samples of a photon work item: one a lane of a block (twice as many in passes
-// with FP64 steps).
-constexpr int phot_block(int prec) { return prec == PREC_F32MIX ? 512 : 256; }
+// Samples of a photon work item: one a lane of a block, 512 where a block takes
+// a CU's LDS (quantum passes with FP64 steps).
+constexpr int phot_block(int prec, bool quantum) {
+    return quantum && prec != PREC_F32 ? 512 : 256;
+}
 // photon energy, electron loss, soft weight; then the Sec. 5.1 angular sums:
 // number, number x theta_x^2, number x theta_y^2, energy, energy x theta_x^2,
 // energy x theta_y^2
@@ -199,6 +213,7 @@ struct ShotGrad {
 };
 
 constexpr int kGradParams = 8;
+constexpr int kGradRows = kPhaseBlock / 64;  // rows of gradient sums a phase item
 constexpr int kTapeFields = 2 + 2 * kGradParams;  // mu, sig2, d mu / dp, d sig2 / dp
 
 // Parameters shared by every shot of a launch.
@@ -213,17 +228,15 @@ struct BatchParams {
     int32_t phase_cap;  // resident phase blocks per CU at most (0: all that fit)
     int32_t dep_cap;    // resident deposit blocks per CU at most (0: all that fit)
     int32_t prec;       // the pass's precision (Prec)
-    int32_t pad1;
+    int32_t quantum;  // the radiation-reaction model
     uint32_t key0, key1;
     double ksig_bins, c_theta;
     int64_t n_items, n_ditems, n_mtiles;  // (n_mtiles: rows of moment sums)
     int64_t n_gitems;   // groups of the passes with FP64 steps
     const ShotParams *shots;
     const ShotOut *outs;
-    uint16_t *order;      // passes with FP64 steps: sample state_off + (group start) + r holds
-                          // the offset in its group of the sample of chi rank r
-    int32_t win_top;      // FP64 table cells above which no sample's chi lies
-    int32_t pad2;
+    uint16_t *order;      // samples in chi order (or null): entry state_off + (group start) + r
+                          // holds the offset in its group of the sample of chi rank r
     const float *rad32;   // [kCells32 * 16]
     const double *rad64;  // [kCells64 * 16]
     const float *rad32d;  // [kCells32 * 4 * kDerivFuncs]
@@ -248,7 +261,8 @@ struct BatchParams {
     unsigned int *queue;           // [2]: phase and deposit work counters
     unsigned long long *fp64_steps;  // [n_shots]: wavefront phase steps taken in FP64 by
                                      // the forward pass's FP32 loop (null: not counted)
-    double *partials;              // [kPartials][n_mtiles]; adjoint: [n_items][kGradParams];
+    double *partials;              // [kPartials][n_mtiles]; adjoint: [kGradParams] columns of
+                                   // kGradRows rows an item (a row a wavefront);
                                    // photons: [kPhotPartials][n_pitems]
 };
 
@@ -267,7 +281,7 @@ hipError_t launch_deposit(const BatchParams &p, int max_hist_words, hipStream_t 
 hipError_t launch_finalize(const BatchParams &p, hipStream_t s);
 hipError_t launch_shadow_diff(const BatchParams &p, int64_t n_items, int max_hist_words,
                               hipStream_t s);
-hipError_t launch_radiation_eval(const float *rad32, const double *rad64, int prec, int64_t n,
+hipError_t launch_radiation_eval(const float *rad32, const double *rad64d, int prec, int64_t n,
                                  const double *chi, double *out, int *flags, hipStream_t s);
 hipError_t launch_radiation_derivs(const float *rad32d, const double *rad64d, int prec, int64_t n,
                                    const double *chi, double *out, int *flags, hipStream_t s);

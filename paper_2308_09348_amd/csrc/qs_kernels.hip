@@ -33,7 +33,7 @@ namespace qs {
 // lane of the wavefront has chi above the threshold at the step start: the
 // amplitude's spatial factor is carried from one step's end to the next
 // step's start, as in the FP64 loop.  Returns the first step not taken.
-template <bool QUANTUM, bool MODES, class Tab>
+template <bool MODES, class Tab>
 __device__ __forceinline__ int fp64_segment(const BatchParams &P, const ShotParams &sp,
                                             const Path<double, MODES> &pd, bool local,
                                             double a0S0, const double *__restrict__ env64, int j,
@@ -41,7 +41,10 @@ __device__ __forceinline__ int fp64_segment(const BatchParams &P, const ShotPara
                                             double &chd) {
     const Phys<double> phd{P.K, P.CD, P.two_over_aS};
     const int N = P.n_steps;
-    double aS1 = local ? sp.a0 * pd.S(fma((double)j, P.h, -P.psi_max) * P.ell_per_psi) : a0S0;
+    AmpFactors<double> A1(
+        (local ? sp.a0 * pd.S(fma((double)j, P.h, -P.psi_max) * P.ell_per_psi) : a0S0) *
+            env64[2 * j],
+        phd);
     bool more = true;
     while (more) {
         const double psi = fma((double)j, P.h, -P.psi_max);
@@ -51,15 +54,13 @@ __device__ __forceinline__ int fp64_segment(const BatchParams &P, const ShotPara
             aS4 = sp.a0 * pd.S((psi + P.h) * P.ell_per_psi);
         }
         double dm, ds;
-        rk4_increment<double, QUANTUM, Tab>(mu, s2, aS1 * env64[2 * j],
-                                                   aSh * env64[2 * j + 1], aS4 * env64[2 * j + 2],
-                                                   P.h, phd, tabd, dm, ds, chd);
+        rk4_q64(mu, s2, A1, aSh * env64[2 * j + 1], aS4 * env64[2 * j + 2], P.h, phd, tabd, dm, ds,
+                chd);
         mu += dm;
         s2 += ds;
-        aS1 = aS4;
         ++j;
         if (j >= N) break;
-        const double chi = P.two_over_aS * mu * fabs(aS1 * env64[2 * j]);
+        const double chi = A1.cpm * mu;
         cmx = fmaxf(cmx, (float)chi);
         more = __any(chi > (double)P.chi_fp64);
     }
@@ -72,7 +73,6 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
                                              const double *__restrict__ env64,
                                              const float *tab32, const Tab &tabd, int &flags,
                                              int &nprom) {
-    const RadTab<float> tabf{tab32};
     const Phys<float> phf{P.Kf, P.CDf, P.two_over_aSf};
     const Phys<double> phd{P.K, P.CD, P.two_over_aS};
     const int N = P.n_steps;
@@ -102,7 +102,10 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
     float chi_hi = 0.0f;  // largest chi of the table reads (range check)
     if (PREC == PREC_F64) {
         double mu = g0, s2 = 0.0, chd = 0.0;
-        double aS_prev = local ? sp.a0 * pd.S(-P.psi_max * P.ell_per_psi) : a0S0;
+        // the amplitude at a step's end is the next one's start
+        double a1 = (local ? sp.a0 * pd.S(-P.psi_max * P.ell_per_psi) : a0S0) * env64[0];
+        AmpFactors<double> A1;
+        if (QUANTUM) A1 = AmpFactors<double>(a1, phd);
         for (int j = 0; j < N; ++j) {
             const double psi = fma((double)j, P.h, -P.psi_max);
             double aSh = a0S0, aS4 = a0S0;
@@ -110,16 +113,19 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
                 aSh = sp.a0 * pd.S(fma(0.5, P.h, psi) * P.ell_per_psi);
                 aS4 = sp.a0 * pd.S((psi + P.h) * P.ell_per_psi);
             }
-            const double a1 = aS_prev * env64[2 * j];
             const double ah = aSh * env64[2 * j + 1];
             const double a4 = aS4 * env64[2 * j + 2];
-            cmx = fmaxf(cmx, (float)(P.two_over_aS * mu * fabs(a1)));
-            double dm, ds;
-            rk4_increment<double, QUANTUM, Tab>(mu, s2, a1, ah, a4, P.h, phd, tabd, dm, ds,
-                                                       chd);
-            mu += dm;
-            s2 += ds;
-            aS_prev = aS4;
+            if constexpr (QUANTUM) {
+                cmx = fmaxf(cmx, (float)(A1.cpm * mu));
+                double dm, ds;
+                rk4_q64(mu, s2, A1, ah, a4, P.h, phd, tabd, dm, ds, chd);
+                mu += dm;
+                s2 += ds;
+            } else {
+                cmx = fmaxf(cmx, (float)(P.two_over_aS * mu * fabs(a1)));
+                mu += rk4_classical(mu, a1, ah, a4, P.h, phd);
+                a1 = a4;
+            }
         }
         mu_f = mu;
         s2_f = s2;
@@ -173,7 +179,7 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
                     double s2d = (double)s2 + (double)s2_lo;
                     g0_rest = 0.0;
                     const int j0 = j;
-                    j = fp64_segment<QUANTUM>(P, sp, pd, local, a0S0, env64, j, tabd, mud, s2d,
+                    j = fp64_segment(P, sp, pd, local, a0S0, env64, j, tabd, mud, s2d,
                                               cmx, chd);
                     nprom += j - j0;  // wave-uniform
                     mu = (float)mud;
@@ -214,9 +220,7 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
                 comp_add(s2, s2_lo, ds);
             } else {
                 cmx = fmaxf(cmx, phf.two_over_aS * mu * fabsf(a1));
-                float dm, ds;
-                rk4_increment<float, false>(mu, s2, a1, ah, a4, P.hf, phf, tabf, dm, ds, chi_hi);
-                comp_add(mu, mu_lo, dm);
+                comp_add(mu, mu_lo, rk4_classical(mu, a1, ah, a4, P.hf, phf));
             }
             aS_prev = aS4;
             ++j;
@@ -263,7 +267,7 @@ __attribute__((amdgpu_waves_per_eu((PREC == PREC_F32 && QUANTUM) ? 4 : 1))) void
         for (int k = threadIdx.x; k < kCells32 * kCellVals / 4; k += blockDim.x) dst[k] = src[k];
         __syncthreads();
     }
-    const RadTab<double> tabd{P.rad64};  // (not read)
+    const NoTable tabd;
     int s_prev = 0;  // the shot of the block's previous item
     for (;;) {
         const int64_t item = next_item(&P.queue[0], &slot);
@@ -293,12 +297,14 @@ __attribute__((amdgpu_waves_per_eu((PREC == PREC_F32 && QUANTUM) ? 4 : 1))) void
 // block a CU holds the FP64 table's cells that the launch reaches in LDS (and
 // the FP32 table); its wavefronts take items of 64 samples each on their own,
 // in passes with FP32 steps in order of the group's chi scale (order_kernel).
-// Bound by FP64 issue: with the table read a wavefront at a time from L2 through
-// LDS staging rows, two wavefronts a SIMD, 2^20 FP64 samples x 512 steps took
-// 8.8 ms, now 6.6 ms (VALU busy 0.79 of the time, by counters); eight quantum
-// shots of 2^18 x 1024 with FP64 steps 17.8 -> 11.5 ms.  Four wavefronts a SIMD in
-// 128 registers in FP64 passes; three in 168 with FP32 steps beside (at four the
-// FP32 steps spill: 23.4 ms; at two 12.7 ms).
+// Bound by FP64 issue and, in FP64 passes whose lanes are not ordered, LDS bank
+// conflicts (VALU busy 0.79 of the time at 1.95 GHz, 7 conflict cycles an LDS
+// instruction, by counters; see `ordered` in the host code): with the table read
+// a wavefront at a time from L2 through LDS staging rows, two wavefronts a SIMD,
+// 2^20 FP64 samples x 512 steps took 8.8 ms, now 4.8 ms; 5000 samples 0.86 and
+// 0.48 ms; eight quantum shots of 2^18 x 1024 with FP64 steps 17.8 and 11.1 ms.
+// Four wavefronts a SIMD in 128 registers in FP64 passes; three in 168 with FP32
+// steps beside (at four the FP32 steps spill: 23.4 ms; at two 12.7 ms).
 template <int PREC>
 constexpr int phase64_block() {
     return PREC == PREC_F32MIX ? 768 : 1024;
@@ -311,8 +317,7 @@ __global__ __launch_bounds__(phase64_block<PREC>()) void phase64_kernel(
     constexpr int kWin = kMix ? kWinMix : kWin64;
     extern __shared__ double2 win[];  // [8][kWin]
     __shared__ __align__(16) float tab32[kMix ? kCells32 * kCellVals : 4];
-    const RadTabWin<kWin> tabd{win, P.rad64, RadTabWin<kWin>::first(P.win_top)};
-    RadTabWin<kWin>::load(win, P.rad64, tabd.c0);
+    const TabWindow<kWin, 4> tabd(win, P.rad64);
     if (kMix) {
         const float4 *src = reinterpret_cast<const float4 *>(P.rad32);
         float4 *dst = reinterpret_cast<float4 *>(tab32);
@@ -334,7 +339,7 @@ __global__ __launch_bounds__(phase64_block<PREC>()) void phase64_kernel(
         const int64_t k = item - kPer * sp.item0;
         int64_t i = 64 * k + lane;
         bool live = i < sp.n_samples;
-        if constexpr (kMix && !NODES) {
+        if (!NODES && (kMix || P.order != nullptr)) {
             if (64 * k >= sp.n_samples) continue;
             const int64_t first = ordered_round<64>(sp.n_samples, k);
             const int64_t base = first & ~(kChiGroup - 1ll);
@@ -934,24 +939,15 @@ hipError_t launch_order(const BatchParams &p, hipStream_t s) {
     return hipGetLastError();
 }
 
-// The phase kernel of a pass: quantum passes with FP64 steps run
-// phase64_kernel (wide: its block size and LDS follow from the launch).
-struct PhaseKernel {
-    const void *fn;
-    int block;  // threads (wide: at most)
-    size_t lds;
-    bool wide;
-};
-
 template <int PREC, bool LOCAL, bool NODES, bool MODES>
-static PhaseKernel phase64_of() {
+static PassKernel phase64_of() {
     return {reinterpret_cast<const void *>(&phase64_kernel<PREC, LOCAL, NODES, MODES>),
             phase64_block<PREC>(),
             sizeof(double2) * 8 * (PREC == PREC_F32MIX ? kWinMix : kWin64), true};
 }
 
 template <int PREC, bool QUANTUM, bool LOCAL, bool NODES, bool MODES>
-static PhaseKernel phase_of() {
+static PassKernel phase_of() {
     if constexpr (QUANTUM && PREC != PREC_F32)
         return phase64_of<PREC, LOCAL, NODES, MODES>();
     else
@@ -961,7 +957,7 @@ static PhaseKernel phase_of() {
 
 // modes: some shot of the launch uses a higher transverse mode
 template <int PREC, bool QUANTUM>
-static PhaseKernel select_phase(bool local, bool modes) {
+static PassKernel select_phase(bool local, bool modes) {
     if (local)
         return modes ? phase_of<PREC, QUANTUM, true, false, true>()
                      : phase_of<PREC, QUANTUM, true, false, false>();
@@ -969,58 +965,23 @@ static PhaseKernel select_phase(bool local, bool modes) {
                  : phase_of<PREC, QUANTUM, false, false, false>();
 }
 
-static hipError_t run_phase(const PhaseKernel &k, const BatchParams &p, const float *env32,
-                            const double *env64, hipStream_t s) {
-    int grid = 0, block = k.block;
-    hipError_t e;
-    if (k.wide) {
-        // a block a CU, with as many wavefronts as the launch has work for
-        // (small launches: one a SIMD at most before a second)
-        int device = 0, ncu = 0;
-        e = hipGetDevice(&device);
-        if (e == hipSuccess)
-            e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds);
-        if (e != hipSuccess) return e;
-        const int64_t waves = p.n_items * (kPhaseBlock / 64);
-        int64_t per = (waves + ncu - 1) / ncu;
-        int most = block / 64;
-        if (p.phase_cap > 0 && most > p.phase_cap * (kPhaseBlock / 64))
-            most = p.phase_cap * (kPhaseBlock / 64);
-        if (per > most) per = most;
-        if (per < 1) per = 1;
-        block = 64 * (int)per;
-        const int64_t blocks = (waves + per - 1) / per;
-        grid = (int)(blocks < ncu ? (blocks < 1 ? 1 : blocks) : ncu);
-    } else {
-        e = resident_grid(k.fn, block, 0, p.n_items, &grid, p.phase_cap);
-        if (e != hipSuccess) return e;
-    }
-    BatchParams pc = p;
-    const float *e32 = env32;
-    const double *e64 = env64;
-    void *args[] = {&pc, &e32, &e64};
-    return hipLaunchKernel(k.fn, dim3((unsigned)grid), dim3(block), args, k.lds, s);
-}
-
 hipError_t launch_phase(const BatchParams &p, const float *env32, const double *env64, int prec,
                         int rr, int amp, hipStream_t s) {
     const bool q = rr == 1, l = amp == 1, m = p.any_mode != 0;
     if (prec == PREC_F32MIX && !q) prec = PREC_F32;  // no radiation table, no promotion
-    PhaseKernel k{};
+    PassKernel k{};
     if (prec == PREC_F32) k = q ? select_phase<PREC_F32, true>(l, m) : select_phase<PREC_F32, false>(l, m);
     if (prec == PREC_F64) k = q ? select_phase<PREC_F64, true>(l, m) : select_phase<PREC_F64, false>(l, m);
     if (prec == PREC_F32MIX) k = select_phase<PREC_F32MIX, true>(l, m);
     if (!k.fn) return hipErrorInvalidValue;
-    return run_phase(k, p, env32, env64, s);
+    return run_pass(k, p, env32, env64, p.phase_cap, s);
 }
 
 hipError_t launch_phase_nodes(const BatchParams &p, const float *env32, const double *env64,
                               int prec, int rr, hipStream_t s) {
     const bool q = rr == 1;
     if (prec == PREC_F32MIX && !q) prec = PREC_F32;
-    PhaseKernel k{};
+    PassKernel k{};
     if (prec == PREC_F32)
         k = q ? phase_of<PREC_F32, true, false, true, false>()
               : phase_of<PREC_F32, false, false, true, false>();
@@ -1029,7 +990,7 @@ hipError_t launch_phase_nodes(const BatchParams &p, const float *env32, const do
               : phase_of<PREC_F64, false, false, true, false>();
     if (prec == PREC_F32MIX) k = phase_of<PREC_F32MIX, true, false, true, false>();
     if (!k.fn) return hipErrorInvalidValue;
-    return run_phase(k, p, env32, env64, s);
+    return run_pass(k, p, env32, env64, p.phase_cap, s);
 }
 
 // edge weights (u64, one per edge) and counters (u32, one per bin and two

@@ -223,7 +223,7 @@ __global__ void ph_cell_kernel(const double *phtab, float *cells) {
     if (cell >= kCells32) return;
     double coef[4] = {0.0, 0.0, 0.0, 0.0};
     for (int m = 0; m < 4; ++m) {
-        const double v = ph_total64(phtab, cell_chi(cell, cheb_node(m), kSB32));
+        const double v = ph_total64(phtab, cell_chi(cell, cheb_node(m), kSB32, kEMin));
         double l[4];
         cheb_basis(m, l);
         for (int k = 0; k < 4; ++k) coef[k] = fma(v, l[k], coef[k]);
@@ -301,13 +301,10 @@ __device__ __forceinline__ void ph_deposit(float D, float lm, float t, float la,
 // Radiation functions per stage in the forward table's combinations
 // T1 = g, T2 = 2g + chi g', T3 = g + 2 chi g' + chi^2 g''/2, T4 = h.  FP32:
 // the LDS table read at stages 2 and 4 only, stage 3 and the next stage 1
-// reusing those cells; FP64: the global table at every stage.
-template <class T>
-struct FwdRad;
+// reusing those cells.
 // With ncell (FP32 angular moments) the cells also bring the photon-number
 // cubic of the same cell: num() gives Phi(1; chi) / chi of the last stage.
-template <>
-struct FwdRad<float> {
+struct FwdRad32 {
     const float *tab;
     const float4 *ncell = nullptr;
     RadCell32 carry, mid;
@@ -339,48 +336,21 @@ struct FwdRad<float> {
         number(carry, ncarry, chi);
     }
 };
-template <>
-struct FwdRad<double> {
-    const double *tab;
-    double nf = 0.0;  // unused: the FP64 pass takes the number from the rows
+// FP64 passes and the FP64 steps of mixed-precision passes: a table window at
+// every stage.
+template <class Tab>
+struct FwdRad64 {
+    const Tab *tab;
+    double nf = 0.0;  // unused: FP64 steps do not take the number from the cells
     __device__ __forceinline__ void init(double) {}
-    __device__ __forceinline__ void ev(double chi, double *t) {
-        double g, G1, G2, hq;
-        rad_eval64(tab, chi, g, G1, G2, hq);
-        t[0] = g;
-        t[1] = fma(2.0, g, G1);
-        t[2] = fma(0.5, G2, fma(2.0, G1, g));
-        t[3] = hq;
-    }
-    __device__ __forceinline__ void s1(double chi, double *t) { ev(chi, t); }
-    __device__ __forceinline__ void s2(double chi, double *t) { ev(chi, t); }
-    __device__ __forceinline__ void s3(double chi, double *t) { ev(chi, t); }
-    __device__ __forceinline__ void s4(double chi, double *t) { ev(chi, t); }
-};
-// The same values from the FP64 table read a wavefront at a time
-// (RadTabWave; every lane of the wavefront active): the FP64 steps of
-// mixed-precision passes.
-struct FwdRadWave {
-    RadTabWave tw;
-    double nf = 0.0;  // unused: FP64 steps take the number from the rows
-    __device__ __forceinline__ FwdRadWave(const double *tab, double2 *stage) : tw(tab, stage) {}
-    __device__ __forceinline__ void init(double) {}
-    __device__ __forceinline__ void ev(double chi, double *t) {
-        double g, G1, G2, hq;
-        tw.eval(chi, g, G1, G2, hq);
-        t[0] = g;
-        t[1] = fma(2.0, g, G1);
-        t[2] = fma(0.5, G2, fma(2.0, G1, g));
-        t[3] = hq;
-    }
-    __device__ __forceinline__ void s1(double chi, double *t) { ev(chi, t); }
-    __device__ __forceinline__ void s2(double chi, double *t) { ev(chi, t); }
-    __device__ __forceinline__ void s3(double chi, double *t) { ev(chi, t); }
-    __device__ __forceinline__ void s4(double chi, double *t) { ev(chi, t); }
+    __device__ __forceinline__ void s1(double chi, double *t) { tab->eval(chi, t); }
+    __device__ __forceinline__ void s2(double chi, double *t) { tab->eval(chi, t); }
+    __device__ __forceinline__ void s3(double chi, double *t) { tab->eval(chi, t); }
+    __device__ __forceinline__ void s4(double chi, double *t) { tab->eval(chi, t); }
 };
 
 // One stage: slopes and the drift A (the photon energy per unit phase is -A).
-template <class T, bool QUANTUM, int S, class R = FwdRad<T>>
+template <class T, bool QUANTUM, int S, class R>
 __device__ __forceinline__ void photon_stage(T mu, T s2, T a, const Phys<T> &ph, R &rad,
                                              T &dmu, T &ds2, T &A, T &chi_hi, T &nf) {
     const T a2 = a * a;
@@ -416,7 +386,6 @@ struct PhotCtx {
     T a0, a0S0, h, psi0, ell, thx, thy;
     float inv_a0, tas;
     bool local, mid, angles, cell_number;
-    bool live;  // the lane's sample is real (else it runs for the wavefront's table reads only)
     const float4 *ncell = nullptr;  // photon-number cubics of the FP32 cells (FP64 steps of mixed passes)
 };
 
@@ -448,7 +417,7 @@ struct PhotState {
 // ANG32: the angular sums' terms in FP32 with the photon number from the FP32
 // cells' cubics (the FP64 steps of a mixed-precision pass, whose angular
 // moments are held to the FP32 pass's bar; the FP64 pass takes them in FP64).
-template <class T, bool QUANTUM, bool MODES, class R = FwdRad<T>, bool ANG32 = false>
+template <class T, bool QUANTUM, bool MODES, bool ANG32, class R>
 __device__ __forceinline__ void photon_step(const PhotCtx<T, MODES> &c, const ShotPhot &pp,
                                             const float *tot, int j, PhotState<T> &st, R &rad,
                                             unsigned long long *grid, PhotAcc &acc) {
@@ -469,7 +438,7 @@ __device__ __forceinline__ void photon_step(const PhotCtx<T, MODES> &c, const Sh
     const T mu = st.mu, s2 = st.s2;
     // stage 4 of the previous step with stage 1 of this one (same
     // amplitude): one deposit at the geometric mean of the two energies
-    if (j > 0 && c.live) {
+    if (j > 0) {
         const float aa = fabsf((float)a1);
         if (aa > 0.0f) {
             const float pm = (float)st.m4_prev * (float)mu;
@@ -486,9 +455,9 @@ __device__ __forceinline__ void photon_step(const PhotCtx<T, MODES> &c, const Sh
     photon_stage<T, QUANTUM, 3, R>(m3, fma(hh, k2s, s2), ah, c.ph, rad, k3m, k3s, A3, st.chi_hi, n3);
     const T m4 = fma(h, k3m, mu);
     photon_stage<T, QUANTUM, 4, R>(m4, fma(h, k3s, s2), a4, c.ph, rad, k4m, k4s, A4, st.chi_hi, n4);
-    if (c.live) acc.e_ph += (double)(h * -(c16 * (A1 + A4) + c13 * (A2 + A3)));
+    acc.e_ph += (double)(h * -(c16 * (A1 + A4) + c13 * (A2 + A3)));
     if constexpr (ANG32) {
-        if (c.angles && c.live) {
+        if (c.angles) {
             auto num = [&](T m, T a) {
                 const float aa = fabsf((float)a);
                 return aa > 0.0f ? ph_number32(c.ncell, c.tas * (float)m * aa) : 0.0f;
@@ -506,7 +475,7 @@ __device__ __forceinline__ void photon_step(const PhotCtx<T, MODES> &c, const Sh
             acc.ex += an.ex;
             acc.ey += an.ey;
         }
-    } else if (c.angles && c.live) {
+    } else if (c.angles) {
         if (!c.cell_number) {  // from the rows
             auto rows = [&](T m, T a) {
                 const float aa = fabsf((float)a);
@@ -529,7 +498,7 @@ __device__ __forceinline__ void photon_step(const PhotCtx<T, MODES> &c, const Sh
         acc.ex += an.ex;
         acc.ey += an.ey;
     }
-    if (c.live) {  // stages 2 and 3 (same amplitude)
+    {  // stages 2 and 3 (same amplitude)
         const float aa = fabsf((float)ah);
         if (aa > 0.0f) {
             const float pm = (float)m2 * (float)m3;
@@ -551,19 +520,17 @@ __device__ __forceinline__ void photon_step(const PhotCtx<T, MODES> &c, const Sh
     st.aS_prev = aS4;
 }
 
-template <int PREC, bool QUANTUM, bool LOCAL, bool MODES>
+template <int PREC, bool QUANTUM, bool LOCAL, bool MODES, class Tab>
 __device__ __forceinline__ void photon_sample(const BatchParams &P, const ShotParams &sp,
                                               const ShotPhot &pp, int64_t i,
                                               const float *__restrict__ env32,
                                               const double *__restrict__ env64,
                                               const float *tab32, unsigned long long *grid,
                                               const float *tot, const float4 *ncell,
-                                              double2 *stage, bool live, PhotAcc &acc,
+                                              const Tab &tabd, PhotAcc &acc,
                                               double &loss) {
     using T = typename std::conditional<PREC == PREC_F64, double, float>::type;
-    // FP32 with FP64 steps where chi is above the threshold (quantum only;
-    // every lane of the wavefront runs, live says whether the lane's sample
-    // is real and deposits, stage holds the wavefront's FP64 table rows)
+    // FP32 with FP64 steps where chi is above the threshold (quantum only)
     constexpr bool MIX = PREC == PREC_F32MIX;
     static_assert(!MIX || QUANTUM, "FP64 steps are a quantum-model option");
     const bool angles = pp.angles != nullptr;
@@ -623,11 +590,10 @@ __device__ __forceinline__ void photon_sample(const BatchParams &P, const ShotPa
     c.angles = angles;
     // FP32 quantum passes take the photon number from the radiation cells
     c.cell_number = PREC != PREC_F64 && QUANTUM && angles;
-    c.live = MIX ? live : true;
 
-    FwdRad<T> rad;
+    typename std::conditional<PREC == PREC_F64, FwdRad64<Tab>, FwdRad32>::type rad;
     if constexpr (PREC == PREC_F64) {
-        rad.tab = P.rad64;
+        rad.tab = &tabd;
     } else {
         rad.tab = tab32;
         if (c.cell_number) rad.ncell = ncell;
@@ -648,7 +614,7 @@ __device__ __forceinline__ void photon_sample(const BatchParams &P, const ShotPa
     st.aS_next = c.mid ? c.a0 * c.pt.S((c.psi0 + c.h) * c.ell) : c.a0S0;
     if (QUANTUM) rad.init(c.ph.two_over_aS * st.mu * fabs(st.aS_prev * c.env[0]));
     // the first stage of the first step deposits alone
-    if (c.live) {
+    {
         const float aa = fabsf((float)(st.aS_prev * c.env[0]));
         if (aa > 0.0f)
             ph_deposit((1.0f / 6.0f) * aa * c.inv_a0, ph_ln((float)st.mu), ph_sqrt((float)st.mu),
@@ -680,7 +646,6 @@ __device__ __forceinline__ void photon_sample(const BatchParams &P, const ShotPa
                 cd.angles = angles;
                 cd.cell_number = false;
                 cd.ncell = ncell;
-                cd.live = c.live;
                 PhotState<double> sd;
                 sd.mu = ((double)st.mu + (double)st.mu_lo) + g0_rest;
                 g0_rest = 0.0;  // now held by the state
@@ -691,9 +656,9 @@ __device__ __forceinline__ void photon_sample(const BatchParams &P, const ShotPa
                 sd.aS_next = 0.0;
                 sd.m4_prev = (double)st.m4_prev;
                 sd.chi_hi = 0.0;
-                FwdRadWave radd(P.rad64, stage);
+                FwdRad64<Tab> radd{&tabd};
                 for (;;) {
-                    photon_step<double, QUANTUM, MODES, FwdRadWave, true>(cd, pp, tot, j, sd, radd, grid,
+                    photon_step<double, QUANTUM, MODES, true>(cd, pp, tot, j, sd, radd, grid,
                                                                    acc);
                     ++j;
                     if (j >= N) break;
@@ -714,10 +679,9 @@ __device__ __forceinline__ void photon_sample(const BatchParams &P, const ShotPa
                 continue;
             }
         }
-        photon_step<T, QUANTUM, MODES>(c, pp, tot, j, st, rad, grid, acc);
+        photon_step<T, QUANTUM, MODES, false>(c, pp, tot, j, st, rad, grid, acc);
         ++j;
     }
-    if (!c.live) return;
     {  // the last stage 4 deposits alone
         const float aa = fabsf((float)(st.aS_prev * c.env[2 * N]));
         if (aa > 0.0f)
@@ -747,31 +711,28 @@ __device__ __forceinline__ int find_phot(const ShotPhot *ph, int n_shots, int64_
     return lo;
 }
 
-// Block size of the photon kernel: mixed-precision passes read the FP64 table
-// a wavefront at a time and stage it in LDS (5 KB a wavefront), which beside
-// the table, grid and photon-number cells (about 69 KB) fits one block of 512
-// a CU; the others run blocks of 256, two a CU.  Either way two waves per
-// SIMD, and the registers are held to that (the FP64 and mixed-precision
-// passes would otherwise take a few more and run one).
+// Blocks of 256, two a CU; quantum passes with FP64 steps one of 512, which holds
+// a window of the FP64 table beside the emission grid (and the FP32 table).
+// Either way two waves per SIMD, and the registers are held to that (the FP64
+// and mixed-precision passes would otherwise take a few more and run one).
 // An item is one sample a lane.  With items of 2048 samples, taken one after
 // another by a block to flush its grid less often, 65,537 samples x 1024 steps
 // ran on 33 of 256 CUs in 11.1 ms, against 1.63 ms; eight shots of 2^18 x 512 steps
 // take 13.0 ms with those items and 12.5 ms with these (x 128 steps: 3.61 and
 // 3.56 ms), so the more frequent flushes cost less than the even load gives.
 template <int PREC, bool QUANTUM, bool LOCAL, bool MODES>
-__global__ __launch_bounds__(phot_block(PREC)) __attribute__((amdgpu_waves_per_eu(2))) void photon_kernel(
+__global__ __launch_bounds__(phot_block(PREC, QUANTUM)) __attribute__((amdgpu_waves_per_eu(2))) void photon_kernel(
     BatchParams P, const float *__restrict__ env32, const double *__restrict__ env64) {
-    constexpr int kBlock = phot_block(PREC);
-    // mixed precision: every lane of a wavefront runs (lanes past an item's
-    // end repeat its last sample without depositing), for the table reads
-    constexpr bool kWave64 = PREC == PREC_F32MIX;
+    constexpr int kBlock = phot_block(PREC, QUANTUM);
+    constexpr bool kMix = PREC == PREC_F32MIX;
+    constexpr bool kTab64 = QUANTUM && PREC != PREC_F32;
     constexpr bool kTab32 = QUANTUM && PREC != PREC_F64;
     __shared__ __align__(16) float tab32[kTab32 ? kCells32 * kCellVals : 4];
     // mixed precision: two copies of the grid, the even lanes of a wavefront
     // depositing into one and the odd lanes into the other (the lanes hold
     // samples of similar chi, so neighbours often hit the same node; the copy
     // is offset by 32 banks), summed when the grid is flushed
-    constexpr int kRep = kWave64 ? 2 : 1;
+    constexpr int kRep = kMix ? 2 : 1;
     constexpr int kRepStride = kPhLdsNodes + 16;
     __shared__ unsigned long long grid[(kRep - 1) * kRepStride + kPhLdsNodes];
     unsigned long long *lgrid = grid + (kRep > 1 ? (threadIdx.x & 1) * kRepStride : 0);
@@ -780,8 +741,22 @@ __global__ __launch_bounds__(phot_block(PREC)) __attribute__((amdgpu_waves_per_e
     __shared__ float4 ncell[kTab32 ? kCells32 : 1];
     __shared__ int64_t slot;
     __shared__ double red[kBlock / 64][kPhotPartials];
-    __shared__ double2 stage[kWave64 ? (kBlock / 64) * kStageChunks : 1];
-    double2 *wstage = stage + (kWave64 ? (threadIdx.x >> 6) * kStageChunks : 0);
+    extern __shared__ double2 win[];  // the window of the FP64 table
+    using Tab = typename std::conditional<
+        !kTab64, NoTable,
+        TabWindow<kMix ? kWinPhotMix : kWinPhot64, 4, kMix>>::type;
+    auto table = [&] {
+        if constexpr (!kTab64)
+            return Tab{};
+        else if constexpr (kMix) {
+            // from the octave below the threshold on
+            const int e = min(max(ilogbf(fmaxf(P.chi_fp64, 1e-30f)) - 1, kEMin64), kEMax - 6);
+            return Tab(win, P.rad64, 1 + ((e - kEMin64) << kSB64));
+        } else {
+            return Tab(win, P.rad64);
+        }
+    };
+    const Tab tabd = table();
     for (int r = threadIdx.x; r < kPhRows; r += blockDim.x)
         tot[r] = (float)(cbrt(kPhYMax) * P.phtab[(size_t)r * (kPhNZ + 1) + kPhNZ]);
     if (kTab32) {
@@ -806,23 +781,22 @@ __global__ __launch_bounds__(phot_block(PREC)) __attribute__((amdgpu_waves_per_e
         PhotAcc acc{0.0, 0.0, 0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
         double loss = 0.0;
         int64_t row = item;  // of the partial sums
-        if constexpr (kWave64) {
-            // a round of a group's samples in order of their chi scale; every
-            // lane of a wavefront with a sample runs
+        if constexpr (kMix) {
+            // a round of a group's samples in order of their chi scale
             const int64_t first = ordered_round<kBlock>(sp.n_samples, item - pp.pitem0);
             const int64_t base = first & ~(kChiGroup - 1ll);
             row = pp.pitem0 + first / kBlock;
             const int cnt = (int)min((int64_t)kChiGroup, sp.n_samples - base);
             const int rank = (int)(first - base) + (int)threadIdx.x;
-            if ((rank & ~63) < cnt)
-                photon_sample<PREC, QUANTUM, LOCAL, MODES>(P, sp, pp, ordered_sample(P, sp, base, cnt, rank),
-                                                    env32, env64, tab32, lgrid, tot, ncell, wstage,
-                                                    rank < cnt, acc, loss);
+            if (rank < cnt)
+                photon_sample<PREC, QUANTUM, LOCAL, MODES>(
+                    P, sp, pp, ordered_sample(P, sp, base, cnt, rank), env32, env64, tab32, lgrid,
+                    tot, ncell, tabd, acc, loss);
         } else {
             const int64_t i = (item - pp.pitem0) * kBlock + threadIdx.x;
             if (i < sp.n_samples)
-                photon_sample<PREC, QUANTUM, LOCAL, MODES>(P, sp, pp, i, env32, env64, tab32, grid, tot,
-                                                    ncell, wstage, true, acc, loss);
+                photon_sample<PREC, QUANTUM, LOCAL, MODES>(P, sp, pp, i, env32, env64, tab32, grid,
+                                                           tot, ncell, tabd, acc, loss);
         }
         if (acc.flags) atomicOr(&P.flags[s], acc.flags);
         const double v[kPhotPartials] = {acc.e_ph, loss, acc.soft, acc.nn, acc.nx,
@@ -930,7 +904,7 @@ __global__ __launch_bounds__(kPhFinBlock) void photon_finalize_kernel(BatchParam
     __shared__ double sums[kPhotPartials];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     if (wid < kPhotPartials) {
-        const int64_t nr = (sp.n_samples + phot_block(P.prec) - 1) / phot_block(P.prec);
+        const int64_t nr = (sp.n_samples + phot_block(P.prec, P.quantum != 0) - 1) / phot_block(P.prec, P.quantum != 0);
         const double *col = P.partials + (size_t)wid * P.n_pitems + pp.pitem0;
         double a = 0.0;
 #pragma unroll 4
@@ -1070,15 +1044,20 @@ hipError_t launch_photon(const BatchParams &p, const float *env32, const double 
                : photon_ptr<PREC_F32MIX, true, false>(modes);
     else
         fn = select_photon<PREC_F32>(q, l, modes);
-    const int block = phot_block(p.prec);
+    const int block = phot_block(p.prec, q);
+    const size_t lds =
+        block == 256 ? 0
+                     : sizeof(double2) * kCellVals / 2 *
+                           (prec == PREC_F32MIX ? kWinPhotMix : kWinPhot64);
     int grid = 0;
-    hipError_t e = resident_grid(fn, block, 0, p.n_pitems, &grid);
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e == hipSuccess) e = resident_grid(fn, block, lds, p.n_pitems, &grid);
     if (e != hipSuccess) return e;
     BatchParams pc = p;
     const float *e32 = env32;
     const double *e64 = env64;
     void *args[] = {&pc, &e32, &e64};
-    return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(block), args, 0, s);
+    return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(block), args, lds, s);
 }
 
 hipError_t launch_photon_finalize(const BatchParams &p, int max_edges, double c_ph,

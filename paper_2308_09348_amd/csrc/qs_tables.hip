@@ -80,7 +80,7 @@ __global__ void rad_node_kernel(const double *yf, double *vals) {
     const int cell_all = node >> 2, m = node & 3;
     const bool t32 = cell_all < kCells32;
     const int cell = t32 ? cell_all : cell_all - kCells32;
-    const double chi = cell_chi(cell, cheb_node(m), t32 ? kSB32 : kSB64);
+    const double chi = cell_chi(cell, cheb_node(m), t32 ? kSB32 : kSB64, t32 ? kEMin : kEMin64);
     double I0 = 0, I1 = 0, I2 = 0, I3 = 0, J0 = 0, J1 = 0;
     for (int i = 0; i < kNY; ++i) {
         const double y = exp(kVLo + i * kDv);
@@ -116,8 +116,8 @@ __global__ void rad_node_kernel(const double *yf, double *vals) {
 }
 
 // Cubic through the four node values of each cell, in monomials of t.  The
-// forward tables take g, chi g', chi^2 g'', h; the derivative tables all six
-// functions (same order as the node values).
+// forward tables take the combinations the drift uses; the derivative tables
+// all six functions (same order as the node values), the FP32 one combined.
 __global__ void rad_coef_kernel(const double *vals, float *rad32, double *rad64, float *rad32d,
                                 double *rad64d) {
     const int cell_all = blockIdx.x * blockDim.x + threadIdx.x;
@@ -131,13 +131,30 @@ __global__ void rad_coef_kernel(const double *vals, float *rad32, double *rad64,
             for (int k = 0; k < 4; ++k) coef[f][k] += v * l[k];
         }
     }
+    if (cell_all == kCells32) {
+        // FP64 cell 0: in the coordinate t of cell 1, chi / 2^kEMin64 = 1 + t / 64
+        constexpr double r = 1.0 / (1 << kSB64);
+        for (int f = 0; f < kNodeVals; ++f) {
+            const double a0 = coef[f][0], a1 = coef[f][1], a2 = coef[f][2], a3 = coef[f][3];
+            coef[f][0] = a0 + a1 + a2 + a3;
+            coef[f][1] = (a1 + 2.0 * a2 + 3.0 * a3) * r;
+            coef[f][2] = (a2 + 3.0 * a3) * r * r;
+            coef[f][3] = a3 * r * r * r;
+        }
+    }
+    // the drift combinations g, 2g + chi g', g + 2 chi g' + chi^2 g''/2, h
+    double mix[4][4];
+    for (int c = 0; c < 4; ++c) {
+        mix[0][c] = coef[0][c];
+        mix[1][c] = 2.0 * coef[0][c] + coef[1][c];
+        mix[2][c] = coef[0][c] + 2.0 * coef[1][c] + 0.5 * coef[2][c];
+        mix[3][c] = coef[3][c];
+    }
     if (cell_all < kCells32) {
-        // function-major: rad32[(f * kCells32 + cell) * 4 + power], holding the
-        // drift combinations g, 2g + chi g', g + 2 chi g' + chi^2 g''/2, h
+        // function-major: rad32[(f * kCells32 + cell) * 4 + power]
         for (int c = 0; c < 4; ++c) {
-            const double mix[4] = {coef[0][c], 2.0 * coef[0][c] + coef[1][c],
-                                   coef[0][c] + 2.0 * coef[1][c] + 0.5 * coef[2][c], coef[3][c]};
-            for (int f = 0; f < 4; ++f) rad32[(f * kCells32 + cell_all) * 4 + c] = (float)mix[f];
+            for (int f = 0; f < 4; ++f)
+                rad32[(f * kCells32 + cell_all) * 4 + c] = (float)mix[f][c];
             // g, E1 = 2g + G1, E2 = 2g + 4 G1 + G2, E3 = 6 G1 + 6 G2 + G3, h, H1
             const double jm[kDerivFuncs] = {
                 coef[0][c], 2.0 * coef[0][c] + coef[1][c],
@@ -149,14 +166,15 @@ __global__ void rad_coef_kernel(const double *vals, float *rad32, double *rad64,
     } else {
         const int cell = cell_all - kCells32;
         for (int f = 0; f < 4; ++f)
-            for (int c = 0; c < 4; ++c) rad64[(size_t)cell * kCellVals + 4 * f + c] = coef[f][c];
+            for (int c = 0; c < 4; ++c) rad64[(size_t)cell * kCellVals + 4 * f + c] = mix[f][c];
         for (int f = 0; f < kDerivFuncs; ++f)
             for (int c = 0; c < 4; ++c)
                 rad64d[(size_t)cell * (4 * kDerivFuncs) + 4 * f + c] = coef[f][c];
     }
 }
 
-__global__ void rad_eval_kernel(const float *rad32, const double *rad64, int prec, int64_t n,
+// (the FP64 functions from the derivative table, which holds them plain)
+__global__ void rad_eval_kernel(const float *rad32, const double *rad64d, int prec, int64_t n,
                                 const double *chi, double *out, int *flags) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n) return;
@@ -170,8 +188,9 @@ __global__ void rad_eval_kernel(const float *rad32, const double *rad64, int pre
         out[4 * k + 2] = 2.0 * ((double)T3 - g - 2.0 * G1);
         out[4 * k + 3] = h;
     } else {
-        double g, G1, G2, h;
-        rad_eval64(rad64, chi[k], g, G1, G2, h);
+        double g, G1, G2, h, t;
+        const int c = rad_index64(chi[k], t);
+        rad_cell_eval64(rad64d + (size_t)c * (4 * kDerivFuncs), t, g, G1, G2, h);
         out[4 * k] = g;
         out[4 * k + 1] = G1;
         out[4 * k + 2] = G2;
@@ -199,11 +218,11 @@ hipError_t build_radiation_tables(float *rad32, double *rad64, float *rad32d, do
     return hipGetLastError();
 }
 
-hipError_t launch_radiation_eval(const float *rad32, const double *rad64, int prec, int64_t n,
+hipError_t launch_radiation_eval(const float *rad32, const double *rad64d, int prec, int64_t n,
                                  const double *chi, double *out, int *flags, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const int64_t blocks = (n + 255) / 256;
-    rad_eval_kernel<<<(unsigned)blocks, 256, 0, s>>>(rad32, rad64, prec, n, chi, out, flags);
+    rad_eval_kernel<<<(unsigned)blocks, 256, 0, s>>>(rad32, rad64d, prec, n, chi, out, flags);
     return hipGetLastError();
 }
 
