@@ -372,7 +372,7 @@ __device__ __forceinline__ SpD<double> spatial_d(double x, double y, double z, d
     const double iq = rq * rq;
     const double p = fma(x, x, y * y) * inv_w0sq * iq;
     SpD<double> r;
-    r.S = exp_neg64(-p) * rq;
+    r.S = exp64(-p) * rq;
     const double m = -2.0 * inv_w0sq * iq;
     r.Lx = m * x;
     r.Ly = m * y;
@@ -479,18 +479,40 @@ __device__ __forceinline__ AdjPath<T> adj_path_cast(const AdjPath<double> &p) {
 //                        dF/ds = (phi((t + b/2)/s) - phi((t - b/2)/s)) / b.
 // Edges beyond 9 standard deviations add nothing at FP64 precision.
 __device__ __forceinline__ double phi_pdf(double z) {
-    return 0.39894228040143267794 * exp(-0.5 * z * z);
+    return 0.39894228040143267794 * exp64(-0.5 * z * z);
 }
 
-__device__ __forceinline__ double phi_diff(double zp, double zm) {  // Phi(zp) - Phi(zm), zp > zm
-    const double r = 0.70710678118654752440;
-    if (zm > 0.0) return 0.5 * (erfc(zm * r) - erfc(zp * r));
-    if (zp < 0.0) return 0.5 * (erfc(-zp * r) - erfc(-zm * r));
-    return 1.0 - 0.5 * (erfc(zp * r) + erfc(-zm * r));
-}
+// The edge weights c_j from the upstream weights W (n bins, underflow, overflow).
+struct EdgeWeights {
+    const double *W;
+    int n;
+    __device__ __forceinline__ double operator()(int j) const {
+        return (j == 0 ? W[n] : W[j - 1]) - (j == n ? W[n + 1] : W[j]);
+    }
+};
 
-__device__ void law_sensitivity(double v, double s2, int dep, double ksig, double lo, double wb,
-                                int n, const double *__restrict__ W, double &lv, double &ls2) {
+// Edges evenly spaced (dz = b/s) let the densities follow by multiplications,
+//   phi(z + dz) = phi(z) r,  r = exp(-z dz - dz^2/2),  r -> r exp(-dz^2),
+// anew from their exponentials every kChunk edges (the products' roundings grow
+// with the square of the edges).  Where the box spans at most a quarter standard
+// deviation its mass is the density at its centre times a polynomial in z^2,
+//   Phi(z + d) - Phi(z - d) = phi(z) Int_(-d)^d e^(-z u - u^2/2) du
+//                           = phi(z) sum_k z^(2k) m_2k / (2k)!,
+//   d = dz/2, m_2k = Int_(-d)^d u^2k e^(-u^2/2) du
+// (eight terms: the ninth is below 3e-17 of the sum at six standard deviations),
+// and the derivative along s takes the densities at the box ends, shared by
+// neighbouring edges; wider boxes take erfc at their ends, shared likewise.
+// The products' roundings stay below 6e-15 of the sum of magnitudes.
+// Bound by FP64 issue, by the widest law of each wavefront.  With two erfc and
+// two exponentials a box edge and one exponential a normal edge the contraction
+// of tapes took 466 us for 50,001 samples (boxes), 367 us for 2^20 (normal
+// laws of both histograms) and 580 us for 2^21 (normal); so 105, 296 and 326 us.
+constexpr int kChunk = 16;
+
+template <class Weights>
+__device__ __forceinline__ void law_sensitivity(double v, double s2, int dep, double ksig,
+                                                double lo, double wb, int n, Weights c, double &lv,
+                                                double &ls2) {
     lv = 0.0;
     ls2 = 0.0;
     const double s = sqrt(fmax(s2, 0.0));
@@ -514,62 +536,107 @@ __device__ void law_sensitivity(double v, double s2, int dep, double ksig, doubl
     const int ja = (int)fmin(fmax(ceil((v - reach - lo) / wb), 0.0), (double)n + 1.0);
     const int jb = (int)fmin(fmax(floor((v + reach - lo) / wb), -1.0), (double)n);
     const double inv_se = mode >= 2 ? 1.0 / se : 0.0;
+    const double dz = wb * inv_se, d = 0.5 * dz;
+    const double q = exp64(-dz * dz);
+    auto z_at = [&](int j) { return (fma((double)j, wb, lo) - v) * inv_se; };
     double sv = 0.0, ss = 0.0;
-    if (mode == 2) {
-        // the Gaussian density along the edges by multiplications:
-        // phi(z + dz) = phi(z) r, r = exp(-z dz - dz^2 / 2), and r itself
-        // advances by exp(-dz^2) (exact in the arithmetic; FP64 rounding adds
-        // an ulp or two an edge)
-        const double dz = wb * inv_se;
-        const double q = exp(-dz * dz);
-        double z = (fma((double)ja, wb, lo) - v) * inv_se;
-        double f = phi_pdf(z) * inv_se;
-        double r = exp(fma(-z, dz, -0.5 * dz * dz));
-        for (int j = ja; j <= jb; ++j) {
-            const double wl = j == 0 ? W[n] : W[j - 1];
-            const double wr = j == n ? W[n + 1] : W[j];
-            const double c = wl - wr;
-            sv = fma(c, f, sv);
-            ss = fma(c, -z * f, ss);
-            f *= r;
-            r *= q;
-            z += dz;
-        }
-        lv = -sv;
-        ls2 = ss * dse;
+    if (mode == 1) {
+        for (int j = ja; j <= jb; ++j)
+            if (fabs(fma((double)j, wb, lo) - v) < half) sv += c(j);
+        lv = -sv / wb;
         return;
     }
-    for (int j = ja; j <= jb; ++j) {
-        const double wl = j == 0 ? W[n] : W[j - 1];
-        const double wr = j == n ? W[n + 1] : W[j];
-        const double c = wl - wr;
-        if (c == 0.0) continue;
-        const double t = fma((double)j, wb, lo) - v;
-        double p, q = 0.0;
-        if (mode == 1) {
-            p = fabs(t) < half ? 1.0 / wb : 0.0;
-        } else if (mode == 2) {
-            const double z = t * inv_se;
-            const double f = phi_pdf(z) * inv_se;
-            p = f;
-            q = -z * f;
-        } else {
-            const double zp = (t + half) * inv_se, zm = (t - half) * inv_se;
-            p = phi_diff(zp, zm) / wb;
-            q = (phi_pdf(zp) - phi_pdf(zm)) / wb;
+    if (mode == 2) {
+        // sv = sum c phi / se, ss = sum c (-z) phi / se
+        for (int j0 = ja; j0 <= jb; j0 += kChunk) {
+            double z = z_at(j0), f = phi_pdf(z), r = exp64(-z * dz - d * dz);
+            const int j1 = min(j0 + kChunk - 1, jb);
+            for (int j = j0; j <= j1; ++j) {
+                const double cf = c(j) * f;
+                sv += cf;
+                ss = fma(-z, cf, ss);
+                f *= r;
+                r *= q;
+                z += dz;
+            }
         }
-        sv = fma(c, p, sv);
-        ss = fma(c, q, ss);
+        lv = -sv * inv_se;
+        ls2 = ss * inv_se * dse;
+        return;
     }
-    lv = -sv;
-    ls2 = ss * dse;
+    if (dz <= 0.25) {
+        // coefficients m_2k / (2k)! of the box mass, m_2k = 2 sum_i (-1)^i
+        // d^(2k+2i+1) / (2^i i! (2k+2i+1)); d <= 1/8
+        constexpr int kTerms = 8;
+        double C[kTerms];
+        {
+            const double d2 = d * d;
+            double lead = 2.0 * d;  // 2 d^(2k+1) / (2k)!
+#pragma unroll
+            for (int k = 0; k < kTerms; ++k) {
+                double m = 0.0, w = 1.0;
+#pragma unroll
+                for (int i = 0; i < 6; ++i) {
+                    m = fma(w, 1.0 / (2 * k + 2 * i + 1), m);
+                    w *= d2 * (-0.5 / (i + 1));
+                }
+                C[k] = lead * m;
+                lead *= d2 * (1.0 / ((2 * k + 1) * (2 * k + 2)));
+            }
+        }
+        for (int j0 = ja; j0 <= jb; j0 += kChunk) {
+            // densities at the centres (f) and at the lower box ends (g)
+            double z = z_at(j0), f = phi_pdf(z), r = exp64(-z * dz - d * dz);
+            double g = phi_pdf(z - d), rg = exp64(-(z - d) * dz - d * dz);
+            const int j1 = min(j0 + kChunk - 1, jb);
+            for (int j = j0; j <= j1; ++j) {
+                const double z2 = z * z, cj = c(j);
+                double p = C[kTerms - 1];
+#pragma unroll
+                for (int k = kTerms - 2; k >= 0; --k) p = fma(p, z2, C[k]);
+                const double g1 = g * rg;
+                sv = fma(cj, f * p, sv);
+                ss = fma(cj, g1 - g, ss);
+                f *= r;
+                r *= q;
+                g = g1;
+                rg *= q;
+                z += dz;
+            }
+        }
+    } else if (ja <= jb) {
+        const double rt = 0.70710678118654752440;
+        double zm = 0.0, em = 0.0, gm = 0.0;
+        for (int j = ja - 1; j <= jb; ++j) {  // (the first: the lower end of box ja only)
+            const double zp = z_at(j) + d, ep = erfc(fabs(zp) * rt), gp = phi_pdf(zp);
+            // Phi(zp) - Phi(zm) from the tails on either side of the centre
+            const double p = zm > 0.0 ? 0.5 * (em - ep)
+                                      : (zp < 0.0 ? 0.5 * (ep - em) : 1.0 - 0.5 * (ep + em));
+            const double cj = j < ja ? 0.0 : c(j);
+            sv = fma(cj, p, sv);
+            ss = fma(cj, gp - gm, ss);
+            zm = zp;
+            em = ep;
+            gm = gp;
+        }
+    }
+    lv = -sv / wb;
+    ls2 = ss / wb * dse;
 }
 
-// Share of one sample in the angle-histogram and moment terms of L, as
-// derivatives along the eight parameters added to g.  The sample's energy
-// state (mu, sig2) and its derivatives come from the trajectory; the draw
-// gives the rest: theta = div n (derivative n in mrad per mrad), gamma0,i =
-// gamma0 + sigma_gamma n3, and a0,eff = a0 S0 with S0 at the collision point
+// Edge weights formed once, in LDS.
+struct EdgesLds {
+    const double *c;
+    __device__ __forceinline__ double operator()(int j) const { return c[j]; }
+};
+
+// One sample's gradient terms g along the eight parameters, from its energy
+// state (mu, sig2), its derivatives (derivs(p, dmu, dsig2), asked for at the
+// end: nothing of them is held over the laws' edges) and the edge weights of
+// the energy (we) and angle (wa) histograms.  OBS: also the angle-histogram
+// and moment terms.  The draw gives the rest of these: theta = div n
+// (derivative n in mrad per mrad), gamma0,i = gamma0 + sigma_gamma n3, and
+// a0,eff = a0 S0 with S0 at the collision point
 // (ln S0 derivatives of spatial_d; the divergence moves the collision point
 // by theta z / 2).  The angle law is N(theta_x, sig_th^2) with sig_th^2 =
 // C^2 a0,eff^2 max(sig2, 0) / mu^4 (Sec. 5.2), deposited like the energy law;
@@ -578,44 +645,49 @@ __device__ void law_sensitivity(double v, double s2, int dep, double ksig, doubl
 //   mean and rms of theta_x (rms with sig_th^2) and theta_y, mean a0,eff,
 //   mean 1 - mu / gamma0,i, mean sqrt(sig2^+);
 // the weight, the largest chi and the FP64-shadow fields carry no derivative.
-__device__ void observable_sensitivity(const BatchParams &P, const ShotParams &sp,
-                                       const ShotGrad &go, int64_t i, double mu, double s2,
-                                       const double *dmu, const double *ds2, double *g) {
-    if (!go.d_angle && !go.d_moments) return;
-    constexpr double kHalfC = 0.5 * 0.299792458;  // d z* / d delay [um/fs]
-    SampleCoords sc;
-    sample_coords(sp, P.key0, P.key1, i, sc);
-    const double *nrm = sc.n;
-    const double z = sc.z;
-    const double xc = fma(sc.thx, 0.5 * z, sc.x), yc = fma(sc.thy, 0.5 * z, sc.y);
-    const double zstar = fma(0.5, z, sp.z_delay);
-    const SpD<double> d0 = spatial_d(xc, yc, zstar, sp.inv_w0sq, sp.inv_zR, sqrt(sp.inv_w0sq));
-    const double aeff = sp.a0 * d0.S;
-    double da[kGradParams];
-    da[0] = d0.S;
-    da[1] = aeff * d0.Lw;
-    da[2] = aeff * d0.Lx;
-    da[3] = aeff * d0.Ly;
-    da[4] = aeff * kHalfC * d0.Lz;
-    da[5] = 0.0;
-    da[6] = 0.0;
-    da[7] = aeff * (0.5 * z) * fma(1e-3 * nrm[4], d0.Lx, 1e-3 * nrm[5] * d0.Ly);
-    const double thx = 1e3 * sc.thx, thy = 1e3 * sc.thy;
-    const double s2p = fmax(s2, 0.0), sigf = sqrt(s2p);
-    const double C = 1e3 * P.c_theta * 0.79788456080286535588;
-    const double q = C * C / (mu * mu * mu * mu);
-    const double sig_th = sqrt(q * aeff * aeff * s2p);
-    // dL = Lmu dmu + Ls2 dsig2^+ + Lx dtheta_x + Ly dtheta_y + Lq dsig_th^2
-    //      + La da0eff + Lg dgamma0,i
-    double Lmu = 0.0, Ls2 = 0.0, Lx = 0.0, Ly = 0.0, Lq = 0.0, La = 0.0, Lg = 0.0;
-    if (go.d_angle) {
-        double lv, ls;
-        law_sensitivity(thx, sig_th * sig_th, P.deposit, P.ksig_bins, sp.th_lo, sp.th_w, sp.n_th,
-                        go.d_angle, lv, ls);
-        Lx += lv;
-        Lq += ls;
+template <bool OBS, class Weights, class Derivs>
+__device__ __forceinline__ void sample_gradient(const BatchParams &P, const ShotParams &sp,
+                                                const ShotGrad &go, int64_t i, double mu,
+                                                double s2, Weights we, Weights wa, Derivs derivs,
+                                                double *g) {
+    const bool obs = OBS && (go.d_angle || go.d_moments);
+    SampleCoords sc{};
+    SpD<double> d0{};
+    double aeff = 0.0, thx = 0.0, q = 0.0, sig_th = 0.0;
+    const double s2p = fmax(s2, 0.0);
+    if (obs) {
+        sample_coords(sp, P.key0, P.key1, i, sc);
+        const double z = sc.z;
+        const double xc = fma(sc.thx, 0.5 * z, sc.x), yc = fma(sc.thy, 0.5 * z, sc.y);
+        const double zstar = fma(0.5, z, sp.z_delay);
+        d0 = spatial_d(xc, yc, zstar, sp.inv_w0sq, sp.inv_zR, sqrt(sp.inv_w0sq));
+        aeff = sp.a0 * d0.S;
+        thx = 1e3 * sc.thx;
+        const double C = 1e3 * P.c_theta * 0.79788456080286535588;
+        q = C * C / (mu * mu * mu * mu);
+        sig_th = sqrt(q * aeff * aeff * s2p);
     }
-    if (go.d_moments) {
+    // dL = Lmu dmu + Ls2 dsig2 + Ls2p dsig2^+ + Lx dtheta_x + Ly dtheta_y
+    //      + Lq dsig_th^2 + La da0eff + Lg dgamma0,i
+    double Lv = 0.0, Ls = 0.0, Lx = 0.0, Lq = 0.0;
+#pragma unroll 1
+    for (int law = 0; law < (OBS ? 2 : 1); ++law) {  // (one copy of the code)
+        if (law ? !go.d_angle : !go.d_energy) continue;
+        double lv, ls;
+        law_sensitivity(law ? thx : mu, law ? sig_th * sig_th : s2, P.deposit, P.ksig_bins,
+                        law ? sp.th_lo : sp.e_lo, law ? sp.th_w : sp.e_w, law ? sp.n_th : sp.n_e,
+                        law ? wa : we, lv, ls);
+        if (law) {
+            Lx = lv;
+            Lq = ls;
+        } else {
+            Lv = lv;
+            Ls = ls;
+        }
+    }
+    double Lmu = 0.0, Ls2 = 0.0, Ly = 0.0, La = 0.0, Lg = 0.0;
+    if (OBS && go.d_moments) {
+        const double thy = 1e3 * sc.thy, sigf = sqrt(s2p);
         const double *u = go.d_moments, *M = go.moments;
         const double iW = 1.0 / (double)sp.n_samples;
         Lmu += u[1] * iW;
@@ -635,15 +707,28 @@ __device__ void observable_sensitivity(const BatchParams &P, const ShotParams &s
         Lg += u[9] * iW * mu / (sc.g0 * sc.g0);
         if (sigf > 0.0) Ls2 += u[10] * iW * 0.5 / sigf;
     }
+    constexpr double kHalfC = 0.5 * 0.299792458;  // d z* / d delay [um/fs]
     const double a2 = aeff * aeff;
 #pragma unroll
     for (int p = 0; p < kGradParams; ++p) {
-        const double ds2p = s2 > 0.0 ? ds2[p] : 0.0;
-        const double dq = q * fma(2.0 * aeff * s2p, da[p], fma(a2, ds2p, -4.0 * a2 * s2p * dmu[p] / mu));
-        const double dth_x = p == 7 ? nrm[4] : 0.0, dth_y = p == 7 ? nrm[5] : 0.0;
-        const double dg = p == 5 ? 1.0 : (p == 6 ? nrm[3] : 0.0);
-        g[p] += Lmu * dmu[p] + Ls2 * ds2p + Lx * dth_x + Ly * dth_y + Lq * dq + La * da[p] +
-                Lg * dg;
+        double dm, ds;
+        derivs(p, dm, ds);
+        g[p] = go.d_energy ? fma(Lv, dm, Ls * ds) : 0.0;
+        if (obs) {
+            double da = 0.0;
+            if (p == 0) da = d0.S;
+            if (p == 1) da = aeff * d0.Lw;
+            if (p == 2) da = aeff * d0.Lx;
+            if (p == 3) da = aeff * d0.Ly;
+            if (p == 4) da = aeff * kHalfC * d0.Lz;
+            if (p == 7)
+                da = aeff * (0.5 * sc.z) * fma(1e-3 * sc.n[4], d0.Lx, 1e-3 * sc.n[5] * d0.Ly);
+            const double ds2p = s2 > 0.0 ? ds : 0.0;
+            const double dq = q * fma(2.0 * aeff * s2p, da, fma(a2, ds2p, -4.0 * a2 * s2p * dm / mu));
+            const double dth_x = p == 7 ? sc.n[4] : 0.0, dth_y = p == 7 ? sc.n[5] : 0.0;
+            const double dg = p == 5 ? 1.0 : (p == 6 ? sc.n[3] : 0.0);
+            g[p] += Lmu * dm + Ls2 * ds2p + Lx * dth_x + Ly * dth_y + Lq * dq + La * da + Lg * dg;
+        }
     }
 }
 
@@ -957,14 +1042,14 @@ __device__ __forceinline__ void tangent_one(const BatchParams &P, const ShotPara
         }
     } else if (!(flags & kFlagNonFinite)) {
         const ShotGrad &go = P.gouts[s];
-        if (go.d_energy) {
-            double lv, ls;
-            law_sensitivity(o.mu, o.s2, P.deposit, P.ksig_bins, sp.e_lo, sp.e_w, sp.n_e,
-                            go.d_energy, lv, ls);
-#pragma unroll
-            for (int p = 0; p < kGradParams; ++p) g[p] = fma(lv, o.dmu[p], ls * o.ds2[p]);
-        }
-        observable_sensitivity(P, sp, go, i, o.mu, o.s2, o.dmu, o.ds2, g);
+        sample_gradient<true>(
+            P, sp, go, i, o.mu, o.s2, EdgeWeights{go.d_energy, sp.n_e},
+            EdgeWeights{go.d_angle, sp.n_th},
+            [&](int p, double &dm, double &ds) {
+                dm = o.dmu[p];
+                ds = o.ds2[p];
+            },
+            g);
     }
     if (flags) atomicOr(&P.flags[s], flags);
 }
@@ -1070,38 +1155,44 @@ __global__ __launch_bounds__(kTangent64Block) void tangent64_kernel(
 // law sensitivities (144 bytes read a sample).
 // OBS: some shot also has angle-histogram or moment weights (the contraction
 // of the energy terms alone keeps its small register budget).
-// The gradient terms gi of sample i from its tape entries; W: the shot's energy
-// weights.  False if the sample's state is not finite.
-template <bool OBS>
+// The gradient terms g of sample i from its tape entries.  False if the sample's
+// state is not finite.
+template <bool OBS, class Weights>
 __device__ __forceinline__ bool contract_sample(const BatchParams &P, const ShotParams &sp, int s,
-                                                int64_t i, const double *W, double *gi) {
+                                                int64_t i, Weights we, Weights wa, double *g) {
     const int64_t n = P.tape_n;
     const double *t = P.tape + sp.state_off + i;
     const double mu = t[0], s2 = t[n];
-    double dm[kGradParams], ds[kGradParams];
+    if (!(mu > 0.0 && isfinite(mu) && isfinite(s2))) {
 #pragma unroll
-    for (int p = 0; p < kGradParams; ++p) {
-        dm[p] = t[(2 + p) * n];
-        ds[p] = t[(2 + kGradParams + p) * n];
-        gi[p] = 0.0;
+        for (int p = 0; p < kGradParams; ++p) g[p] = 0.0;
+        return false;
     }
-    if (!(mu > 0.0 && isfinite(mu) && isfinite(s2))) return false;
-    const ShotGrad &go = P.gouts[s];
-    if (go.d_energy) {
-        double lv, ls;
-        law_sensitivity(mu, s2, P.deposit, P.ksig_bins, sp.e_lo, sp.e_w, sp.n_e, W, lv, ls);
-#pragma unroll
-        for (int p = 0; p < kGradParams; ++p) gi[p] = fma(lv, dm[p], ls * ds[p]);
-    }
-    if (OBS) observable_sensitivity(P, sp, go, i, mu, s2, dm, ds, gi);
+    sample_gradient<OBS>(
+        P, sp, P.gouts[s], i, mu, s2, we, wa,
+        [&](int p, double &dm, double &ds) {
+            dm = t[(2 + p) * n];
+            ds = t[(2 + kGradParams + p) * n];
+        },
+        g);
     return true;
+}
+
+// The edge weights of shot s to LDS: n_e + 1 words of the energy histogram,
+// (OBS) then n_th + 1 of the angle histogram.
+template <bool OBS>
+__device__ __forceinline__ void edges_to_lds(const BatchParams &P, const ShotParams &sp, int s,
+                                             double *wsh) {
+    const EdgeWeights we{P.gouts[s].d_energy, sp.n_e}, wa{P.gouts[s].d_angle, sp.n_th};
+    if (we.W)
+        for (int k = threadIdx.x; k <= sp.n_e; k += blockDim.x) wsh[k] = we(k);
+    if (OBS && wa.W)
+        for (int k = threadIdx.x; k <= sp.n_th; k += blockDim.x) wsh[sp.n_e + 1 + k] = wa(k);
 }
 
 template <bool OBS>
 __global__ __launch_bounds__(kPhaseBlock) void contract_kernel(BatchParams P) {
-    // the energy-histogram weights of the block's current shot (n_e + 2
-    // words), read from LDS by every edge of every sample's law
-    extern __shared__ double wsh[];
+    extern __shared__ double wsh[];  // the edge weights of the block's current shot
     __shared__ int64_t slot;
     int s_w = -1;  // the shot whose weights wsh holds (block-uniform)
     for (;;) {
@@ -1111,9 +1202,7 @@ __global__ __launch_bounds__(kPhaseBlock) void contract_kernel(BatchParams P) {
         const ShotParams &sp = P.shots[s];
         if (s != s_w) {
             // (the previous item's reads ended at next_item's barriers)
-            const double *W = P.gouts[s].d_energy;
-            if (W)
-                for (int k = threadIdx.x; k < sp.n_e + 2; k += blockDim.x) wsh[k] = W[k];
+            edges_to_lds<OBS>(P, sp, s, wsh);
             __syncthreads();
             s_w = s;
         }
@@ -1121,7 +1210,8 @@ __global__ __launch_bounds__(kPhaseBlock) void contract_kernel(BatchParams P) {
 #pragma unroll
         for (int p = 0; p < kGradParams; ++p) g[p] = 0.0;
         const int64_t i = (item - sp.item0) * kPhaseBlock + threadIdx.x;
-        if (i < sp.n_samples && !contract_sample<OBS>(P, sp, s, i, wsh, g))
+        if (i < sp.n_samples &&
+            !contract_sample<OBS>(P, sp, s, i, EdgesLds{wsh}, EdgesLds{wsh + sp.n_e + 1}, g))
             atomicOr(&P.flags[s], kFlagNonFinite);
         grad_row(P, item * kGradRows + (threadIdx.x >> 6), g);
     }
@@ -1133,14 +1223,14 @@ __global__ __launch_bounds__(kPhaseBlock) void contract_kernel(BatchParams P) {
 // order (every tape line read once, whole) and go through LDS, from where
 // they are summed as the tangent pass sums them, so that the result equals
 // the recomputing adjoint's bit for bit.  (Reading the tape in chi order fetched
-// every line about eight times: 2^21 samples 1283 -> 583 us with the order in a
+// every line about eight times: 2^21 samples 1283 -> 580 us with the order in a
 // kernel of its own.)
 constexpr int kContractBlock = 512;
 
-template <bool OBS>
-__global__ __launch_bounds__(kContractBlock) void contract_group_kernel(BatchParams P,
-                                                                        int lds_weights) {
-    extern __shared__ double terms[];  // [kGradParams][kChiGroup], then the shot's energy weights
+template <bool OBS, bool LDSW>
+__global__ __launch_bounds__(kContractBlock) void contract_group_kernel(BatchParams P) {
+    // [kGradParams][kChiGroup], then (LDSW) the shot's edge weights
+    extern __shared__ double terms[];
     double *wsh = terms + kGradParams * kChiGroup;
     __shared__ int64_t slot;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -1152,15 +1242,20 @@ __global__ __launch_bounds__(kContractBlock) void contract_group_kernel(BatchPar
         const ShotParams &sp = P.shots[s];
         const int64_t base = (group - sp.gitem0) * kChiGroup;
         const int cnt = (int)min((int64_t)kChiGroup, sp.n_samples - base);
-        const double *W = P.gouts[s].d_energy;
-        if (lds_weights && s != s_w && W)
-            for (int k = threadIdx.x; k < sp.n_e + 2; k += kContractBlock) wsh[k] = W[k];
+        if (LDSW && s != s_w) edges_to_lds<OBS>(P, sp, s, wsh);
         s_w = s;
         __syncthreads();  // (also: the previous group's terms have been summed)
         for (int q = threadIdx.x; q < cnt; q += kContractBlock) {
             double g[kGradParams];
-            if (!contract_sample<OBS>(P, sp, s, base + q, lds_weights ? wsh : W, g))
-                atomicOr(&P.flags[s], kFlagNonFinite);
+            bool ok;
+            if constexpr (LDSW)
+                ok = contract_sample<OBS>(P, sp, s, base + q, EdgesLds{wsh},
+                                          EdgesLds{wsh + sp.n_e + 1}, g);
+            else
+                ok = contract_sample<OBS>(P, sp, s, base + q,
+                                          EdgeWeights{P.gouts[s].d_energy, sp.n_e},
+                                          EdgeWeights{P.gouts[s].d_angle, sp.n_th}, g);
+            if (!ok) atomicOr(&P.flags[s], kFlagNonFinite);
 #pragma unroll
             for (int p = 0; p < kGradParams; ++p) terms[p * kChiGroup + q] = g[p];
         }
@@ -1286,27 +1381,30 @@ hipError_t launch_tangent(const BatchParams &p, const float *env32, const double
                     p, env32, env64, 0, s);
 }
 
-hipError_t launch_contract(const BatchParams &p, bool obs, int max_ne, hipStream_t s) {
+hipError_t launch_contract(const BatchParams &p, bool obs, int max_edges, hipStream_t s) {
     // a tape of a pass with FP64 steps is summed over that pass's rounds
     const bool grouped = p.prec == PREC_F32MIX;
-    const void *fn = grouped ? (obs ? reinterpret_cast<const void *>(&contract_group_kernel<true>)
-                                    : reinterpret_cast<const void *>(&contract_group_kernel<false>))
-                             : (obs ? reinterpret_cast<const void *>(&contract_kernel<true>)
-                                    : reinterpret_cast<const void *>(&contract_kernel<false>));
+    // the edge weights in LDS: at most 64 KB (4096 bins each); beside a
+    // group's terms (128 KB) those that fit, else they are read from memory
+    const size_t wb = (size_t)max_edges * sizeof(double);
+    const bool ldsw = !grouped || wb <= 24 * 1024;
+    const void *fn =
+        !grouped ? (obs ? reinterpret_cast<const void *>(&contract_kernel<true>)
+                        : reinterpret_cast<const void *>(&contract_kernel<false>))
+        : ldsw   ? (obs ? reinterpret_cast<const void *>(&contract_group_kernel<true, true>)
+                        : reinterpret_cast<const void *>(&contract_group_kernel<false, true>))
+                 : (obs ? reinterpret_cast<const void *>(&contract_group_kernel<true, false>)
+                        : reinterpret_cast<const void *>(&contract_group_kernel<false, false>));
     const int block = grouped ? kContractBlock : kPhaseBlock;
-    // the energy weights in LDS: at most 32 KB (n_e <= 4096); beside a group's
-    // terms (128 KB) those that fit, else they are read from memory
-    const size_t wb = (size_t)(max_ne + 2) * sizeof(double);
-    int lds_weights = grouped ? wb <= 24 * 1024 : 1;
     const size_t lds = (grouped ? (size_t)kGradParams * kChiGroup * sizeof(double) : 0) +
-                       (lds_weights ? wb : 0);
+                       (ldsw ? wb : 0);
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     int grid = 0;
     if (e == hipSuccess)
         e = resident_grid(fn, block, lds, grouped ? p.n_gitems : p.n_items, &grid);
     if (e != hipSuccess) return e;
     BatchParams pc = p;
-    void *args[] = {&pc, &lds_weights};  // (the ungrouped kernel takes the first)
+    void *args[] = {&pc};
     return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(block), args, lds, s);
 }
 

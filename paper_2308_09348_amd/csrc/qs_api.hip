@@ -1391,12 +1391,11 @@ qs_status backward_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_
         return hip_fail(c, e, "order kernel");
     if (tape) {
         bool obs = false;
-        int max_ne = 1;
-        for (int k = 0; k < n_shots; ++k) {
-            obs = obs || O[k].d_angle_hist || O[k].d_moments;
-            max_ne = std::max(max_ne, H[k].n_e);
-        }
-        if ((e = qs::launch_contract(bp, obs, max_ne, s)) != hipSuccess)
+        int max_edges = 1;
+        for (int k = 0; k < n_shots; ++k) obs = obs || O[k].d_angle_hist || O[k].d_moments;
+        for (int k = 0; k < n_shots; ++k)
+            max_edges = std::max(max_edges, H[k].n_e + 1 + (obs ? H[k].n_th + 1 : 0));
+        if ((e = qs::launch_contract(bp, obs, max_edges, s)) != hipSuccess)
             return hip_fail(c, e, "contraction kernel");
     } else if ((e = qs::launch_tangent(bp, c->env32, c->env64, b.prec, N->rr_model, N->amp_mode,
                                        false, s)) != hipSuccess) {

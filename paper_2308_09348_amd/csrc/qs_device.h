@@ -293,9 +293,9 @@ __device__ __forceinline__ double inv_sqrt64(double q) {
     return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-// e^x for x <= 0 (0 below -800): x = k ln 2 + r, |r| <= ln 2 / 2, the Taylor
+// e^x for x < 700 (0 below -800): x = k ln 2 + r, |r| <= ln 2 / 2, the Taylor
 // polynomial of degree 12 (remainder 1.7e-16 relative), scaled by 2^k.
-__device__ __forceinline__ double exp_neg64(double x) {
+__device__ __forceinline__ double exp64(double x) {
     x = fmax(x, -800.0);
     const double k = rint(x * 1.44269504088896340736);
     const double r = fma(-k, 1.9082149292705877e-10, fma(-k, 0.693147180369123816490, x));
@@ -331,7 +331,7 @@ __device__ __forceinline__ double spatial(double x, double y, double z, double i
     const double zz = z * inv_zR;
     const double rq = inv_sqrt64(fma(zz, zz, 1.0));  // 1/sqrt(q); 1/q = rq^2
     const double r2 = fma(x, x, y * y) * inv_w0sq;
-    return exp_neg64(-r2 * (rq * rq)) * rq;
+    return exp64(-r2 * (rq * rq)) * rq;
 }
 
 // Higher transverse modes (amplitude only, peak 1 in the focal plane): with

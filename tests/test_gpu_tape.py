@@ -153,3 +153,55 @@ def test_tape_rejects_bad_tensor(gpu):
     p = _case(n_samples=100)
     with pytest.raises(ValueError):
         gpu.forward(p, tape=torch.empty((18, 99), dtype=torch.float64, device="cuda"))
+
+
+@pytest.mark.parametrize("chi_fp64,n_e", [(0.0, 60), (0.0, 4096), (0.1, 60), (0.1, 4096)])
+@pytest.mark.parametrize("deposit", ["point", "cic", "gauss"])
+def test_contraction_of_given_laws(gpu, deposit, chi_fp64, n_e):
+    """The law sensitivities alone: a tape whose derivatives are one (of mu along
+    a0, of sig2 along w0) gives the sums of dL/dmu and dL/dsig2, here against
+    erfc and exp, for laws from point-like to 50 bins wide, on either side of
+    the box law's change of form at a quarter bin (s = 4 bins), in and outside
+    the window.  The densities follow by products of at most 16 factors, so
+    terms carry up to ~16^2 roundings and the erfc differences n_e 1e-16 of
+    theirs: 1e-12 of the sum of magnitudes."""
+    import torch
+    from scipy.special import erfc
+    p = _case(n_samples=2100, n_e=n_e, e_lo=0.0, e_hi=3000.0, deposit=deposit,
+              chi_fp64=chi_fp64)
+    wb = p["e_hi"] / n_e
+    rng = np.random.Generator(np.random.PCG64(3))
+    s = wb * np.resize([0.0, 0.05, 0.5, 1.0, 3.999, 4.0, 4.001, 7.3, 20.0, 50.0], 2100)
+    mu = rng.uniform(1.0, p["e_hi"] + 20 * wb, 2100)
+    tape = gpu.new_tape(2100)
+    tape.zero_()
+    tape[0] = torch.tensor(mu)
+    tape[1] = torch.tensor(s * s)
+    tape[2] = 1.0
+    tape[2 + 8 + 1] = 1.0
+    w = _weights(n_e)
+    gpu.forward(p)  # (the tables of this precision)
+    g = gpu.backward(p, w, tape=tape).cpu().numpy()
+
+    W = w.cpu().numpy()
+    c = np.concatenate([[W[n_e]], W[:n_e]]) - np.concatenate([W[:n_e], [W[n_e + 1]]])
+    t = wb * np.arange(n_e + 1)[None] - mu[:, None]
+    se = np.hypot(s, p["kernel_sigma_bins"] * wb) if deposit == "gauss" else s
+    with np.errstate(divide="ignore", invalid="ignore"):
+        dse = np.where(s > 0, 0.5 / se, 0.0)[:, None]
+        pdf = lambda x: np.exp(-0.5 * (x / se[:, None]) ** 2) / np.sqrt(2 * np.pi)
+        if deposit == "cic":
+            a, b = np.abs(t) - 0.5 * wb, np.abs(t) + 0.5 * wb  # (even in t)
+            r = se[:, None] * np.sqrt(2.0)
+            dv = -0.5 * (erfc(a / r) - erfc(b / r)) / wb
+            ds = (pdf(t + 0.5 * wb) - pdf(t - 0.5 * wb)) / wb * dse
+            dv = np.where(s[:, None] > 0, dv, np.where(np.abs(t) < 0.5 * wb, -1.0 / wb, 0.0))
+        else:
+            dv = -pdf(t) / se[:, None]
+            ds = -(t / se[:, None]) * pdf(t) / se[:, None] * dse
+            if deposit == "point":
+                dv = np.where(s[:, None] > 0, dv, 0.0)
+        ds = np.where(s[:, None] > 0, ds, 0.0)
+    assert abs(g[0] - (c * dv).sum()) <= 1e-12 * np.abs(c * dv).sum()
+    assert abs(g[1] - (c * ds).sum()) <= 1e-12 * np.abs(c * ds).sum()
+    assert not g[2:].any()
