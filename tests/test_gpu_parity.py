@@ -344,3 +344,20 @@ def test_focused_full_size_sampled(gpu, oracle):
     _check_moments(_run(gpu, q), oracle.forward(q), q)
     m = g["moments"]
     assert 0 < m[1] < p["gamma0"] and m[2] > 0 and math.isfinite(m[4])
+
+
+@pytest.mark.parametrize("precision,rtol", [("fp64", 1e-12), ("fp32", 2e-6)])
+@pytest.mark.parametrize("amp_mode", ["a0eff", "local"])
+@pytest.mark.parametrize("n_steps", [1, 3, 4, 5, 8, 11])
+def test_classical_step_counts(gpu, oracle, n_steps, amp_mode, precision, rtol):
+    """The classical model reads the envelope four steps at a time: counts below,
+    at and between multiples of four.  A weak pulse keeps even one step over all
+    of it tame (a0 = 5); a step rounds some thirty operations, in FP64 (1e-12
+    holds eleven steps with room) or in FP32 beside an amplitude and an envelope
+    rounded to FP32 (the loss, a few tenths of mu, to some 1e-7: 2e-6)."""
+    p = workloads.scaled(workloads.focused_3d(), n_samples=300, n_steps=n_steps, a0=5.0,
+                         sigma_gamma=0.0, rr_model="classical", amp_mode=amp_mode,
+                         precision=precision)
+    g = _run(gpu, p, sample_stride=1, n_sample_records=300)
+    ref = oracle.samples(p, range(300))
+    assert np.allclose(g["samples"][:, 0], ref[:, oracle.S_MU], rtol=rtol, atol=0)
