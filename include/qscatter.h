@@ -235,7 +235,7 @@ qs_status qs_forward(qs_ctx *ctx, const qs_laser *laser, const qs_beam *beam,
  * tables, the accumulators, the moment partials and the device shot table --
  * taken from one static device array of about 55 MiB that each GPU the library
  * runs on holds until the process ends (its address is looked up by
- * qs_create, which also makes the call's pinned staging block and event).
+ * qs_create).
  * The call itself allocates nothing: no hipMalloc, hipFree or allocating
  * library routine, and it never captures a HIP graph.  Limits: one shot of at
  * most QS_NOALLOC_MAX_SAMPLES samples; every other size as qs_forward (steps
@@ -545,7 +545,8 @@ qs_status qs_sync_status(qs_ctx *ctx, const int32_t *status, void *stream);
 qs_status qs_set_profiling(qs_ctx *ctx, int on);
 
 /* Durations in milliseconds of the kernels of the last qs_forward enqueued
- * with profiling on: ms[0] envelope table, ms[1] accumulator clear, ms[2]
+ * with profiling on: ms[0] set-up (envelope table, accumulator clear, a small
+ * shot table), ms[1] nothing (the clear, when it had a kernel of its own), ms[2]
  * phase integration, ms[3] deposit, ms[4] finalize (host array of 5).  After
  * qs_forward_factorised: ms[2] node runs, ms[3] interpolation pass, ms[4]
  * deposit and finalize.

