@@ -443,7 +443,7 @@ __device__ __forceinline__ unsigned int block_scan(unsigned int v, unsigned int 
 }
 
 // Bin masses of one histogram of n bins from the edge accumulators of a tile
-// (see wave_deposit): edge e carries T(e) = Q[e] (- QU[e]) + 2^32 C(e), C(e) =
+// (see wave_deposit): edge e carries T(e) = Q[e] (- QU[-e]) + 2^32 C(e), C(e) =
 // sum_(c <= e) cnt[c]; bin b gets T(b+1) - T(b), the underflow T(0), the
 // overflow 2^32 S - T(n) with S = sum of all cnt (every sample counts once).
 // Added to the global words G[0 .. n+1] (bins, underflow, overflow).
@@ -451,7 +451,7 @@ template <bool SPLIT>
 __device__ void flush_edges(const unsigned long long *Q, const unsigned long long *QU,
                             const unsigned int *cnt, int n, unsigned long long *G,
                             unsigned int *wsum) {
-    auto q = [&](int e) { return SPLIT ? Q[e] - QU[e] : Q[e]; };
+    auto q = [&](int e) { return SPLIT ? Q[e] - QU[-e] : Q[e]; };
     const int m = (n + 2 + kDepBlock - 1) / kDepBlock;  // cnt entries a thread
     const int c0 = threadIdx.x * m, c1 = min(c0 + m, n + 2);
     unsigned int local = 0;
@@ -559,10 +559,11 @@ __global__ __launch_bounds__(kPhaseBlock) void shadow_diff_kernel(BatchParams P,
     }
 }
 
-// Held to 128 VGPRs (four waves per SIMD): 113 without spills, since the moment
-// sums of a round are formed before the laws are walked rather than carried
-// through them (focused laws, 2^22 samples: 731 -> 690 us; a fold of the sums by
-// halves took 47 scratch accesses and 8% more time).
+// Held to 80 VGPRs (six waves per SIMD): the runs are bound by LDS atomics and
+// FP32 issue in turn, and more waves fill both (focused laws, 2^22 samples, with
+// four / five / six waves: 706 / 671 / 661 us; the spills at six are block
+// constants, stored once and read back a round).  The moment sums of a round are
+// formed before the laws are walked rather than carried through them.
 // SPLIT: the runs' upper-side tails in arrays of their own (16 bytes an edge
 // instead of 8; histograms of up to 64 KB of LDS words take it).
 // Small launches are bound by the rounds of 256 samples that a block takes one
@@ -571,7 +572,7 @@ __global__ __launch_bounds__(kPhaseBlock) void shadow_diff_kernel(BatchParams P,
 // 39 us, 2^18 445 -> 106 us, 2^20 447 -> 219 us (focused laws; items of 4096
 // before).
 template <bool SPLIT>
-__global__ __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(4))) void deposit_kernel(
+__global__ __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(6))) void deposit_kernel(
     BatchParams P) {
     constexpr int kGroups = kDepBlock / 64;        // wavefronts
     constexpr int kRounds = kMomTile / kDepBlock;  // rounds of a moment tile
@@ -598,7 +599,7 @@ __global__ __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(4))) 
         const ShotOut &so = P.outs[s];
         const int nh_e = sp.n_e + 2, nh_t = sp.n_th + 2;
         // LDS: edge weights Qe [n_e + 1], Qt [n_th + 1] (u64; SPLIT: and the
-        // upper tails QeU [n_e + 1], QtU [n_th + 1]); counters ce [n_e + 2],
+        // upper tails QeU [n_e + 1], QtU [n_th + 1], backwards); counters ce [n_e + 2],
         // ct [n_th + 2], ca [n_a] (u32)
         unsigned long long *Qe = reinterpret_cast<unsigned long long *>(smem);
         unsigned long long *Qt = Qe + sp.n_e + 1;
@@ -720,8 +721,8 @@ __global__ __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(4))) 
                     lt = law_setup(v_t, s_t, P.deposit, P.ksig_bins, sp.th_lo, sp.th_w, inv_wt,
                                    sp.n_th);
                 }
-                wave_deposit<SPLIT>(le, sp.e_w, hfe, Qe, QeU, ce, WL);
-                wave_deposit<SPLIT>(lt, sp.th_w, hft, Qt, QtU, ct, WL);
+                wave_deposit<SPLIT>(le, P.deposit, sp.e_w, hfe, Qe, QeU + sp.n_e, ce, WL);
+                wave_deposit<SPLIT>(lt, P.deposit, sp.th_w, hft, Qt, QtU + sp.n_th, ct, WL);
             }
 
             // ---- one row of moment sums (fixed order) ----
@@ -764,8 +765,8 @@ __global__ __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(4))) 
         }
         if (flags) atomicOr(&P.flags[s], flags);
         unsigned long long *G = P.hist + sp.hist_off;
-        flush_edges<SPLIT>(Qe, QeU, ce, sp.n_e, G, wsum);
-        flush_edges<SPLIT>(Qt, QtU, ct, sp.n_th, G + nh_e, wsum);
+        flush_edges<SPLIT>(Qe, QeU + sp.n_e, ce, sp.n_e, G, wsum);
+        flush_edges<SPLIT>(Qt, QtU + sp.n_th, ct, sp.n_th, G + nh_e, wsum);
         for (int k = threadIdx.x; k < sp.n_a; k += kDepBlock)
             if (ca[k]) atomicAdd(&G[nh_e + nh_t + k], kOne * ca[k]);
         __syncthreads();  // the next item clears the LDS words
