@@ -548,8 +548,8 @@ qs_status qs_set_profiling(qs_ctx *ctx, int on);
  * with profiling on: ms[0] set-up (envelope table, accumulator clear, a small
  * shot table), ms[1] nothing (the clear, when it had a kernel of its own), ms[2]
  * phase integration, ms[3] deposit, ms[4] finalize (host array of 5).  After
- * qs_forward_factorised: ms[2] node runs, ms[3] interpolation pass, ms[4]
- * deposit and finalize.
+ * qs_forward_factorised: ms[2] node runs and sample draws, ms[3] node weights
+ * (where asked for), ms[4] interpolation, deposit and finalize.
  * Waits for that call's last event.  Errors: QS_EINVAL (profiling off or no
  * profiled call yet), QS_EDEVICE. */
 qs_status qs_last_timings(qs_ctx *ctx, double *ms);

@@ -1247,7 +1247,7 @@ qs_status forward_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_b
                 return hip_fail(c, e, "shadow difference kernel");
         }
         if ((e = mark(3)) != hipSuccess) return hip_fail(c, e, "event record");
-        if ((e = qs::launch_deposit(bp, b.max_nh, q)) != hipSuccess)
+        if ((e = qs::launch_deposit(bp, b.max_nh, false, q)) != hipSuccess)
             return hip_fail(c, e, "deposit kernel");
         if ((e = mark(4)) != hipSuccess) return hip_fail(c, e, "event record");
         if ((e = qs::launch_finalize(bp, q)) != hipSuccess) return hip_fail(c, e, "finalize kernel");
@@ -1663,6 +1663,7 @@ qs_status factor_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_be
     qs::ShotParams *nv = reinterpret_cast<qs::ShotParams *>(b.outs + sizeof(qs::ShotOut) * n_shots);
     int64_t node_off = 0, node_items = 0, hoff = 0;
     int weight_words = 0;
+    bool node_outputs = false;
     for (int k = 0; k < n_shots; ++k) {
         qs::ShotParams &p = b.sp[k];
         const int na = G[k].n_a, ng = G[k].n_g, nn = na * ng;
@@ -1674,6 +1675,7 @@ qs_status factor_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_be
         p.hist_off = hoff;  // [energy | angle | a0,eff | node weights]
         hoff += H[k].n_e + 2 + H[k].n_th + 2 + H[k].n_a + nn;
         if (G[k].node_weights) weight_words = std::max(weight_words, nn);
+        node_outputs = node_outputs || G[k].node_weights || G[k].node_states;
         nv[k] = p;
         nv[k].n_samples = nn;
         nv[k].state_off = node_off;
@@ -1707,7 +1709,7 @@ qs_status factor_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_be
     const size_t narr = ((size_t)node_off * 8 + 255) / 256 * 256;
     const size_t narrf = ((size_t)node_off * 4 + 255) / 256 * 256;
     const size_t flag_words = ((size_t)n_shots + 1) / 2;
-    const size_t accum_words = 1 + flag_words + (size_t)b.hist_words;
+    const size_t accum_words = 2 + flag_words + (size_t)b.hist_words;
     if ((st = grow(c, &c->env32, &c->env32_cap, nenv, "envelope table")) != QS_OK) return st;
     if ((st = grow(c, &c->env64, &c->env64_cap, nenv, "envelope table")) != QS_OK) return st;
     if ((st = grow(c, &c->accum, &c->accum_cap, accum_words, "accumulators")) != QS_OK) return st;
@@ -1738,14 +1740,17 @@ qs_status factor_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_be
     bp.st = states_at(c->states, arr, arrf);
     bp.nst = states_at(c->states + 6 * arr + arrf, narr, narrf);
     bp.queue = reinterpret_cast<unsigned int *>(c->accum);
-    bp.flags = reinterpret_cast<int *>(c->accum + 1);
-    bp.hist = c->accum + 1 + flag_words;
+    bp.flags = reinterpret_cast<int *>(c->accum + 2);
+    bp.hist = c->accum + 2 + flag_words;
     bp.partials = c->partials;
     qs::BatchParams bn = bp;  // the node pass: node view, writes the node states
     bn.shots = reinterpret_cast<const qs::ShotParams *>(
         c->shot_tab + (sizeof(qs::ShotParams) + sizeof(qs::ShotOut)) * n_shots);
     bn.n_items = node_items;
     bn.st = bp.nst;
+    bn.draw_shots = bp.shots;
+    bn.draw_st = bp.st;
+    bn.n_draws = bp.n_items;
 
     // ---- enqueue ----
     hipError_t e;
@@ -1764,13 +1769,13 @@ qs_status factor_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_be
         hipSuccess)
         return hip_fail(c, e, "node kernel");
     if ((e = mark(3)) != hipSuccess) return hip_fail(c, e, "event record");
-    if ((e = qs::launch_interp(bp, weight_words, s)) != hipSuccess)
-        return hip_fail(c, e, "interpolation kernel");
+    if ((e = qs::launch_node_weights(bp, weight_words, s)) != hipSuccess)
+        return hip_fail(c, e, "node weight kernel");
     if ((e = mark(4)) != hipSuccess) return hip_fail(c, e, "event record");
-    if ((e = qs::launch_deposit(bp, b.max_nh, s)) != hipSuccess)
+    if ((e = qs::launch_deposit(bp, b.max_nh, true, s)) != hipSuccess)
         return hip_fail(c, e, "deposit kernel");
     if ((e = qs::launch_finalize(bp, s)) != hipSuccess) return hip_fail(c, e, "finalize kernel");
-    if ((e = qs::launch_node_outputs(bp, s)) != hipSuccess)
+    if (node_outputs && (e = qs::launch_node_outputs(bp, s)) != hipSuccess)
         return hip_fail(c, e, "node output kernel");
     if ((e = mark(5)) != hipSuccess) return hip_fail(c, e, "event record");
     if (prof) advance_timing_ring(c);

@@ -698,6 +698,64 @@ __device__ __forceinline__ int64_t next_item(unsigned int *counter, int64_t *slo
     return item;
 }
 
+// Bilinear weights of a sample on its shot's node grid (a0,eff / a0 = S0 in
+// [0, 1]; with one gamma0 node the last two weights are zero) and the nodes' states.
+struct NodeCell {
+    double w[4];
+    int n[4];
+    __device__ __forceinline__ NodeCell(const ShotParams &sp, double S0, double g0) {
+        const int K = sp.n_anode, M = sp.n_gnode;
+        const double ta = S0 * (double)(K - 1);
+        const int k = min((int)ta, K - 2);
+        const double fa = ta - (double)k;
+        int m = 0;
+        double fg = 0.0;
+        if (M > 1) {
+            const double tg =
+                fmin(fmax((g0 - sp.g_node_lo) / sp.g_node_step, 0.0), (double)(M - 1));
+            m = min((int)tg, M - 2);
+            fg = tg - (double)m;
+        }
+        w[0] = (1.0 - fa) * (1.0 - fg);
+        w[1] = fa * (1.0 - fg);
+        w[2] = (1.0 - fa) * fg;
+        w[3] = fa * fg;
+        n[0] = k * M + m;
+        n[1] = n[0] + M;
+        n[2] = M > 1 ? n[0] + 1 : n[0];
+        n[3] = M > 1 ? n[1] + 1 : n[1];
+    }
+};
+
+// Coordinates of the samples of a plane-wave reconstruction (S0, gamma0, the
+// angles), a wavefront a tile of kPhaseBlock samples.
+__device__ __forceinline__ void draw_samples(const BatchParams &P) {
+    const int lane = threadIdx.x & 63;
+    int s_prev = 0;  // the shot of the wavefront's previous tile
+    for (;;) {
+        unsigned int taken = 0;
+        if (lane == 0) taken = atomicAdd(&P.queue[2], 1u);
+        const int64_t item = __builtin_amdgcn_readfirstlane(taken);
+        if (item >= P.n_draws) break;
+        const int s = __builtin_amdgcn_readfirstlane(
+            find_shot_from(P.draw_shots, P.n_shots, item, false, s_prev));
+        s_prev = s;
+        const ShotParams &sp = P.draw_shots[s];
+        const int64_t i0 = (item - sp.item0) * kPhaseBlock;
+        const int64_t i1 = i0 + kPhaseBlock < sp.n_samples ? i0 + kPhaseBlock : sp.n_samples;
+        for (int64_t i = i0 + lane; i < i1; i += 64) {
+            double g0, thx, thy, S0;
+            Path<double> pd;
+            draw_sample(sp, P.key0, P.key1, i, g0, thx, thy, pd, S0);
+            const int64_t o = sp.state_off + i;
+            P.draw_st.S0[o] = S0;
+            P.draw_st.g0[o] = g0;
+            P.draw_st.thx[o] = thx;
+            P.draw_st.thy[o] = thy;
+        }
+    }
+}
+
 // ===========================================================================
 // Deposit of sample laws into fixed-point histograms
 // ===========================================================================
@@ -1195,7 +1253,10 @@ inline hipError_t run_pass(const PassKernel &k, const BatchParams &p, const floa
         const int64_t blocks = (waves + per - 1) / per;
         grid = (int)(blocks < ncu ? (blocks < 1 ? 1 : blocks) : ncu);
     } else {
-        e = resident_grid(k.fn, block, k.lds, p.n_items, &grid, cap);
+        // (a block draws a tile a wavefront)
+        constexpr int kPer = kPhaseBlock / 64;
+        e = resident_grid(k.fn, block, k.lds, p.n_items + (p.n_draws + kPer - 1) / kPer, &grid,
+                          cap);
         if (e != hipSuccess) return e;
     }
     BatchParams pc = p;

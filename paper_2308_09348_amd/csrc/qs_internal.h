@@ -251,6 +251,11 @@ struct BatchParams {
     int64_t tape_n;         // samples over the batch (tape field stride)
     SampleState st;
     SampleState nst;        // plane-wave reconstruction: final states of the nodes
+    // node pass: the samples drawn beside it (tiles of kPhaseBlock of draw_shots, into
+    // draw_st; counter queue[2])
+    const ShotParams *draw_shots;
+    SampleState draw_st;
+    int64_t n_draws;
     SampleState sst;        // FP64 shadow states of an FP32 pass
     // accumulators (device scratch, cleared before each launch)
     unsigned long long *hist;      // per shot: [n_e + 2 | n_th + 2 | n_a] in 32.32 fixed point
@@ -258,7 +263,7 @@ struct BatchParams {
                                    // (FP32-state law - FP64-state law) bin masses, signed, 2^-40
     unsigned int *chimax_bits;     // [n_shots]
     int *flags;                    // [n_shots]
-    unsigned int *queue;           // [2]: phase and deposit work counters
+    unsigned int *queue;           // work counters: [0] phase, [1] deposit, [2] draws
     unsigned long long *fp64_steps;  // [n_shots]: wavefront phase steps taken in FP64 by
                                      // the forward pass's FP32 loop (null: not counted)
     double *partials;              // [kPartials][n_mtiles]; adjoint: [kGradParams] columns of
@@ -283,7 +288,8 @@ hipError_t launch_order(const BatchParams &p, hipStream_t s);
 hipError_t launch_phase(const BatchParams &p, const float *env32, const double *env64, int prec,
                         int rr, int amp, hipStream_t s);
 size_t deposit_lds_bytes(int max_hist_words);
-hipError_t launch_deposit(const BatchParams &p, int max_hist_words, hipStream_t s);
+// nodes: the states are interpolated from the shots' nodes
+hipError_t launch_deposit(const BatchParams &p, int max_hist_words, bool nodes, hipStream_t s);
 hipError_t launch_finalize(const BatchParams &p, hipStream_t s);
 hipError_t launch_shadow_diff(const BatchParams &p, int64_t n_items, int max_hist_words,
                               hipStream_t s);
@@ -315,7 +321,7 @@ hipError_t launch_grad_shadow(const BatchParams &p, int64_t span, hipStream_t s)
 // pass writes sample states for the deposit and finalize kernels
 hipError_t launch_phase_nodes(const BatchParams &p, const float *env32, const double *env64,
                               int prec, int rr, hipStream_t s);
-hipError_t launch_interp(const BatchParams &p, int weight_words, hipStream_t s);
+hipError_t launch_node_weights(const BatchParams &p, int weight_words, hipStream_t s);
 hipError_t launch_node_outputs(const BatchParams &p, hipStream_t s);
 
 }  // namespace qs

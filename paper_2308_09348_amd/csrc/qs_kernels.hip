@@ -304,9 +304,15 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
 
 // FP32 passes and classical FP64 passes: blocks take items of kPhaseBlock
 // samples.
-template <int PREC, bool QUANTUM, bool LOCAL, bool NODES = false, bool MODES = false>
+// DRAW: node passes of the reconstruction of few blocks.  Their wavefronts have
+// long chains and leave the device idle (61 x 64 nodes: 61 wavefronts, 376 us of
+// 1024 steps), so the launch's other blocks draw the samples meanwhile (2^22
+// samples: about 100 us as a pass of their own), one block a CU, since beside
+// other wavefronts a node's steps take longer (the launch 389 us, 426 us without).
+template <int PREC, bool QUANTUM, bool LOCAL, bool NODES = false, bool MODES = false,
+          bool DRAW = false>
 __global__ __launch_bounds__(kPhaseBlock)
-__attribute__((amdgpu_waves_per_eu((PREC == PREC_F32 && QUANTUM) ? 4 : 1))) void phase_kernel(BatchParams P,
+__attribute__((amdgpu_waves_per_eu((PREC == PREC_F32 && QUANTUM && !DRAW) ? 4 : 1))) void phase_kernel(BatchParams P,
                                                             const float *__restrict__ env32,
                                                             const double *__restrict__ env64) {
     static_assert(PREC == PREC_F32 || !QUANTUM, "phase64_kernel");
@@ -347,7 +353,11 @@ __attribute__((amdgpu_waves_per_eu((PREC == PREC_F32 && QUANTUM) ? 4 : 1))) void
             if (flags) atomicOr(&P.flags[s], flags);
         }
     }
+    if constexpr (DRAW) draw_samples(P);
 }
+
+// The draws by themselves, before the other node passes.
+__global__ __launch_bounds__(kPhaseBlock) void draw_kernel(BatchParams P) { draw_samples(P); }
 
 // Quantum passes with FP64 steps (all of them, or where chi is high).  One
 // block a CU holds the FP64 table's cells that the launch reaches in LDS (and
@@ -571,8 +581,11 @@ __global__ __launch_bounds__(kPhaseBlock) void shadow_diff_kernel(BatchParams P,
 // the work item shrinks with the launch (default_dep_tile): 5003 samples 440 ->
 // 39 us, 2^18 445 -> 106 us, 2^20 447 -> 219 us (focused laws; items of 4096
 // before).
-template <bool SPLIT>
-__global__ __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(6))) void deposit_kernel(
+// NODES: a sample's final state is the bilinear interpolant of its shot's nodes
+// (four reads, L2-resident, beside some 6,000 vector instructions of a round: a
+// pass of its own that wrote the states took 75 us more at 2^22 samples).
+template <bool SPLIT, bool NODES>
+__global__ __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(NODES ? 5 : 6))) void deposit_kernel(
     BatchParams P) {
     constexpr int kGroups = kDepBlock / 64;        // wavefronts
     constexpr int kRounds = kMomTile / kDepBlock;  // rounds of a moment tile
@@ -634,10 +647,27 @@ __global__ __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(6))) 
                 for (int m = 0; m < P_N; ++m) acc[m] = 0.0;
                 if (i < i1) {
                     const int64_t k = sp.state_off + i;
-                    const double mu_f = P.st.mu[k], s2_f = P.st.s2[k], S0 = P.st.S0[k];
-                    const double g0 = P.st.g0[k];
+                    const double S0 = P.st.S0[k], g0 = P.st.g0[k];
                     const double thx_m = 1e3 * P.st.thx[k], thy_m = 1e3 * P.st.thy[k];
-                    const float cmx = P.st.cmx[k];
+                    double mu_f, s2_f;
+                    float cmx;
+                    if constexpr (NODES) {
+                        const NodeCell c(sp, S0, g0);
+                        double cm = 0.0;
+                        mu_f = s2_f = 0.0;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const int64_t g = sp.node_off + c.n[j];
+                            mu_f += c.w[j] * P.nst.mu[g];
+                            s2_f += c.w[j] * P.nst.s2[g];
+                            cm += c.w[j] * (double)P.nst.cmx[g];
+                        }
+                        cmx = (float)cm;
+                    } else {
+                        mu_f = P.st.mu[k];
+                        s2_f = P.st.s2[k];
+                        cmx = P.st.cmx[k];
+                    }
                     if (!(mu_f > 0.0) || !isfinite(mu_f) || !isfinite(s2_f)) {
                         flags |= kFlagNonFinite;  // also raised by the phase kernel
                     } else {
@@ -778,8 +808,9 @@ __global__ __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(6))) 
 // ===========================================================================
 // Bound by latency (one block).  One wavefront a column of the moment rows
 // (stored column after column): lane l adds the tiles l, l + 64, ..., then the
-// wavefront's sum: 16.3 -> 4.8 us at 5003 samples, 52 -> 23 us at 2^22, against
-// a block that took the columns in turn, each with a tree of eight barriers.
+// wavefront's sum: 16.3 -> 4.8 us at 5003 samples, 52 -> 11 us at 2^22 (23 us with
+// four rows in flight), against a block that took the columns in turn, each with
+// a tree of eight barriers.
 constexpr int kFinBlock = 64 * 16;
 static_assert(kPartials <= kFinBlock / 64, "a wavefront a column");
 
@@ -796,12 +827,18 @@ __global__ __launch_bounds__(kFinBlock) void finalize_kernel(BatchParams P) {
         const double *col = P.partials + (size_t)wid * P.n_mtiles + sp.mtile0;
         const bool mx = wid >= P_N;
         double acc = 0.0;
+        if (per == 1) {
+            // (sixteen rows in flight a lane)
+#pragma unroll 16
+            for (int64_t b = lane; b < nrow; b += 64) acc = mx ? fmax(acc, col[b]) : acc + col[b];
+        } else {
 #pragma unroll 4
-        for (int64_t b = (int64_t)lane * per; b < nrow; b += 64 * per) {
-            double v = col[b];
-            for (int r = 1; r < per && b + r < nrow; ++r)
-                v = mx ? fmax(v, col[b + r]) : v + col[b + r];
-            acc = mx ? fmax(acc, v) : acc + v;
+            for (int64_t b = (int64_t)lane * per; b < nrow; b += 64 * per) {
+                double v = col[b];
+                for (int r = 1; r < per && b + r < nrow; ++r)
+                    v = mx ? fmax(v, col[b + r]) : v + col[b + r];
+                acc = mx ? fmax(acc, v) : acc + v;
+            }
         }
         acc = mx ? wave_max(acc) : wave_sum(acc);
         if (lane == 0) sums[wid] = acc;
@@ -1043,16 +1080,44 @@ hipError_t launch_phase_nodes(const BatchParams &p, const float *env32, const do
                               int prec, int rr, hipStream_t s) {
     const bool q = rr == 1;
     if (prec == PREC_F32MIX && !q) prec = PREC_F32;
+    int device = 0, ncu = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e == hipSuccess)
+        e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device);
+    if (e != hipSuccess) return e;
+    BatchParams pn = p;
+    const bool wide = q && prec != PREC_F32;
     PassKernel k{};
-    if (prec == PREC_F32)
-        k = q ? phase_of<PREC_F32, true, false, true, false>()
-              : phase_of<PREC_F32, false, false, true, false>();
-    if (prec == PREC_F64)
-        k = q ? phase_of<PREC_F64, true, false, true, false>()
-              : phase_of<PREC_F64, false, false, true, false>();
-    if (prec == PREC_F32MIX) k = phase_of<PREC_F32MIX, true, false, true, false>();
-    if (!k.fn) return hipErrorInvalidValue;
-    return run_pass(k, p, env32, env64, p.phase_cap, s);
+    if (!wide && p.n_items <= ncu) {
+        // with the draws: LDS for one block a CU
+        k = {prec == PREC_F64
+                 ? reinterpret_cast<const void *>(
+                       &phase_kernel<PREC_F64, false, false, true, false, true>)
+             : q ? reinterpret_cast<const void *>(
+                       &phase_kernel<PREC_F32, true, false, true, false, true>)
+                 : reinterpret_cast<const void *>(
+                       &phase_kernel<PREC_F32, false, false, true, false, true>),
+             kPhaseBlock, 84 * 1024, false};
+        e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds);
+        if (e != hipSuccess) return e;
+    } else {
+        if (prec == PREC_F32)
+            k = q ? phase_of<PREC_F32, true, false, true, false>()
+                  : phase_of<PREC_F32, false, false, true, false>();
+        if (prec == PREC_F64)
+            k = q ? phase_of<PREC_F64, true, false, true, false>()
+                  : phase_of<PREC_F64, false, false, true, false>();
+        if (prec == PREC_F32MIX) k = phase_of<PREC_F32MIX, true, false, true, false>();
+        if (!k.fn) return hipErrorInvalidValue;
+        int grid = 0;
+        e = resident_grid(reinterpret_cast<const void *>(&draw_kernel), kPhaseBlock, 0,
+                          (p.n_draws + kPhaseBlock / 64 - 1) / (kPhaseBlock / 64), &grid);
+        if (e != hipSuccess) return e;
+        draw_kernel<<<grid, kPhaseBlock, 0, s>>>(p);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        pn.n_draws = 0;
+    }
+    return run_pass(k, pn, env32, env64, p.phase_cap, s);
 }
 
 // edge weights (u64, one per edge) and counters (u32, one per bin and two
@@ -1060,10 +1125,12 @@ hipError_t launch_phase_nodes(const BatchParams &p, const float *env32, const do
 // runs' upper tails apart)
 size_t deposit_lds_bytes(int max_hist_words) { return (size_t)max_hist_words * 12; }
 
-hipError_t launch_deposit(const BatchParams &p, int max_hist_words, hipStream_t s) {
+hipError_t launch_deposit(const BatchParams &p, int max_hist_words, bool nodes, hipStream_t s) {
     const bool split = (size_t)max_hist_words * 20 <= 64 * 1024;
-    const void *fn = split ? reinterpret_cast<const void *>(&deposit_kernel<true>)
-                           : reinterpret_cast<const void *>(&deposit_kernel<false>);
+    const void *fn = split ? (nodes ? reinterpret_cast<const void *>(&deposit_kernel<true, true>)
+                                    : reinterpret_cast<const void *>(&deposit_kernel<true, false>))
+                           : (nodes ? reinterpret_cast<const void *>(&deposit_kernel<false, true>)
+                                    : reinterpret_cast<const void *>(&deposit_kernel<false, false>));
     const size_t lds = (size_t)max_hist_words * (split ? 20 : 12);
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;

@@ -240,3 +240,28 @@ def test_full_size_against_oracle(gpu, oracle):
     l1 = np.abs(g["energy_hist"] - d["energy_hist"]).sum() / n
     assert l1 < 5e-3, l1
     assert abs(g["moments"][1] - d["moments"][1]) <= 2e-4 * d["moments"][1]
+
+
+@pytest.mark.parametrize("rr,precision,chi_fp64", [("quantum", "fp32", 0.0),
+                                                   ("quantum", "fp32", 0.1),
+                                                   ("quantum", "fp64", 0.0),
+                                                   ("classical", "fp32", 0.0),
+                                                   ("classical", "fp64", 0.0)])
+def test_draws_beside_and_before_the_nodes(gpu, rr, precision, chi_fp64):
+    """One shot's 61 x 64 nodes are 16 blocks, whose launch also draws the samples
+    (passes with an FP64 table draw before the nodes); 17 shots' are 272, more
+    than the device's 256 CUs, and the draws are a kernel of their own.  The same
+    bits either way, with the node weights (their own pass) and without."""
+    import torch
+    shots = [_case(n_samples=200 + 91 * k, n_steps=32, a0=20.0 + k, rr_model=rr,
+                   precision=precision, chi_fp64=chi_fp64) for k in range(17)]
+    outs = gpu.forward_factorised_batched(shots, 61, 64, nodes=True)
+    bare = gpu.forward_factorised_batched(shots, 61, 64)
+    for k in (0, 5, 16):
+        one = gpu.forward_factorised(dict(shots[k], shot=shots[0]["shot"] + k), 61, 64, nodes=True)
+        for key in one:
+            assert torch.equal(outs[k][key], one[key]), (k, key)
+        for key in bare[k]:
+            assert torch.equal(bare[k][key], one[key]), (k, key)
+        w = one["node_weights"]
+        assert float(w.sum()) == shots[k]["n_samples"]
