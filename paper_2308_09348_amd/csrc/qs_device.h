@@ -582,8 +582,12 @@ __device__ __forceinline__ void rk4_q64(double mu, double s2, AmpFactors<double>
 // One FP32 RK4 step of the quantum moment system with two table reads:
 // stage 2 and stage 4 read LDS, stage 3 reuses stage 2's cell, and stage 4's
 // cell is handed to the next step's stage 1 (with its amplitude factors).
-__device__ __forceinline__ void rk4_q32(float mu, float s2, AmpQ &A1, float ah, float a4, float h,
-                                        const Phys<float> &ph, const float *__restrict__ tab,
+// Ah, A4: the factors at psi_j + h/2 and psi_j + h (A1 is replaced by A4).
+// ROUND: the sum k2 + k3 of the energy takes both rounded, where the compiler
+// would fuse k2's last product into it (see phase_pair_kernel).
+template <bool ROUND = false>
+__device__ __forceinline__ void rk4_q32(float mu, float s2, AmpQ &A1, const AmpQ &Ah,
+                                        const AmpQ &A4, float h, const float *__restrict__ tab,
                                         RadCell32 &carry, float &dmu, float &ds2,
                                         float &chi_hi) {
     const float hh = 0.5f * h;
@@ -594,7 +598,6 @@ __device__ __forceinline__ void rk4_q32(float mu, float s2, AmpQ &A1, float ah, 
     float k1m, k1s;
     rhs_quantum(mu, s2, A1, g, G1, G2, hq, k1m, k1s);
     // stage 2 (table read)
-    const AmpQ Ah(ah, ph);
     const float m2 = fmaf(hh, k1m, mu), s22 = fmaf(hh, k1s, s2);
     const float c2 = Ah.cpm * m2;
     RadCell32 mid;
@@ -608,8 +611,9 @@ __device__ __forceinline__ void rk4_q32(float mu, float s2, AmpQ &A1, float ah, 
     rad_cell_eval(mid, c3, g, G1, G2, hq);
     float k3m, k3s;
     rhs_quantum(m3, s23, Ah, g, G1, G2, hq, k3m, k3s);
+    if constexpr (ROUND) asm("" : "+v"(k2m), "+v"(k3m));
     // stage 4 (table read; its cell serves the next step's stage 1)
-    A1 = AmpQ(a4, ph);
+    A1 = A4;
     const float m4 = fmaf(h, k3m, mu), s24 = fmaf(h, k3s, s2);
     const float c4 = A1.cpm * m4;
     rad_lookup32(tab, c4, carry);

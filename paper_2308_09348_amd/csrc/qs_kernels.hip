@@ -67,6 +67,65 @@ __device__ __forceinline__ int fp64_segment(const BatchParams &P, const ShotPara
     return j;
 }
 
+// The FP32 path of a sample from its FP64 draw.
+template <bool MODES>
+__device__ __forceinline__ Path<float, MODES> path32(const ShotParams &sp,
+                                                     const Path<double, MODES> &pd, double thx,
+                                                     double thy) {
+    Path<float, MODES> pf;
+    pf.xc = (float)pd.xc;
+    pf.yc = (float)pd.yc;
+    pf.thx = (float)thx;
+    pf.thy = (float)thy;
+    pf.zstar = (float)pd.zstar;
+    pf.inv_w0sq = sp.inv_w0sqf;
+    pf.inv_zR = sp.inv_zRf;
+    pf.mode = sp.mode;
+    pf.mm = sp.mode_m;
+    pf.mn = sp.mode_n;
+    pf.inv_norm = sp.mode_inv_normf;
+    return pf;
+}
+
+// The amplitudes' spatial parts at the middle and end of FP32 step j.  Local
+// amplitude: one spatial factor per step, at psi_{j+2}; the stage-2/3 value at
+// psi_j + h/2 is the quadratic through psi_j (aS_prev), psi_{j+1} (aS_next) and
+// psi_{j+2} (error of order h^3 times the third derivative of S, far below
+// FP32 rounding).
+template <bool MODES>
+__device__ __forceinline__ void mid_end32(const BatchParams &P, const ShotParams &sp,
+                                          const Path<float, MODES> &pf, float a0f, float a0S0f,
+                                          bool local, int j, float &aS_prev, float &aS_next,
+                                          float &aSh, float &aS4) {
+    aSh = aS4 = a0S0f;
+    if (local && sp.mid_interp) {
+        const float psi2 = fmaf((float)(j + 2), P.hf, P.psi0f);
+        const float aS_far = a0f * pf.S(psi2 * P.ellf);
+        aS4 = aS_next;
+        aSh = fmaf(0.375f, aS_prev, fmaf(0.75f, aS4, -0.125f * aS_far));
+        aS_next = aS_far;
+    } else if (local) {  // coarse steps: both points exactly
+        const float psi = fmaf((float)j, P.hf, P.psi0f);
+        aSh = a0f * pf.S(fmaf(0.5f, P.hf, psi) * P.ellf);
+        aS4 = a0f * pf.S((psi + P.hf) * P.ellf);
+    }
+    aS_prev = aS4;
+}
+
+// The final state of sample i.
+__device__ __forceinline__ void store_state(const BatchParams &P, const ShotParams &sp, int64_t i,
+                                            double mu_f, double s2_f, double S0, double g0,
+                                            double thx, double thy, float cmx) {
+    const int64_t k = sp.state_off + i;
+    P.st.mu[k] = mu_f;
+    P.st.s2[k] = s2_f;
+    P.st.S0[k] = S0;
+    P.st.g0[k] = g0;
+    P.st.thx[k] = thx;
+    P.st.thy[k] = thy;
+    P.st.cmx[k] = cmx;
+}
+
 // N steps of the classical model, step(eh, e4) with the envelope at the step's
 // middle and end.  A step is some thirty dependent operations, less than the
 // latency of a scalar read: small launches (a wavefront alone on its SIMD)
@@ -171,18 +230,7 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
         s2_f = s2;
         chi_hi = (float)chd;
     } else {
-        Path<float, MODES> pf;
-        pf.xc = (float)pd.xc;
-        pf.yc = (float)pd.yc;
-        pf.thx = (float)thx;
-        pf.thy = (float)thy;
-        pf.zstar = (float)pd.zstar;
-        pf.inv_w0sq = sp.inv_w0sqf;
-        pf.inv_zR = sp.inv_zRf;
-        pf.mode = sp.mode;
-        pf.mm = sp.mode_m;
-        pf.mn = sp.mode_n;
-        pf.inv_norm = sp.mode_inv_normf;
+        const Path<float, MODES> pf = path32(sp, pd, thx, thy);
         const float a0f = sp.a0f;
         const float a0S0f = (float)a0S0;
         float mu = (float)g0, mu_lo = (float)(g0 - (double)mu), s2 = 0.0f, s2_lo = 0.0f;
@@ -197,26 +245,9 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
             amp1 = AmpQ(aS_prev * env32[0], phf);
             rad_lookup32(tab32, amp1.cpm * mu, carry);
         }
-        // local amplitude: one spatial factor per step, at psi_{j+2}; the
-        // stage-2/3 value at psi_j + h/2 is the quadratic through psi_j,
-        // psi_{j+1} and psi_{j+2} (error of order h^3 times the third
-        // derivative of S, far below FP32 rounding)
         float aS_next = local ? a0f * pf.S((P.psi0f + P.hf) * P.ellf) : a0S0f;
-        // the amplitudes' spatial parts at the middle and end of step j
         auto mid_end = [&](int j, float &aSh, float &aS4) {
-            aSh = aS4 = a0S0f;
-            if (local && sp.mid_interp) {
-                const float psi2 = fmaf((float)(j + 2), P.hf, P.psi0f);
-                const float aS_far = a0f * pf.S(psi2 * P.ellf);
-                aS4 = aS_next;
-                aSh = fmaf(0.375f, aS_prev, fmaf(0.75f, aS4, -0.125f * aS_far));
-                aS_next = aS_far;
-            } else if (local) {  // coarse steps: both points exactly
-                const float psi = fmaf((float)j, P.hf, P.psi0f);
-                aSh = a0f * pf.S(fmaf(0.5f, P.hf, psi) * P.ellf);
-                aS4 = a0f * pf.S((psi + P.hf) * P.ellf);
-            }
-            aS_prev = aS4;
+            mid_end32(P, sp, pf, a0f, a0S0f, local, j, aS_prev, aS_next, aSh, aS4);
         };
         if constexpr (!QUANTUM) {
             float a1 = aS_prev * env32[0];
@@ -276,7 +307,7 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
             const float a4 = aS4 * env32[2 * j + 2];
             if (PREC != PREC_F32MIX) cmx = fmaxf(cmx, amp1.cpm * mu);
             float dm, ds;
-            rk4_q32(mu, s2, amp1, ah, a4, P.hf, phf, tab32, carry, dm, ds, chi_hi);
+            rk4_q32(mu, s2, amp1, AmpQ(ah, phf), AmpQ(a4, phf), P.hf, tab32, carry, dm, ds, chi_hi);
             comp_add(mu, mu_lo, dm);
             comp_add(s2, s2_lo, ds);
             ++j;
@@ -292,14 +323,7 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
     }
     if (QUANTUM && !(chi_hi < chi_top)) flags |= kFlagRange;
     if (!(mu_f > 0.0) || !isfinite(mu_f) || !isfinite(s2_f)) flags |= kFlagNonFinite;
-    const int64_t k = sp.state_off + i;
-    P.st.mu[k] = mu_f;
-    P.st.s2[k] = s2_f;
-    P.st.S0[k] = S0;
-    P.st.g0[k] = g0;
-    P.st.thx[k] = thx;
-    P.st.thy[k] = thy;
-    P.st.cmx[k] = cmx;
+    store_state(P, sp, i, mu_f, s2_f, S0, g0, thx, thy, cmx);
 }
 
 // FP32 passes and classical FP64 passes: blocks take items of kPhaseBlock
@@ -358,6 +382,142 @@ __attribute__((amdgpu_waves_per_eu((PREC == PREC_F32 && QUANTUM && !DRAW) ? 4 : 
 
 // The draws by themselves, before the other node passes.
 __global__ __launch_bounds__(kPhaseBlock) void draw_kernel(BatchParams P) { draw_samples(P); }
+
+// Small FP32 quantum launches with the local amplitude: at most an item a CU, so
+// that a wavefront of the kernel above would be alone on its SIMD.  Such a
+// wavefront issues an instruction in four to five clocks, where two issue one in
+// little more than two, and its steps are one dependent chain.  Here every
+// wavefront of samples has a helper on its SIMD, which forms the amplitude factors
+// (the spatial factor, the envelope: 45 of a step's 180 instructions, none of
+// which needs the state) kPairSteps ahead and passes them through LDS (two
+// buffers, a barrier of the block a buffer).  5003 samples x 512 steps 237 ->
+// 197 us, 50,001 248 -> 214 us; from 257 items on (a second round; 131,072 samples
+// 416 us, 297 us above) the kernel above is the better one.
+// The results are the same bits: its loop is unrolled twice with the next
+// step's spatial factor between, which leaves the sum k2 + k3 of even steps (but
+// not a last one) its own rounding, where one block of code forms a fused
+// operation (ROUND of rk4_q32).
+constexpr int kPairSteps = 8;
+constexpr int kPairBlock = 2 * kPhaseBlock;
+static_assert(kPairSteps % 2 == 0, "a buffer begins with an even step");
+
+struct PairLds {
+    float4 m[2][kPhaseBlock / 64][kPairSteps][64];  // at the middle nu, cd, cpm; at the end nu
+    float2 e[2][kPhaseBlock / 64][kPairSteps][64];  // at the end cd, cpm
+};
+
+__global__ __launch_bounds__(kPairBlock) void phase_pair_kernel(BatchParams P,
+                                                                const float *__restrict__ env32,
+                                                                const double *__restrict__ env64) {
+    __shared__ __align__(16) float tab32[kCells32 * kCellVals];
+    __shared__ int64_t slot;
+    extern __shared__ __align__(16) unsigned char pair_lds[];
+    PairLds &B = *reinterpret_cast<PairLds *>(pair_lds);
+    {
+        const float4 *src = reinterpret_cast<const float4 *>(P.rad32);
+        float4 *dst = reinterpret_cast<float4 *>(tab32);
+        for (int k = threadIdx.x; k < kCells32 * kCellVals / 4; k += blockDim.x) dst[k] = src[k];
+        __syncthreads();
+    }
+    constexpr int kPairs = kPhaseBlock / 64;
+    const Phys<float> phf{P.Kf, P.CDf, P.two_over_aSf};
+    const int N = P.n_steps, nbuf = (N + kPairSteps - 1) / kPairSteps;
+    const int lane = threadIdx.x & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), pair = wid % kPairs;
+    int s_prev = 0;  // the shot of the block's previous item
+    for (;;) {
+        const int64_t item = next_item(&P.queue[0], &slot);
+        if (item >= P.n_items) break;
+        const int s = __builtin_amdgcn_readfirstlane(
+            find_shot_from(P.shots, P.n_shots, item, false, s_prev));
+        s_prev = s;
+        const ShotParams &sp = P.shots[s];
+        const bool local = !sp.plane_wave;
+        // (lanes past the samples take the last one: every wavefront meets the
+        // same barriers)
+        const int64_t k = (item - sp.item0) * kPhaseBlock + 64 * pair + lane;
+        const bool live = k < sp.n_samples;
+        const int64_t i = live ? k : sp.n_samples - 1;
+        double g0, thx, thy, S0;
+        Path<double, false> pd{};
+        draw_sample<false>(sp, P.key0, P.key1, i, g0, thx, thy, pd, S0);
+        const Path<float, false> pf = path32(sp, pd, thx, thy);
+        const float a0f = sp.a0f;
+        const double a0S0 = sp.a0 * S0;
+        const float a0S0f = (float)a0S0;
+        float aS_prev = local ? a0f * pf.S(P.psi0f * P.ellf) : a0S0f;
+        if (wid >= kPairs) {  // the helpers
+            float aS_next = local ? a0f * pf.S((P.psi0f + P.hf) * P.ellf) : a0S0f;
+            auto fill = [&](int c) {
+                const int j0 = c * kPairSteps, j1 = min(N, j0 + kPairSteps);
+#pragma unroll 2
+                for (int j = j0; j < j1; ++j) {
+                    float aSh, aS4;
+                    mid_end32(P, sp, pf, a0f, a0S0f, local, j, aS_prev, aS_next, aSh, aS4);
+                    const AmpQ Ah(aSh * env32[2 * j + 1], phf), A4(aS4 * env32[2 * j + 2], phf);
+                    B.m[c & 1][pair][j - j0][lane] = make_float4(Ah.nu, Ah.cd, Ah.cpm, A4.nu);
+                    B.e[c & 1][pair][j - j0][lane] = make_float2(A4.cd, A4.cpm);
+                }
+            };
+            fill(0);
+            __syncthreads();
+            for (int c = 0; c < nbuf; ++c) {
+                if (c + 1 < nbuf) fill(c + 1);
+                __syncthreads();
+            }
+        } else {
+            float mu = (float)g0, mu_lo = (float)(g0 - (double)mu), s2 = 0.0f, s2_lo = 0.0f;
+            const double g0_rest = (g0 - (double)mu) - (double)mu_lo;
+            float cmx = 0.0f, chi_hi = 0.0f;
+            AmpQ amp1(aS_prev * env32[0], phf);
+            RadCell32 carry;
+            rad_lookup32(tab32, amp1.cpm * mu, carry);
+            __syncthreads();
+            for (int c = 0; c < nbuf; ++c) {
+                auto step = [&](int q, auto round) {
+                    const float4 m = B.m[c & 1][pair][q][lane];
+                    const float2 e = B.e[c & 1][pair][q][lane];
+                    AmpQ Ah, A4;
+                    Ah.nu = m.x;
+                    Ah.nu2 = 2.0f * m.x;
+                    Ah.cd = m.y;
+                    Ah.cpm = m.z;
+                    A4.nu = m.w;
+                    A4.nu2 = 2.0f * m.w;
+                    A4.cd = e.x;
+                    A4.cpm = e.y;
+                    cmx = fmaxf(cmx, amp1.cpm * mu);
+                    float dm, ds;
+                    rk4_q32<decltype(round)::value>(mu, s2, amp1, Ah, A4, P.hf, tab32, carry, dm,
+                                                    ds, chi_hi);
+                    comp_add(mu, mu_lo, dm);
+                    comp_add(s2, s2_lo, ds);
+                };
+                const int n = min(kPairSteps, N - c * kPairSteps);
+                int q = 0;
+                for (; q + 1 < n; q += 2) {
+                    step(q, std::integral_constant<bool, true>{});
+                    step(q + 1, std::integral_constant<bool, false>{});
+                }
+                if (q < n) step(q, std::integral_constant<bool, false>{});
+                __syncthreads();
+            }
+            const double mu_f = ((double)mu + (double)mu_lo) + g0_rest;
+            const double s2_f = (double)s2 + (double)s2_lo;
+            // chi at the end of the last step (the pulse tail)
+            const double aN =
+                (local ? sp.a0 * pd.S(P.psi_max * P.ell_per_psi) : a0S0) * env64[2 * N];
+            cmx = fmaxf(cmx, (float)(P.two_over_aS * mu_f * fabs(aN)));
+            if (live) {
+                int flags = 0;
+                if (!(chi_hi < (float)(1 << (kEMax + 1)))) flags |= kFlagRange;
+                if (!(mu_f > 0.0) || !isfinite(mu_f) || !isfinite(s2_f)) flags |= kFlagNonFinite;
+                store_state(P, sp, i, mu_f, s2_f, S0, g0, thx, thy, cmx);
+                if (flags) atomicOr(&P.flags[s], flags);
+            }
+        }
+    }
+}
 
 // Quantum passes with FP64 steps (all of them, or where chi is high).  One
 // block a CU holds the FP64 table's cells that the launch reaches in LDS (and
@@ -1069,7 +1229,18 @@ hipError_t launch_phase(const BatchParams &p, const float *env32, const double *
     const bool q = rr == 1, l = amp == 1, m = p.any_mode != 0;
     if (prec == PREC_F32MIX && !q) prec = PREC_F32;  // no radiation table, no promotion
     PassKernel k{};
-    if (prec == PREC_F32) k = q ? select_phase<PREC_F32, true>(l, m) : select_phase<PREC_F32, false>(l, m);
+    int device = 0, ncu = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e == hipSuccess)
+        e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device);
+    if (e != hipSuccess) return e;
+    if (prec == PREC_F32 && q && l && !m && p.n_items <= ncu) {
+        k = {reinterpret_cast<const void *>(&phase_pair_kernel), kPairBlock, sizeof(PairLds), false};
+        e = hipFuncSetAttribute(k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.lds);
+        if (e != hipSuccess) return e;
+    } else if (prec == PREC_F32) {
+        k = q ? select_phase<PREC_F32, true>(l, m) : select_phase<PREC_F32, false>(l, m);
+    }
     if (prec == PREC_F64) k = q ? select_phase<PREC_F64, true>(l, m) : select_phase<PREC_F64, false>(l, m);
     if (prec == PREC_F32MIX) k = select_phase<PREC_F32MIX, true>(l, m);
     if (!k.fn) return hipErrorInvalidValue;

@@ -275,3 +275,20 @@ def test_status_words_of_many_threads(qs):
         got = list(pool.map(read, range(40)))
     assert got == [[k] * 20 for k in range(40)]
     ctx.close()
+
+
+@pytest.mark.parametrize("n_samples,n_steps", [(1, 130), (64, 131), (65, 8), (300, 7), (1111, 9),
+                                               (2500, 512), (513, 1), (700, 1023)])
+@pytest.mark.parametrize("plane_wave", [False, True])
+def test_small_launches_have_the_bits_of_large_ones(qs, n_samples, n_steps, plane_wave):
+    """FP32 quantum passes of at most an item a CU give every wavefront of samples
+    a helper for the amplitudes; beside a shot of 70,000 samples (274 items) the
+    same shot goes through the general kernel.  Counts of steps at and between
+    multiples of the helper's eight, odd and even; coarse and fine steps; samples
+    at the edges of wavefronts and items."""
+    shot = _case(n_samples=n_samples, n_steps=n_steps, a0=3.0 if n_steps < 100 else 30.0,
+                 **({"w0_um": 0.0} if plane_wave else {}))
+    ctx = qs.Context(0)
+    big = dict(shot, n_samples=70_000)
+    _same(_np(ctx.forward(shot)), _np(ctx.forward_batched([shot, big])[0]), "small")
+    ctx.close()
