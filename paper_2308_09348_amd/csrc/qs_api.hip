@@ -64,10 +64,10 @@ struct qs_ctx {
     size_t states_cap = 0;
     uint16_t *order = nullptr;  // chi order of the samples (passes with FP64 steps)
     size_t order_cap = 0;
-    // per-shot tables: pinned staging on the host, a device copy.  Calls
-    // take the staging blocks in turn, so the host can stage a call while
-    // the copies of the kStageSlots - 1 calls before it still wait on the
-    // stream; a block is reused once its own copy has run.
+    // per-shot tables too large for the set-up kernel's argument: pinned staging
+    // on the host, a device copy.  Calls take the staging blocks in turn, so the
+    // host can stage a call while the copies of the kStageSlots - 1 calls before
+    // it still wait on the stream; a block is reused once its own copy has run.
     unsigned char *stage[kStageSlots] = {};
     size_t stage_cap[kStageSlots] = {};
     hipEvent_t stage_done[kStageSlots] = {};  // the last copy out of each block
@@ -788,7 +788,7 @@ namespace {
 
 // Shared set-up of a batch: validation of the shots, the constants of the
 // shared phase grid (Sec. 2 eq. a0eff, Sec. 4 eq. dpdtRR) and the per-shot
-// table, built in pinned staging memory as [ShotParams x n][OutT x n].
+// table, built on the host as [ShotParams x n][OutT x n].
 struct Batch {
     qs::BatchParams bp{};
     double psi_max = 0, h = 0, omega_tau = 0;
@@ -803,8 +803,8 @@ struct Batch {
     qs::SetupTab small{};            // direct: the table
     unsigned char *stage = nullptr;  // the table: `small` or a pinned staging buffer
     int slot = 0;                    // its block in the context's ring (not direct)
-    qs::ShotParams *sp = nullptr;  // in the staging buffer
-    unsigned char *outs = nullptr;  // in the staging buffer, after the ShotParams
+    qs::ShotParams *sp = nullptr;   // in the table
+    unsigned char *outs = nullptr;  // in the table, after the ShotParams
 };
 
 int ilog2(int64_t v) {
@@ -840,11 +840,10 @@ const TuneEntry *find_tune(const qs_ctx *c, const TuneKey &k) {
 // The deposit work item of launches without a tuned choice: 1024 samples, and
 // for small launches as few as leave about 512 items, so that they spread over
 // the device (256 CUs).  Measured on focused laws, items of 256 / 512 / 1024 /
-// 4096 samples: 5003 samples 39 / 69 / 122 / 454 us, 50,001 51 / 72 / 124 / 457 us,
-// 2^18 123 / 106 / 135 / 458 us, 2^20 357 / 266 / 219 / 460 us, 2^22 1308 / 794 /
-// 690 / 749 us (an earlier form of the kernel: 2^19 235 / 184 / 168 / 510 us; 128 shots
-// of 2^12 .. 2^18 1688 / 1551 / 1516 / 2056 us, their uneven ends need the smaller
-// items; 1500 shots 19.8 / 17.3 / 16.2 / 16.2 ms).
+// 4096 samples: 5003 samples 39 / 68 / 120 / 441 us, 50,001 51 / 71 / 121 / 445 us,
+// 2^18 123 / 104 / 132 / 443 us, 2^20 364 / 260 / 215 / 449 us, 2^22 1329 / 772 /
+// 592 / 684 us, 128 shots of 2^12 .. 2^18 1205 / 1129 / 1175 / 1439 us, 1500 shots
+// 14.0 / 12.5 / 12.0 / 12.1 ms.
 int default_dep_tile(int64_t total) {
     int tile = qs::kDepTile;
     while (tile > qs::kMomRow && total / tile < qs::kDepItems) tile >>= 1;
