@@ -205,3 +205,22 @@ def test_contraction_of_given_laws(gpu, deposit, chi_fp64, n_e):
     assert abs(g[0] - (c * dv).sum()) <= 1e-12 * np.abs(c * dv).sum()
     assert abs(g[1] - (c * ds).sum()) <= 1e-12 * np.abs(c * ds).sum()
     assert not g[2:].any()
+
+
+@pytest.mark.parametrize("n_samples,n_steps", [(1, 130), (64, 131), (65, 4), (300, 3), (1111, 5),
+                                               (2500, 513), (513, 1)])
+def test_small_tape_has_the_bits_of_a_large_one(gpu, n_samples, n_steps):
+    """FP32 quantum tape passes of at most an item a CU divide a step over three
+    wavefronts; beside a shot of 70,000 samples (274 items) the same shot goes
+    through the general kernel.  Counts of steps at and between multiples of the
+    four that a buffer holds, samples at the edges of wavefronts and items."""
+    import torch
+    p = _case(n_samples=n_samples, n_steps=n_steps, a0=3.0 if n_steps < 100 else 30.0)
+    big = dict(p, n_samples=70_000)
+    t1 = gpu.new_tape(n_samples)
+    o1 = gpu.forward(p, tape=t1)
+    t2 = gpu.new_tape(n_samples + 70_000)
+    o2 = gpu.forward_batched([p, big], tape=t2)[0]
+    assert torch.equal(t1, t2[:, :n_samples])
+    for key in o1:
+        assert torch.equal(o1[key], o2[key]), key
