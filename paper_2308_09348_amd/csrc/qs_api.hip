@@ -564,7 +564,7 @@ qs_status qs_radiation_eval(qs_ctx *c, int32_t precision, int64_t n, const doubl
         (precision != QS_PREC_FP32 && precision != QS_PREC_FP64))
         return set_err(c, "invalid radiation_eval arguments"), QS_EINVAL;
     DeviceGuard guard(c->device);
-    hipError_t e = qs::launch_radiation_eval(c->rad32, c->rad64d, precision, n, chi, out,
+    hipError_t e = qs::launch_radiation_eval(c->rad32, c->rad64, precision, n, chi, out,
                                              c->eval_flags, reinterpret_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(c, e, "radiation_eval kernel");
     return QS_OK;

@@ -225,6 +225,13 @@ __device__ __forceinline__ void cheb_basis(int m, double l[4]) {
     l[0] = -(r[0] * r[1] * r[2]) / den;
 }
 
+// The drift's combinations of the forward functions (any linear one of them:
+// values or coefficients).
+__device__ __forceinline__ double drift_mix2(double g, double G1) { return fma(2.0, g, G1); }
+__device__ __forceinline__ double drift_mix3(double g, double G1, double G2) {
+    return fma(0.5, G2, fma(2.0, G1, g));
+}
+
 // The table of a pass without FP64 steps of the quantum model.
 struct NoTable {
     __device__ __forceinline__ void eval(double, double *) const {}
@@ -236,7 +243,8 @@ struct NoTable {
 // global table.  The two branches meet in the functions' values: meeting in the
 // coefficients took 4 F more registers, and reads of the same width in both are
 // merged by the compiler into flat loads, which wait for both memories.  The
-// values are those of the global table.
+// values are those of the global table; the forward table's (F = 4) are combined
+// for the drift (T1 .. T4), coefficient by coefficient, as the cells are staged.
 template <int N, int F, bool BASED = false>
 struct TabWindow {
     const double2 *win;  // [2 F][N]
@@ -254,7 +262,16 @@ struct TabWindow {
             for (int f = 0; f < F; ++f)
                 v[f] = fma(t, fma(t, fma(t, q[2 * f + 1].y, q[2 * f + 1].x), q[2 * f].y), q[2 * f].x);
         } else {
-            const double *q = p + (size_t)c * (4 * F);
+            double q[4 * F];
+#pragma unroll
+            for (int e = 0; e < 4 * F; ++e) q[e] = p[(size_t)c * (4 * F) + e];
+            if constexpr (F == 4) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    q[8 + e] = drift_mix3(q[e], q[4 + e], q[8 + e]);
+                    q[4 + e] = drift_mix2(q[e], q[4 + e]);
+                }
+            }
 #pragma unroll
             for (int f = 0; f < F; ++f)
                 v[f] = fma(t, fma(t, fma(t, q[4 * f + 3], q[4 * f + 2]), q[4 * f + 1]), q[4 * f]);
@@ -265,9 +282,22 @@ struct TabWindow {
         : win(w), p(tab), c0(first) {
         static_assert(N <= kCells64, "a part of the table");
         const double2 *src = reinterpret_cast<const double2 *>(tab) + 2 * F * (size_t)first;
-        for (int k = threadIdx.x; k < 2 * F * N; k += blockDim.x) {
-            const int cell = k / (2 * F);
-            w[(k - cell * (2 * F)) * N + cell] = src[k];
+        if constexpr (F == 4) {
+            for (int k = threadIdx.x; k < 2 * N; k += blockDim.x) {  // half a cell
+                const int cell = k >> 1, half = k & 1;
+                const double2 *q = src + 8 * cell + half;
+                const double2 g = q[0], G1 = q[2], G2 = q[4], h = q[6];
+                double2 *o = w + half * N + cell;
+                o[0] = g;
+                o[2 * N] = make_double2(drift_mix2(g.x, G1.x), drift_mix2(g.y, G1.y));
+                o[4 * N] = make_double2(drift_mix3(g.x, G1.x, G2.x), drift_mix3(g.y, G1.y, G2.y));
+                o[6 * N] = h;
+            }
+        } else {
+            for (int k = threadIdx.x; k < 2 * F * N; k += blockDim.x) {
+                const int cell = k / (2 * F);
+                w[(k - cell * (2 * F)) * N + cell] = src[k];
+            }
         }
     }
 };

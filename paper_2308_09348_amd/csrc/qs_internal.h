@@ -8,8 +8,9 @@
 namespace qs {
 
 // ---- radiation-function tables -------------------------------------------
-// g, 2g + chi g', g + 2 chi g' + chi^2 g''/2 and h (the combinations of the
-// drift) are stored as one cubic per cell in the local coordinate t in [0, 1).  Cell 0 covers chi in [0, 2^kEMin); cell
+// g, chi g', chi^2 g'' and h (FP64) or the drift's combinations of them, g,
+// 2g + chi g', g + 2 chi g' + chi^2 g''/2 and h (FP32), are stored as one cubic per
+// cell in the local coordinate t in [0, 1).  Cell 0 covers chi in [0, 2^kEMin); cell
 // 1 + (e - kEMin) * 2^SB + s covers the s-th of 2^SB equal sub-intervals of
 // the octave [2^e, 2^(e+1)), e = kEMin .. kEMax.  Each cell holds 16 values:
 // four functions x four monomial coefficients (t^0 .. t^3).  The FP32 table is
@@ -293,7 +294,7 @@ hipError_t launch_deposit(const BatchParams &p, int max_hist_words, bool nodes, 
 hipError_t launch_finalize(const BatchParams &p, hipStream_t s);
 hipError_t launch_shadow_diff(const BatchParams &p, int64_t n_items, int max_hist_words,
                               hipStream_t s);
-hipError_t launch_radiation_eval(const float *rad32, const double *rad64d, int prec, int64_t n,
+hipError_t launch_radiation_eval(const float *rad32, const double *rad64, int prec, int64_t n,
                                  const double *chi, double *out, int *flags, hipStream_t s);
 hipError_t launch_radiation_derivs(const float *rad32d, const double *rad64d, int prec, int64_t n,
                                    const double *chi, double *out, int *flags, hipStream_t s);

@@ -116,8 +116,9 @@ __global__ void rad_node_kernel(const double *yf, double *vals) {
 }
 
 // Cubic through the four node values of each cell, in monomials of t.  The
-// forward tables take the combinations the drift uses; the derivative tables
-// all six functions (same order as the node values), the FP32 one combined.
+// FP64 tables hold the plain functions (forward: g, chi g', chi^2 g'', h;
+// derivative: all six, in the order of the node values), the FP32 ones the
+// combinations that the steps use.
 __global__ void rad_coef_kernel(const double *vals, float *rad32, double *rad64, float *rad32d,
                                 double *rad64d) {
     const int cell_all = blockIdx.x * blockDim.x + threadIdx.x;
@@ -142,19 +143,13 @@ __global__ void rad_coef_kernel(const double *vals, float *rad32, double *rad64,
             coef[f][3] = a3 * r * r * r;
         }
     }
-    // the drift combinations g, 2g + chi g', g + 2 chi g' + chi^2 g''/2, h
-    double mix[4][4];
-    for (int c = 0; c < 4; ++c) {
-        mix[0][c] = coef[0][c];
-        mix[1][c] = 2.0 * coef[0][c] + coef[1][c];
-        mix[2][c] = coef[0][c] + 2.0 * coef[1][c] + 0.5 * coef[2][c];
-        mix[3][c] = coef[3][c];
-    }
     if (cell_all < kCells32) {
-        // function-major: rad32[(f * kCells32 + cell) * 4 + power]
+        // function-major: rad32[(f * kCells32 + cell) * 4 + power], the drift
+        // combinations g, 2g + chi g', g + 2 chi g' + chi^2 g''/2, h
         for (int c = 0; c < 4; ++c) {
-            for (int f = 0; f < 4; ++f)
-                rad32[(f * kCells32 + cell_all) * 4 + c] = (float)mix[f][c];
+            const double mix[4] = {coef[0][c], 2.0 * coef[0][c] + coef[1][c],
+                                   coef[0][c] + 2.0 * coef[1][c] + 0.5 * coef[2][c], coef[3][c]};
+            for (int f = 0; f < 4; ++f) rad32[(f * kCells32 + cell_all) * 4 + c] = (float)mix[f];
             // g, E1 = 2g + G1, E2 = 2g + 4 G1 + G2, E3 = 6 G1 + 6 G2 + G3, h, H1
             const double jm[kDerivFuncs] = {
                 coef[0][c], 2.0 * coef[0][c] + coef[1][c],
@@ -166,15 +161,14 @@ __global__ void rad_coef_kernel(const double *vals, float *rad32, double *rad64,
     } else {
         const int cell = cell_all - kCells32;
         for (int f = 0; f < 4; ++f)
-            for (int c = 0; c < 4; ++c) rad64[(size_t)cell * kCellVals + 4 * f + c] = mix[f][c];
+            for (int c = 0; c < 4; ++c) rad64[(size_t)cell * kCellVals + 4 * f + c] = coef[f][c];
         for (int f = 0; f < kDerivFuncs; ++f)
             for (int c = 0; c < 4; ++c)
                 rad64d[(size_t)cell * (4 * kDerivFuncs) + 4 * f + c] = coef[f][c];
     }
 }
 
-// (the FP64 functions from the derivative table, which holds them plain)
-__global__ void rad_eval_kernel(const float *rad32, const double *rad64d, int prec, int64_t n,
+__global__ void rad_eval_kernel(const float *rad32, const double *rad64, int prec, int64_t n,
                                 const double *chi, double *out, int *flags) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n) return;
@@ -190,7 +184,7 @@ __global__ void rad_eval_kernel(const float *rad32, const double *rad64d, int pr
     } else {
         double g, G1, G2, h, t;
         const int c = rad_index64(chi[k], t);
-        rad_cell_eval64(rad64d + (size_t)c * (4 * kDerivFuncs), t, g, G1, G2, h);
+        rad_cell_eval64(rad64 + (size_t)c * kCellVals, t, g, G1, G2, h);
         out[4 * k] = g;
         out[4 * k + 1] = G1;
         out[4 * k + 2] = G2;
@@ -218,11 +212,11 @@ hipError_t build_radiation_tables(float *rad32, double *rad64, float *rad32d, do
     return hipGetLastError();
 }
 
-hipError_t launch_radiation_eval(const float *rad32, const double *rad64d, int prec, int64_t n,
+hipError_t launch_radiation_eval(const float *rad32, const double *rad64, int prec, int64_t n,
                                  const double *chi, double *out, int *flags, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const int64_t blocks = (n + 255) / 256;
-    rad_eval_kernel<<<(unsigned)blocks, 256, 0, s>>>(rad32, rad64d, prec, n, chi, out, flags);
+    rad_eval_kernel<<<(unsigned)blocks, 256, 0, s>>>(rad32, rad64, prec, n, chi, out, flags);
     return hipGetLastError();
 }
 
