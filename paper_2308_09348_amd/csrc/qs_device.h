@@ -163,20 +163,23 @@ __device__ __forceinline__ void rad_cell_eval(const RadCell32 &cell, float chi, 
     hq = fmaf(t, fmaf(t, fmaf(t, cell.q3.w, cell.q3.z), cell.q3.y), cell.q3.x);
 }
 
-// FP64 cell of chi and the coordinate t in the cell (chi beyond the table is
-// clamped to the last cell and reported by the caller).
+// FP64 cell of chi and the coordinate t in the cell (chi beyond the table gives a
+// cell past the last one, to be clamped to that; reported by the caller).
 // All in the upper word: the cell from its top bits, t = (chi - cell start)
-// 2^(SB - e), both operations exact; cell 0 takes the coordinate of cell 1,
-// t = 64 (chi / 2^kEMin64 - 1) in [-64, 0).
+// 2^(SB - e), both operations exact.  Below 2^kEMin64 the same of y = chi / 8 +
+// (7/8) 2^kEMin64, which runs evenly through the last 16 cells of the octave below
+// (above, y is less than chi): two operations on every chi, no branch and no
+// selects (an even cell index by selects of its own cost FP64 passes 10%).
 __device__ __forceinline__ int rad_index64(double chi, double &t) {
     constexpr int kLow = 20 - kSB64;  // bits of the upper word below the cell index
-    const uint32_t hi = (uint32_t)__double2hiint(chi);
-    const uint32_t hc = max(hi, (uint32_t)(1023 + kEMin64) << 20);
-    const double start = __hiloint2double((int)(hc >> kLow << kLow), 0);
-    const double inv = __hiloint2double((int)((uint32_t)(2046 + kSB64) - (hc >> 20)) << 20, 0);
-    t = (chi - start) * inv;
-    const int c = (int)(hi >> kLow) - ((1023 + kEMin64) << kSB64) + 1;
-    return min(max(c, 0), kCells64 - 1);
+    constexpr double kMin = 1.0 / (1 << -kEMin64);
+    static_assert(kLow64 == 16 && kSB64 == 6, "an eighth of an octave");
+    const double y = fmax(chi, fma(chi, 0.125, 0.875 * kMin));
+    const uint32_t hi = (uint32_t)__double2hiint(y);
+    const double start = __hiloint2double((int)(hi >> kLow << kLow), 0);
+    const double inv = __hiloint2double((int)((uint32_t)(2046 + kSB64) - (hi >> 20)) << 20, 0);
+    t = (y - start) * inv;
+    return (int)(hi >> kLow) - ((1023 + kEMin64) << kSB64) + kLow64;
 }
 
 __device__ __forceinline__ void rad_cell_eval64(const double *q, double t, double &g, double &G1,
@@ -194,12 +197,13 @@ __device__ __forceinline__ void wave_sync_lds() {
 }
 
 // Chi at coordinate t in [0, 1) of a table cell (sb: sub-cells per octave, emin:
-// the lowest octave; cell 0 is linear in chi below 2^emin), the four Chebyshev nodes of a cell
+// the lowest octave; the `low` cells before it, a power of two of them, are even
+// in chi below 2^emin), the four Chebyshev nodes of a cell
 // and the monomial coefficients l[0..3] of the Lagrange polynomial of node m
 // (a cubic through the node values v_m is sum_m v_m l_m(t)).
-__device__ __forceinline__ double cell_chi(int cell, double t, int sb, int emin) {
-    if (cell == 0) return ldexp(t, emin);
-    const int c = cell - 1;
+__device__ __forceinline__ double cell_chi(int cell, double t, int sb, int emin, int low) {
+    if (cell < low) return ldexp(((double)cell + t) / (double)low, emin);
+    const int c = cell - low;
     const int e = emin + (c >> sb);
     const int sub = c & ((1 << sb) - 1);
     return ldexp(1.0 + ((double)sub + t) / (double)(1 << sb), e);
@@ -264,7 +268,7 @@ struct TabWindow {
         } else {
             double q[4 * F];
 #pragma unroll
-            for (int e = 0; e < 4 * F; ++e) q[e] = p[(size_t)c * (4 * F) + e];
+            for (int e = 0; e < 4 * F; ++e) q[e] = p[(size_t)min(c, kCells64 - 1) * (4 * F) + e];
             if constexpr (F == 4) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {

@@ -21,25 +21,28 @@ constexpr int kEMax = 7;
 constexpr int kSB32 = 4;  // FP32 table: 16 sub-cells per octave (LDS resident)
 constexpr int kSB64 = 6;  // FP64 table: 64 sub-cells per octave (global)
 constexpr int kCells32 = 1 + (kEMax - kEMin + 1) * (1 << kSB32);
-// The FP64 tables begin at 2^kEMin64: below it one cubic is within 1.6e-13 of g
-// and 2.3e-12 of the other combinations (5.1e-12 of chi h'), less than the cells
-// above 2^-4 (up to 3e-11 and 7e-11).
+// The octaves of the FP64 tables begin at 2^kEMin64; below it lie kLow64 even cells.
+// A cubic over [0, 2^-12) would be off by 1.5e-13 (g) to 5e-12 (chi h'), which
+// falls with the fourth power of the cell: over its sixteenth parts the cubics are at
+// the rounding of their nodes, as 64 cells an octave down to 2^-20 are, which would
+// take 512 cells of the windows below instead of 16.
 constexpr int kEMin64 = -12;
-constexpr int kCells64 = 1 + (kEMax - kEMin64 + 1) * (1 << kSB64);
+constexpr int kLow64 = 16;
+constexpr int kCells64 = kLow64 + (kEMax - kEMin64 + 1) * (1 << kSB64);
 constexpr int kCellVals = 16;
 // Cells of the FP64 table held in LDS (128 bytes each; a block takes a CU's LDS):
-// chi below 178 in FP64 passes, below 18 beside the FP32 table in passes with
+// chi below 192 in FP64 passes, below 19.75 beside the FP32 table in passes with
 // FP64 steps.
-constexpr int kWin64 = 1248;
-constexpr int kWinMix = 1040;
-// The derivative passes: the derivative table (192 bytes a cell) below chi 1.9, or
-// the forward table beside the FP32 derivative table below 4.6.
-constexpr int kWinDeriv64 = 832;
-constexpr int kWinDerivMix = 912;
-// The photon pass, beside the emission grid: chi below 9.2 in FP64 passes; with
+constexpr int kWin64 = kLow64 + 1248;
+constexpr int kWinMix = kLow64 + 1039;
+// The derivative passes: the derivative table (192 bytes a cell) below chi 2, or
+// the forward table beside the FP32 derivative table below 5.
+constexpr int kWinDeriv64 = kLow64 + 832;
+constexpr int kWinDerivMix = kLow64 + 912;
+// The photon pass, beside the emission grid: chi below 10 in FP64 passes; with
 // FP64 steps 7 octaves from the one below the threshold on (0.03 to 4 at 0.1),
 // where those steps' stages mostly lie.
-constexpr int kWinPhot64 = 976;
+constexpr int kWinPhot64 = kLow64 + 976;
 constexpr int kWinPhotMix = 440;
 // Derivative tables (adjoint): six functions per cell, in the order g,
 // chi g', chi^2 g'', h, chi^3 g''', chi h'; FP32 function-major

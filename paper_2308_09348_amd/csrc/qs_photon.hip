@@ -223,7 +223,7 @@ __global__ void ph_cell_kernel(const double *phtab, float *cells) {
     if (cell >= kCells32) return;
     double coef[4] = {0.0, 0.0, 0.0, 0.0};
     for (int m = 0; m < 4; ++m) {
-        const double v = ph_total64(phtab, cell_chi(cell, cheb_node(m), kSB32, kEMin));
+        const double v = ph_total64(phtab, cell_chi(cell, cheb_node(m), kSB32, kEMin, 1));
         double l[4];
         cheb_basis(m, l);
         for (int k = 0; k < 4; ++k) coef[k] = fma(v, l[k], coef[k]);
@@ -751,7 +751,7 @@ __global__ __launch_bounds__(phot_block(PREC, QUANTUM)) __attribute__((amdgpu_wa
         else if constexpr (kMix) {
             // from the octave below the threshold on
             const int e = min(max(ilogbf(fmaxf(P.chi_fp64, 1e-30f)) - 1, kEMin64), kEMax - 6);
-            return Tab(win, P.rad64, 1 + ((e - kEMin64) << kSB64));
+            return Tab(win, P.rad64, kLow64 + ((e - kEMin64) << kSB64));
         } else {
             return Tab(win, P.rad64);
         }

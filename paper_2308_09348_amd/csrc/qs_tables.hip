@@ -80,7 +80,8 @@ __global__ void rad_node_kernel(const double *yf, double *vals) {
     const int cell_all = node >> 2, m = node & 3;
     const bool t32 = cell_all < kCells32;
     const int cell = t32 ? cell_all : cell_all - kCells32;
-    const double chi = cell_chi(cell, cheb_node(m), t32 ? kSB32 : kSB64, t32 ? kEMin : kEMin64);
+    const double chi = t32 ? cell_chi(cell, cheb_node(m), kSB32, kEMin, 1)
+                           : cell_chi(cell, cheb_node(m), kSB64, kEMin64, kLow64);
     double I0 = 0, I1 = 0, I2 = 0, I3 = 0, J0 = 0, J1 = 0;
     for (int i = 0; i < kNY; ++i) {
         const double y = exp(kVLo + i * kDv);
@@ -132,17 +133,6 @@ __global__ void rad_coef_kernel(const double *vals, float *rad32, double *rad64,
             for (int k = 0; k < 4; ++k) coef[f][k] += v * l[k];
         }
     }
-    if (cell_all == kCells32) {
-        // FP64 cell 0: in the coordinate t of cell 1, chi / 2^kEMin64 = 1 + t / 64
-        constexpr double r = 1.0 / (1 << kSB64);
-        for (int f = 0; f < kNodeVals; ++f) {
-            const double a0 = coef[f][0], a1 = coef[f][1], a2 = coef[f][2], a3 = coef[f][3];
-            coef[f][0] = a0 + a1 + a2 + a3;
-            coef[f][1] = (a1 + 2.0 * a2 + 3.0 * a3) * r;
-            coef[f][2] = (a2 + 3.0 * a3) * r * r;
-            coef[f][3] = a3 * r * r * r;
-        }
-    }
     if (cell_all < kCells32) {
         // function-major: rad32[(f * kCells32 + cell) * 4 + power], the drift
         // combinations g, 2g + chi g', g + 2 chi g' + chi^2 g''/2, h
@@ -183,7 +173,7 @@ __global__ void rad_eval_kernel(const float *rad32, const double *rad64, int pre
         out[4 * k + 3] = h;
     } else {
         double g, G1, G2, h, t;
-        const int c = rad_index64(chi[k], t);
+        const int c = min(rad_index64(chi[k], t), kCells64 - 1);
         rad_cell_eval64(rad64 + (size_t)c * kCellVals, t, g, G1, G2, h);
         out[4 * k] = g;
         out[4 * k + 1] = G1;

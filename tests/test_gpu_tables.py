@@ -1,6 +1,8 @@
 """The radiation-function tables as the FP64 steps read them: each kernel with
 FP64 steps holds a window of a table in LDS and reads the cells outside it from
 memory; qs_radiation_eval evaluates the forward table in memory."""
+import math
+
 import numpy as np
 import pytest
 
@@ -82,3 +84,52 @@ def test_steps_use_the_evaluated_table(gpu, precision, chi64):
         assert np.abs(got[1] / s2 - 1.0).max() <= 2e-12
     loss = gpu.photons(p)["energy"].cpu().numpy()[1]
     assert abs(loss / (g0 - mu).sum() - 1.0) <= 2e-12
+
+
+def _small_chi(chi, terms=9):
+    """The functions of the derivative table (g and h with their derivatives) by
+    their expansions in chi: with s = 3 chi y / 2,
+      g = (9 sqrt3 / 8 pi) Int y   (1+s)^-3 F dy,
+      h = (81 / 55 pi)     Int y^2 (1+s)^-4 F dy,
+      F = (1/(1+s) + 1 + s) K_2/3(y) - Int_y K_1/3,
+    the binomials expanded in s and the integrals by
+    Int y^m K_nu dy = 2^(m-1) Gamma((m+1+nu)/2) Gamma((m+1-nu)/2)."""
+    def k_moment(m, nu):
+        return 2.0 ** (m - 1) * math.gamma((m + 1 + nu) / 2) * math.gamma((m + 1 - nu) / 2)
+
+    def binomial(a, n):
+        return math.prod((a - i) / (i + 1) for i in range(n))
+
+    def series(power, q):
+        return np.array([1.5 ** n * ((binomial(-q - 1, n) + binomial(-q + 1, n))
+                                     * k_moment(power + n, 2 / 3)
+                                     - binomial(-q, n) * k_moment(power + n + 1, 1 / 3)
+                                     / (power + n + 1)) for n in range(terms)])
+
+    g = 9.0 * math.sqrt(3.0) / (8.0 * math.pi) * series(1, 3)
+    h = 81.0 / (55.0 * math.pi) * series(2, 4)
+    n = np.arange(terms)
+    x = chi[:, None] ** n
+    return np.stack([x @ g, x @ (n * g), x @ (n * (n - 1) * g), x @ h,
+                     x @ (n * (n - 1) * (n - 2) * g), x @ (n * h)])
+
+
+def test_tables_at_small_chi(gpu):
+    """The FP64 tables below chi = 2^-11 (through the even cells below 2^-12 and
+    on both sides of their ends) are at the rounding of their nodes: sums of 583
+    terms that are sums of up to 600, sqrt(583 * 600) roundings of 2^-53, times the
+    sum of the magnitudes combined (I_k = (k+1)! I_0 at small chi: 1, I_1 + 2 I_0 =
+    4, 24, 192; J_1 + 3 J_0 = 6).  (One cubic over [0, 2^-12) is off by 1.5e-13,
+    6.2e-13, 1.8e-12, 1.3e-12 of g, chi g', chi^2 g'', h and by 5.1e-12 of chi h'.)"""
+    import torch
+    edges = np.arange(1, 17) * 2.0 ** -16
+    chi = np.concatenate([np.exp(np.linspace(math.log(1e-9), math.log(2.0 ** -11), 997)),
+                          edges * (1 - 2.0 ** -50), edges, edges * (1 + 2.0 ** -50)])
+    ref = _small_chi(chi)
+    tol = math.sqrt(583 * 600) * 2.0 ** -53 * np.array([1.0, 4.0, 24.0, 1.0, 192.0, 6.0])
+    err = np.abs(_eval(gpu, chi) - ref[:4]).max(axis=1)
+    assert np.all(err <= tol[:4]), err
+    d = gpu.radiation_derivs(torch.tensor(chi, device="cuda"), "fp64").cpu().numpy().T
+    err = np.abs(d - ref).max(axis=1)
+    assert np.all(err <= tol), err
+    assert np.array_equal(d[:4], _eval(gpu, chi))
