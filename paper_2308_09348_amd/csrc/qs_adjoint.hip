@@ -80,7 +80,7 @@ __device__ __forceinline__ void rad6_cell_eval64(const double *q, double t,
 __device__ __forceinline__ void rad6_plain64(const double *__restrict__ tab, double chi,
                                              double v[kDerivFuncs]) {
     double t;
-    const int c = min(rad_index64(chi, t), kCells64 - 1);
+    const uint32_t c = min(rad_index64(chi, t), (uint32_t)kCells64 - 1);
     rad6_cell_eval64(tab + (size_t)c * (4 * kDerivFuncs), t, v);
 }
 

@@ -163,14 +163,15 @@ __device__ __forceinline__ void rad_cell_eval(const RadCell32 &cell, float chi, 
     hq = fmaf(t, fmaf(t, fmaf(t, cell.q3.w, cell.q3.z), cell.q3.y), cell.q3.x);
 }
 
-// FP64 cell of chi and the coordinate t in the cell (chi beyond the table gives a
-// cell past the last one, to be clamped to that; reported by the caller).
+// FP64 cell of chi and the coordinate t in the cell.  Chi outside the table (also any
+// negative chi that does not round to 0, and NaN) gives a number past the last cell, to be
+// clamped to that; it is reported by the caller.
 // All in the upper word: the cell from its top bits, t = (chi - cell start)
 // 2^(SB - e), both operations exact.  Below 2^kEMin64 the same of y = chi / 8 +
 // (7/8) 2^kEMin64, which runs evenly through the last 16 cells of the octave below
 // (above, y is less than chi): two operations on every chi, no branch and no
 // selects (an even cell index by selects of its own cost FP64 passes 10%).
-__device__ __forceinline__ int rad_index64(double chi, double &t) {
+__device__ __forceinline__ uint32_t rad_index64(double chi, double &t) {
     constexpr int kLow = 20 - kSB64;  // bits of the upper word below the cell index
     constexpr double kMin = 1.0 / (1 << -kEMin64);
     static_assert(kLow64 == 16 && kSB64 == 6, "an eighth of an octave");
@@ -179,7 +180,8 @@ __device__ __forceinline__ int rad_index64(double chi, double &t) {
     const double start = __hiloint2double((int)(hi >> kLow << kLow), 0);
     const double inv = __hiloint2double((int)((uint32_t)(2046 + kSB64) - (hi >> 20)) << 20, 0);
     t = (y - start) * inv;
-    return (int)(hi >> kLow) - ((1023 + kEMin64) << kSB64) + kLow64;
+    // (unsigned: the small y of a negative chi wraps)
+    return (hi >> kLow) - (((1023 + kEMin64) << kSB64) - kLow64);
 }
 
 __device__ __forceinline__ void rad_cell_eval64(const double *q, double t, double &g, double &G1,
@@ -256,8 +258,8 @@ struct TabWindow {
     int c0;
     __device__ __forceinline__ void eval(double chi, double v[F]) const {
         double t;
-        const int c = rad_index64(chi, t), k = BASED ? c - c0 : c;
-        if (__all((unsigned)k < (unsigned)N)) {
+        const uint32_t c = rad_index64(chi, t), k = BASED ? c - (uint32_t)c0 : c;
+        if (__all(k < (uint32_t)N)) {
             const double2 *w = win + k;
             double2 q[2 * F];
 #pragma unroll
@@ -268,7 +270,7 @@ struct TabWindow {
         } else {
             double q[4 * F];
 #pragma unroll
-            for (int e = 0; e < 4 * F; ++e) q[e] = p[(size_t)min(c, kCells64 - 1) * (4 * F) + e];
+            for (int e = 0; e < 4 * F; ++e) q[e] = p[(size_t)min(c, (uint32_t)kCells64 - 1) * (4 * F) + e];
             if constexpr (F == 4) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {

@@ -173,7 +173,7 @@ __global__ void rad_eval_kernel(const float *rad32, const double *rad64, int pre
         out[4 * k + 3] = h;
     } else {
         double g, G1, G2, h, t;
-        const int c = min(rad_index64(chi[k], t), kCells64 - 1);
+        const uint32_t c = min(rad_index64(chi[k], t), (uint32_t)kCells64 - 1);
         rad_cell_eval64(rad64 + (size_t)c * kCellVals, t, g, G1, G2, h);
         out[4 * k] = g;
         out[4 * k + 1] = G1;

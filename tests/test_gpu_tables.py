@@ -133,3 +133,28 @@ def test_tables_at_small_chi(gpu):
     err = np.abs(d - ref).max(axis=1)
     assert np.all(err <= tol), err
     assert np.array_equal(d[:4], _eval(gpu, chi))
+
+
+def test_negative_chi_stays_in_the_table(gpu):
+    """Steps too coarse for the field drive the energy through zero, and chi of the
+    next stages below it by any amount: such chi takes the last cell (or cell 0
+    where it rounds to 0), by itself and in every pass with FP64 steps, and the
+    next call on the context gives what it gave before."""
+    import torch
+    from paper_2308_09348_amd import _lib
+    chi = np.concatenate([-2.0 ** np.arange(-60.0, 9.0), [-0.0]])
+    assert np.isfinite(_eval(gpu, chi)).all()
+    d = gpu.radiation_derivs(torch.tensor(chi, device="cuda"), "fp64").cpu().numpy()
+    assert np.isfinite(d).all()
+    good = dict(workloads.quantum_batch(n_shots=1)[0], n_samples=700, n_steps=256)
+    for precision, chi64 in (("fp64", 0.0), ("fp32", 0.1)):
+        q = dict(good, precision=precision, chi_fp64=chi64)
+        p = dict(q, n_steps=16)
+        ref = gpu.forward(q)["energy_hist"].clone()
+        for run in (lambda: gpu.forward(p, check=False),
+                    lambda: gpu.forward(p, tape=gpu.new_tape(p["n_samples"]), check=False),
+                    lambda: gpu.photons(p, check=False, angles=True)):
+            print("negative chi:", precision, chi64, flush=True)
+            status = run()["status"].item()
+            assert status in (_lib.QS_OK, _lib.QS_ENONFINITE, _lib.QS_ERANGE)
+            assert torch.equal(gpu.forward(q)["energy_hist"], ref)
