@@ -1127,48 +1127,53 @@ __global__ __launch_bounds__(kSetupBlock) void setup_kernel(
 // of a quantum shot, 2048 steps, 15.0 -> 6.4 ms), and the pass keeps no LDS for
 // it.  28 us for 128 groups, 110 us for 1024.
 constexpr int kOrderBlock = kChiGroup / 2;
+// Most blocks of a launch, which take group after group (2^36 samples are 2^25
+// groups or more; a grid holds less than 2^32 threads).
+constexpr int kOrderGrid = 4096;
 
 __global__ __launch_bounds__(kOrderBlock) void order_kernel(BatchParams P) {
     __shared__ unsigned long long w[kChiGroup];
-    const int64_t group = blockIdx.x;
-    const int s = __builtin_amdgcn_readfirstlane(find_group_shot(P.shots, P.n_shots, group));
-    const ShotParams &sp = P.shots[s];
-    const int64_t base = (group - sp.gitem0) * kChiGroup;
-    const int cnt = (int)min((int64_t)kChiGroup, sp.n_samples - base);
-    int m = 64;  // words sorted
-    while (m < cnt) m <<= 1;
-    for (int q = threadIdx.x; q < m; q += kOrderBlock) {
-        uint32_t key = 0xffffffffu;  // past the samples
-        if (q < cnt) {
-            double g0, thx, thy, S0;
-            Path<double, false> pd{};
-            draw_sample<false>(sp, P.key0, P.key1, base + q, g0, thx, thy, pd, S0);
-            // the float's bits in increasing order (+0: one zero)
-            const uint32_t b = __float_as_uint((float)(S0 * g0) + 0.0f);
-            key = b & 0x80000000u ? ~b : b | 0x80000000u;
+    for (int64_t group = blockIdx.x; group < P.n_gitems; group += gridDim.x) {
+        const int s = __builtin_amdgcn_readfirstlane(find_group_shot(P.shots, P.n_shots, group));
+        const ShotParams &sp = P.shots[s];
+        const int64_t base = (group - sp.gitem0) * kChiGroup;
+        const int cnt = (int)min((int64_t)kChiGroup, sp.n_samples - base);
+        int m = 64;  // words sorted
+        while (m < cnt) m <<= 1;
+        __syncthreads();  // the previous group's words have been read
+        for (int q = threadIdx.x; q < m; q += kOrderBlock) {
+            uint32_t key = 0xffffffffu;  // past the samples
+            if (q < cnt) {
+                double g0, thx, thy, S0;
+                Path<double, false> pd{};
+                draw_sample<false>(sp, P.key0, P.key1, base + q, g0, thx, thy, pd, S0);
+                // the float's bits in increasing order (+0: one zero)
+                const uint32_t b = __float_as_uint((float)(S0 * g0) + 0.0f);
+                key = b & 0x80000000u ? ~b : b | 0x80000000u;
+            }
+            w[q] = ((unsigned long long)key << 32) | (unsigned int)q;
         }
-        w[q] = ((unsigned long long)key << 32) | (unsigned int)q;
-    }
-    __syncthreads();
-    for (int k = 2; k <= m; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            // pairs at most 64 apart stay within the 128 words of a wavefront
-            if (j >= 64)
-                __syncthreads();
-            else
-                wave_sync_lds();
-            if (threadIdx.x < m / 2) {
-                const int t = (int)threadIdx.x, a = ((t & -j) << 1) | (t & (j - 1)), b = a + j;
-                const unsigned long long x = w[a], y = w[b];
-                if ((x > y) == ((a & k) == 0)) {
-                    w[a] = y;
-                    w[b] = x;
+        __syncthreads();
+        for (int k = 2; k <= m; k <<= 1)
+            for (int j = k >> 1; j > 0; j >>= 1) {
+                // pairs at most 64 apart stay within the 128 words of a wavefront
+                if (j >= 64)
+                    __syncthreads();
+                else
+                    wave_sync_lds();
+                if (threadIdx.x < m / 2) {
+                    const int t = (int)threadIdx.x, a = ((t & -j) << 1) | (t & (j - 1)), b = a + j;
+                    const unsigned long long x = w[a], y = w[b];
+                    if ((x > y) == ((a & k) == 0)) {
+                        w[a] = y;
+                        w[b] = x;
+                    }
                 }
             }
-        }
-    __syncthreads();
-    for (int q = threadIdx.x; q < cnt; q += kOrderBlock)
-        P.order[sp.state_off + base + q] = (uint16_t)w[q];
+        __syncthreads();
+        for (int q = threadIdx.x; q < cnt; q += kOrderBlock)
+            P.order[sp.state_off + base + q] = (uint16_t)w[q];
+    }
 }
 
 // ===========================================================================
@@ -1193,8 +1198,7 @@ hipError_t launch_setup(const SetupTab *tab, size_t tab_bytes, unsigned char *sh
 
 hipError_t launch_order(const BatchParams &p, hipStream_t s) {
     if (p.n_gitems < 1) return hipSuccess;
-    if (p.n_gitems > (int64_t)INT_MAX) return hipErrorInvalidValue;  // (2^36 samples: 2^25)
-    order_kernel<<<(unsigned)p.n_gitems, kOrderBlock, 0, s>>>(p);
+    order_kernel<<<(unsigned)std::min(p.n_gitems, (int64_t)kOrderGrid), kOrderBlock, 0, s>>>(p);
     return hipGetLastError();
 }
 

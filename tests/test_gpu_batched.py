@@ -102,3 +102,18 @@ def test_fp64_table_window_of_a_batch(gpu, precision, chi64, amp):
         assert single["energy_hist"].sum() == p["n_samples"]
         for key in ("energy_hist", "angle_hist", "a0eff_hist", "moments", "status"):
             assert np.array_equal(batch[k][key], single[key]), (k, key)
+
+
+def test_more_groups_than_blocks_order_them(gpu):
+    """The chi order of passes with FP64 steps is formed by at most 4096 blocks,
+    each taking every 4096th group: shots of a batch of more groups than that (one
+    a shot, after a batch of larger ones, so that an entry that was not written
+    anew names another sample) have every sample once, as alone."""
+    base = dict(workloads.quantum_batch(n_shots=1)[0], n_steps=256, n_e=64, n_th=16, n_a=16)
+    gpu.forward(dict(base, n_samples=20000))
+    shots = [dict(base, n_samples=3, shot=k) for k in range(4103)]
+    batch = gpu.forward_batched(shots)
+    for k in (0, 1, 4095, 4096, 4102):
+        single = gpu.forward(dict(base, n_samples=3, shot=k))
+        for key in ("energy_hist", "angle_hist", "a0eff_hist", "moments"):
+            assert np.array_equal(batch[k][key].cpu().numpy(), single[key].cpu().numpy()), (k, key)
