@@ -839,8 +839,8 @@ __global__ __launch_bounds__(phot_block(PREC, QUANTUM)) __attribute__((amdgpu_wa
 constexpr int kPhEdges = 8;  // edges a block
 
 __global__ __launch_bounds__(256) void photon_spectrum_kernel(BatchParams P) {
-    const ShotPhot &pp = P.phot[blockIdx.y];
-    const int n_edges = pp.n_ph + 2, e0 = blockIdx.x * kPhEdges;
+    const ShotPhot &pp = P.phot[blockIdx.x];  // (up to 2^20 shots: not in y)
+    const int n_edges = pp.n_ph + 2, e0 = blockIdx.y * kPhEdges;
     if (e0 >= n_edges) return;
     // the grid with an empty column on either side; the rows' cube roots
     __shared__ double G[kPhNU * (kPhNV + 2)];
@@ -1062,7 +1062,7 @@ hipError_t launch_photon(const BatchParams &p, const float *env32, const double 
 
 hipError_t launch_photon_finalize(const BatchParams &p, int max_edges, double c_ph,
                                   hipStream_t s) {
-    photon_spectrum_kernel<<<dim3((max_edges + kPhEdges - 1) / kPhEdges, p.n_shots), 256, 0, s>>>(p);
+    photon_spectrum_kernel<<<dim3(p.n_shots, (max_edges + kPhEdges - 1) / kPhEdges), 256, 0, s>>>(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     photon_finalize_kernel<<<p.n_shots, kPhFinBlock, 0, s>>>(p, c_ph);

@@ -287,3 +287,15 @@ def test_photon_edges_merge(gpu, n_ph):
                              n_ph=7 * n_ph)))["photon_hist"]
     merged = np.concatenate([f[:7 * n_ph].reshape(n_ph, 7).sum(1), f[7 * n_ph:]])
     assert np.all(np.abs(g - merged) <= 1e-12 * g.sum()), np.abs(g - merged).max() / g.sum()
+
+
+def test_more_shots_than_a_grid_has_rows(gpu):
+    """The device reports no more than 2^16 blocks along a grid's second axis: the
+    spectra of a batch of more shots than that are the shots' own."""
+    p = dict(workloads.scaled(workloads.focused_3d(), n_samples=1, n_steps=64),
+             n_ph=8, ph_lo=0.0, ph_hi=2400.0)
+    outs = gpu.photons_batched([p] * 65540, check=False)
+    for k in (0, 1, 65534, 65535, 65536, 65539):
+        single = gpu.photons(dict(p, shot=p["shot"] + k))
+        for key in ("photon_hist", "energy", "status"):
+            assert np.array_equal(outs[k][key].cpu().numpy(), single[key].cpu().numpy()), (k, key)
