@@ -567,7 +567,8 @@ qs_status qs_timings_sum(qs_ctx *ctx, int32_t *n_calls, double *ms);
  * changes a result bit: moment partial sums are kept per tile of 1024
  * samples whatever the deposit tile. */
 typedef struct qs_tuning {
-    int32_t dep_tile;    /* samples of one deposit work item: 1024 .. 8192      */
+    int32_t dep_tile;    /* samples of one deposit work item: 1024 .. 8192 (1024:
+                            256 or 512 in launches of few samples, see qs_tune) */
     int32_t phase_cap;   /* resident phase blocks per compute unit at most; 0 =
                             as many as fit                                    */
     int32_t dep_cap;     /* the same for the deposit kernel                     */
@@ -592,8 +593,9 @@ typedef struct qs_tuning {
  * keyed by the device (architecture and compute-unit count) and the class.
  * A cache line for this device and class is used instead of timing.  `out`
  * (host, optional) receives the choice.  Blocks until the trial launches
- * end; allocates its own trial outputs.  Launches of other classes keep the
- * defaults (deposit tile 4096, all resident blocks).
+ * end; allocates its own trial outputs.  A deposit tile of 1024 is that of
+ * launches of other classes too: 1024 samples a work item, 512 or 256 where the
+ * launch has fewer than 2^19 or 2^18 samples; they take all resident blocks.
  * Errors: QS_EINVAL (as qs_forward_batched; a cache file that cannot be
  * appended to), QS_EUNSUPPORTED, QS_ENOMEM, QS_EDEVICE. */
 qs_status qs_tune(qs_ctx *ctx, int32_t n_shots, const qs_laser *lasers, const qs_beam *beams,

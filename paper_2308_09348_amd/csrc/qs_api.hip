@@ -837,9 +837,9 @@ const TuneEntry *find_tune(const qs_ctx *c, const TuneKey &k) {
     return nullptr;
 }
 
-// The deposit work item of launches without a tuned choice: 1024 samples, and
-// for small launches as few as leave about 512 items, so that they spread over
-// the device (256 CUs).  Measured on focused laws, items of 256 / 512 / 1024 /
+// The deposit work item of launches without a tuned choice or tuned to kDepTile:
+// 1024 samples, and for small launches as few as leave about 512 items, so that
+// they spread over the device (256 CUs).  Measured on focused laws, items of 256 / 512 / 1024 /
 // 4096 samples: 5003 samples 39 / 68 / 120 / 441 us, 50,001 51 / 71 / 121 / 445 us,
 // 2^18 123 / 104 / 132 / 443 us, 2^20 364 / 260 / 215 / 449 us, 2^22 1329 / 772 /
 // 592 / 684 us, 128 shots of 2^12 .. 2^18 1205 / 1129 / 1175 / 1439 us, 1500 shots
@@ -904,7 +904,7 @@ qs_status prepare_batch(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_
     bp.c_theta = N->c_theta;
     // launch choices of this launch class (qs_tune), else the defaults
     const TuneEntry *tune = find_tune(c, tune_key(N, b.prec, b.max_nh, b.total, n_shots));
-    bp.dep_tile = tune ? tune->dep_tile : default_dep_tile(b.total);
+    bp.dep_tile = tune && tune->dep_tile != qs::kDepTile ? tune->dep_tile : default_dep_tile(b.total);
     bp.mom_row = bp.dep_tile < qs::kMomTile ? qs::kMomRow : qs::kMomTile;
     bp.phase_cap = tune ? tune->phase_cap : 0;
     bp.dep_cap = tune ? tune->dep_cap : 0;
@@ -1841,6 +1841,9 @@ bool read_tune_cache(const char *path, const std::string &tag, const TuneKey &ke
 // the profiling events around the phase and deposit kernels; keeps the
 // fastest, installs it for launches of the same class and appends it to the
 // cache file.  Every candidate gives the same results (moment tiles are fixed).
+// The tile kDepTile stands for default_dep_tile, so that the choice of an untuned
+// launch is among the candidates at every size (5003 samples tuned to items of
+// 1024 themselves: deposit 120 us, untuned 39).
 qs_status tune_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_beam *B,
                     const int64_t *n_samples, const qs_numerics *N, const qs_bins *H,
                     const char *path, qs_tuning *out, hipStream_t s) {
@@ -1956,7 +1959,7 @@ qs_status tune_impl(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_beam
             best.phase_cap = pcap;
         }
     }
-    for (int tile : {1024, 2048, 4096, 8192}) {
+    for (int tile : {qs::kDepTile, 2048, 4096, 8192}) {
         for (int dcap : {0, 4, 2}) {
             TuneEntry t = best;
             t.dep_tile = tile;
