@@ -268,19 +268,28 @@ struct TabWindow {
             for (int f = 0; f < F; ++f)
                 v[f] = fma(t, fma(t, fma(t, q[2 * f + 1].y, q[2 * f + 1].x), q[2 * f].y), q[2 * f].x);
         } else {
-            double q[4 * F];
+            // (two powers at a time: with a whole cell's 4 F coefficients at once in
+            // registers the mixed tape pass spilled more: eight shots of 2^18 x 2048
+            // steps 68.1 ms, 65.6 so)
+            const double *cell = p + (size_t)min(c, (uint32_t)kCells64 - 1) * (4 * F);
 #pragma unroll
-            for (int e = 0; e < 4 * F; ++e) q[e] = p[(size_t)min(c, (uint32_t)kCells64 - 1) * (4 * F) + e];
-            if constexpr (F == 4) {
+            for (int e = 2; e >= 0; e -= 2) {
+                double q[2][F];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    q[8 + e] = drift_mix3(q[e], q[4 + e], q[8 + e]);
-                    q[4 + e] = drift_mix2(q[e], q[4 + e]);
+                for (int k = 0; k < 2; ++k) {
+#pragma unroll
+                    for (int f = 0; f < F; ++f) q[k][f] = cell[4 * f + e + k];
+                    if constexpr (F == 4) {
+                        q[k][2] = drift_mix3(q[k][0], q[k][1], q[k][2]);
+                        q[k][1] = drift_mix2(q[k][0], q[k][1]);
+                    }
                 }
-            }
 #pragma unroll
-            for (int f = 0; f < F; ++f)
-                v[f] = fma(t, fma(t, fma(t, q[4 * f + 3], q[4 * f + 2]), q[4 * f + 1]), q[4 * f]);
+                for (int f = 0; f < F; ++f)
+                    v[f] = e == 2 ? fma(t, q[1][f], q[0][f])
+                                  : fma(t, fma(t, v[f], q[1][f]), q[0][f]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     }
     // filled by all threads of the block; a barrier must follow
