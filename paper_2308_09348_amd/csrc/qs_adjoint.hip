@@ -368,8 +368,8 @@ __device__ __forceinline__ SpD<float> spatial_d(float x, float y, float z, float
 __device__ __forceinline__ SpD<double> spatial_d(double x, double y, double z, double inv_w0sq,
                                                  double inv_zR, double inv_w0) {
     const double zz = z * inv_zR;
-    const double rq = inv_sqrt64(fma(zz, zz, 1.0));
-    const double iq = rq * rq;
+    double iq;
+    const double rq = inv_sqrt64(fma(zz, zz, 1.0), iq);
     const double p = fma(x, x, y * y) * inv_w0sq * iq;
     SpD<double> r;
     r.S = exp64(-p) * rq;

@@ -329,23 +329,31 @@ struct Phys {
     T K, CD, two_over_aS;
 };
 
-// 1/sqrt(q) for q >= 1: the hardware estimate (about 2^-24) and one step of third
-// order, within an ulp (q beyond 1e300 counts as 1e300, the factor it gives as 0).
-__device__ __forceinline__ double inv_sqrt64(double q) {
+// 1/sqrt(q) and iq = 1/q for q >= 1, from the hardware's estimate y of the root
+// (about 2^-24): with e = 1 - q y^2, q^-1/2 = y (1 + e/2 + 3 e^2/8 + ..) and 1/q =
+// y^2 (1 + e + e^2 + ..), each within an ulp (the square of the rounded root has
+// two).  q beyond 1e300 counts as 1e300, the factor it gives as 0.
+__device__ __forceinline__ double inv_sqrt64(double q, double &iq) {
     q = fmin(q, 1e300);
-    const double y = __builtin_amdgcn_rsq(q);
-    const double e = fma(-q * y, y, 1.0);
+    const double y = __builtin_amdgcn_rsq(q), y2 = y * y;
+    const double e = fma(-q, y2, 1.0);
+    iq = fma(y2, fma(e, e, e), y2);
     return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-// e^x for x < 700 (0 below -800): x = k ln 2 + r, |r| <= ln 2 / 2, the Taylor
-// polynomial of degree 12 (remainder 1.7e-16 relative), scaled by 2^k.
+// e^x for x < 700 (0 below -800): x = k ln 2 + r, |r| <= ln 2 / 2, ln 2 in two parts
+// of which the upper has 33 bits, so that k times it is exact (Cody and Waite's
+// reduction, with the parts of fdlibm's e_exp.c), then the Taylor polynomial of
+// degree 12, scaled by 2^k.  Of the remainder, r^13 / 13!, the share 0.955 (ln 2 / 2)^2
+// r^11 / 13! goes into the eleventh coefficient, which leaves 8e-18 of it (1.7e-16
+// at the ends without): over [-20, 0] within 1.45e-16 of e^x, rms 4.9e-17 (3.5e-16,
+// 6.1e-17).
 __device__ __forceinline__ double exp64(double x) {
     x = fmax(x, -800.0);
     const double k = rint(x * 1.44269504088896340736);
     const double r = fma(-k, 1.9082149292705877e-10, fma(-k, 0.693147180369123816490, x));
     double p = 1.0 / 479001600.0;
-    p = fma(p, r, 1.0 / 39916800.0);
+    p = fma(p, r, 1.0 / 39916800.0 + 0.955 * 0.120113253 / 6227020800.0);
     p = fma(p, r, 1.0 / 3628800.0);
     p = fma(p, r, 1.0 / 362880.0);
     p = fma(p, r, 1.0 / 40320.0);
@@ -374,9 +382,10 @@ __device__ __forceinline__ float spatial(float x, float y, float z, float inv_w0
 __device__ __forceinline__ double spatial(double x, double y, double z, double inv_w0sq,
                                           double inv_zR) {
     const double zz = z * inv_zR;
-    const double rq = inv_sqrt64(fma(zz, zz, 1.0));  // 1/sqrt(q); 1/q = rq^2
+    double iq;
+    const double rq = inv_sqrt64(fma(zz, zz, 1.0), iq);
     const double r2 = fma(x, x, y * y) * inv_w0sq;
-    return exp64(-r2 * (rq * rq)) * rq;
+    return exp64(-r2 * iq) * rq;
 }
 
 // Higher transverse modes (amplitude only, peak 1 in the focal plane): with
