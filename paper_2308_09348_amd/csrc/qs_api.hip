@@ -12,6 +12,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <mutex>
 #include <new>
 #include <string>
@@ -944,6 +945,11 @@ qs_status prepare_batch(qs_ctx *c, int32_t n_shots, const qs_laser *L, const qs_
         p.a0 = l.a0;
         p.inv_w0sq = plane_wave ? 0.0 : 1.0 / (l.w0_um * l.w0_um);
         p.inv_zR = plane_wave ? 0.0 : l.lambda_um / (kPi * l.w0_um * l.w0_um);
+        // a focus so small that these overflow has no spatial factor (0 times them
+        // is no number, which the FP64 factor's clamps would take for 0): an
+        // amplitude that is none either, so that every sample is reported
+        if (!std::isfinite(p.inv_w0sq) || !std::isfinite(p.inv_zR))
+            p.a0 = std::numeric_limits<double>::quiet_NaN();
         p.x_off = l.x_off_um;
         p.y_off = l.y_off_um;
         p.z_delay = 0.5 * kC_um_per_fs * l.delay_fs;

@@ -51,3 +51,15 @@ def test_rounding(gpu):
     rms = float(np.sqrt(np.mean(err ** 2)))
     print("rms", rms, "largest", err.max())
     assert rms < 3.5e-16
+
+
+@pytest.mark.parametrize("model", ["classical", "quantum"])
+def test_nan_is_reported(gpu, model):
+    """w0 = 1e-160 um: 1 / w0^2 overflows, and on the axis 0 times it is no
+    number; the pass reports it rather than a factor of 0."""
+    import paper_2308_09348_amd as qs
+    from paper_2308_09348_amd import _lib
+    with pytest.raises(qs.QScatterError) as e:
+        gpu.forward(_point(w0_um=1e-160, rr_model=model))
+    assert e.value.status == _lib.QS_ENONFINITE
+    assert gpu.forward(_point(rr_model=model))["energy_hist"].sum().item() == 1.0
