@@ -598,11 +598,12 @@ struct AmpFactors {
 };
 using AmpQ = AmpFactors<float>;
 
+// x: dmu/dpsi over nu.
 template <class T>
 __device__ __forceinline__ void rhs_quantum(T mu, T s2, const AmpFactors<T> &A, T T1, T T2, T T3,
-                                            T T4, T &dmu, T &ds2) {
+                                            T T4, T &x, T &ds2) {
     const T mu2 = mu * mu;
-    dmu = A.nu * fma(mu2, T1, s2 * T3);
+    x = fma(mu2, T1, s2 * T3);
     ds2 = fma(A.nu2 * mu * s2, T2, A.cd * (mu2 * mu2) * T4);
 }
 
@@ -620,7 +621,9 @@ __device__ __forceinline__ void rk4_q64(double mu, double s2, AmpFactors<double>
         chi_hi = fmax(chi_hi, chi);
         double T[4];
         tab.eval(chi, T);
-        rhs_quantum(m, s, A, T[0], T[1], T[2], T[3], km, ks);
+        double x;
+        rhs_quantum(m, s, A, T[0], T[1], T[2], T[3], x, ks);
+        km = A.nu * x;
     };
     stage(mu, s2, A1, k1m, k1s);
     const AmpFactors<double> Ah(ah, ph);
@@ -637,55 +640,81 @@ __device__ __forceinline__ void rk4_q64(double mu, double s2, AmpFactors<double>
 // stage 2 and stage 4 read LDS, stage 3 reuses stage 2's cell, and stage 4's
 // cell is handed to the next step's stage 1 (with its amplitude factors).
 // Ah, A4: the factors at psi_j + h/2 and psi_j + h (A1 is replaced by A4).
-// ROUND: the sum k2 + k3 of the energy takes both rounded, where the compiler
-// would fuse k2's last product into it (see phase_pair_kernel).
-template <bool ROUND = false>
+// The increments are h6 dm and h6 ds, h6 = h/6.  Products that are added to
+// something are fused here by name, not as the compiler finds them: it does so
+// within a block of code, and the kernels that share this step divide it
+// differently.  ROUND: the sum k2 + k3 of the energy takes both rounded, else the
+// product of k2 unrounded (see q32_steps).
+template <bool ROUND>
 __device__ __forceinline__ void rk4_q32(float mu, float s2, AmpQ &A1, const AmpQ &Ah,
                                         const AmpQ &A4, float h, const float *__restrict__ tab,
-                                        RadCell32 &carry, float &dmu, float &ds2,
-                                        float &chi_hi) {
+                                        RadCell32 &carry, float &dm, float &ds, float &chi_hi) {
+#pragma clang fp contract(off)
     const float hh = 0.5f * h;
     float g, G1, G2, hq;
     // stage 1 (cell and amplitude factors carried from the previous stage 4)
     const float c1 = A1.cpm * mu;
     rad_cell_eval(carry, c1, g, G1, G2, hq);
-    float k1m, k1s;
-    rhs_quantum(mu, s2, A1, g, G1, G2, hq, k1m, k1s);
+    float x1, k1s;
+    rhs_quantum(mu, s2, A1, g, G1, G2, hq, x1, k1s);
+    const float k1m = A1.nu * x1;
     // stage 2 (table read)
     const float m2 = fmaf(hh, k1m, mu), s22 = fmaf(hh, k1s, s2);
     const float c2 = Ah.cpm * m2;
     RadCell32 mid;
     rad_lookup32(tab, c2, mid);
     rad_cell_eval(mid, c2, g, G1, G2, hq);
-    float k2m, k2s;
-    rhs_quantum(m2, s22, Ah, g, G1, G2, hq, k2m, k2s);
+    float x2, k2s;
+    rhs_quantum(m2, s22, Ah, g, G1, G2, hq, x2, k2s);
     // stage 3 (same phase as stage 2: reuse its cell)
+    const float k2m = Ah.nu * x2;
     const float m3 = fmaf(hh, k2m, mu), s23 = fmaf(hh, k2s, s2);
     const float c3 = Ah.cpm * m3;
     rad_cell_eval(mid, c3, g, G1, G2, hq);
-    float k3m, k3s;
-    rhs_quantum(m3, s23, Ah, g, G1, G2, hq, k3m, k3s);
-    if constexpr (ROUND) asm("" : "+v"(k2m), "+v"(k3m));
+    float x3, k3s;
+    rhs_quantum(m3, s23, Ah, g, G1, G2, hq, x3, k3s);
+    const float k3m = Ah.nu * x3;
+    const float k23 = ROUND ? k2m + k3m : fmaf(Ah.nu, x2, k3m);
     // stage 4 (table read; its cell serves the next step's stage 1)
     A1 = A4;
     const float m4 = fmaf(h, k3m, mu), s24 = fmaf(h, k3s, s2);
     const float c4 = A1.cpm * m4;
     rad_lookup32(tab, c4, carry);
     rad_cell_eval(carry, c4, g, G1, G2, hq);
-    float k4m, k4s;
-    rhs_quantum(m4, s24, A1, g, G1, G2, hq, k4m, k4s);
+    float x4, k4s;
+    rhs_quantum(m4, s24, A1, g, G1, G2, hq, x4, k4s);
     // the range check takes the chi of the table reads: stages 1 and 3
     // evaluate the cells of stages 4 and 2 at a chi a hair away (the state
     // moved by less than one step's increment)
     chi_hi = fmaxf(chi_hi, fmaxf(c2, c4));
-    const float h6 = h * (1.0f / 6.0f);
-    dmu = h6 * (k1m + 2.0f * (k2m + k3m) + k4m);
-    ds2 = h6 * (k1s + 2.0f * (k2s + k3s) + k4s);
+    dm = fmaf(A1.nu, x4, fmaf(2.0f, k23, k1m));
+    ds = fmaf(2.0f, k2s + k3s, k1s) + k4s;
 }
 
-// Compensated accumulation: (hi, lo) += d, renormalised (Fast2Sum, |hi| >= |d|).
+// Steps j0 .. j1 - 1 (j0 even) of the FP32 quantum model with the local amplitude by
+// step(j, round): of two steps the first rounds k2 (rk4_q32), a last one does not.
+// Every kernel that takes such steps has this rule, so that a shot gives the same
+// bits in all of them; which of the two a step takes is of no account (a last bit of
+// its increment), and these are what the passes have always given.
+template <class Step>
+__device__ __forceinline__ void q32_steps(int j0, int j1, Step step) {
+    int j = j0;
+    for (; j + 1 < j1; j += 2) {
+        step(j, std::true_type{});
+        step(j + 1, std::false_type{});
+    }
+    if (j < j1) step(j, std::false_type{});
+}
+
+// Compensated accumulation: (hi, lo) += d or c d, renormalised (Fast2Sum, |hi| >= |d|).
 __device__ __forceinline__ void comp_add(float &hi, float &lo, float d) {
     const float dd = d + lo;
+    const float s = hi + dd;
+    lo = dd - (s - hi);
+    hi = s;
+}
+__device__ __forceinline__ void comp_add(float &hi, float &lo, float c, float d) {
+    const float dd = fmaf(c, d, lo);
     const float s = hi + dd;
     lo = dd - (s - hi);
     hi = s;

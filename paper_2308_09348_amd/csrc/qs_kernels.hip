@@ -238,6 +238,7 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
         // or taken into the state by the first FP64 step
         double g0_rest = (g0 - (double)mu) - (double)mu_lo;
         double chd = 0.0;
+        const float h6 = P.hf * (1.0f / 6.0f);
         float aS_prev = local ? a0f * pf.S(P.psi0f * P.ellf) : a0S0f;
         RadCell32 carry;
         AmpQ amp1;  // amplitude factors of the next stage 1
@@ -266,13 +267,31 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
                 for (int j = 0; j < N; ++j) step(j, env32[2 * j + 1], env32[2 * j + 2]);
             }
         }
-        int j = 0;
+        auto step32 = [&](int j, auto round) {
+            float aSh, aS4;
+            mid_end(j, aSh, aS4);
+            const float ah = aSh * env32[2 * j + 1];
+            const float a4 = aS4 * env32[2 * j + 2];
+            if (PREC != PREC_F32MIX) cmx = fmaxf(cmx, amp1.cpm * mu);
+            float dm, ds;
+            rk4_q32<decltype(round)::value>(mu, s2, amp1, AmpQ(ah, phf), AmpQ(a4, phf), P.hf, tab32,
+                                            carry, dm, ds, chi_hi);
+            comp_add(mu, mu_lo, h6, dm);
+            comp_add(s2, s2_lo, h6, ds);
+        };
         // two steps an iteration: the loop's bookkeeping and the moves of the
         // carried values at its back edge are halved (FP32 quantum pass 3%
         // faster; four steps no faster, with spills)
+        if constexpr (QUANTUM && PREC == PREC_F32) {
+            if constexpr (LOCAL) {
+                q32_steps(0, N, step32);
+            } else {
 #pragma clang loop unroll_count(2)
-        while (QUANTUM && j < N) {
-            if (PREC == PREC_F32MIX) {
+                for (int j = 0; j < N; ++j) step32(j, std::false_type{});
+            }
+        }
+        if constexpr (QUANTUM && PREC == PREC_F32MIX) {
+            for (int j = 0; j < N;) {
                 const float chi1 = amp1.cpm * mu;
                 cmx = fmaxf(cmx, chi1);
                 if (__any(chi1 > P.chi_fp64)) {
@@ -300,17 +319,9 @@ __device__ __forceinline__ void phase_sample(const BatchParams &P, const ShotPar
                     }
                     continue;
                 }
+                step32(j, std::false_type{});
+                ++j;
             }
-            float aSh, aS4;
-            mid_end(j, aSh, aS4);
-            const float ah = aSh * env32[2 * j + 1];
-            const float a4 = aS4 * env32[2 * j + 2];
-            if (PREC != PREC_F32MIX) cmx = fmaxf(cmx, amp1.cpm * mu);
-            float dm, ds;
-            rk4_q32(mu, s2, amp1, AmpQ(ah, phf), AmpQ(a4, phf), P.hf, tab32, carry, dm, ds, chi_hi);
-            comp_add(mu, mu_lo, dm);
-            comp_add(s2, s2_lo, ds);
-            ++j;
         }
         mu_f = ((double)mu + (double)mu_lo) + g0_rest;
         s2_f = (double)s2 + (double)s2_lo;
@@ -393,10 +404,7 @@ __global__ __launch_bounds__(kPhaseBlock) void draw_kernel(BatchParams P) { draw
 // buffers, a barrier of the block a buffer).  5003 samples x 512 steps 237 ->
 // 197 us, 50,001 248 -> 214 us; from 257 items on (a second round; 131,072 samples
 // 416 us, 297 us above) the kernel above is the better one.
-// The results are the same bits: its loop is unrolled twice with the next
-// step's spatial factor between, which leaves the sum k2 + k3 of even steps (but
-// not a last one) its own rounding, where one block of code forms a fused
-// operation (ROUND of rk4_q32).
+// The results are the same bits (rk4_q32, mid_end32 and q32_steps are shared).
 constexpr int kPairSteps = 8;
 constexpr int kPairBlock = 2 * kPhaseBlock;
 static_assert(kPairSteps % 2 == 0, "a buffer begins with an even step");
@@ -468,15 +476,17 @@ __global__ __launch_bounds__(kPairBlock) void phase_pair_kernel(BatchParams P,
         } else {
             float mu = (float)g0, mu_lo = (float)(g0 - (double)mu), s2 = 0.0f, s2_lo = 0.0f;
             const double g0_rest = (g0 - (double)mu) - (double)mu_lo;
+            const float h6 = P.hf * (1.0f / 6.0f);
             float cmx = 0.0f, chi_hi = 0.0f;
             AmpQ amp1(aS_prev * env32[0], phf);
             RadCell32 carry;
             rad_lookup32(tab32, amp1.cpm * mu, carry);
             __syncthreads();
             for (int c = 0; c < nbuf; ++c) {
-                auto step = [&](int q, auto round) {
-                    const float4 m = B.m[c & 1][pair][q][lane];
-                    const float2 e = B.e[c & 1][pair][q][lane];
+                const int j0 = c * kPairSteps;
+                q32_steps(j0, min(N, j0 + kPairSteps), [&](int j, auto round) {
+                    const float4 m = B.m[c & 1][pair][j - j0][lane];
+                    const float2 e = B.e[c & 1][pair][j - j0][lane];
                     AmpQ Ah, A4;
                     Ah.nu = m.x;
                     Ah.nu2 = 2.0f * m.x;
@@ -490,16 +500,9 @@ __global__ __launch_bounds__(kPairBlock) void phase_pair_kernel(BatchParams P,
                     float dm, ds;
                     rk4_q32<decltype(round)::value>(mu, s2, amp1, Ah, A4, P.hf, tab32, carry, dm,
                                                     ds, chi_hi);
-                    comp_add(mu, mu_lo, dm);
-                    comp_add(s2, s2_lo, ds);
-                };
-                const int n = min(kPairSteps, N - c * kPairSteps);
-                int q = 0;
-                for (; q + 1 < n; q += 2) {
-                    step(q, std::integral_constant<bool, true>{});
-                    step(q + 1, std::integral_constant<bool, false>{});
-                }
-                if (q < n) step(q, std::integral_constant<bool, false>{});
+                    comp_add(mu, mu_lo, h6, dm);
+                    comp_add(s2, s2_lo, h6, ds);
+                });
                 __syncthreads();
             }
             const double mu_f = ((double)mu + (double)mu_lo) + g0_rest;
