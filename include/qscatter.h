@@ -604,8 +604,8 @@ qs_status qs_tune(qs_ctx *ctx, int32_t n_shots, const qs_laser *lasers, const qs
 
 /* Enable (on != 0) or disable HIP graphs for qs_forward and
  * qs_forward_batched on this context: the device work of a launch after the
- * shot-table copy (envelope table, accumulator clear, phase, deposit,
- * finalize kernels) is captured once into a graph and replayed by later
+ * shot-table copy (set-up, chi order, phase, deposit and finalize
+ * kernels) is captured once into a graph and replayed by later
  * launches whose kernel arguments are byte-identical (same shapes, sample
  * counts, numerics and scratch buffers; the per-shot parameters and output
  * pointers travel in the shot table, which is copied before every replay).

@@ -19,7 +19,7 @@ namespace qs {
 constexpr int kEMin = -20;
 constexpr int kEMax = 7;
 constexpr int kSB32 = 4;  // FP32 table: 16 sub-cells per octave (LDS resident)
-constexpr int kSB64 = 6;  // FP64 table: 64 sub-cells per octave (global)
+constexpr int kSB64 = 6;  // FP64 table: 64 sub-cells per octave (windows of it LDS resident)
 constexpr int kCells32 = 1 + (kEMax - kEMin + 1) * (1 << kSB32);
 // The octaves of the FP64 tables begin at 2^kEMin64; below it lie kLow64 even cells.
 // A cubic over [0, 2^-12) would be off by 1.5e-13 (g) to 5e-12 (chi h'), which
@@ -89,7 +89,8 @@ constexpr int kPartials = P_N + 3;  // moment sums and maxima of a moment tile
 // their tapes, photons): the samples of a group of up to kChiGroup consecutive
 // samples of one shot are taken in order of their chi scale (order_kernel), so
 // that wavefronts hold samples of similar chi over a wider pool than one work
-// item; a work item is a round of kPhaseBlock of them (photons: its own round).
+// item; a work item is a wavefront's 64 of them (photons: a block's; contraction:
+// the group).
 constexpr int kChiGroup = 2048;
 constexpr int kMoments = 21;        // moments a shot returns (QS_M_N)
 
