@@ -1264,8 +1264,8 @@ __global__ __launch_bounds__(kTrioBlock) void tangent_trio_kernel(
 // on their own, with FP32 steps in order of the group's chi scale.  Two
 // wavefronts a SIMD (256 registers; the passes with FP32 steps spill about 100
 // accesses, most of them where FP64 steps begin and end).  Bound by VALU issue:
-// eight quantum shots of 2^18 x 512 with the tape 26.9 -> 18.2 ms, 100,001 FP64
-// samples x 512 3.74 -> 2.75 ms, 5000 2.02 -> 1.35 ms, against the tables read from
+// eight quantum shots of 2^18 x 512 with the tape 26.9 -> 18.4 ms, 100,001 FP64
+// samples x 512 3.74 -> 2.09 ms, 5000 2.02 -> 1.28 ms, against the tables read from
 // L2 (with FP32 steps a wavefront at a time through LDS staging rows).
 constexpr int kTangent64Block = 512;
 

@@ -530,8 +530,8 @@ __global__ __launch_bounds__(kPairBlock) void phase_pair_kernel(BatchParams P,
 // conflicts (VALU busy 0.79 of the time at 1.95 GHz, 7 conflict cycles an LDS
 // instruction, by counters; see `ordered` in the host code): with the table read
 // a wavefront at a time from L2 through LDS staging rows, two wavefronts a SIMD,
-// 2^20 FP64 samples x 512 steps took 8.8 ms, now 4.8 ms; 5000 samples 0.86 and
-// 0.48 ms; eight quantum shots of 2^18 x 1024 with FP64 steps 17.8 and 11.1 ms.
+// 2^20 FP64 samples x 512 steps took 8.8 ms, now 4.9 ms; 5000 samples 0.86 and
+// 0.49 ms; eight quantum shots of 2^18 x 1024 with FP64 steps 17.8 and 11.4 ms.
 // Four wavefronts a SIMD in 128 registers in FP64 passes; three in 168 with FP32
 // steps beside (at four the FP32 steps spill: 23.4 ms; at two 12.7 ms).
 template <int PREC>
