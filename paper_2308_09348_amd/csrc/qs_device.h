@@ -516,7 +516,9 @@ __device__ __forceinline__ void chi_order32(const ShotParams &sp, uint32_t key0,
     __syncthreads();  // the previous group's order is no longer read
     for (int q = threadIdx.x; q < G; q += B) {
         const int64_t i = base + q;
-        s_key[q] = i < end ? chi_key32(sp, key0, key1, i) : __builtin_inff();
+        // (a key that is no number, where 1/w0^2 overflows FP32, has no rank: lowest)
+        s_key[q] = i < end ? fmaxf(chi_key32(sp, key0, key1, i), -0x1.fffffep127f)
+                           : __builtin_inff();
     }
     __syncthreads();
     for (int q = threadIdx.x; q < G; q += B) {

@@ -63,3 +63,17 @@ def test_nan_is_reported(gpu, model):
         gpu.forward(_point(w0_um=1e-160, rr_model=model))
     assert e.value.status == _lib.QS_ENONFINITE
     assert gpu.forward(_point(rr_model=model))["energy_hist"].sum().item() == 1.0
+
+
+def test_samples_without_an_order_key(gpu):
+    """w0 = 1e-25 um: 1 / w0^2 overflows FP32, so that the key by which FP32 passes
+    order an item's samples is no number, while the FP64 factor at the collision
+    point is about 1e-50.  Every sample is still taken once: the spectra of a beam
+    that meets no field."""
+    p = workloads.scaled(workloads.focused_3d(), n_samples=80_001, n_steps=16,
+                         amp_mode="a0eff")
+    got = gpu.forward(dict(p, w0_um=1e-25))
+    ref = gpu.forward(dict(p, a0=0.0))
+    for k in ("energy_hist", "angle_hist"):
+        assert (got[k] == ref[k]).all(), k
+    assert got["moments"][1] == ref["moments"][1]
