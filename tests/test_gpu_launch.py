@@ -294,34 +294,32 @@ def test_small_launches_have_the_bits_of_large_ones(qs, n_samples, n_steps, plan
     ctx.close()
 
 
-@pytest.mark.parametrize("n", [5003, 300_003])
+@pytest.mark.parametrize("n", [5003, 50_001])
 def test_tuned_small_launch_keeps_its_items(qs, tmp_path, n):
-    """A small launch tuned to tiles of 1024 deposits as the untuned one does
-    (in items of 256 and 512 samples here): items of 1024 themselves take three
-    times (5003 samples) and a quarter more than these, the same items the same
-    time within the spread of the fastest of 40 launches (a tenth)."""
+    """A small launch tuned to tiles of 1024 deposits as the untuned one does (in
+    items of 256 samples here).  Items of 1024 themselves take 3.1 and 2.4 times as
+    long, so that the fastest of 40 launches of either, in turn, tells them apart
+    at 1.5."""
     p = _case(n_samples=n, n_steps=16)
     cache = tmp_path / "tune.txt"
-    times = {}
-    plain, tuned = qs.Context(0), qs.Context(0)
-    plain.tune(p, cache_path=str(cache))
+    first, plain, tuned = qs.Context(0), qs.Context(0), qs.Context(0)
+    first.tune(p, cache_path=str(cache))
     line = cache.read_text().split()
     line[10:13] = ["1024", "0", "0"]
     cache.write_text(" ".join(line) + "\n")
-    plain.close()
-    plain = qs.Context(0)
     assert tuned.tune(p, cache_path=str(cache))["dep_tile"] == 1024
-    ref = _np(plain.forward(p))
-    _same(_np(tuned.forward(p)), ref, "tuned")
-    for name, ctx in (("plain", plain), ("tuned", tuned)):
+    _same(_np(tuned.forward(p)), _np(plain.forward(p)), "tuned")
+    both = (plain, tuned)
+    out = []
+    for ctx in both:
         ctx.set_profiling(True)
-        out = ctx.forward(p)
-        t = []
-        for _ in range(40):
-            ctx.forward(p, out=out, check=False)
-            t.append(ctx.last_timings()["deposit"])
-        times[name] = min(t)
-    print(n, times)
-    assert times["tuned"] <= 1.1 * times["plain"] + 1e-3
-    plain.close()
-    tuned.close()
+        out.append(ctx.forward(p))
+    ms = [1e9, 1e9]
+    for _ in range(40):
+        for k, ctx in enumerate(both):
+            ctx.forward(p, out=out[k], check=False)
+            ms[k] = min(ms[k], ctx.last_timings()["deposit"])
+    print(n, ms)
+    assert ms[1] <= 1.5 * ms[0]
+    for ctx in (first, plain, tuned):
+        ctx.close()
