@@ -497,17 +497,24 @@ struct EdgeWeights {
 // with the square of the edges).  Where the box spans at most a quarter standard
 // deviation its mass is the density at its centre times a polynomial in z^2,
 //   Phi(z + d) - Phi(z - d) = phi(z) Int_(-d)^d e^(-z u - u^2/2) du
-//                           = phi(z) sum_k z^(2k) m_2k / (2k)!,
+//                           = phi(z) P(z^2),  P(x) = sum_k x^k m_2k / (2k)!,
 //   d = dz/2, m_2k = Int_(-d)^d u^2k e^(-u^2/2) du
 // (eight terms: the ninth is below 3e-17 of the sum at six standard deviations),
-// and the derivative along s takes the densities at the box ends, shared by
-// neighbouring edges; wider boxes take erfc at their ends, shared likewise.
-// The products' roundings stay below 6e-15 of the sum of magnitudes.
+// and the derivative along s is that of the mass by z,
+//   phi(z + d) - phi(z - d) = -z phi(z) (P(z^2) - 2 P'(z^2)),
+// without the difference of the densities, which cancels in small boxes; wider
+// boxes take erfc at their ends, shared by neighbouring edges.
+// Over random laws with edges 0.003 to 1 standard deviations apart the sums of
+// normal laws are 3e-16 to 2.0e-15 of the sum of magnitudes off (rms; an exponential
+// an edge 2e-16 to 1.8e-15, sixteen edges a chunk 4e-16 to 3.9e-15), those of boxes
+// 3e-16 to 8e-16 (two erfc and two exponentials an edge 3e-16 to 1.8e-15, sixteen
+// edges a chunk and the difference of the densities 4e-16 to 7.3e-15).
 // Bound by FP64 issue, by the widest law of each wavefront.  With two erfc and
 // two exponentials a box edge and one exponential a normal edge the contraction
 // of tapes took 466 us for 50,001 samples (boxes), 367 us for 2^20 (normal
-// laws of both histograms) and 580 us for 2^21 (normal); so 105, 296 and 326 us.
-constexpr int kChunk = 16;
+// laws of both histograms) and 580 us for 2^21 (normal); so 110, 322 and
+// 386 us (four edges a chunk: 114, 408, 498).
+constexpr int kChunk = 8;
 
 template <class Weights>
 __device__ __forceinline__ void law_sensitivity(double v, double s2, int dep, double ksig,
@@ -568,7 +575,7 @@ __device__ __forceinline__ void law_sensitivity(double v, double s2, int dep, do
         // coefficients m_2k / (2k)! of the box mass, m_2k = 2 sum_i (-1)^i
         // d^(2k+2i+1) / (2^i i! (2k+2i+1)); d <= 1/8
         constexpr int kTerms = 8;
-        double C[kTerms];
+        double C[kTerms], D[kTerms];  // of P and P - 2 P'
         {
             const double d2 = d * d;
             double lead = 2.0 * d;  // 2 d^(2k+1) / (2k)!
@@ -583,24 +590,25 @@ __device__ __forceinline__ void law_sensitivity(double v, double s2, int dep, do
                 C[k] = lead * m;
                 lead *= d2 * (1.0 / ((2 * k + 1) * (2 * k + 2)));
             }
+#pragma unroll
+            for (int k = 0; k < kTerms; ++k)
+                D[k] = k + 1 < kTerms ? fma(-2.0 * (k + 1), C[k + 1], C[k]) : C[k];
         }
         for (int j0 = ja; j0 <= jb; j0 += kChunk) {
-            // densities at the centres (f) and at the lower box ends (g)
             double z = z_at(j0), f = phi_pdf(z), r = exp64(-z * dz - d * dz);
-            double g = phi_pdf(z - d), rg = exp64(-(z - d) * dz - d * dz);
             const int j1 = min(j0 + kChunk - 1, jb);
             for (int j = j0; j <= j1; ++j) {
-                const double z2 = z * z, cj = c(j);
-                double p = C[kTerms - 1];
+                const double z2 = z * z, cf = c(j) * f;
+                double p = C[kTerms - 1], dp = D[kTerms - 1];
 #pragma unroll
-                for (int k = kTerms - 2; k >= 0; --k) p = fma(p, z2, C[k]);
-                const double g1 = g * rg;
-                sv = fma(cj, f * p, sv);
-                ss = fma(cj, g1 - g, ss);
+                for (int k = kTerms - 2; k >= 0; --k) {
+                    p = fma(p, z2, C[k]);
+                    dp = fma(dp, z2, D[k]);
+                }
+                sv = fma(cf, p, sv);
+                ss = fma(-z * cf, dp, ss);
                 f *= r;
                 r *= q;
-                g = g1;
-                rg *= q;
                 z += dz;
             }
         }

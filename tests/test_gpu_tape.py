@@ -224,3 +224,53 @@ def test_small_tape_has_the_bits_of_a_large_one(gpu, n_samples, n_steps):
     assert torch.equal(t1, t2[:, :n_samples])
     for key in o1:
         assert torch.equal(o1[key], o2[key]), key
+
+
+@pytest.mark.parametrize("deposit,n_e,dz,bound_v,bound_s", [
+    ("cic", 4096, (0.0032, 0.032), 1.2e-15, 1.5e-15), ("point", 256, (0.032, 0.25), 6.5e-16, 7e-16)])
+def test_contraction_rounding(gpu, deposit, n_e, dz, bound_v, bound_s):
+    """Derivatives of laws given by the tape (one sample a shot) against extended
+    precision, as a share of the sum of magnitudes, rms over 400 laws.  The same
+    recurrences on the CPU give 3.1e-16 (centre) and 4.1e-16 (width) for boxes of 0.003
+    to 0.03 standard deviations, 4.0e-16 and 5.3e-16 for normal laws; with the box
+    ends' densities subtracted 7.3e-15 (width), with sixteen edges a chunk 8.7e-16 and
+    9.2e-16 for normal laws."""
+    import torch
+    n, width = 400, 3072.0 / n_e
+    rng = np.random.Generator(np.random.PCG64(8))
+    step = np.exp(rng.uniform(np.log(dz[0]), np.log(dz[1]), n))
+    mu, s2 = 3072.0 * rng.uniform(0.2, 0.8, n), (width / step) ** 2
+    shots = [dict(_case(n_samples=1, n_steps=8), precision="fp64", deposit=deposit, n_e=n_e,
+                  e_lo=0.0, e_hi=3072.0) for _ in range(n)]
+    tape = np.zeros((18, n))
+    tape[0], tape[1] = mu, s2
+    tape[2] = 1.0        # the first parameter moves mu
+    tape[2 + 8 + 1] = 1.0  # the second sig2
+    ph, fr = rng.uniform(0, 6, n), rng.uniform(0, 0.5, n)
+    w = np.zeros((n, n_e + 2))
+    w[:, :n_e] = np.sin(ph[:, None] + fr[:, None] * np.arange(n_e))
+    w[:, n_e], w[:, n_e + 1] = np.sin(ph - fr), np.sin(ph + fr * n_e)
+    grads = gpu.backward_batched(shots, [torch.tensor(a, device="cuda") for a in w],
+                                 tape=torch.tensor(tape, device="cuda"))
+    g = np.array([x.cpu().numpy() for x in grads])
+    L = np.longdouble
+    e = L(width) * np.arange(n_e + 1)
+    x, gw = np.polynomial.legendre.leggauss(12)
+    norm = 1 / np.sqrt(2 * np.arccos(L(-1)))
+    err = []
+    for k in range(n):
+        c = L(np.concatenate(([w[k, n_e]], w[k, :n_e])) -
+              np.concatenate((w[k, :n_e], [w[k, n_e + 1]])))
+        s = np.sqrt(L(s2[k]))
+        z, d = (e - L(mu[k])) / s, L(width) / s / 2
+        phi = lambda t: norm * np.exp(-t * t / 2)
+        if deposit == "cic":
+            mass = sum(L(b) * phi(z + d * L(a)) for a, b in zip(x, gw)) * d
+            dv, ds = -c * mass / width, c * (phi(z + d) - phi(z - d)) / width / (2 * s)
+        else:
+            dv, ds = -c * phi(z) / s, -c * z * phi(z) / s / (2 * s)
+        err.append([float((g[k, 0] - dv.sum()) / np.abs(dv).sum()),
+                    float((g[k, 1] - ds.sum()) / np.abs(ds).sum())])
+    rms = np.sqrt(np.mean(np.square(err), axis=0))
+    print("centre, width", rms)
+    assert rms[0] < bound_v and rms[1] < bound_s
